@@ -119,6 +119,14 @@ slkv_status slkv_score_heads_ex(const slkv_score_params* params, const float* d_
                                 double* d_acc, double* d_scores,
                                 void* d_workspace, size_t workspace_bytes, void* hip_stream);
 
+/* The first of a series of calls: as slkv_score_heads (params NULL, d_acc [L][H][5]) or slkv_score_heads_ex
+ * (d_acc [L][H][8]) on accumulators of zeros, which need not be zeroed: they are written without being read. */
+slkv_status slkv_score_heads_first(const slkv_score_params* params, const float* d_rows,
+                                   int32_t L, int32_t H, int32_t T, int64_t n,
+                                   int64_t needle_start, int32_t needle_len, int32_t topk,
+                                   double* d_acc, double* d_scores,
+                                   void* d_workspace, size_t workspace_bytes, void* hip_stream);
+
 /* Stage 1 without attention rows in memory (Section 3.1, Eq. 2-4, feeding Algorithm 1): the row of
  * query head hq at decode step t is softmax_j(q[l][hq][t] . k[l][hq / (Hq/Hkv)][j] / sqrt(d)) over the
  * n context keys; the kernels compute the logits, the top-K set and the weight cells of every row
@@ -138,6 +146,12 @@ slkv_status slkv_score_heads_qk(const void* d_q, const void* d_k, int32_t L, int
                                 int64_t needle_start, int32_t needle_len, int32_t topk,
                                 double* d_acc, double* d_scores,
                                 void* d_workspace, size_t workspace_bytes, void* hip_stream);
+/* The same on accumulators of zeros, which are written without being read (see slkv_score_heads_first). */
+slkv_status slkv_score_heads_qk_first(const void* d_q, const void* d_k, int32_t L, int32_t Hq, int32_t Hkv,
+                                      int32_t T, int64_t n, int32_t d,
+                                      int64_t needle_start, int32_t needle_len, int32_t topk,
+                                      double* d_acc, double* d_scores,
+                                      void* d_workspace, size_t workspace_bytes, void* hip_stream);
 size_t slkv_score_heads_qk_workspace_bytes(int32_t L, int32_t Hq, int32_t T, int64_t n);
 
 /* ------------------------------------------------------------------ Stage 2a ----------

@@ -95,11 +95,12 @@ class RaggedCall:
 def score_heads(rows, needle_start, needle_len, topk, acc=None, stream=None):
     """rows: [L,H,T,n] fp32 device tensor.  Returns (acc [L,H,5], scores [L,H,3]) float64 device tensors."""
     L, H, T, n = rows.shape
-    if acc is None:
-        acc = torch.zeros((L, H, 5), dtype=torch.float64, device=rows.device)
+    first = acc is None
+    if first:
+        acc = torch.empty((L, H, 5), dtype=torch.float64, device=rows.device)
     scores = torch.empty((L, H, 3), dtype=torch.float64, device=rows.device)
     ws = torch.empty((max(B.slkv_score_heads_workspace_bytes(L, H, T, n), 16),), dtype=torch.uint8, device=rows.device)
-    B.slkv_score_heads(rows, needle_start, needle_len, topk, acc, scores, ws, stream)
+    B.slkv_score_heads(rows, needle_start, needle_len, topk, acc, scores, ws, stream, first)
     return acc, scores
 
 
@@ -107,11 +108,12 @@ def score_heads_ex(rows, needle_start, needle_len, topk, aggregation=B.SLKV_AGG_
                    acc=None, stream=None):
     """As score_heads through slkv_score_heads_ex: acc is [L,H,8]."""
     L, H, T, n = rows.shape
-    if acc is None:
-        acc = torch.zeros((L, H, 8), dtype=torch.float64, device=rows.device)
+    first = acc is None
+    if first:
+        acc = torch.empty((L, H, 8), dtype=torch.float64, device=rows.device)
     scores = torch.empty((L, H, 3), dtype=torch.float64, device=rows.device)
     ws = torch.empty((max(B.slkv_score_heads_workspace_bytes(L, H, T, n), 16),), dtype=torch.uint8, device=rows.device)
-    B.slkv_score_heads_ex(rows, needle_start, needle_len, topk, acc, scores, ws, aggregation, components, stream)
+    B.slkv_score_heads_ex(rows, needle_start, needle_len, topk, acc, scores, ws, aggregation, components, stream, first)
     return acc, scores
 
 
@@ -119,9 +121,10 @@ def score_heads_qk(q, k, needle_start, needle_len, topk, acc=None, stream=None):
     """q [L,Hq,T,d], k [L,Hkv,n,d] bf16 device tensors.  Returns (acc [L,Hq,5], scores [L,Hq,3]) float64 device tensors."""
     L, Hq, T, d = q.shape
     n = k.shape[2]
-    if acc is None:
-        acc = torch.zeros((L, Hq, 5), dtype=torch.float64, device=q.device)
+    first = acc is None
+    if first:
+        acc = torch.empty((L, Hq, 5), dtype=torch.float64, device=q.device)
     scores = torch.empty((L, Hq, 3), dtype=torch.float64, device=q.device)
     ws = torch.empty((B.slkv_score_heads_qk_workspace_bytes(L, Hq, T, n),), dtype=torch.uint8, device=q.device)
-    B.slkv_score_heads_qk(q, k, needle_start, needle_len, topk, acc, scores, ws, stream)
+    B.slkv_score_heads_qk(q, k, needle_start, needle_len, topk, acc, scores, ws, stream, first)
     return acc, scores

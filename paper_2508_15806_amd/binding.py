@@ -23,6 +23,7 @@ STATUS_NAMES = {0: "SLKV_OK", 1: "SLKV_ERR_NULL", 2: "SLKV_ERR_BAD_ARG", 3: "SLK
                 4: "SLKV_ERR_UNSUPPORTED", 5: "SLKV_ERR_WORKSPACE", 6: "SLKV_ERR_CAPACITY", 7: "SLKV_ERR_HIP"}
 
 EXPORTS = ["slkv_status_str", "slkv_last_error", "slkv_version", "slkv_init", "slkv_score_heads", "slkv_score_heads_ex", "slkv_score_heads_qk",
+           "slkv_score_heads_first", "slkv_score_heads_qk_first",
            "slkv_score_heads_qk_workspace_bytes",
            "slkv_score_heads_workspace_bytes", "slkv_allocate_budgets", "slkv_fixed_from_beta",
            "slkv_compacted_sizes", "slkv_workspace_bytes", "slkv_compress_layer", "slkv_compress_layer_static",
@@ -119,6 +120,10 @@ def lib():
         L.slkv_score_heads_qk.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int64,
                                           C.c_int32, C.c_int64, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p,
                                           C.c_size_t, C.c_void_p]
+        L.slkv_score_heads_first.restype = C.c_int
+        L.slkv_score_heads_first.argtypes = L.slkv_score_heads_ex.argtypes
+        L.slkv_score_heads_qk_first.restype = C.c_int
+        L.slkv_score_heads_qk_first.argtypes = L.slkv_score_heads_qk.argtypes
         L.slkv_profile_begin.restype = C.c_int
         L.slkv_profile_begin.argtypes = [C.c_int32]
         L.slkv_profile_end.restype = C.c_int
@@ -249,36 +254,37 @@ def slkv_score_heads_workspace_bytes(L, H, T, n):
     return int(lib().slkv_score_heads_workspace_bytes(L, H, T, n))
 
 
-def slkv_score_heads(rows, needle_start, needle_len, topk, acc, scores, workspace, stream=None):
-    """rows: [L, H, T, n] fp32 device tensor; acc [L, H, 5] float64 (in/out); scores [L, H, 3] float64 or None."""
+def slkv_score_heads(rows, needle_start, needle_len, topk, acc, scores, workspace, stream=None, first=False):
+    """rows: [L, H, T, n] fp32 device tensor; acc [L, H, 5] float64 (in/out; first: out only); scores [L, H, 3] float64 or None."""
     L, H, T, n = rows.shape
-    _check(lib().slkv_score_heads(_ptr(rows), L, H, T, n, int(needle_start), int(needle_len), int(topk), _ptr(acc),
-                                  _ptr(scores), _ptr(workspace), int(workspace.numel() * workspace.element_size()),
-                                  _stream(stream)))
+    args = (_ptr(rows), L, H, T, n, int(needle_start), int(needle_len), int(topk), _ptr(acc), _ptr(scores), _ptr(workspace),
+            int(workspace.numel() * workspace.element_size()), _stream(stream))
+    _check(lib().slkv_score_heads_first(None, *args) if first else lib().slkv_score_heads(*args))
 
 
 def slkv_score_heads_ex(rows, needle_start, needle_len, topk, acc, scores, workspace, aggregation=SLKV_AGG_MICRO,
-                        components=(True, True, True), stream=None):
+                        components=(True, True, True), stream=None, first=False):
     """As slkv_score_heads with acc [L, H, 8]; aggregation and the (WO, WD, WS) switches of the ablation."""
     L, H, T, n = rows.shape
     prm = ScoreParams(C.sizeof(ScoreParams), int(aggregation), int(bool(components[0])), int(bool(components[1])),
                       int(bool(components[2])), 0)
-    _check(lib().slkv_score_heads_ex(C.byref(prm), _ptr(rows), L, H, T, n, int(needle_start), int(needle_len), int(topk),
-                                     _ptr(acc), _ptr(scores), _ptr(workspace),
-                                     int(workspace.numel() * workspace.element_size()), _stream(stream)))
+    call = lib().slkv_score_heads_first if first else lib().slkv_score_heads_ex
+    _check(call(C.byref(prm), _ptr(rows), L, H, T, n, int(needle_start), int(needle_len), int(topk), _ptr(acc), _ptr(scores),
+                _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream(stream)))
 
 
 def slkv_score_heads_qk_workspace_bytes(L, Hq, T, n):
     return int(lib().slkv_score_heads_qk_workspace_bytes(L, Hq, T, n))
 
 
-def slkv_score_heads_qk(q, k, needle_start, needle_len, topk, acc, scores, workspace, stream=None):
-    """q: [L, Hq, T, d], k: [L, Hkv, n, d] bf16 device tensors; acc [L, Hq, 5] float64 (in/out); scores [L, Hq, 3] or None."""
+def slkv_score_heads_qk(q, k, needle_start, needle_len, topk, acc, scores, workspace, stream=None, first=False):
+    """q: [L, Hq, T, d], k: [L, Hkv, n, d] bf16 device tensors; acc [L, Hq, 5] float64 (in/out; first: out only);
+    scores [L, Hq, 3] or None."""
     L, Hq, T, d = q.shape
     Hkv, n = k.shape[1], k.shape[2]
-    _check(lib().slkv_score_heads_qk(_ptr(q), _ptr(k), L, Hq, Hkv, T, n, d, int(needle_start), int(needle_len), int(topk),
-                                     _ptr(acc), _ptr(scores), _ptr(workspace),
-                                     int(workspace.numel() * workspace.element_size()), _stream(stream)))
+    call = lib().slkv_score_heads_qk_first if first else lib().slkv_score_heads_qk
+    _check(call(_ptr(q), _ptr(k), L, Hq, Hkv, T, n, d, int(needle_start), int(needle_len), int(topk), _ptr(acc), _ptr(scores),
+                _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream(stream)))
 
 
 def slkv_profile_begin(max_records):

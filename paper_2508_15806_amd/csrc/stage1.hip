@@ -5,6 +5,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "launch.h"
@@ -12,210 +13,268 @@
 
 namespace slkv {
 
-constexpr int kS1Threads = 256;
-constexpr int kS1Resident = 64;   // elements per thread held in registers (rows up to 16384)
-constexpr int kS1Cand = 512;      // weights at or above the bound that the exact ranking can hold
+constexpr int kS1Threads = 256;   // workgroup of the general row path
+constexpr int kS1Groups = 16;     // 16-byte groups per thread that the resident row path holds in registers, at most
+constexpr int kS1TopK = 64;       // largest K of the resident row path
 
-// One workgroup per row.  RESIDENT (n % 4 == 0, n <= 256*64, K <= 64): the row is read once with
-// 16-byte loads and stays in registers for the small-K path.  The general radix select reads
-// the row from memory in every sweep.
-// cells[row] = (WO, WD, WS, Wide).
-template <bool RESIDENT>
-__device__ __forceinline__ void row_cells_impl(const float* __restrict__ W, int32_t n, int32_t needle_start,
-                                               int32_t needle_len, int32_t topk, double* __restrict__ c_out) {
-  constexpr int NT = kS1Threads;
-  __shared__ uint32_t hist[kHistBins];
-  __shared__ uint32_t sh_scan[NT / 64];
-  __shared__ uint32_t res[2];
-  __shared__ double sh_d[NT / 64];
-  __shared__ uint32_t sh_u[NT / 64];
-
-  const int tid = threadIdx.x;
-  const int32_t ne = needle_start + needle_len;
-
-  // sweep helper of the general path: f(position, value) over the row, re-read from memory
-  auto sweep = [&](auto f) {
-    for (int32_t j = tid; j < n; j += NT) f(j, W[j]);
+// LDS of the row paths with NT threads: the candidate lists of the resident path (per wave; a needle's
+// neighbouring tokens fall to one wave) and the histogram of the general path share one area.
+template <int NT>
+struct RowLds {
+  static constexpr int NW = NT / kWave;
+  static constexpr int kWaveCand = NW == 1 ? 512 : (NW == 2 ? 256 : 128);
+  union {
+    struct {
+      uint64_t key[NW * kWaveCand];   // (order-preserving key of the weight) << 32 | ~position
+      float val[NW * kWaveCand];
+    } cand;
+    uint32_t hist[kHistBins];
   };
+  uint32_t sh_scan[NW], res[2], sh_u[NW], cnt[NW];
+  double sh_d[NW], tot[NW], tnw[NW];
+  float bound[NW], tau;
+};
+
+__device__ __forceinline__ void store_cells(double* c, double WO, double WD, double tot, double tnw) {
+  const double WS = fmax(0.0, tnw - WO);
+  c[0] = WO;
+  c[1] = WD;
+  c[2] = WS;
+  c[3] = tot - WO - WD - WS;
+}
+
+// Resident row path: the row is read once, NG 16-byte groups per thread, and stays in registers.  Rows begin
+// where the row before them ends, so a row of any length begins at some float of a 16-byte group: the groups
+// are counted from the aligned address at or below the row's begin (`lead` floats before it).  The floats of the
+// first group that belong to the row before are taken out; those of a last group that is not whole (it may reach
+// past the tensor) are held one each by the first threads.
+// A lower bound of the K-th largest weight comes from the lane maxima of each wave (K distinct elements); the
+// few weights at or above the bound are collected in LDS and ranked exactly (larger first, equal weights by
+// lower position).  Returns false, with nothing written, if a list overflows (many ties at the bound).
+// WHOLE: every row is whole 16-byte groups (n % 4 == 0).
+template <int NT, int NG, bool WHOLE>
+__device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, int32_t n, int32_t needle_start,
+                                                   int32_t needle_len, int32_t topk, double* __restrict__ c_out, RowLds<NT>& S) {
+  constexpr int NW = NT / kWave, kWaveCand = RowLds<NT>::kWaveCand;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int32_t ne = needle_start + needle_len;
+  const int32_t lead = WHOLE ? 0 : (int32_t)((reinterpret_cast<uintptr_t>(W) >> 2) & 3u);
+  const int32_t end = lead + n;                        // floats are counted from the aligned address
+  const int32_t ngroups = end >> 2;                    // whole groups (at least one: n >= 4)
+  const f32x4* W4 = reinterpret_cast<const f32x4*>(W - lead);
+
+  // group i of this thread: i * NT + tid; all loads are issued first.  The rows are read exactly once:
+  // non-temporal loads (they do not displace anything in the caches) stream about 13 % faster than plain
+  // ones on this part.
+  f32x4 v[NG];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) v[i] = __builtin_nontemporal_load(W4 + min(i * NT + tid, ngroups - 1));   // past the end: loaded again, never used
+  const int32_t jx = 4 * ngroups + tid - lead;         // position of this thread's float of the last group
+  const bool have_x = !WHOLE && tid < (end & 3) && jx >= 0;
+  const float vx = have_x ? W[jx] : 0.f;
+  const int32_t jn = needle_start + tid;
+  const float nd = W[jn < ne ? jn : needle_start];
 
   double tot = 0.0, tnw = 0.0;           // row sum and needle sum, in double
-  if (RESIDENT) {
-    // Small K on a row held in registers.  A lower bound of the K-th largest weight comes from
-    // the lane maxima of each wave (K distinct elements); the few weights at or above the bound
-    // are collected in LDS and ranked exactly (larger first, equal weights by lower position).
-    constexpr int NW = NT / kWave;
-    constexpr int kWaveCand = kS1Cand / NW;
-    __shared__ double sh_tot[NW], sh_tnw[NW];
-    __shared__ float sh_bound[NW];
-    __shared__ uint32_t sh_cnt[NW];
-    __shared__ float cand_val[kS1Cand];
-    __shared__ uint64_t cand_key[kS1Cand];   // (order-preserving key of the weight) << 32 | ~position
-    const int lane = tid & 63, wv = tid >> 6;
-    const int32_t ngroups = n >> 2;      // n % 4 == 0: the row is whole 16-byte groups
-
-    // group i of this thread: positions 4 * (i * NT + tid) .. + 3; all loads are issued first
-    // The rows are read exactly once: non-temporal loads (they do not displace anything in the
-    // caches) stream about 13 % faster than plain ones on this part.
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const f32x4* W4 = reinterpret_cast<const f32x4*>(W);
-    float4 v[kS1Resident / 4];
+  if (!WHOLE && tid == 0) {
 #pragma unroll
-    for (int i = 0; i < kS1Resident / 4; ++i) {
-      const int32_t g = i * NT + tid;
-      const f32x4 x = __builtin_nontemporal_load(W4 + (g < ngroups ? g : ngroups - 1));   // past the end: loaded again, never used
-      v[i] = make_float4(x.x, x.y, x.z, x.w);
-    }
-    const int32_t jn = needle_start + tid;
-    const float nd = W[jn < ne ? jn : needle_start];
-
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kS1Resident / 4; ++i) {
-      if (i * NT + tid < ngroups) {
-        tot += (double)v[i].x;
-        tot += (double)v[i].y;
-        tot += (double)v[i].z;
-        tot += (double)v[i].w;
-        mx = fmaxf(fmaxf(mx, fmaxf(v[i].x, v[i].y)), fmaxf(v[i].z, v[i].w));
-      }
-    }
-    if (jn < ne) tnw = (double)nd;
-    for (int32_t j = jn + NT; j < ne; j += NT) tnw += (double)W[j];
-    tot = wave_sum<double>(tot);
-    tnw = wave_sum<double>(tnw);
-
-    // Each wave finds a value at or below the ceil(K/4)-th largest of its 64 lane maxima
-    // (bisection on the upper 20 bits of the order-preserving key, with ballots).  At least K
-    // weights are >= the smallest of the four values, so it bounds the K-th largest from below.
-    const uint32_t want = (uint32_t)(topk + NW - 1) / NW;
-    const uint32_t mkey = tid < ngroups ? float_key(mx) : 0u;   // lanes without data never count
-    uint32_t tkey = 0;
-#pragma unroll
-    for (int b = 31; b >= 12; --b) {
-      const uint32_t trial = tkey | (1u << b);
-      if ((uint32_t)__popcll(__ballot(mkey >= trial)) >= want) tkey = trial;
-    }
-    // the float whose key is tkey (low bits cleared: not above the value found); 0 keys: -inf
-    const float bound_w = tkey == 0 ? -INFINITY
-                                    : __uint_as_float((tkey & 0x80000000u) ? (tkey ^ 0x80000000u) : ~tkey);
-    if (lane == 0) {
-      sh_tot[wv] = tot;
-      sh_tnw[wv] = tnw;
-      sh_bound[wv] = bound_w;
-    }
-    __syncthreads();
-    tot = sh_tot[0];
-    tnw = sh_tnw[0];
-    float bound = sh_bound[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) {
-      tot += sh_tot[i];
-      tnw += sh_tnw[i];
-      bound = fminf(bound, sh_bound[i]);
-    }
-
-    // Candidates of this wave go to its own part of the list; the slot of a lane is the number
-    // of candidates found so far plus the candidates of the same element in lower lanes.
-    uint32_t base = 0;                   // wave-uniform
-    float* my_val = cand_val + wv * kWaveCand;
-    uint64_t* my_key = cand_key + wv * kWaveCand;
-#pragma unroll
-    for (int i = 0; i < kS1Resident / 4; ++i) {
-      const int32_t g = i * NT + tid;
-      const float bnd = g < ngroups ? bound : INFINITY;
-      const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const bool is = x[c] >= bnd;
-        const unsigned long long mask = __ballot(is);
-        if (mask) {
-          const uint32_t slot = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-          if (is && slot < (uint32_t)kWaveCand) {
-            my_val[slot] = x[c];
-            my_key[slot] = ((uint64_t)float_key(x[c]) << 32) | (uint32_t)(~(uint32_t)(4 * g + c));
-          }
-          base += (uint32_t)__popcll(mask);
-        }
-      }
-    }
-    if (lane == 0) sh_cnt[wv] = base;
-    __syncthreads();
-    uint32_t cnt[NW], nc = 0;
-    bool fits = true;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      cnt[i] = sh_cnt[i];
-      nc += cnt[i];
-      fits = fits && cnt[i] <= (uint32_t)kWaveCand;
-    }
-    if (fits && nc >= (uint32_t)topk) {
-      // A candidate belongs to T_k if fewer than K candidates are ahead of it (larger, or equal
-      // at a lower position: one comparison of the packed keys).  Up to 256 candidates are handled
-      // by the first wave alone, each lane counting for up to four of them; the other waves retire.
-      constexpr int kPerLane = 4;
-      const bool one_wave = nc <= (uint32_t)(kWave * kPerLane);
-      if (one_wave && wv != 0) return;
-      double wo = 0.0, wd = 0.0;
-      const uint32_t stride = one_wave ? kWave : NT;
-      const uint32_t per_thread = (nc + stride - 1) / stride;    // uniform over the workgroup
-      for (uint32_t c0 = 0; c0 < per_thread; c0 += kPerLane) {
-        uint64_t mine[kPerLane];
-        float xval[kPerLane];
-        uint32_t ahead[kPerLane];
-#pragma unroll
-        for (int q = 0; q < kPerLane; ++q) {
-          const uint32_t c = (c0 + q) * stride + (one_wave ? lane : tid);
-          uint32_t part = 0, idx = c;
-#pragma unroll
-          for (int i = 0; i < NW - 1; ++i)
-            if (part == (uint32_t)i && idx >= cnt[i]) {
-              idx -= cnt[i];
-              part = i + 1;
-            }
-          const bool have = c < nc;
-          mine[q] = have ? cand_key[part * kWaveCand + idx] : ~0ull;   // nothing is ahead of the filler, and it is never summed
-          xval[q] = have ? cand_val[part * kWaveCand + idx] : 0.f;
-          ahead[q] = have ? 0u : (uint32_t)topk;
-        }
-#pragma unroll
-        for (int p = 0; p < NW; ++p)
-          for (uint32_t o = 0; o < cnt[p]; ++o) {
-            const uint64_t ko = cand_key[p * kWaveCand + o];
-#pragma unroll
-            for (int q = 0; q < kPerLane; ++q) ahead[q] += ko > mine[q] ? 1u : 0u;
-          }
-#pragma unroll
-        for (int q = 0; q < kPerLane; ++q)
-          if (ahead[q] < (uint32_t)topk) {
-            const int32_t px = (int32_t)(~(uint32_t)mine[q]);
-            if (px >= needle_start && px < ne) wo += (double)xval[q]; else wd += (double)xval[q];
-          }
-      }
-      if (one_wave) {
-        wo = wave_sum<double>(wo);
-        wd = wave_sum<double>(wd);
-      } else {
-        wo = block_sum<NT, double>(wo, sh_d);
-        wd = block_sum<NT, double>(wd, sh_d);
-      }
-      if (tid == 0) {
-        const double WS = fmax(0.0, tnw - wo);
-        double* c = c_out;
-        c[0] = wo;
-        c[1] = wd;
-        c[2] = WS;
-        c[3] = tot - wo - wd - WS;
-      }
-      return;
-    }
-    // too many ties at the bound: the general select below re-reads the row
-  } else {
-    sweep([&](int32_t, float x) { tot += (double)x; });
-    for (int32_t j = needle_start + tid; j < ne; j += NT) tnw += (double)W[j];
-    tot = block_sum<NT, double>(tot, sh_d);
-    tnw = block_sum<NT, double>(tnw, sh_d);
+    for (int c = 0; c < 3; ++c)
+      if (c < lead) v[0][c] = 0.f;
   }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    if (i * NT + tid < ngroups) {
+      tot += (double)v[i].x;
+      tot += (double)v[i].y;
+      tot += (double)v[i].z;
+      tot += (double)v[i].w;
+      if (!WHOLE && i == 0 && tid == 0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          if (c < lead) v[0][c] = -INFINITY;
+      }
+      mx = fmaxf(fmaxf(mx, fmaxf(v[i].x, v[i].y)), fmaxf(v[i].z, v[i].w));
+    }
+  }
+  if (!WHOLE) {
+    tot += (double)vx;
+    if (have_x) mx = fmaxf(mx, vx);
+  }
+  if (jn < ne) tnw = (double)nd;
+  for (int32_t j = jn + NT; j < ne; j += NT) tnw += (double)W[j];
+  tot = wave_sum<double>(tot);
+  tnw = wave_sum<double>(tnw);
+
+  // Each wave finds a value at or below the ceil(K/NW)-th largest of its 64 lane maxima (bisection on the
+  // upper 20 bits of the order-preserving key, with ballots).  At least K weights are >= the smallest of
+  // the waves' values, so it bounds the K-th largest from below.
+  const uint32_t want = (uint32_t)(topk + NW - 1) / NW;
+  const uint32_t mkey = tid < ngroups || have_x ? float_key(mx) : 0u;   // lanes without data never count
+  uint32_t tkey = 0;
+#pragma unroll
+  for (int b = 31; b >= 12; --b) {
+    const uint32_t trial = tkey | (1u << b);
+    if ((uint32_t)__popcll(__ballot(mkey >= trial)) >= want) tkey = trial;
+  }
+  // the float whose key is tkey (low bits cleared: not above the value found); 0 keys: -inf
+  float bound = tkey == 0 ? -INFINITY : __uint_as_float((tkey & 0x80000000u) ? (tkey ^ 0x80000000u) : ~tkey);
+  if (NW > 1) {
+    if (lane == 0) {
+      S.tot[wv] = tot;
+      S.tnw[wv] = tnw;
+      S.bound[wv] = bound;
+    }
+    __syncthreads();
+    tot = S.tot[0];
+    tnw = S.tnw[0];
+    bound = S.bound[0];
+#pragma unroll 4
+    for (int i = 1; i < NW; ++i) {
+      tot += S.tot[i];
+      tnw += S.tnw[i];
+      bound = fminf(bound, S.bound[i]);
+    }
+  }
+
+  // Candidates of this wave go to its own part of the list; the slot of a lane is the number
+  // of candidates found so far plus the candidates of the same element in lower lanes.
+  uint32_t base = 0;                   // wave-uniform
+  float* my_val = S.cand.val + wv * kWaveCand;
+  uint64_t* my_key = S.cand.key + wv * kWaveCand;
+  auto collect = [&](bool is, float x, int32_t j) __attribute__((always_inline)) {
+    const unsigned long long mask = __ballot(is);
+    if (mask) {
+      const uint32_t slot = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      if (is && slot < (uint32_t)kWaveCand) {
+        my_val[slot] = x;
+        my_key[slot] = ((uint64_t)float_key(x) << 32) | (uint32_t)(~(uint32_t)j);
+      }
+      base += (uint32_t)__popcll(mask);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const int32_t g = i * NT + tid;
+    const float bnd = g < ngroups ? bound : INFINITY;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int32_t j = 4 * g + c - lead;              // (before the row: -inf by now, listed only under a bound of -inf)
+      collect(v[i][c] >= bnd && (WHOLE || i > 0 || c == 3 || j >= 0), v[i][c], j);
+    }
+  }
+  if (!WHOLE) collect(have_x && vx >= bound, vx, jx);
+  if (lane == 0) S.cnt[wv] = base;
+  __syncthreads();
+  uint32_t nc = 0;
+  bool fits = true;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const uint32_t ci = S.cnt[i];
+    nc += ci;
+    fits = fits && ci <= (uint32_t)kWaveCand;
+  }
+  if (!(fits && nc >= (uint32_t)topk)) return false;   // (the same in every thread)
+  // A candidate belongs to T_k if fewer than K candidates are ahead of it (larger, or equal at a lower
+  // position: one comparison of the packed keys).  Up to 256 candidates are handled by the first wave alone,
+  // one or four of them in each lane, every lane's read by all in turn; the other waves retire.
+  auto candidate = [&](uint32_t c, uint64_t& key, float& x) __attribute__((always_inline)) {
+    uint32_t part = 0, idx = c;
+#pragma unroll
+    for (int i = 0; i < NW - 1; ++i) {
+      const uint32_t ci = S.cnt[i];
+      if (part == (uint32_t)i && idx >= ci) {
+        idx -= ci;
+        part = i + 1;
+      }
+    }
+    const bool have = c < nc;
+    key = have ? S.cand.key[part * kWaveCand + idx] : 0ull;      // (the filler is ahead of nothing)
+    x = have ? S.cand.val[part * kWaveCand + idx] : 0.f;
+  };
+  double wo = 0.0, wd = 0.0;
+  auto add = [&](bool in, uint64_t key, float x) __attribute__((always_inline)) {
+    const int32_t px = (int32_t)(~(uint32_t)key);
+    if (in && px >= needle_start && px < ne) wo += (double)x;
+    else if (in) wd += (double)x;
+  };
+  auto rank_in_wave = [&](auto per_c) __attribute__((always_inline)) {
+    constexpr int PER = decltype(per_c)::value;
+    uint64_t mine[PER];
+    float x[PER];
+    uint32_t ahead[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      candidate(q * kWave + lane, mine[q], x[q]);
+      ahead[q] = 0;
+    }
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int cnt = min((int)nc - p * kWave, kWave);
+#pragma unroll 4
+      for (int o = 0; o < cnt; ++o) {
+        const uint64_t ko = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine[p] >> 32), o) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine[p], o);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) ahead[q] += ko > mine[q] ? 1u : 0u;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) add((uint32_t)(q * kWave + lane) < nc && ahead[q] < (uint32_t)topk, mine[q], x[q]);
+    wo = wave_sum<double>(wo);
+    wd = wave_sum<double>(wd);
+  };
+  if (nc <= (uint32_t)kWave * 4u) {
+    if (wv != 0) return true;
+    if (nc <= (uint32_t)kWave) rank_in_wave(std::integral_constant<int, 1>{});
+    else rank_in_wave(std::integral_constant<int, 4>{});
+  } else {
+    for (uint32_t c = tid; c < (nc + NT - 1) / NT * NT; c += NT) {
+      uint64_t mine;
+      float x;
+      candidate(c, mine, x);
+      uint32_t ahead = 0;
+#pragma unroll 1
+      for (int p = 0; p < NW; ++p) {
+        const uint32_t cnt = S.cnt[p];
+        for (uint32_t o = 0; o < cnt; ++o) ahead += S.cand.key[p * kWaveCand + o] > mine ? 1u : 0u;
+      }
+      add(c < nc && ahead < (uint32_t)topk, mine, x);
+    }
+    wo = block_sum<NT, double>(wo, S.sh_d);
+    wd = block_sum<NT, double>(wd, S.sh_d);
+  }
+  if (tid == 0) store_cells(c_out, wo, wd, tot, tnw);
+  return true;
+}
+
+// General row path: any length, any K, any number of equal weights; the row is read from memory in every sweep.
+// RARE: reached from the resident path only, so kept small.
+template <int NT, bool RARE>
+__device__ __forceinline__ void row_cells_general(const float* __restrict__ W, int32_t n, int32_t needle_start,
+                                                  int32_t needle_len, int32_t topk, double* __restrict__ c_out, RowLds<NT>& S) {
+  const int tid = threadIdx.x;
+  const int32_t ne = needle_start + needle_len;
+  auto& hist = S.hist;
+  auto& sh_scan = S.sh_scan;
+  auto& res = S.res;
+  auto& sh_d = S.sh_d;
+  auto& sh_u = S.sh_u;
+  // f(position, value) over the row
+  auto sweep = [&](auto f) __attribute__((always_inline)) {
+    if constexpr (RARE) {
+#pragma unroll 1
+      for (int32_t j = tid; j < n; j += NT) f(j, W[j]);
+    } else {
+      for (int32_t j = tid; j < n; j += NT) f(j, W[j]);
+    }
+  };
+  double tot = 0.0, tnw = 0.0;           // row sum and needle sum, in double
+  sweep([&](int32_t, float x) { tot += (double)x; });
+  for (int32_t j = needle_start + tid; j < ne; j += NT) tnw += (double)W[j];
+  tot = block_sum<NT, double>(tot, sh_d);
+  tnw = block_sum<NT, double>(tnw, sh_d);
 
   // K-th largest weight: three histogram levels over the order-preserving key
   uint32_t prefix = 0, k = (uint32_t)topk;
@@ -258,14 +317,11 @@ __device__ __forceinline__ void row_cells_impl(const float* __restrict__ W, int3
   eq_all = block_sum<NT, uint32_t>(eq_all, sh_u);
   eq_needle = block_sum<NT, uint32_t>(eq_needle, sh_u);
   // every tie has the same value; fetch it from any thread that saw one
-  {
-    __shared__ float sh_tau;
-    if (tid == 0) sh_tau = 0.f;
-    __syncthreads();
-    if (float_key(tau_val) == tau) sh_tau = tau_val;
-    __syncthreads();
-    tau_val = sh_tau;
-  }
+  if (tid == 0) S.tau = 0.f;
+  __syncthreads();
+  if (float_key(tau_val) == tau) S.tau = tau_val;
+  __syncthreads();
+  tau_val = S.tau;
 
   uint32_t take_needle;                  // ties inside the needle that belong to T_k
   if (need_eq == eq_all) {
@@ -298,23 +354,21 @@ __device__ __forceinline__ void row_cells_impl(const float* __restrict__ W, int3
     });
     take_needle = block_sum<NT, uint32_t>(cntn, sh_u);
   }
-  if (tid == 0) {
-    const double WO = wo + (double)tau_val * (double)take_needle;
-    const double WD = wd + (double)tau_val * (double)(need_eq - take_needle);
-    const double WS = fmax(0.0, tnw - WO);
-    double* c = c_out;
-    c[0] = WO;
-    c[1] = WD;
-    c[2] = WS;
-    c[3] = tot - WO - WD - WS;
-  }
+  if (tid == 0) store_cells(c_out, wo + (double)tau_val * (double)take_needle, wd + (double)tau_val * (double)(need_eq - take_needle), tot, tnw);
 }
 
-template <bool RESIDENT>
-__global__ __launch_bounds__(kS1Threads, 4) void row_cells_kernel(const float* __restrict__ rows, int32_t n,
-                                                                  int32_t needle_start, int32_t needle_len, int32_t topk,
-                                                                  double* __restrict__ cells) {
-  row_cells_impl<RESIDENT>(rows + (int64_t)blockIdx.x * n, n, needle_start, needle_len, topk, cells + (int64_t)blockIdx.x * 4);
+// One workgroup per row; cells[row] = (WO, WD, WS, Wide).  NG = 0: the general path.
+template <int NT, int NG, bool WHOLE>
+__global__ __launch_bounds__(NT, 4) void row_cells_kernel(const float* __restrict__ rows, int32_t n, int32_t needle_start,
+                                                          int32_t needle_len, int32_t topk, double* __restrict__ cells) {
+  __shared__ RowLds<NT> S;
+  const float* W = rows + (int64_t)blockIdx.x * n;
+  double* c = cells + (int64_t)blockIdx.x * 4;
+  if constexpr (NG > 0) {
+    if (row_cells_resident<NT, NG, WHOLE>(W, n, needle_start, needle_len, topk, c, S)) return;
+    __syncthreads();                     // the candidate lists have been read
+  }
+  row_cells_general<NT, (NG > 0)>(W, n, needle_start, needle_len, topk, c, S);
 }
 
 // Steps 5-7 of Algorithm 1 (0/0 = 0); a component that is switched off enters as 0.
@@ -327,44 +381,59 @@ __device__ __forceinline__ void sf_lg(double WO, double WD, double WS, int use_w
   LG = (WO + WS) > 0.0 ? WO / (WO + WS) : 0.0;
 }
 
-// One thread per head: adds the head's T rows (in order) into the accumulators and finalises
-// SF, LG, INF (Algorithm 1, steps 5-7).  STRIDE 5: the accumulators of slkv_score_heads;
-// STRIDE 8: those of slkv_score_heads_ex, which also carry the sums of the per-row SF and LG.
+// One wave per head: adds the head's T rows (a fixed tree: results are bit-reproducible) into the accumulators
+// (fresh: which count as zero and are not read) and finalises SF, LG, INF (Algorithm 1, steps 5-7).  STRIDE 5:
+// the accumulators of slkv_score_heads; STRIDE 8: those of slkv_score_heads_ex, which also carry the sums of the
+// per-row SF and LG.
+// Bound: the latency of one load and, with STRIDE 8, of the rows' divisions: a lane per row (one thread per head,
+// its rows one after the other, took 5.4 us on 1024 heads x 16 rows).
+constexpr int kReduceHeads = 4;          // heads (waves) of a workgroup
+
 template <int STRIDE>
-__global__ void head_reduce_kernel(const double* __restrict__ cells, int32_t heads, int32_t T, double* __restrict__ acc,
-                                   double* __restrict__ scores, int macro, int use_wo, int use_wd, int use_ws) {
-  const int hd = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(64 * kReduceHeads) void head_reduce_kernel(const double* __restrict__ cells, int32_t heads, int32_t T,
+                                                                        double* __restrict__ acc, double* __restrict__ scores,
+                                                                        int fresh, int macro, int use_wo, int use_wd, int use_ws) {
+  const int lane = threadIdx.x & 63;
+  const int hd = blockIdx.x * kReduceHeads + (threadIdx.x >> 6);
   if (hd >= heads) return;
-  double a[4] = {0.0, 0.0, 0.0, 0.0}, sf_sum = 0.0, lg_sum = 0.0;
-  for (int t = 0; t < T; ++t) {
-    const double* c = cells + ((int64_t)hd * T + t) * 4;
-    for (int i = 0; i < 4; ++i) a[i] += c[i];
-    if (STRIDE == 8) {
+  double* A = acc + (int64_t)hd * STRIDE;
+  double was = 0.0;                      // lane i: accumulator i
+  if (!fresh && lane < STRIDE) was = A[lane];
+  const double2* c2 = reinterpret_cast<const double2*>(cells) + (int64_t)hd * T * 2;
+  double a[STRIDE == 8 ? 6 : 4] = {};
+  for (int t = lane; t < T; t += kWave) {
+    const double2 lo = c2[t * 2], hi = c2[t * 2 + 1];
+    a[0] += lo.x;
+    a[1] += lo.y;
+    a[2] += hi.x;
+    a[3] += hi.y;
+    if constexpr (STRIDE == 8) {
       double sf, lg;
-      sf_lg(c[0], c[1], c[2], use_wo, use_wd, use_ws, sf, lg);
-      sf_sum += sf;
-      lg_sum += lg;
+      sf_lg(lo.x, lo.y, hi.x, use_wo, use_wd, use_ws, sf, lg);
+      a[4] += sf;
+      a[5] += lg;
     }
   }
-  double* A = acc + (int64_t)hd * STRIDE;
-  for (int i = 0; i < 4; ++i) A[i] += a[i];
-  A[4] += (double)T;
-  if (STRIDE == 8) {
-    A[5] += sf_sum;
-    A[6] += lg_sum;
+#pragma unroll
+  for (int i = 0; i < (STRIDE == 8 ? 6 : 4); ++i) {
+    const double s = wave_sum<double>(a[i]);
+    was += lane == (i < 4 ? i : i + 1) ? s : 0.0;
   }
+  was += lane == 4 ? (double)T : 0.0;
+  if (lane < STRIDE) A[lane] = was;
   if (scores) {
+    double now[STRIDE];
+#pragma unroll
+    for (int i = 0; i < STRIDE; ++i) now[i] = __shfl(was, i, kWave);
     double SF, LG;
     if (STRIDE == 8 && macro) {
-      SF = A[4] > 0.0 ? A[5] / A[4] : 0.0;
-      LG = A[4] > 0.0 ? A[6] / A[4] : 0.0;
+      SF = now[4] > 0.0 ? now[STRIDE == 8 ? 5 : 0] / now[4] : 0.0;
+      LG = now[4] > 0.0 ? now[STRIDE == 8 ? 6 : 0] / now[4] : 0.0;
     } else {
-      sf_lg(A[0], A[1], A[2], use_wo, use_wd, use_ws, SF, LG);
+      sf_lg(now[0], now[1], now[2], use_wo, use_wd, use_ws, SF, LG);
     }
     const double INF = (SF + LG) > 0.0 ? 2.0 * SF * LG / (SF + LG) : 0.0;
-    scores[(int64_t)hd * 3 + 0] = SF;
-    scores[(int64_t)hd * 3 + 1] = LG;
-    scores[(int64_t)hd * 3 + 2] = INF;
+    if (lane < 3) scores[(int64_t)hd * 3 + lane] = lane == 0 ? SF : lane == 1 ? LG : INF;
   }
 }
 
@@ -827,6 +896,7 @@ __global__ __launch_bounds__(kS1Threads) void qk_fallback_kernel(const uint16_t*
                                                                  int needle_start, int needle_len, int topk, float c_log2,
                                                                  const unsigned char* __restrict__ overflow, float* __restrict__ slots,
                                                                  double* __restrict__ cells) {
+  __shared__ RowLds<kS1Threads> rowlds;
   __shared__ float qs[DK];
   __shared__ float red[kS1Threads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -894,7 +964,7 @@ __global__ __launch_bounds__(kS1Threads) void qk_fallback_kernel(const uint16_t*
     for (int j = tid; j < n; j += kS1Threads) W[j] *= inv;
     __threadfence_block();
     __syncthreads();
-    row_cells_impl<false>(W, n, needle_start, needle_len, topk, cells + row * 4);
+    row_cells_general<kS1Threads, true>(W, n, needle_start, needle_len, topk, cells + row * 4, rowlds);
     __syncthreads();
   }
   }
@@ -914,7 +984,7 @@ namespace {
 
 slkv_status run_score_heads(const float* d_rows, int32_t L, int32_t H, int32_t T, int64_t n, int64_t needle_start,
                             int32_t needle_len, int32_t topk, double* d_acc, double* d_scores, void* d_workspace,
-                            size_t workspace_bytes, void* hip_stream, const slkv_score_params* prm) {
+                            size_t workspace_bytes, void* hip_stream, const slkv_score_params* prm, bool fresh) {
   if (!d_rows || !d_acc || !d_workspace) return fail(SLKV_ERR_NULL, "d_rows, d_acc and d_workspace are required");
   if (L < 1 || H < 1 || T < 1 || n < 1) return fail(SLKV_ERR_BAD_ARG, "L, H, T, n must be >= 1");
   if (n >= (int64_t(1) << 31)) return fail(SLKV_ERR_BAD_ARG, "n >= 2^31");
@@ -931,25 +1001,41 @@ slkv_status run_score_heads(const float* d_rows, int32_t L, int32_t H, int32_t T
 
   hipStream_t st = (hipStream_t)hip_stream;
   double* cells = (double*)d_workspace;
-  const bool resident = (n % 4 == 0) && n >= 4 && n <= (int64_t)kS1Threads * kS1Resident && topk <= kWave;
+  // Whole 16-byte groups of a row, up to three floats of the row before it included: the threads of a row
+  // hold them at 4, 8 or 16 a thread.
+  const int64_t groups = (n % 4 == 0 ? n : n + 3) / 4;
   {
     ScopedKernelTimer tm(SLKV_K_ROW_CELLS, st);
-    if (resident)
-      SLKV_LAUNCH(row_cells_kernel<true>, dim3((unsigned)nrows), dim3(kS1Threads), 0, st, d_rows, (int32_t)n,
-                  (int32_t)needle_start, needle_len, topk, cells);
-    else
-      SLKV_LAUNCH(row_cells_kernel<false>, dim3((unsigned)nrows), dim3(kS1Threads), 0, st, d_rows, (int32_t)n,
-                  (int32_t)needle_start, needle_len, topk, cells);
+    auto launch = [&](auto nt, auto ng) {
+      constexpr int NT = decltype(nt)::value, NG = decltype(ng)::value;
+      if (n % 4 == 0)
+        SLKV_LAUNCH((row_cells_kernel<NT, NG, true>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
+                    (int32_t)needle_start, needle_len, topk, cells);
+      else
+        SLKV_LAUNCH((row_cells_kernel<NT, NG, false>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
+                    (int32_t)needle_start, needle_len, topk, cells);
+    };
+    using std::integral_constant;
+    if (topk > kS1TopK || n < 4 || groups > 1024 * kS1Groups) launch(integral_constant<int, kS1Threads>{}, integral_constant<int, 0>{});
+    else if (groups <= 64 * 4) launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+    else if (groups <= 64 * 8) launch(integral_constant<int, 64>{}, integral_constant<int, 8>{});
+    else if (groups <= 64 * 16) launch(integral_constant<int, 64>{}, integral_constant<int, 16>{});
+    else if (groups <= 128 * 16) launch(integral_constant<int, 128>{}, integral_constant<int, 16>{});
+    else if (groups <= 256 * 16) launch(integral_constant<int, 256>{}, integral_constant<int, 16>{});
+    else if (groups <= 512 * 16) launch(integral_constant<int, 512>{}, integral_constant<int, 16>{});
+    else launch(integral_constant<int, 1024>{}, integral_constant<int, 16>{});
   }
   const int heads = L * H;
   {
     ScopedKernelTimer tm(SLKV_K_HEAD_REDUCE, st);
     if (prm)
-      SLKV_LAUNCH(head_reduce_kernel<8>, dim3((heads + 127) / 128), dim3(128), 0, st, (const double*)cells, heads, T, d_acc,
-                  d_scores, (int)(prm->aggregation == SLKV_AGG_MACRO), prm->use_wo, prm->use_wd, prm->use_ws);
+      SLKV_LAUNCH(head_reduce_kernel<8>, dim3((heads + kReduceHeads - 1) / kReduceHeads), dim3(64 * kReduceHeads), 0, st,
+                  (const double*)cells, heads, T, d_acc,
+                  d_scores, (int)fresh, (int)(prm->aggregation == SLKV_AGG_MACRO), prm->use_wo, prm->use_wd, prm->use_ws);
     else
-      SLKV_LAUNCH(head_reduce_kernel<5>, dim3((heads + 127) / 128), dim3(128), 0, st, (const double*)cells, heads, T, d_acc,
-                  d_scores, 0, 1, 1, 1);
+      SLKV_LAUNCH(head_reduce_kernel<5>, dim3((heads + kReduceHeads - 1) / kReduceHeads), dim3(64 * kReduceHeads), 0, st,
+                  (const double*)cells, heads, T, d_acc,
+                  d_scores, (int)fresh, 0, 1, 1, 1);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SLKV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -963,15 +1049,12 @@ extern "C" slkv_status slkv_score_heads(const float* d_rows, int32_t L, int32_t 
                                         double* d_scores, void* d_workspace, size_t workspace_bytes, void* hip_stream) {
   clear_error();
   return run_score_heads(d_rows, L, H, T, n, needle_start, needle_len, topk, d_acc, d_scores, d_workspace, workspace_bytes,
-                         hip_stream, nullptr);
+                         hip_stream, nullptr, false);
 }
 
-extern "C" slkv_status slkv_score_heads_ex(const slkv_score_params* params, const float* d_rows, int32_t L, int32_t H,
-                                           int32_t T, int64_t n, int64_t needle_start, int32_t needle_len, int32_t topk,
-                                           double* d_acc, double* d_scores, void* d_workspace, size_t workspace_bytes,
-                                           void* hip_stream) {
-  clear_error();
-  if (!params) return fail(SLKV_ERR_NULL, "params is NULL");
+namespace {
+
+slkv_status check_score_params(const slkv_score_params* params) {
   if (params->struct_size != sizeof(slkv_score_params))
     return fail(SLKV_ERR_BAD_ARG, "params.struct_size %u != %zu", params->struct_size, sizeof(slkv_score_params));
   if (params->aggregation != SLKV_AGG_MICRO && params->aggregation != SLKV_AGG_MACRO)
@@ -980,8 +1063,34 @@ extern "C" slkv_status slkv_score_heads_ex(const slkv_score_params* params, cons
   for (int32_t f : flags)
     if (f != 0 && f != 1) return fail(SLKV_ERR_BAD_ARG, "use_wo / use_wd / use_ws must be 0 or 1");
   if (params->reserved != 0) return fail(SLKV_ERR_BAD_ARG, "params.reserved must be 0");
+  return SLKV_OK;
+}
+
+}  // namespace
+
+extern "C" slkv_status slkv_score_heads_ex(const slkv_score_params* params, const float* d_rows, int32_t L, int32_t H,
+                                           int32_t T, int64_t n, int64_t needle_start, int32_t needle_len, int32_t topk,
+                                           double* d_acc, double* d_scores, void* d_workspace, size_t workspace_bytes,
+                                           void* hip_stream) {
+  clear_error();
+  if (!params) return fail(SLKV_ERR_NULL, "params is NULL");
+  const slkv_status ps = check_score_params(params);
+  if (ps != SLKV_OK) return ps;
   return run_score_heads(d_rows, L, H, T, n, needle_start, needle_len, topk, d_acc, d_scores, d_workspace, workspace_bytes,
-                         hip_stream, params);
+                         hip_stream, params, false);
+}
+
+extern "C" slkv_status slkv_score_heads_first(const slkv_score_params* params, const float* d_rows, int32_t L, int32_t H,
+                                              int32_t T, int64_t n, int64_t needle_start, int32_t needle_len, int32_t topk,
+                                              double* d_acc, double* d_scores, void* d_workspace, size_t workspace_bytes,
+                                              void* hip_stream) {
+  clear_error();
+  if (params) {
+    const slkv_status ps = check_score_params(params);
+    if (ps != SLKV_OK) return ps;
+  }
+  return run_score_heads(d_rows, L, H, T, n, needle_start, needle_len, topk, d_acc, d_scores, d_workspace, workspace_bytes,
+                         hip_stream, params, true);
 }
 
 // ------------------------------------------------------------------ Stage 1 from queries and keys
@@ -1026,7 +1135,7 @@ hipError_t qk_prepare() {
 template <int DK>
 slkv_status qk_launch(const uint16_t* q, const uint16_t* k, int32_t L, int32_t Hq, int32_t Hkv, int32_t T, int32_t n,
                       int32_t needle_start, int32_t needle_len, int32_t topk, double* d_acc, double* d_scores,
-                      unsigned char* ws, const QkLayout& w, hipStream_t st) {
+                      unsigned char* ws, const QkLayout& w, hipStream_t st, bool fresh) {
   hipError_t pe = qk_prepare<DK>();
   if (pe != hipSuccess) return fail(SLKV_ERR_HIP, "kernel set-up failed: %s", hipGetErrorString(pe));
   const int G = Hq / Hkv, R = G * T, rowgroups = (R + kQkRows - 1) / kQkRows;
@@ -1048,8 +1157,9 @@ slkv_status qk_launch(const uint16_t* q, const uint16_t* k, int32_t L, int32_t H
   const int heads = L * Hq;
   {
     ScopedKernelTimer tm(SLKV_K_HEAD_REDUCE, st);
-    SLKV_LAUNCH(head_reduce_kernel<5>, dim3((heads + 127) / 128), dim3(128), 0, st, (const double*)cells, heads, T, d_acc,
-                d_scores, 0, 1, 1, 1);
+    SLKV_LAUNCH(head_reduce_kernel<5>, dim3((heads + kReduceHeads - 1) / kReduceHeads), dim3(64 * kReduceHeads), 0, st,
+                  (const double*)cells, heads, T, d_acc,
+                d_scores, (int)fresh, 0, 1, 1, 1);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SLKV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -1063,10 +1173,10 @@ extern "C" size_t slkv_score_heads_qk_workspace_bytes(int32_t L, int32_t Hq, int
   return qk_layout((int64_t)L * Hq * T, n).total;
 }
 
-extern "C" slkv_status slkv_score_heads_qk(const void* d_q, const void* d_k, int32_t L, int32_t Hq, int32_t Hkv, int32_t T,
-                                           int64_t n, int32_t d, int64_t needle_start, int32_t needle_len, int32_t topk,
-                                           double* d_acc, double* d_scores, void* d_workspace, size_t workspace_bytes,
-                                           void* hip_stream) {
+static slkv_status run_score_heads_qk(const void* d_q, const void* d_k, int32_t L, int32_t Hq, int32_t Hkv, int32_t T,
+                                      int64_t n, int32_t d, int64_t needle_start, int32_t needle_len, int32_t topk,
+                                      double* d_acc, double* d_scores, void* d_workspace, size_t workspace_bytes,
+                                      void* hip_stream, bool fresh) {
   clear_error();
   if (!d_q || !d_k || !d_acc || !d_workspace) return fail(SLKV_ERR_NULL, "d_q, d_k, d_acc and d_workspace are required");
   if (L < 1 || Hq < 1 || Hkv < 1 || T < 1 || n < 1) return fail(SLKV_ERR_BAD_ARG, "L, Hq, Hkv, T, n must be >= 1");
@@ -1088,7 +1198,23 @@ extern "C" slkv_status slkv_score_heads_qk(const void* d_q, const void* d_k, int
   hipStream_t st = (hipStream_t)hip_stream;
   if (d == 128)
     return qk_launch<128>((const uint16_t*)d_q, (const uint16_t*)d_k, L, Hq, Hkv, T, (int32_t)n, (int32_t)needle_start, needle_len,
-                          topk, d_acc, d_scores, (unsigned char*)d_workspace, w, st);
+                          topk, d_acc, d_scores, (unsigned char*)d_workspace, w, st, fresh);
   return qk_launch<64>((const uint16_t*)d_q, (const uint16_t*)d_k, L, Hq, Hkv, T, (int32_t)n, (int32_t)needle_start, needle_len, topk,
-                       d_acc, d_scores, (unsigned char*)d_workspace, w, st);
+                       d_acc, d_scores, (unsigned char*)d_workspace, w, st, fresh);
+}
+
+extern "C" slkv_status slkv_score_heads_qk(const void* d_q, const void* d_k, int32_t L, int32_t Hq, int32_t Hkv, int32_t T,
+                                           int64_t n, int32_t d, int64_t needle_start, int32_t needle_len, int32_t topk,
+                                           double* d_acc, double* d_scores, void* d_workspace, size_t workspace_bytes,
+                                           void* hip_stream) {
+  return run_score_heads_qk(d_q, d_k, L, Hq, Hkv, T, n, d, needle_start, needle_len, topk, d_acc, d_scores, d_workspace,
+                            workspace_bytes, hip_stream, false);
+}
+
+extern "C" slkv_status slkv_score_heads_qk_first(const void* d_q, const void* d_k, int32_t L, int32_t Hq, int32_t Hkv,
+                                                 int32_t T, int64_t n, int32_t d, int64_t needle_start, int32_t needle_len,
+                                                 int32_t topk, double* d_acc, double* d_scores, void* d_workspace,
+                                                 size_t workspace_bytes, void* hip_stream) {
+  return run_score_heads_qk(d_q, d_k, L, Hq, Hkv, T, n, d, needle_start, needle_len, topk, d_acc, d_scores, d_workspace,
+                            workspace_bytes, hip_stream, true);
 }
