@@ -51,6 +51,8 @@ __device__ __forceinline__ void store_cells(double* c, double WO, double WD, dou
 // A lower bound of the K-th largest weight comes from the lane maxima of each wave (K distinct elements); the
 // few weights at or above the bound are collected in LDS and ranked exactly (larger first, equal weights by
 // lower position).  Returns false, with nothing written, if a list overflows (many ties at the bound).
+// Bound: HBM.  32 x 32 heads x 16 rows of 16384 floats (1 GiB): 160-165 us, 6.6 TB/s.  Rows of 13867 floats went
+// through the general path, five sweeps over memory: 350 us for 227 MB; here 43 us, 5.2 TB/s.
 // WHOLE: every row is whole 16-byte groups (n % 4 == 0).
 template <int NT, int NG, bool WHOLE>
 __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, int32_t n, int32_t needle_start,
