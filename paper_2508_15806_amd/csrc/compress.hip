@@ -48,7 +48,6 @@ struct SegTable {
   int32_t seg_global[kMaxSegPerLaunch];  // index b*Hkv + h
   int32_t blk_begin[kMaxSegPerLaunch + 1];    // prefix of selection-block counts (no block when not ranked)
   int32_t hblk[kMaxSegPerLaunch];        // first block histogram of the segment
-  int32_t tick[kMaxSegPerLaunch];        // ticket slot of the segment (segments of several key chunks)
 };
 
 // The same table in device memory, for calls with more segments than fit a kernel argument.
@@ -56,13 +55,8 @@ struct SegTable {
 struct SegTableDev {
   int32_t nseg;
   int32_t total_chunks;
-  int32_t *tok_begin, *n, *kkeep, *out_off, *head, *qrow_off, *score_off, *chunk_begin, *seg_global, *blk_begin, *hblk, *tick;
+  int32_t *tok_begin, *n, *kkeep, *out_off, *head, *qrow_off, *score_off, *chunk_begin, *seg_global, *blk_begin, *hblk;
 };
-
-// The workspace starts with ticket words (zero between calls): slot t counts the key chunks of a
-// segment that have finished the statistics pass.
-constexpr int kTicketSlots = 16384;
-constexpr size_t kTicketBytes = (size_t)kTicketSlots * sizeof(uint32_t);
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -106,79 +100,49 @@ __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float 
   m = mn;
 }
 
-// Data that one workgroup writes and another workgroup of the SAME kernel reads (after a ticket
-// tells it that the writers are done) moves with device-scope accesses: the stores are written
-// through to memory and the loads do not take a line that another XCD's L2 may hold newer, so no
-// L2 write-back / invalidate (a device-scope fence costs tens of microseconds per kernel here) is
-// needed.  The writer waits for its stores (workgroup release fence + barrier) before one thread
-// takes the ticket.
-__device__ __forceinline__ void st_dev(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void st_dev(uint32_t* p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float ld_dev(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ uint32_t ld_dev(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// Takes a ticket of `count` arrivals after the workgroup's device-scope stores have completed.
-// Returns true in the workgroup that arrives last (its ticket word is zero again afterwards).
-// `flag` is one word of LDS.  Every thread of the workgroup must call it.
-__device__ __forceinline__ bool last_arrival(uint32_t* ticket, uint32_t count, uint32_t* flag) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the stores above have been performed
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old == count - 1u) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *flag = old;
-  }
-  __syncthreads();
-  const bool last = *flag == count - 1u;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  return last;
-}
-
-// Per-row log-sum-exp (log2 domain) of a segment from the log-sum-exp of its key chunks
-// (part[chunk][row]; -inf for a chunk without keys for the row), one thread per row.  The loads
-// of a batch are all in flight together and the exponentials are independent of each other;
-// only the additions run in chunk order, so the result does not depend on timing.
-__device__ __forceinline__ void segment_lse(int c0, int c1, int seg, int Rpad, const float* __restrict__ part,
-                                            float* __restrict__ lse) {
-  constexpr int NB = 64;   // as many loads as a wave can have in flight
-  for (int row = threadIdx.x; row < Rpad; row += blockDim.x) {
-    float mm = -INFINITY, ss = 0.f;
-    for (int c = c0; c < c1; c += NB) {
+// Start of the second scoring pass: log-sum-exp (log2 domain) of rows row0 .. of a segment from that of its key
+// chunks c0 .. c1 - 1 (part[chunk][row]; -inf for a chunk without keys for the row), in the threads tid < ROWS of the
+// workgroup's NT (row row0 + tid).  The chunks of a row are dealt to NT / ROWS threads in turn, whose sums are added
+// up in LDS (`fold`: NT entries), so every workgroup of the segment gets the same bits.  +inf for a row without any
+// key.  ROWS >= NT: a thread per row.  Every thread must call it; ends with a barrier if LDS was used.
+// (The chunk that arrives last at a per-segment ticket did this at the end of the first pass: 4 us there, against
+// 0.5 to 3 us here, where the loads travel with those of the keys and queries.)
+__device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c0, int c1, int Rpad, int row0, int rows, int nt,
+                                           float2* fold) {
+  const int tid = threadIdx.x;
+  const int nsub = rows < nt ? nt / rows : 1;
+  const int row = nsub > 1 ? tid % rows : tid, sub = nsub > 1 ? tid / rows : 0;
+  float mm = -INFINITY, ss = 0.f;
+  if (sub < nsub && row0 + row < Rpad) {
+    constexpr int NB = 16;
+    for (int c = c0 + sub; c < c1; c += NB * nsub) {
       float v[NB];
 #pragma unroll
-      for (int u = 0; u < NB; ++u) v[u] = c + u < c1 ? ld_dev(part + (int64_t)(c + u) * Rpad + row) : -INFINITY;
+      for (int u = 0; u < NB; ++u) v[u] = part[(int64_t)min(c + u * nsub, c1 - 1) * Rpad + row0 + row];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) v[u] = c + u * nsub < c1 ? v[u] : -INFINITY;
       float bm = v[0];
 #pragma unroll
       for (int u = 1; u < NB; ++u) bm = fmaxf(bm, v[u]);
       const float mn = fmaxf(mm, bm);
       const float mu = mn == -INFINITY ? 0.f : mn;
-      float e[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) e[u] = fast_exp2(v[u] - mu);
       ss *= fast_exp2(mm - mu);
 #pragma unroll
-      for (int u = 0; u < NB; ++u) ss += e[u];
+      for (int u = 0; u < NB; ++u) ss += fast_exp2(v[u] - mu);
       mm = mn;
     }
-    lse[seg * Rpad + row] = ss > 0.f ? mm + log2f(ss) : INFINITY;
   }
-}
-
-// End of the statistics pass of one key chunk (its pairs are written): the chunk that arrives
-// last at the segment's ticket folds all chunks into the segment's log-sum-exp and clears the
-// ticket for the next call.  `flag` is one word of LDS.
-template <class TAB>
-__device__ __forceinline__ void finish_stats_chunk(const TAB& tab, int seg, int Rpad, const float* __restrict__ part,
-                                                   float* __restrict__ lse, uint32_t* __restrict__ tickets, uint32_t* flag) {
-  const int c0 = tab.chunk_begin[seg], c1 = tab.chunk_begin[seg + 1];
-  if (c1 - c0 > 1) {
-    if (!last_arrival(tickets + tab.tick[seg], (uint32_t)(c1 - c0), flag)) return;
-    SLKV_STAMP(256 + blockIdx.x, 3);
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if (nsub > 1) {
+    fold[tid] = make_float2(mm, ss);
+    __syncthreads();
+    if (sub == 0)
+      for (int v = 1; v < nsub; ++v) {
+        const float2 o = fold[v * rows + row];
+        merge_stats(mm, ss, o.x, o.y);
+      }
     __syncthreads();
   }
-  segment_lse(c0, c1, seg, Rpad, part, lse);
+  return ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : INFINITY;
 }
 
 // The two workgroups that share a CU would otherwise run one after the other: the scheduler
@@ -194,7 +158,7 @@ __device__ __forceinline__ void tile_priority(int t) {
 }
 
 // ------------------------------------------------------------------------------------------
-// MFMA scoring of 16-bit inputs (bfloat16, or half when F16).  One workgroup (4 waves) owns one chunk of history keys of one segment.
+// MFMA scoring of 16-bit inputs (bfloat16 or half).  One workgroup (4 waves) owns one chunk of history keys of one segment.
 // K is staged in LDS in tiles of 64 keys (two buffers); up to kPrefetch further tiles are in
 // flight from HBM into registers.  Wave (rb, ks) holds rows [rb*32*MT, (rb+1)*32*MT) of the
 // G*w query rows in registers for the whole chunk and works on the 32-key sub-tiles
@@ -207,30 +171,24 @@ __device__ __forceinline__ void tile_priority(int t) {
 constexpr int kTileKeys = 64;
 constexpr int kPrefetch = 2;
 
-template <int DK, int MT, int RB, int PASS, int KIND, class TAB>   // KIND: 0 bf16, 1 fp16, 2 bf16 queries with E4M3 keys
-__global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_bf16_kernel(const TAB tab, const uint16_t* __restrict__ q,
+template <int DK, int MT, int RB, int PASS, int KIND, class TAB>   // KIND: 0 bf16, 1 fp16
+__global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kernel(const TAB tab, const uint16_t* __restrict__ q,
                                                          const void* __restrict__ kmat_v, int64_t k_stride_tok,
                                                          int64_t k_stride_head, int R, int Rpad, int w, int CH,
                                                          float c_log2, float* __restrict__ part,
-                                                         const float* __restrict__ lse, float* __restrict__ imp,
-                                                         float* __restrict__ lse_out, uint32_t* __restrict__ tickets,
-                                                         int grid2d) {
+                                                         float* __restrict__ imp, int grid2d) {
   constexpr int KS = 4 / RB;               // waves along the keys
   constexpr int TK = kTileKeys;
   constexpr int NSUB = TK / 32 / KS;       // 32-key sub-tiles per wave per tile
   constexpr int KK = DK / 16;
   constexpr int ROWB = DK * 2 + 16;        // padded LDS row (bf16 / fp16 elements): conflict-free 16-byte reads down a column
-  constexpr bool KF8 = KIND == 2;          // keys arrive as E4M3 bytes and are widened to bf16 on their way into LDS
-  constexpr int EB = KF8 ? 1 : 2;          // bytes per key element in memory
-  constexpr int CPR = DK * EB / 16;        // 16-byte pieces per key row in memory
+  constexpr int CPR = DK * 2 / 16;          // 16-byte pieces per key row in memory
   constexpr int LPT = TK * CPR / 256;      // pieces per thread per tile
   constexpr int NPF = kPrefetch;
   static_assert(TK * CPR % 256 == 0 && LPT < 16, "tile must divide over the workgroup; LPT is or-ed into a wait count");
   __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TK * ROWB];
   __shared__ float red[2][RB][TK];
   __shared__ float2 comb[KS][RB * 32 * MT];
-  __shared__ uint32_t sh_flag;
-
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int rb = wv % RB, ks = wv / RB;
   const int l32 = lane & 31, half = lane >> 5;
@@ -269,8 +227,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_bf16_kernel(cons
   const int ntiles = ((key_end - key_begin + TK - 1) / TK + 1) & ~1;
   // uniform 64-bit base of the segment's keys + 32-bit byte offsets (the host checks the range)
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat_v) +
-      ((int64_t)se.head * k_stride_head + (int64_t)se.tok_begin * k_stride_tok) * EB;
-  const uint32_t row_bytes = (uint32_t)k_stride_tok * (uint32_t)EB;
+      ((int64_t)se.head * k_stride_head + (int64_t)se.tok_begin * k_stride_tok) * 2;
+  const uint32_t row_bytes = (uint32_t)k_stride_tok * 2u;
   const uint32_t piece_off = (uint32_t)(tid % CPR) * 16u;
   const int piece_row = tid / CPR;
 
@@ -288,30 +246,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_bf16_kernel(cons
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
       const int idx = i * 256 + tid;
-      if constexpr (KF8) {
-        // 16 E4M3 bytes -> 16 bf16: the hardware converter gives exact fp32 values (checked against the
-        // format's definition for all 256 codes), whose upper halves are the bf16 patterns
-        u32x4 lo, hi;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8((int)pf[i][j], false);
-          const f32x2 b = __builtin_amdgcn_cvt_pk_f32_fp8((int)pf[i][j], true);
-          const uint32_t p0 = __builtin_amdgcn_perm(__float_as_uint(a[1]), __float_as_uint(a[0]), 0x07060302u);
-          const uint32_t p1 = __builtin_amdgcn_perm(__float_as_uint(b[1]), __float_as_uint(b[0]), 0x07060302u);
-          if (j < 2) {
-            lo[2 * j] = p0;
-            lo[2 * j + 1] = p1;
-          } else {
-            hi[2 * (j - 2)] = p0;
-            hi[2 * (j - 2) + 1] = p1;
-          }
-        }
-        unsigned char* dst = &ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 32];
-        *reinterpret_cast<u32x4*>(dst) = lo;
-        *reinterpret_cast<u32x4*>(dst + 16) = hi;
-      } else {
-        *reinterpret_cast<u32x4*>(&ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
-      }
+      *reinterpret_cast<u32x4*>(&ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
     }
   };
   static_assert(NPF == 2, "the tile loop below is written out for two register slots");
@@ -329,14 +264,15 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_bf16_kernel(cons
       qreg[mt][kk] = p.b;
     }
   }
-  // pass 2: the log-sum-exp of the workgroup's rows, one coalesced load per thread here, handed
-  // to the lanes through LDS once the loads have landed
-  constexpr int NLSE = (RB * 32 * MT + 255) / 256;
+  // pass 2: log-sum-exp of the rows from that of the segment's chunks (see fold_rows), handed to the lanes
+  // through LDS once the other loads have landed
+  constexpr int ROWS = RB * 32 * MT, NLSE = (ROWS + 255) / 256;
   float lse_ld[PASS == 2 ? NLSE : 1];
   float lse_r[PASS == 2 ? MT : 1][16];
   if (PASS == 2) {
+    float2* const fold = reinterpret_cast<float2*>(&ktile[0][0]);   // (no key has been stored yet)
 #pragma unroll
-    for (int j = 0; j < NLSE; ++j) lse_ld[j] = lse[seg * Rpad + min(tid + j * 256, Rpad - 1)];
+    for (int j = 0; j < NLSE; ++j) lse_ld[j] = fold_rows(part, se.chunk0, se.chunk1, Rpad, j * 256, ROWS, 256, fold);
   }
   float m_run[MT], s_run[MT];
 #pragma unroll
@@ -633,119 +569,352 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_bf16_kernel(cons
 #pragma unroll
       for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
       // the chunk's log-sum-exp of the row (-inf: no key)
-      if (row < Rpad) st_dev(part + (int64_t)bid * Rpad + row, ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY);
+      if (row < Rpad) part[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
     }
     SLKV_STAMP(256 + bid, 2);
-    finish_stats_chunk(tab, seg, Rpad, part, lse_out, tickets, &sh_flag);
-    SLKV_STAMP(256 + bid, 4);
   }
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 scoring with plain FMAs (small shapes).  Same chunking and outputs as the bf16 kernels.
-// PASS 1: thread = query row, K tile in LDS (broadcast reads).  PASS 2: thread = key, Q rows in LDS.
-template <int DK, int PASS, class TAB>
-__global__ __launch_bounds__(256) void score_f32_kernel(const TAB tab, const float* __restrict__ q,
-                                                        const float* __restrict__ kmat, int64_t k_stride_tok,
-                                                        int64_t k_stride_head, int R, int Rpad, int w, int CH,
-                                                        float c_log2, float* __restrict__ part,
-                                                        const float* __restrict__ lse, float* __restrict__ imp,
-                                                        float* __restrict__ lse_out, uint32_t* __restrict__ tickets) {
-  constexpr int TROWS = 32;                 // keys (pass 1) or query rows (pass 2) per LDS tile
-  constexpr int NSUB = 256 / TROWS;         // thread = (lane32, sub): 32 rows x 8 key subsets, or 32 keys x 8 row subsets
-  __shared__ __attribute__((aligned(16))) float tile[TROWS][DK];
-  __shared__ float lse_s[TROWS];
-  __shared__ float2 red[NSUB][TROWS];
-  __shared__ uint32_t sh_flag;
-  const int tid = threadIdx.x;
-  const int l32 = tid & (TROWS - 1), sub = tid / TROWS;
-  const int bid = blockIdx.x;
-  const int seg = find_segment(tab.chunk_begin, tab.nseg, bid);
-  const int chunk = bid - tab.chunk_begin[seg];
-  const int m = tab.n[seg] - w;
-  const int key_begin = chunk * CH;
-  const int key_end = min(m, key_begin + CH);
-  const float* kbase = kmat + (int64_t)tab.head[seg] * k_stride_head + (int64_t)tab.tok_begin[seg] * k_stride_tok;
-  const float* qbase = q + (int64_t)tab.qrow_off[seg] * DK;
+// Scoring of E4M3 keys (bf16 queries) and of fp32 inputs, on the matrix cores.
+//
+// A workgroup (4 or 8 waves) owns one chunk of history keys of one segment.  The query rows of the segment
+// (in blocks of RBT 32-row tiles) sit in LDS, staged once; a wave holds a group of GK keys in registers as
+// MFMA operands, loaded straight from memory (16 bytes of one key row per lane and load), and walks the query
+// tiles over it while the loads of its next group are in flight.  Nothing is shared between the waves inside
+// the loop, so there is no barrier in it and no key passes through LDS; E4M3 keys are widened to bf16 once, in
+// registers.
+//   PASS 1: D[key][row]: a lane owns one query row per tile -> sum of exp2(x - reference), kept per lane in
+//           LDS between the groups; at the end the chunk's log-sum-exp of every row goes to `part`.
+//   PASS 2: the segment's chunks are folded into the rows' log-sum-exp while the first keys are on their way;
+//           D[row][key]: a lane owns one key per tile -> sum over all rows of exp2(x - lse[row]).
+// A segment of a single chunk needs nobody else's rows: PASS 1 runs both passes over it.
+//
+// fp32 products run on the 32x32x2 fp32 MFMA: twice the rate of plain FMAs, and an operand is read from LDS once
+// for 32 products instead of once for each (4 heads x 1024 keys, d 64: 16.4 + 12.1 us with FMAs, 8.6 + 7.8 us).
+// E4M3, 8 heads x 32704 keys x 256 rows: 29.0 + 25.5 -> 26.5 + 23.2 us against score_q_resident_kernel's layout,
+// which widened every key on its way into LDS.  For 16-bit keys that layout is the better one (see there): at
+// these sizes both are bound by the power that the MFMAs and exponentials take, and it takes less.
+//
+// The 32x32x16 MFMA takes, per lane, 8 consecutive k-elements of row (lane%32) at k offset 8*(lane/32) for both
+// operands (the 32x32x2 fp32 MFMA: one element, k offset lane/32) and returns in result register i the element
+// at row 8*(i/4) + 4*(lane/32) + i%4, column lane%32.  Which 16-byte pieces of the rows meet in which MFMA is
+// free as long as keys and queries agree: piece i of a key row is bytes 32*i + 16*(lane/32) of it.
+// Rows beyond R and keys beyond the chunk are loaded from a clamped (valid) address and masked.
+template <int DK, int KIND>   // KIND: 2 bf16 queries with E4M3 keys, 3 fp32
+struct ScoreCfg {
+  static constexpr bool F32 = KIND == 3, F8 = KIND == 2;
+  static constexpr int QB = F32 ? 4 : 2;              // bytes of a query element
+  static constexpr int KB = F32 ? 4 : 1;              // bytes of a key element in memory
+  static constexpr int ROWB = DK * QB + 16;           // padded LDS row: conflict-free 16-byte reads down a column
+  static constexpr int PPR = DK * QB / 16;            // 16-byte pieces of a query row
+  static constexpr int KK = PPR / 2;                  // operand pieces per lane and row
+  static constexpr int RAW = DK * KB / 32;            // pieces per lane and key as they come from memory
+  static constexpr int KT = F32 && DK == 128 ? 1 : 2; // 32-key tiles of a group
+  static constexpr int GK = 32 * KT;
+  static constexpr int RBT = F32 && DK == 128 ? 4 : 8;   // query tiles per row block
+};
 
-  if (PASS == 1) {
-    // 32 query rows at a time; the thread's key subset is keys sub, sub + 8, ... of every tile
-    for (int r0 = 0; r0 < Rpad; r0 += TROWS) {
-      const int row = r0 + l32;
-      float qr[DK];
-#pragma unroll
-      for (int p = 0; p < DK; ++p) qr[p] = row < R ? qbase[(int64_t)row * DK + p] : 0.f;
-      float mm = -INFINITY, ss = 0.f;
-      for (int k0 = key_begin; k0 < key_end; k0 += TROWS) {
-        __syncthreads();
-        for (int idx = tid; idx < TROWS * DK; idx += 256) {
-          const int kr = idx / DK, p = idx % DK;
-          tile[kr][p] = k0 + kr < key_end ? kbase[(int64_t)(k0 + kr) * k_stride_tok + p] : 0.f;
-        }
-        __syncthreads();
-        float x[TROWS / NSUB];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < TROWS / NSUB; ++i) {
-          const int kr = sub + i * NSUB;
-          float acc = 0.f;
-#pragma unroll
-          for (int p = 0; p < DK; ++p) acc = fmaf(qr[p], tile[kr][p], acc);
-          x[i] = k0 + kr < key_end ? acc * c_log2 : -INFINITY;
-          mx = fmaxf(mx, x[i]);
-        }
-        const float mn = fmaxf(mm, mx);
-        const float mu = mn == -INFINITY ? 0.f : mn;
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < TROWS / NSUB; ++i) sum += fast_exp2(x[i] - mu);
-        ss = ss * fast_exp2(mm - mu) + sum;
-        mm = mn;
-      }
-      __syncthreads();
-      red[sub][l32] = make_float2(mm, ss);
-      __syncthreads();
-      if (sub == 0) {
-#pragma unroll
-        for (int k2 = 1; k2 < NSUB; ++k2) merge_stats(mm, ss, red[k2][l32].x, red[k2][l32].y);
-        st_dev(part + (int64_t)bid * Rpad + row, (row < R && ss > 0.f) ? mm + __builtin_amdgcn_logf(ss) : -INFINITY);
-      }
-    }
-    finish_stats_chunk(tab, seg, Rpad, part, lse_out, tickets, &sh_flag);
+// LDS of a scoring workgroup: query tiles of a row block, {reference, sum} per (wave, tile, lane) or the
+// merge buffer of the prologue, log-sum-exp of the block's rows.
+template <int DK, int KIND>
+constexpr size_t score_lds_bytes(int tiles, int waves) {
+  return (size_t)tiles * 32 * ScoreCfg<DK, KIND>::ROWB + (size_t)waves * tiles * 64 * sizeof(float2) + (size_t)tiles * 32 * sizeof(float);
+}
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
+template <int DK, int KIND, int PASS, class TAB>
+__global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab, const void* __restrict__ qmat, const void* __restrict__ kmat,
+                                                       int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w,
+                                                       int CH, float c_log2, float* __restrict__ part, float* __restrict__ imp,
+                                                       int grid2d) {
+  using C = ScoreCfg<DK, KIND>;
+  constexpr int KK = C::KK, KT = C::KT, RAW = C::RAW, GK = C::GK, RBT = C::RBT, ROWB = C::ROWB, PPR = C::PPR;
+  extern __shared__ __attribute__((aligned(16))) unsigned char score_smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nthr = blockDim.x, NW = nthr >> 6;
+  const int l32 = lane & 31, half = lane >> 5;
+
+  // Which chunk of which segment.  With a two-dimensional grid (grid2d; the host chooses it when the
+  // segments' chunk counts are alike enough) blockIdx.y is the segment and blockIdx.x the chunk, and
+  // workgroups past a segment's last chunk leave at once; otherwise blockIdx.x counts the chunks of
+  // all segments and the segment is searched in the table.  The table is read through the scalar
+  // cache, cold at every launch, so each dependent lookup costs a memory round trip before the
+  // first key can be requested: the entries of segment blockIdx.y are therefore fetched before it
+  // is known which case applies (y is 0 with a one-dimensional grid: a valid entry either way).
+  struct SegEntry {
+    int32_t n, tok_begin, head, qrow_off, chunk0, chunk1;
+  };
+  auto entry_of = [&](int s) {
+    return SegEntry{tab.n[s], tab.tok_begin[s], tab.head[s], tab.qrow_off[s], tab.chunk_begin[s], tab.chunk_begin[s + 1]};
+  };
+  int seg = (int)blockIdx.y;
+  SegEntry se = entry_of(seg);
+  asm volatile("" :: "s"(se.n), "s"(se.tok_begin), "s"(se.head), "s"(se.qrow_off), "s"(se.chunk0), "s"(se.chunk1));   // fetched here, not behind the branch
+  int bid;
+  if (grid2d) {
+    bid = se.chunk0 + (int)blockIdx.x;
+    if (bid >= se.chunk1) return;
   } else {
-    // 32 keys at a time; the thread's row subset is rows sub, sub + 8, ... of every query tile
-    for (int k0 = key_begin; k0 < key_end; k0 += TROWS) {
-      const int key = k0 + l32;
-      float kr[DK];
+    bid = blockIdx.x;
+    seg = find_segment(tab.chunk_begin, tab.nseg, bid);
+    se = entry_of(seg);
+  }
+  const int nchunks = se.chunk1 - se.chunk0;
+  if (PASS == 2 && nchunks == 1) return;               // done by pass 1
+  const int key_begin = (bid - se.chunk0) * CH;
+  const int key_end = min(se.n - w, key_begin + CH);
+  const int ngroups = (key_end - key_begin + GK - 1) / GK;
+  // uniform 64-bit base of the segment's keys + 32-bit byte offsets (the host checks the range)
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat) +
+      ((int64_t)se.head * k_stride_head + (int64_t)se.tok_begin * k_stride_tok) * C::KB;
+  const uint32_t row_bytes = (uint32_t)k_stride_tok * (uint32_t)C::KB;
+
+  // ---- the keys: group g of the chunk as this wave's operand registers
+  u32x4 rawA[KT][RAW], rawB[KT][RAW];
+  auto load = [&](u32x4 (&raw)[KT][RAW], int g) __attribute__((always_inline)) {
 #pragma unroll
-      for (int p = 0; p < DK; ++p) kr[p] = key < key_end ? kbase[(int64_t)key * k_stride_tok + p] : 0.f;
-      float colsum = 0.f;
-      for (int r0 = 0; r0 < R; r0 += TROWS) {
-        __syncthreads();
-        for (int idx = tid; idx < TROWS * DK; idx += 256) {
-          const int rr = idx / DK, p = idx % DK;
-          tile[rr][p] = r0 + rr < R ? qbase[(int64_t)(r0 + rr) * DK + p] : 0.f;
-        }
-        if (tid < TROWS) lse_s[tid] = r0 + tid < R ? lse[seg * Rpad + r0 + tid] : INFINITY;
-        __syncthreads();
+    for (int kt = 0; kt < KT; ++kt) {
+      const int key = min(key_begin + g * GK + kt * 32 + l32, key_end - 1);
+      const unsigned char* row = kbase + ((uint32_t)key * row_bytes + (uint32_t)half * 16u);
 #pragma unroll
-        for (int i = 0; i < TROWS / NSUB; ++i) {
-          const int rr = sub + i * NSUB;
-          float acc = 0.f;
+      for (int i = 0; i < RAW; ++i) raw[kt][i] = *reinterpret_cast<const u32x4*>(row + i * 32);
+    }
+  };
+  // f(registers, group) over this wave's groups wv, wv + NW, ..., two in registers in turn.  The loads past
+  // the last group are issued too (of the chunk's last key): only so does the compiler know how many loads
+  // follow those it waits for.  preloaded: the first two groups are on their way already.
+  auto sweep = [&](bool preloaded, auto f) __attribute__((always_inline)) {
+    int g = wv;
+    if (g >= ngroups) return;
+    if (!preloaded) {
+      load(rawA, g);
+      load(rawB, g + NW);
+    }
+    for (;;) {
+      f(rawA, g);
+      load(rawA, g + 2 * NW);
+      g += NW;
+      if (g >= ngroups) break;
+      f(rawB, g);
+      load(rawB, g + 2 * NW);
+      g += NW;
+      if (g >= ngroups) break;
+    }
+  };
+  // pieces of a group as MFMA operands: what came from memory, or E4M3 bytes widened to bf16 (the hardware
+  // converter gives exact fp32 values, checked against the format's definition for all 256 codes, whose upper
+  // halves are the bf16 patterns; memory piece p becomes operand pieces 2p and 2p + 1)
+  auto widen = [&](const u32x4 (&raw)[KT][RAW], u32x4 (&op)[KT][KK]) __attribute__((always_inline)) {
 #pragma unroll
-          for (int p = 0; p < DK; ++p) acc = fmaf(tile[rr][p], kr[p], acc);
-          colsum += fast_exp2(fmaf(acc, c_log2, -lse_s[rr]));   // rows past R: exp2(-inf) = 0
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int p = 0; p < RAW; ++p) {
+        if constexpr (C::F8) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[kt][p][j], false);
+            const f32x2 b = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[kt][p][j], true);
+            op[kt][2 * p + (j >> 1)][2 * (j & 1)] = __builtin_amdgcn_perm(__float_as_uint(a[1]), __float_as_uint(a[0]), 0x07060302u);
+            op[kt][2 * p + (j >> 1)][2 * (j & 1) + 1] = __builtin_amdgcn_perm(__float_as_uint(b[1]), __float_as_uint(b[0]), 0x07060302u);
+          }
+        } else {
+          op[kt][p] = raw[kt][p];
         }
       }
-      __syncthreads();
-      red[sub][l32].x = colsum;
-      __syncthreads();
-      if (sub == 0) {
+  };
+  // ---- the queries: LDS address of this lane's piece kk of its row of tile rt
+  unsigned char* const qs = score_smem;
+  auto q_piece = [&](int rt, int kk) __attribute__((always_inline)) {
+    // E4M3 keys: memory piece p holds elements 32p + 16*half .. + 15, in operand pieces 2p, 2p + 1
+    const int off = C::F8 ? (kk >> 1) * 64 + half * 32 + (kk & 1) * 16 : kk * 32 + half * 16;
+    return *reinterpret_cast<const u32x4*>(qs + (rt * 32 + l32) * ROWB + off);
+  };
+  // logits of a group's keys and query tile rt (unscaled): keys x rows (pass 1) or rows x keys (pass 2)
+  auto logits = [&](const u32x4 (&op)[KT][KK], int rt, auto keys_first_c, f32x16 (&acc)[KT]) __attribute__((always_inline)) {
+    constexpr bool KEYS_FIRST = decltype(keys_first_c)::value;
+    f32x16 z;
 #pragma unroll
-        for (int k2 = 1; k2 < NSUB; ++k2) colsum += red[k2][l32].x;
-        if (key < key_end) imp[tab.score_off[seg] + key] = colsum;
+    for (int i = 0; i < 16; ++i) z[i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const u32x4 qp = q_piece(rt, kk);
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+        if constexpr (C::F32) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float kf = __uint_as_float(op[kt][kk][e]), qf = __uint_as_float(qp[e]);
+            acc[kt] = __builtin_amdgcn_mfma_f32_32x32x2f32(KEYS_FIRST ? kf : qf, KEYS_FIRST ? qf : kf, kk + e ? acc[kt] : z, 0, 0, 0);
+          }
+        } else {
+          Pack16 kp, qq;
+          kp.u = op[kt][kk];
+          qq.u = qp;
+          acc[kt] = mfma16<false>(KEYS_FIRST ? kp.b : qq.b, KEYS_FIRST ? qq.b : kp.b, kk ? acc[kt] : z);
+        }
       }
     }
+  };
+
+  // ---- LDS behind the queries (sized for the first row block, the largest)
+  const int tiles0 = min((R + 31) >> 5, RBT);
+  float2* const stat = reinterpret_cast<float2*>(score_smem + (size_t)tiles0 * 32 * ROWB);   // [wave][tile][lane]
+  float* const lse_s = reinterpret_cast<float*>(stat + (size_t)NW * tiles0 * 64);             // [row of the block]
+
+  bool preloaded = true;
+  load(rawA, wv);
+  for (int rb0 = 0; rb0 < R; rb0 += RBT * 32) {
+    const int rows = min(R - rb0, RBT * 32), rts = (rows + 31) >> 5;
+    // queries of the block: memory -> LDS
+    if (rb0 > 0) __syncthreads();
+    {
+      const unsigned char* qsrc = reinterpret_cast<const unsigned char*>(qmat) + ((int64_t)se.qrow_off + rb0) * (DK * C::QB);
+      const int pieces = rts * 32 * PPR;
+      for (int i0 = tid; i0 < pieces; i0 += 8 * nthr) {
+        u32x4 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int i = min(i0 + u * nthr, pieces - 1);
+          t[u] = *reinterpret_cast<const u32x4*>(qsrc + (size_t)min(i / PPR, rows - 1) * (DK * C::QB) + (i % PPR) * 16);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int i = min(i0 + u * nthr, pieces - 1);
+          *reinterpret_cast<u32x4*>(qs + (i / PPR) * ROWB + (i % PPR) * 16) = t[u];
+        }
+      }
+    }
+    if (preloaded) load(rawB, wv + NW);                // behind the queries: the first group does not wait for it
+
+    if (PASS == 1) {
+      float2* const mine = stat + (size_t)wv * tiles0 * 64 + lane;
+      for (int rt = 0; rt < rts; ++rt) mine[rt * 64] = make_float2(0.f, 0.f);
+      __syncthreads();
+      // ONLINE: running maximum instead of a fixed reference
+      auto stats_group = [&](const u32x4 (&raw)[KT][RAW], int g, auto online_c) __attribute__((always_inline)) {
+        constexpr bool ONLINE = decltype(online_c)::value;
+        u32x4 op[KT][KK];
+        widen(raw, op);
+        const int key0 = key_begin + g * GK;
+        const bool first = g == wv, tail = key0 + GK > key_end;
+#pragma unroll 1
+        for (int rt = 0; rt < rts; ++rt) {
+          float2 st = mine[rt * 64];
+          f32x16 acc[KT];
+          logits(op, rt, std::true_type{}, acc);
+          // lane: query row l32 of the tile, keys key0 + kt*32 + 8*(i/4) + 4*half + i%4
+          if (tail) {
+            int left = key_end - key0 - 4 * half;
+            asm volatile("" : "+v"(left));               // the comparisons stay here (hoisted out of the loop they would spill)
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+              for (int i = 0; i < 16; ++i)
+                if (kt * 32 + 8 * (i >> 2) + (i & 3) >= left) acc[kt][i] = -INFINITY;
+          }
+          if (first || ONLINE) {
+            // The reference of the exponentials is fixed by the lane's first logits of the chunk (any finite
+            // reference gives the same log-sum-exp); later logits may exceed it by up to ~2^100 before the
+            // sum overflows, which is detected below and repeated ONLINE.
+            float mx = acc[0][0];
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[kt][i]);
+            const float ref = mx == -INFINITY ? (first ? 0.f : st.x) : mx * c_log2;
+            if (first) {
+              st = make_float2(ref, 0.f);
+            } else if (ref > st.x) {
+              st.y *= fast_exp2(st.x - ref);
+              st.x = ref;
+            }
+          }
+          float sum[KT];
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) {
+            sum[kt] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum[kt] += fast_exp2(fmaf(acc[kt][i], c_log2, -st.x));
+          }
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) st.y += sum[kt];
+          mine[rt * 64] = st;
+        }
+      };
+      sweep(preloaded, [&](const u32x4 (&raw)[KT][RAW], int g) __attribute__((always_inline)) { stats_group(raw, g, std::false_type{}); });
+      bool bad = false;
+      for (int rt = 0; rt < rts; ++rt) bad = bad || !(mine[rt * 64].y < INFINITY);
+      if (__syncthreads_or(bad ? 1 : 0)) {
+        // a sum that left the fp32 range (logits far above the chunk's first ones); not taken for ordinary inputs
+        for (int g = wv; g < ngroups; g += NW) {
+          load(rawA, g);
+          stats_group(rawA, g, std::true_type{});
+        }
+        preloaded = false;
+        __syncthreads();
+      } else {
+        preloaded = false;
+      }
+      // the chunk's log-sum-exp of every row of the block (-inf: no key)
+      for (int row = tid; row < rts * 32; row += nthr) {
+        const float2* p = stat + (row >> 5) * 64 + (row & 31);
+        float mm = -INFINITY, ss = 0.f;
+        for (int v = 0; v < NW; ++v) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            // (reference, sum) -> (log-sum-exp, 1): a sum referenced to early logits can be very large or
+            // small, and merging such pairs directly could lose it to an underflowing factor
+            const float2 s = p[(size_t)v * tiles0 * 64 + h * 32];
+            if (s.y > 0.f) merge_stats(mm, ss, s.x + __builtin_amdgcn_logf(s.y), 1.f);
+          }
+        }
+        const float l = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+        if (nchunks == 1) lse_s[row] = row < rows && ss > 0.f ? l : INFINITY;
+        else part[(int64_t)bid * Rpad + rb0 + row] = l;
+      }
+      if (nchunks > 1) {
+        preloaded = false;
+        continue;
+      }
+      __syncthreads();
+    } else {
+      const float l = fold_rows(part, se.chunk0, se.chunk1, Rpad, rb0, rts * 32, nthr, stat);
+      if (tid < rts * 32) lse_s[tid] = tid < rows ? l : INFINITY;
+      __syncthreads();
+    }
+
+    // ---- importance of the chunk's keys: sum over the rows of exp2(x - lse)
+    float* const dst = imp + tab.score_off[seg];
+    sweep(preloaded, [&](const u32x4 (&raw)[KT][RAW], int g) __attribute__((always_inline)) {
+      u32x4 op[KT][KK];
+      widen(raw, op);
+      float colsum[KT];
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) colsum[kt] = 0.f;
+#pragma unroll 1
+      for (int rt = 0; rt < rts; ++rt) {
+        // lane: key l32 of tile kt, query rows rt*32 + 8*(i/4) + 4*half + i%4
+        f32x16 acc[KT];
+        logits(op, rt, std::false_type{}, acc);
+        f32x4v l[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) l[j] = *reinterpret_cast<const f32x4v*>(&lse_s[rt * 32 + 8 * j + 4 * half]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) colsum[kt] += fast_exp2(fmaf(acc[kt][i], c_log2, -l[i >> 2][i & 3]));
+      }
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) colsum[kt] += __shfl_xor(colsum[kt], 32, 64);
+      const float v = KT == 2 && half ? colsum[KT - 1] : colsum[0];
+      const int key = key_begin + g * GK + (KT == 2 ? lane : l32);
+      if (key < key_end && (KT == 2 || half == 0)) dst[key] = rb0 ? dst[key] + v : v;   // (a later row block adds to what this lane wrote)
+    });
+    preloaded = false;
   }
 }
 
@@ -798,7 +967,6 @@ constexpr int kSelTrackMax = 512;         // up to this many wanted keys the fir
 constexpr int kSelCandidates = 12288;     // scores of one first-level digit that the LDS list can hold
 constexpr int kDigitShift = 20;           // first-level digit = key >> 20: sign (0), 8 exponent and 3 mantissa bits
 constexpr uint32_t kKeyNone = 0xffffffffu;
-static_assert(kTicketBytes == SLKV_WORKSPACE_HEADER_BYTES, "the header documents the size of the ticket area");
 static_assert((0x7f800000u >> kDigitShift) < (uint32_t)kHistBins, "every key has a first-level digit inside the histogram");
 
 // Key of a pooled score: its bit pattern; anything that is not a non-negative number (cannot
@@ -1845,7 +2013,6 @@ __global__ void table_write_kernel(const SegTable part, int s0, const SegTableDe
     dst.score_off[s0 + i] = part.score_off[i];
     dst.seg_global[s0 + i] = part.seg_global[i];
     dst.hblk[s0 + i] = part.hblk[i];
-    dst.tick[s0 + i] = part.tick[i];
   }
   if (i <= part.nseg) {
     dst.out_off[s0 + i] = part.out_off[i];
@@ -1878,9 +2045,9 @@ struct Geometry {
 struct Plan {
   int R, Rpad, CH;
   int64_t hist_blocks;   // block histograms of the selection
-  int64_t ticketed;      // segments that need a ticket slot
-  size_t part_bytes, lse_bytes, score_bytes, hist_bytes, table_bytes;
-  size_t off_part, off_lse, off_imp, off_pooled, off_hist, off_table, total_bytes;
+  int waves;             // per workgroup of the scoring passes
+  size_t part_bytes, score_bytes, hist_bytes, table_bytes;
+  size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
 };
 
 static bool seg_ranked(int64_t n, int64_t w, int64_t cap) { return n > w && n > cap && cap > w; }
@@ -1888,28 +2055,91 @@ static bool seg_ranked(int64_t n, int64_t w, int64_t cap) { return n > w && n > 
 static int64_t seg_chunks(const Seg& s, int w, int64_t ch) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + ch - 1) / ch : 0; }
 static int64_t seg_blocks(const Seg& s, int w) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + kSelBlock - 1) / kSelBlock : 0; }
 
-static void make_plan(const Geometry& g, Plan& p) {
-  p.R = (g.Hq / g.Hkv) * g.w;
-  p.Rpad = (p.R + 31) / 32 * 32;
+// f(head dimension, KIND) of a call, as integral constants.
+template <class F>
+static auto with_score_kind(int d, int dtype, F f) {
+  const int kind = dtype == SLKV_BF16 ? 0 : dtype == SLKV_F16 ? 1 : dtype == SLKV_BF16_KV_FP8 ? 2 : 3;
+  if (d == 128) {
+    switch (kind) {
+      case 0: return f(std::integral_constant<int, 128>{}, std::integral_constant<int, 0>{});
+      case 1: return f(std::integral_constant<int, 128>{}, std::integral_constant<int, 1>{});
+      case 2: return f(std::integral_constant<int, 128>{}, std::integral_constant<int, 2>{});
+      default: return f(std::integral_constant<int, 128>{}, std::integral_constant<int, 3>{});
+    }
+  }
+  switch (kind) {
+    case 0: return f(std::integral_constant<int, 64>{}, std::integral_constant<int, 0>{});
+    case 1: return f(std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 64>{}, std::integral_constant<int, 2>{});
+    default: return f(std::integral_constant<int, 64>{}, std::integral_constant<int, 3>{});
+  }
+}
+
+// Workgroup size and chunk length of score_k_resident_kernel.  A workgroup of 8 waves has a CU to itself (its waves
+// use all registers); two of 4 waves share one where their LDS fits twice, which deals the keys out in smaller
+// portions.  Of the chunk lengths, the one whose rounds of workgroups take the least time: a workgroup's start
+// and end (queries into LDS, first keys, row statistics: kStartUs) and its groups one after the other, each of
+// them R/32 query tiles long (kTileUs with both wave slots of a SIMD taken, so with 8 waves on the CU).
+static void plan_k_resident(const Geometry& g, Plan& p) {
+  constexpr double kStartUs = 4.0, kTileUs = 0.5;
+  int gk = 0, tiles = 0, max_tiles = 0;
+  size_t lds4 = 0;
+  with_score_kind(g.d, g.dtype, [&](auto dk, auto kind) {
+    using C = ScoreCfg<decltype(dk)::value, decltype(kind)::value>;
+    gk = C::GK;
+    tiles = (p.R + 31) / 32;
+    max_tiles = std::min(tiles, C::RBT);
+    lds4 = score_lds_bytes<decltype(dk)::value, decltype(kind)::value>(max_tiles, 4);
+  });
+  // ranked history lengths, equal ones together (a call has few different ones compared with its segments)
+  std::vector<std::pair<int64_t, int64_t>> hist;
+  for (const Seg& s : g.segs)
+    if (seg_ranked(s.n, g.w, s.cap)) {
+      if (!hist.empty() && hist.back().first == s.n - g.w) hist.back().second += 1;
+      else hist.emplace_back(s.n - g.w, 1);
+    }
+  int64_t longest = 1;
+  for (const auto& h : hist) longest = std::max(longest, h.first);
+  double best = 0;
+  p.waves = 8;
+  p.CH = 8 * gk;
+  for (const int waves : {4, 8}) {
+    const bool pairs = waves == 4 && 2 * (lds4 + 256) <= 160 * 1024;
+    const int64_t slots = pairs ? 512 : 256;
+    const double tile_us = waves == 4 && !pairs ? 0.6 * kTileUs : kTileUs;
+    const int64_t unit = (int64_t)waves * gk, most = (longest + unit - 1) / unit;
+    for (int64_t gpw = 1;;) {
+      int64_t count = 0;
+      for (const auto& h : hist) count += h.second * ((h.first + gpw * unit - 1) / (gpw * unit));
+      const double rounds = (double)((count + slots - 1) / slots);
+      const double t = rounds * (kStartUs + (double)std::min(gpw, most) * tiles * tile_us);
+      if (best == 0 || t < best) {
+        best = t;
+        p.waves = waves;
+        p.CH = (int)(gpw * unit);
+      }
+      if (gpw >= most || rounds <= 1) break;           // longer chunks only idle workgroups from here on
+      gpw += std::max<int64_t>(1, gpw / 16);
+    }
+  }
+}
+
+// Chunk length of score_q_resident_kernel.
+static void plan_q_resident(const Geometry& g, Plan& p) {
   // keys to score over all ranked segments -> chunk length giving about 512 workgroups
   int64_t keys = 0;
   for (const Seg& s : g.segs)
     if (seg_ranked(s.n, g.w, s.cap)) keys += s.n - g.w;
   int64_t ch = (keys + 511) / 512;
-  if (g.dtype != SLKV_F32) {                  // MFMA kernels: pairs of 64-key tiles
-    ch = (ch + 127) / 128 * 128;
-    ch = std::max<int64_t>(256, std::min<int64_t>(ch, 1 << 16));
-  } else {                                    // fp32 kernels: 32-key tiles
-    ch = (ch + 31) / 32 * 32;
-    ch = std::max<int64_t>(32, std::min<int64_t>(ch, 1 << 16));
-  }
+  ch = (ch + 127) / 128 * 128;                // pairs of 64-key tiles
+  ch = std::max<int64_t>(256, std::min<int64_t>(ch, 1 << 16));
   // All chunks should be resident at once (two 256-thread workgroups per CU on 256 CUs): the
   // partial last chunk of every segment can push the count a little over that, and the surplus
   // workgroups would then run alone in a second round that doubles the kernel's time.  Lengthen
   // the chunk, by up to a quarter, until the count fits.
   {
     constexpr int64_t kSlots = 512;
-    const int64_t granule = g.dtype != SLKV_F32 ? 128 : 32;
+    constexpr int64_t granule = 128;
     auto count = [&](int64_t c) {
       int64_t total = 0;
       for (const Seg& s : g.segs)
@@ -1924,29 +2154,34 @@ static void make_plan(const Geometry& g, Plan& p) {
         }
   }
   p.CH = (int)ch;
+  p.waves = 4;
+}
+
+static void make_plan(const Geometry& g, Plan& p) {
+  p.R = (g.Hq / g.Hkv) * g.w;
+  p.Rpad = (p.R + 31) / 32 * 32;
+  if (g.dtype == SLKV_BF16 || g.dtype == SLKV_F16) plan_q_resident(g, p);
+  else plan_k_resident(g, p);
+  const int64_t ch = p.CH;
   int64_t chunks = 0;
   p.hist_blocks = 0;
-  p.ticketed = 0;
   for (const Seg& s : g.segs) {
     const int64_t nc = seg_chunks(s, g.w, ch), nb = seg_blocks(s, g.w);
     chunks += nc;
     p.hist_blocks += nb;
-    if (nc > 1) p.ticketed += 1;
   }
   auto align = [](size_t x) { return (x + 255) / 256 * 256; };
   p.part_bytes = align((size_t)std::max<int64_t>(chunks, 1) * p.Rpad * sizeof(float));
-  p.lse_bytes = align(std::max<size_t>(g.segs.size(), 1) * p.Rpad * sizeof(float));
   p.score_bytes = align((size_t)std::max<int64_t>(1, g.score_elems) * sizeof(float));
   p.hist_bytes = align((size_t)p.hist_blocks * kHistBins * sizeof(uint32_t));
-  p.off_part = kTicketBytes;                   // the ticket words come first
-  p.off_lse = p.off_part + p.part_bytes;
-  p.off_imp = p.off_lse + p.lse_bytes;
+  p.off_part = SLKV_WORKSPACE_HEADER_BYTES;
+  p.off_imp = p.off_part + p.part_bytes;
   p.off_pooled = p.off_imp + p.score_bytes;
   p.off_hist = p.off_pooled + p.score_bytes;
   p.off_table = p.off_hist + p.hist_bytes;
   // device-resident segment table: only for calls with more segments than one kernel argument holds
   const size_t S = g.segs.size();
-  p.table_bytes = S > (size_t)kMaxSegPerLaunch ? align((12 * S + 3) * sizeof(int32_t)) : 0;
+  p.table_bytes = S > (size_t)kMaxSegPerLaunch ? align((11 * S + 3) * sizeof(int32_t)) : 0;
   p.total_bytes = p.off_table + p.table_bytes;
 }
 
@@ -2000,53 +2235,46 @@ struct ScoreGrid {
 };
 
 template <int DK, int MT, int RB, int KIND, class TAB>
-static void launch_bf16(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                        const Geometry& g, const Plan& p, float c_log2, float* part, float* lse, float* imp,
-                        uint32_t* tickets) {
+static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
+                              const Geometry& g, const Plan& p, float c_log2, float* part, float* imp) {
   // segments with like chunk counts: one grid row per segment (see the kernel's first lines)
   const bool two = grid.rows > 0;
   const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
   if (pass == 1)
-    SLKV_LAUNCH((score_bf16_kernel<DK, MT, RB, 1, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q,
-                       k, g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, lse, imp,
-                       lse, tickets, two ? 1 : 0);
+    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, 1, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
   else
-    SLKV_LAUNCH((score_bf16_kernel<DK, MT, RB, 2, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q,
-                       k, g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, lse, imp,
-                       lse, tickets, two ? 1 : 0);
+    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, 2, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
 }
 
 template <int DK, int KIND, class TAB>
-static void launch_bf16_rows(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                             const Geometry& g, const Plan& p, float c_log2, float* part, float* lse, float* imp,
-                             uint32_t* tickets) {
-  if (p.R <= 64) launch_bf16<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-  else if (p.R <= 128) launch_bf16<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-  else if (p.R <= 256) launch_bf16<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-  else launch_bf16<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
+static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
+                           const Geometry& g, const Plan& p, float c_log2, float* part, float* imp) {
+  if constexpr (KIND <= 1) {
+    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+  } else {
+    const bool two = grid.rows > 0;
+    const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
+    const size_t lds = score_lds_bytes<DK, KIND>(std::min((p.R + 31) / 32, ScoreCfg<DK, KIND>::RBT), p.waves);
+    if (pass == 1)
+      SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 1, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
+    else
+      SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 2, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
+  }
 }
 
 template <class TAB>
 static void launch_score(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                         const Geometry& g, const Plan& p, float c_log2, float* part, float* lse, float* imp,
-                         uint32_t* tickets) {
-  if (g.dtype == SLKV_BF16) {
-    if (g.d == 128) launch_bf16_rows<128, 0>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-    else launch_bf16_rows<64, 0>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-  } else if (g.dtype == SLKV_F16) {
-    if (g.d == 128) launch_bf16_rows<128, 1>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-    else launch_bf16_rows<64, 1>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-  } else if (g.dtype == SLKV_BF16_KV_FP8) {
-    if (g.d == 128) launch_bf16_rows<128, 2>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-    else launch_bf16_rows<64, 2>(pass, grid, st, tab, q, k, g, p, c_log2, part, lse, imp, tickets);
-  } else {
-#define SLKV_F32_LAUNCH(DKV, PS)                                                                                     \
-  SLKV_LAUNCH((score_f32_kernel<DKV, PS, TAB>), dim3(grid.chunks), dim3(256), 0, st, tab, (const float*)q, (const float*)k, \
-                     g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, lse, imp, lse, tickets)
-    if (g.d == 128) { if (pass == 1) SLKV_F32_LAUNCH(128, 1); else SLKV_F32_LAUNCH(128, 2); }
-    else { if (pass == 1) SLKV_F32_LAUNCH(64, 1); else SLKV_F32_LAUNCH(64, 2); }
-#undef SLKV_F32_LAUNCH
-  }
+                         const Geometry& g, const Plan& p, float c_log2, float* part, float* imp) {
+  with_score_kind(g.d, g.dtype, [&](auto dk, auto kind) {
+    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+  });
 }
 
 template <class TAB>
@@ -2117,6 +2345,30 @@ static hipError_t raise_lds_limits() {
   return raise_lds_limit<-1, EPT>();
 }
 
+template <int DK, int KIND, class TAB>
+static hipError_t raise_score_limit() {
+  if constexpr (KIND <= 1) return hipSuccess;          // (score_q_resident_kernel has static LDS)
+  else {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 1, TAB>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 2, TAB>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+  }
+}
+
+static hipError_t raise_score_limits() {
+  for (const int d : {64, 128})
+    for (const int dtype : {SLKV_F32, SLKV_BF16_KV_FP8}) {
+      const hipError_t e = with_score_kind(d, dtype, [](auto dk, auto kind) {
+        const hipError_t a = raise_score_limit<decltype(dk)::value, decltype(kind)::value, SegTable>();
+        return a != hipSuccess ? a : raise_score_limit<decltype(dk)::value, decltype(kind)::value, SegTableDev>();
+      });
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+
 static hipError_t ensure_device_init() {
   static std::mutex mu;
   static uint64_t done = 0;                      // bit per device
@@ -2126,6 +2378,7 @@ static hipError_t ensure_device_init() {
   std::lock_guard<std::mutex> lk(mu);
   const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t(1) << dev) : 0;
   if (done & bit) return hipSuccess;
+  if ((e = raise_score_limits()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPT>()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPTMid>()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPTSmall>()) != hipSuccess) return e;
@@ -2220,9 +2473,6 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   if (total_kept >= (int64_t(1) << 31)) return fail(SLKV_ERR_BAD_ARG, "kept rows >= 2^31");
   Plan p;
   make_plan(g, p);
-  if (p.ticketed > kTicketSlots)
-    return fail(SLKV_ERR_UNSUPPORTED, "%lld segments span several key chunks (limit %d)",
-                (long long)p.ticketed, kTicketSlots);
   if (workspace_bytes < p.total_bytes)
     return fail(SLKV_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, p.total_bytes);
   if (out_capacity_rows < total_kept)
@@ -2231,7 +2481,6 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   hipStream_t st = (hipStream_t)hip_stream;
   unsigned char* ws = (unsigned char*)d_workspace;
   float* part = (float*)(ws + p.off_part);
-  float* lse = (float*)(ws + p.off_lse);
   float* imp = d_importance ? d_importance : (float*)(ws + p.off_imp);
   float* pooled = d_pooled ? d_pooled : (float*)(ws + p.off_pooled);
   const float c_log2 = (float)(1.4426950408889634 / std::sqrt((double)g.d));
@@ -2251,12 +2500,15 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   ga.pos_in = d_pos_in;
   ga.pos_out = d_pos_out;
 
-  uint32_t* tickets = (uint32_t*)ws;
   uint32_t* blockhist = (uint32_t*)(ws + p.off_hist);
   // candidate lists of the block-wise selection: the workspace's importance area, which is either
   // unused (the caller asked for the importance scores in an array of its own) or dead by then
   // (pooling has consumed the scores)
   uint32_t* lists = (uint32_t*)(ws + p.off_imp);
+
+  const hipError_t ie = ensure_device_init();
+  if (ie != hipSuccess) return fail(SLKV_ERR_HIP, "device set-up failed: %s", hipGetErrorString(ie));
+  const bool k_resident = g.dtype == SLKV_F32 || g.dtype == SLKV_BF16_KV_FP8;
 
   // The kernels of the pass over the segments one table describes.
   // Selection kernel: if every history fits one round, the one-workgroup-per-segment kernel;
@@ -2279,11 +2531,11 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     if (chunks > 0) {
       {
         ScopedKernelTimer tm(SLKV_K_SCORE_STATS, st);
-        launch_score(1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, lse, imp, tickets);
+        launch_score(1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp);
       }
-      {
+      if (max_chunks > 1 || !k_resident) {             // (score_k_resident_kernel completes segments of one chunk in its first pass)
         ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
-        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, lse, imp, tickets);
+        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp);
       }
     }
     {
@@ -2322,14 +2574,13 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     dev.score_off = t; t += S;
     dev.seg_global = t; t += S;
     dev.hblk = t; t += S;
-    dev.tick = t; t += S;
     dev.out_off = t; t += S + 1;
     dev.chunk_begin = t; t += S + 1;
     dev.blk_begin = t;
     dev.nseg = (int32_t)S;
   }
-  // running totals over the call: output rows, key chunks, selection blocks, block histograms, tickets
-  int64_t out_run = 0, chunks = 0, max_chunks = 0, blocks = 0, hist_run = 0, tick_run = 0;
+  // running totals over the call: output rows, key chunks, selection blocks, block histograms
+  int64_t out_run = 0, chunks = 0, max_chunks = 0, blocks = 0, hist_run = 0;
   bool any_large = false;
   for (int64_t s0 = 0; s0 < S; s0 += kMaxSegPerLaunch) {
     SegTable tab;
@@ -2354,12 +2605,10 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       tab.chunk_begin[i] = (int32_t)chunks;
       tab.blk_begin[i] = (int32_t)blocks;
       tab.hblk[i] = (int32_t)hist_run;
-      tab.tick[i] = (int32_t)tick_run;
       chunks += nc;
       max_chunks = std::max(max_chunks, nc);
       blocks += nb;
       hist_run += nb;
-      if (nc > 1) tick_run += 1;
     }
     if (chunks >= (int64_t(1) << 31) || blocks >= (int64_t(1) << 31)) return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
     // the remaining entries repeat the end values so that searches stay inside the table
@@ -2400,7 +2649,7 @@ static slkv_status static_scratch(void** out) {
     void* ptr = nullptr;
     e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess || !ptr) return fail(SLKV_ERR_HIP, "hipGetSymbolAddress(scratch) failed: %s", hipGetErrorString(e));
-    e = hipMemset(ptr, 0, kTicketBytes);      // the counters at its start begin at zero (once; not under capture)
+    e = hipMemset(ptr, 0, SLKV_WORKSPACE_HEADER_BYTES);      // the counters at its start begin at zero (once; not under capture)
     if (e != hipSuccess) return fail(SLKV_ERR_HIP, "clearing the static scratch failed: %s", hipGetErrorString(e));
     ptrs[dev] = ptr;
   }
