@@ -33,29 +33,62 @@ extern "C" int slkv_trace_read(long long* h, int n) {
 
 namespace slkv {
 
-// Per-launch table of (sequence, KV head) segments, passed by value as a kernel argument.
-struct SegTable {
-  int32_t nseg;
-  int32_t total_chunks;
-  int32_t tok_begin[kMaxSegPerLaunch];   // first token of the sequence in the packed K/V
-  int32_t n[kMaxSegPerLaunch];           // tokens in the sequence
-  int32_t kkeep[kMaxSegPerLaunch];       // history rows to keep; -1 = keep every token
-  int32_t out_off[kMaxSegPerLaunch + 1]; // first output row of the segment
-  int32_t head[kMaxSegPerLaunch];        // KV head
-  int32_t qrow_off[kMaxSegPerLaunch];    // first row of the segment's [G*w][d] query block
-  int32_t score_off[kMaxSegPerLaunch];   // offset of the segment in the importance / pooled arrays
-  int32_t chunk_begin[kMaxSegPerLaunch + 1];  // prefix of key-chunk counts (0 chunks when not ranked)
-  int32_t seg_global[kMaxSegPerLaunch];  // index b*Hkv + h
-  int32_t blk_begin[kMaxSegPerLaunch + 1];    // prefix of selection-block counts (no block when not ranked)
-  int32_t hblk[kMaxSegPerLaunch];        // first block histogram of the segment
+// The (sequence, KV head) segments of a call, as every kernel finds them: segment s = b*hkv + h is head h of
+// sequence b.
+struct SegShape {
+  int n;           // tokens (rows) of the segment; the last w are the window
+  int tok_begin;   // its first token (row) in K / V
+  int head;        // multiplied by the head stride (0 for a ragged cache)
+  int kk;          // history rows to keep; -1 = keep every token
+  int score_off;   // offset of the segment in the importance / pooled arrays
 };
 
-// The same table in device memory, for calls with more segments than fit a kernel argument.
-// chunk_begin, blk_begin and out_off are prefixes over all segments of the call.
-struct SegTableDev {
+// Up to kMaxSegPerLaunch segments: everything per segment, in a kernel argument, so that one round of loads from
+// it (cold at every launch) answers a workgroup that knows its segment.
+struct SegTable {
   int32_t nseg;
-  int32_t total_chunks;
-  int32_t *tok_begin, *n, *kkeep, *out_off, *head, *qrow_off, *score_off, *chunk_begin, *seg_global, *blk_begin, *hblk;
+  int32_t tok_[kMaxSegPerLaunch], n_[kMaxSegPerLaunch], head_[kMaxSegPerLaunch], kk_[kMaxSegPerLaunch], score_[kMaxSegPerLaunch];
+  int32_t out_[kMaxSegPerLaunch + 1];     // first output row of the segment
+  int32_t chunk_[kMaxSegPerLaunch + 1];   // prefix of key-chunk counts (0 chunks when not ranked)
+  int32_t blk_[kMaxSegPerLaunch + 1];     // prefix of selection-block counts (no block when not ranked)
+  __device__ __forceinline__ int out_off(int s) const { return out_[s]; }
+  __device__ __forceinline__ int chunk_begin(int s) const { return chunk_[s]; }
+  __device__ __forceinline__ int blk_begin(int s) const { return blk_[s]; }
+  __device__ __forceinline__ SegShape shape(int s) const { return SegShape{n_[s], tok_[s], head_[s], kk_[s], score_[s]}; }
+};
+
+// More segments: what depends on the sequence or the head alone is stored once per sequence or head and the rest
+// follows from it, one round of loads later.  The words travel in the kernel argument as well if they fit (a
+// decode batch of 32 sequences x 8 heads does), otherwise they are in the workspace, put there by upload_kernel.
+// (With everything per segment in the workspace, a launch of 4 us per 64 segments came before the first scoring
+// pass: 16 of the decode batch's 97 us.)
+constexpr int kArgWords = 900;
+struct SegTableBig {
+  const int32_t* mem;                     // the words; NULL: words[]
+  int32_t nseg, hkv, w, ragged;
+  int32_t off_out, off_chunk, off_blk, off_cap;   // where in the words; at 0: first token of every sequence, or (ragged) first row of every segment
+  int32_t words[kArgWords];
+  // The words in the constant address space: read with scalar loads.  The table is every kernel's first argument.
+  typedef const __attribute__((address_space(4))) int32_t* Words;
+  __device__ __forceinline__ Words data() const {
+    if (mem) return (Words)(uintptr_t)mem;
+    return (Words)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SegTableBig, words) / sizeof(int32_t);
+  }
+  __device__ __forceinline__ int out_off(int s) const { return data()[off_out + s]; }
+  __device__ __forceinline__ int chunk_begin(int s) const { return data()[off_chunk + s]; }
+  __device__ __forceinline__ int blk_begin(int s) const { return data()[off_blk + s]; }
+  __device__ __forceinline__ SegShape shape(int s) const {
+    const Words t = data();
+    const int b = s / hkv, h = s - b * hkv, i = ragged ? s : b;
+    SegShape r;
+    r.tok_begin = t[i];
+    r.n = t[i + 1] - r.tok_begin;
+    r.head = ragged ? 0 : h;
+    const int cap = t[off_cap + h];
+    r.kk = r.n <= w || r.n <= cap ? -1 : min(max(cap - w, 0), r.n - w);
+    r.score_off = ragged ? r.tok_begin - t[0] : hkv * r.tok_begin + h * r.n;
+    return r;
+  }
 };
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -80,12 +113,13 @@ __device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// Segment of a block / row: the largest s with prefix[s] <= x (prefix non-decreasing, prefix[nseg] > x).
-__device__ __forceinline__ int find_segment(const int32_t* prefix, int nseg, int x) {
+// Segment of a block / row: the largest s with prefix(s) <= x (prefix non-decreasing, prefix(nseg) > x).
+template <class F>
+__device__ __forceinline__ int find_segment(int nseg, int x, F prefix) {
   int lo = 0, hi = nseg - 1;
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
-    if (prefix[mid] <= x) lo = mid; else hi = mid - 1;
+    if (prefix(mid) <= x) lo = mid; else hi = mid - 1;
   }
   return lo;
 }
@@ -201,10 +235,11 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   // first key can be requested: the entries of segment blockIdx.y are therefore fetched before it
   // is known which case applies (y is 0 with a one-dimensional grid: a valid entry either way).
   struct SegEntry {
-    int32_t n, tok_begin, head, qrow_off, chunk0, chunk1;
+    int32_t n, tok_begin, head, qrow_off, score_off, chunk0, chunk1;
   };
   auto entry_of = [&](int s) {
-    return SegEntry{tab.n[s], tab.tok_begin[s], tab.head[s], tab.qrow_off[s], tab.chunk_begin[s], tab.chunk_begin[s + 1]};
+    const SegShape sg = tab.shape(s);
+    return SegEntry{sg.n, sg.tok_begin, sg.head, s * R, sg.score_off, tab.chunk_begin(s), tab.chunk_begin(s + 1)};
   };
   int seg = (int)blockIdx.y;
   SegEntry se = entry_of(seg);
@@ -215,7 +250,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     if (bid >= se.chunk1) return;
   } else {
     bid = blockIdx.x;
-    seg = find_segment(tab.chunk_begin, tab.nseg, bid);
+    seg = find_segment(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
     se = entry_of(seg);
   }
   if (PASS == 1) SLKV_STAMP(256 + bid, 0);
@@ -296,7 +331,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 #pragma unroll
       for (int r = 0; r < RB; ++r) v += red[buf ^ 1][r][tid];
       const int key = key_begin + (t - 1) * TK + tid;
-      if (key < key_end) imp[tab.score_off[seg] + key] = v;
+      if (key < key_end) imp[se.score_off + key] = v;
     }
 #pragma unroll
     for (int sb = 0; sb < NSUB; ++sb) {
@@ -549,7 +584,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 #pragma unroll
       for (int r = 0; r < RB; ++r) v += red[t & 1][r][tid];
       const int key = key_begin + t * TK + tid;
-      if (key < key_end) imp[tab.score_off[seg] + key] = v;
+      if (key < key_end) imp[se.score_off + key] = v;
     }
   } else {
 #pragma unroll
@@ -646,10 +681,11 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
   // first key can be requested: the entries of segment blockIdx.y are therefore fetched before it
   // is known which case applies (y is 0 with a one-dimensional grid: a valid entry either way).
   struct SegEntry {
-    int32_t n, tok_begin, head, qrow_off, chunk0, chunk1;
+    int32_t n, tok_begin, head, qrow_off, score_off, chunk0, chunk1;
   };
   auto entry_of = [&](int s) {
-    return SegEntry{tab.n[s], tab.tok_begin[s], tab.head[s], tab.qrow_off[s], tab.chunk_begin[s], tab.chunk_begin[s + 1]};
+    const SegShape sg = tab.shape(s);
+    return SegEntry{sg.n, sg.tok_begin, sg.head, s * R, sg.score_off, tab.chunk_begin(s), tab.chunk_begin(s + 1)};
   };
   int seg = (int)blockIdx.y;
   SegEntry se = entry_of(seg);
@@ -660,7 +696,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
     if (bid >= se.chunk1) return;
   } else {
     bid = blockIdx.x;
-    seg = find_segment(tab.chunk_begin, tab.nseg, bid);
+    seg = find_segment(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
     se = entry_of(seg);
   }
   const int nchunks = se.chunk1 - se.chunk0;
@@ -888,7 +924,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
     }
 
     // ---- importance of the chunk's keys: sum over the rows of exp2(x - lse)
-    float* const dst = imp + tab.score_off[seg];
+    float* const dst = imp + se.score_off;
     sweep(preloaded, [&](const u32x4 (&raw)[KT][RAW], int g) __attribute__((always_inline)) {
       u32x4 op[KT][KK];
       widen(raw, op);
@@ -989,15 +1025,16 @@ __global__ __launch_bounds__(kSelThreads) void select_pool_kernel(const TAB tab,
   __shared__ float stage[kSelBlock + 2 * kSelHaloMax];
   const int tid = threadIdx.x;
   const int bid = blockIdx.x;
-  const int seg = find_segment(tab.blk_begin, tab.nseg, bid);
-  const int blk = bid - tab.blk_begin[seg];
-  const int n = tab.n[seg];
-  const int kk = tab.kkeep[seg];
+  const int seg = find_segment(tab.nseg, bid, [&](int s) { return tab.blk_begin(s); });
+  const int blk = bid - tab.blk_begin(seg);
+  const SegShape sg = tab.shape(seg);
+  const int n = sg.n;
+  const int kk = sg.kk;
   const int m = n - w;
   if (!(kk > 0 && kk < m)) return;                    // not ranked: nothing to pool (such segments have no block)
   SLKV_STAMP(bid, 0);
-  const float* I = imp + tab.score_off[seg];
-  float* P = pooled + tab.score_off[seg];
+  const float* I = imp + sg.score_off;
+  float* P = pooled + sg.score_off;
   const int radius = RADIUS >= 0 ? RADIUS : pool_kernel / 2;
   const bool is_max = pool_mode != SLKV_POOL_AVG;
   const float fill = is_max ? -INFINITY : 0.f;
@@ -1027,7 +1064,7 @@ __global__ __launch_bounds__(kSelThreads) void select_pool_kernel(const TAB tab,
     }
   }
   __syncthreads();
-  uint32_t* bh = blockhist + (size_t)(tab.hblk[seg] + blk) * kHistBins;
+  uint32_t* bh = blockhist + (size_t)(tab.blk_begin(seg) + blk) * kHistBins;
   for (int i = tid; i < kHistBins; i += NT) bh[i] = hist[i];
   SLKV_STAMP(bid, 1);
 }
@@ -1051,16 +1088,17 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
   const int seg = blockIdx.x;
   const int bid = seg;
   (void)bid;                                           // (only the development stamps use it)
-  const int nblk = tab.blk_begin[seg + 1] - tab.blk_begin[seg];
-  const int n = tab.n[seg];
-  const int kk = tab.kkeep[seg];
+  const int nblk = tab.blk_begin(seg + 1) - tab.blk_begin(seg);
+  const SegShape sg = tab.shape(seg);
+  const int n = sg.n;
+  const int kk = sg.kk;
   const int m = n - w;
-  const int kept = tab.out_off[seg + 1] - tab.out_off[seg];
+  const int kept = tab.out_off(seg + 1) - tab.out_off(seg);
   const bool small_seg = !split_emit && kept <= kInlineGatherRows;   // (split_emit: the launch has ranked segments, and gather_kernel copies every row)
-  int32_t* out = kept_idx + tab.out_off[seg];
+  int32_t* out = kept_idx + tab.out_off(seg);
   if (d_out_offsets && tid == 0 && phase != 0) {
-    d_out_offsets[tab.seg_global[seg]] = tab.out_off[seg];
-    if (seg == tab.nseg - 1) d_out_offsets[tab.seg_global[seg] + 1] = tab.out_off[tab.nseg];
+    d_out_offsets[seg] = tab.out_off(seg);
+    if (seg == tab.nseg - 1) d_out_offsets[seg + 1] = tab.out_off(tab.nseg);
   }
   auto emit = [&](int pos, int j) __attribute__((always_inline)) {   // kept position j goes to output slot pos
     if ((uint32_t)pos < (uint32_t)kept) {
@@ -1080,7 +1118,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
   //   phase 1: rank the list, or, if the digit holds more scores than the LDS list, narrow it by
   //            sweeps over the pooled array; write the window's positions.
   if (phase == 0 && !ranked) return;
-  uint32_t* const hdr = blockhist + (size_t)tab.hblk[seg] * kHistBins;   // (used for ranked segments only)
+  uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;   // (used for ranked segments only)
   if (!ranked) {
     if (kk < 0) {
       for (int j = tid; j < n; j += NT) emit(j, j);
@@ -1088,11 +1126,11 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
       for (int j = tid; j < w; j += NT) emit(j, m + j);   // kk == 0: the window alone
     }
   } else {
-    const float* P = pooled + tab.score_off[seg];
+    const float* P = pooled + sg.score_off;
     if (phase == 0) {
       // first-level histogram of the segment: the sum of its blocks' histograms
       static_assert(kHistBins == 2 * NT, "a thread adds up two bins");
-      const uint32_t* bh0 = blockhist + (size_t)tab.hblk[seg] * kHistBins;
+      const uint32_t* bh0 = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
       uint32_t a0 = 0, a1 = 0;
       for (int b0 = 0; b0 < nblk; b0 += 24) {             // 48 loads in flight
         uint32_t v0[24], v1[24];
@@ -1151,7 +1189,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
     const uint32_t ncand = min(hdr[7], (uint32_t)kSelCandidates);   // (== in_range when the list is used)
     if (use_list) {
       // the scores of the chosen digit, listed by the blocks: into LDS
-      const uint32_t* L = lists + tab.score_off[seg];
+      const uint32_t* L = lists + sg.score_off;
       for (uint32_t i = tid; i < ncand; i += NT) cand[i] = L[i];
       __syncthreads();
     } else if (!multi) {
@@ -1236,7 +1274,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
   // to gather_kernel, which skips the segments handled here.
   if (kept > 0 && small_seg) {
     __syncthreads();                                // sh_pos is complete
-    const int64_t tok0 = tab.tok_begin[seg], h = tab.head[seg], row0 = tab.out_off[seg];
+    const int64_t tok0 = sg.tok_begin, h = sg.head, row0 = tab.out_off(seg);
     const int pieces = kept * ga.lanes_per_row;
     for (int idx = tid; idx < pieces; idx += NT) {
       const int row = idx / ga.lanes_per_row, c = idx % ga.lanes_per_row;
@@ -1266,23 +1304,24 @@ __global__ __launch_bounds__(kSelEmitThreads) void select_collect_kernel(const T
   if (seg0 >= 0) {
     seg = seg0 + (int)blockIdx.y;
     blk = blockIdx.x;
-    if (blk >= tab.blk_begin[seg + 1] - tab.blk_begin[seg]) return;
+    if (blk >= tab.blk_begin(seg + 1) - tab.blk_begin(seg)) return;
   } else {
-    seg = find_segment(tab.blk_begin, tab.nseg, (int)blockIdx.x);
-    blk = (int)blockIdx.x - tab.blk_begin[seg];
+    seg = find_segment(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
+    blk = (int)blockIdx.x - tab.blk_begin(seg);
   }
-  const int m = tab.n[seg] - w;
-  const int kk = tab.kkeep[seg];
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w;
+  const int kk = sg.kk;
   if (!(kk > 0 && kk < m)) return;
-  uint32_t* hdr = blockhist + (size_t)tab.hblk[seg] * kHistBins;
-  const float* P = pooled + tab.score_off[seg];
+  uint32_t* hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
+  const float* P = pooled + sg.score_off;
   const int p0 = blk * kSelBlock + wv * (64 * PER) + lane;
   float pv[PER];
 #pragma unroll
   for (int j = 0; j < PER; ++j) pv[j] = P[min(p0 + j * 64, m - 1)];
   if (hdr[9] == 0u) return;
   const uint32_t lo = hdr[4], span = hdr[5] - lo;
-  uint32_t* L = lists + tab.score_off[seg];         // as long as the history: every list fits
+  uint32_t* L = lists + sg.score_off;         // as long as the history: every list fits
   uint32_t key[PER];
   uint32_t c = 0;
 #pragma unroll
@@ -1324,17 +1363,18 @@ __global__ __launch_bounds__(kSelEmitThreads) void select_count_kernel(const TAB
   if (seg0 >= 0) {
     seg = seg0 + (int)blockIdx.y;
     blk = blockIdx.x;
-    if (blk >= tab.blk_begin[seg + 1] - tab.blk_begin[seg]) return;
+    if (blk >= tab.blk_begin(seg + 1) - tab.blk_begin(seg)) return;
   } else {
-    seg = find_segment(tab.blk_begin, tab.nseg, (int)blockIdx.x);
-    blk = (int)blockIdx.x - tab.blk_begin[seg];
+    seg = find_segment(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
+    blk = (int)blockIdx.x - tab.blk_begin(seg);
   }
-  const int m = tab.n[seg] - w;
-  const int kk = tab.kkeep[seg];
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w;
+  const int kk = sg.kk;
   if (!(kk > 0 && kk < m)) return;                    // (such segments have no block)
-  uint32_t* row0 = blockhist + (size_t)tab.hblk[seg] * kHistBins;
+  uint32_t* row0 = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
   const uint32_t tau = row0[2];
-  const float* P = pooled + tab.score_off[seg];
+  const float* P = pooled + sg.score_off;
   const int p0 = blk * kSelBlock + tid;               // (which thread counts which position does not matter here)
   uint32_t cg = 0, ce = 0;
 #pragma unroll
@@ -1367,19 +1407,20 @@ __global__ __launch_bounds__(kSelEmitThreads) void select_emit_kernel(const TAB 
   if (seg0 >= 0) {
     seg = seg0 + (int)blockIdx.y;
     blk = blockIdx.x;
-    if (blk >= tab.blk_begin[seg + 1] - tab.blk_begin[seg]) return;
+    if (blk >= tab.blk_begin(seg + 1) - tab.blk_begin(seg)) return;
   } else {
-    seg = find_segment(tab.blk_begin, tab.nseg, (int)blockIdx.x);
-    blk = (int)blockIdx.x - tab.blk_begin[seg];
+    seg = find_segment(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
+    blk = (int)blockIdx.x - tab.blk_begin(seg);
   }
-  const int m = tab.n[seg] - w;
-  const int kk = tab.kkeep[seg];
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w;
+  const int kk = sg.kk;
   if (!(kk > 0 && kk < m)) return;
-  const uint32_t* row0 = blockhist + (size_t)tab.hblk[seg] * kHistBins;
+  const uint32_t* row0 = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
   const uint32_t tau = row0[2], need_eq = row0[3];
-  const int kept = tab.out_off[seg + 1] - tab.out_off[seg];
-  int32_t* out = kept_idx + tab.out_off[seg];
-  const float* P = pooled + tab.score_off[seg];
+  const int kept = tab.out_off(seg + 1) - tab.out_off(seg);
+  int32_t* out = kept_idx + tab.out_off(seg);
+  const float* P = pooled + sg.score_off;
   // this block's own positions first (the loads fly while the earlier blocks are added up): a wave
   // owns 64 * PER consecutive positions, lane l the positions 64 j + l, so that loads are coalesced
   // and ballots are in position order
@@ -1473,15 +1514,16 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int seg = blockIdx.x;
-  const int n = tab.n[seg];
-  const int kk = tab.kkeep[seg];
+  const SegShape sg = tab.shape(seg);
+  const int n = sg.n;
+  const int kk = sg.kk;
   const int m = n - w;
-  const int kept = tab.out_off[seg + 1] - tab.out_off[seg];
+  const int kept = tab.out_off(seg + 1) - tab.out_off(seg);
   const bool small_seg = kept <= kInlineGatherRows;
-  int32_t* out = kept_idx + tab.out_off[seg];
+  int32_t* out = kept_idx + tab.out_off(seg);
   if (d_out_offsets && tid == 0) {
-    d_out_offsets[tab.seg_global[seg]] = tab.out_off[seg];
-    if (seg == tab.nseg - 1) d_out_offsets[tab.seg_global[seg] + 1] = tab.out_off[tab.nseg];
+    d_out_offsets[seg] = tab.out_off(seg);
+    if (seg == tab.nseg - 1) d_out_offsets[seg + 1] = tab.out_off(tab.nseg);
   }
   auto emit = [&](int pos, int j) __attribute__((always_inline)) {   // kept position j goes to output slot pos
     if ((uint32_t)pos < (uint32_t)kept) {
@@ -1511,8 +1553,8 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
     }
   }
   if (ranked) {
-  const float* I = imp + tab.score_off[seg];
-  float* P = pooled + tab.score_off[seg];
+  const float* I = imp + sg.score_off;
+  float* P = pooled + sg.score_off;
   const int radius = RADIUS >= 0 ? RADIUS : pool_kernel / 2;
   const bool is_max = pool_mode != SLKV_POOL_AVG;
   const float fill = 0.f;                          // scores are >= 0, so zero padding leaves window maxima as they are
@@ -1546,7 +1588,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
     __syncthreads();
     // (behind the barrier: every score has arrived, and nothing waits for these loads before the end)
     {
-      const int64_t tok = (int64_t)tab.tok_begin[seg] + m + win_row, h = tab.head[seg];
+      const int64_t tok = (int64_t)sg.tok_begin + m + win_row, h = sg.head;
       win_k = *reinterpret_cast<const u32x4*>(ga.k + (h * ga.k_stride_head + tok * ga.k_stride_tok) * ga.elt_bytes + win_c * 16);
       win_v = *reinterpret_cast<const u32x4*>(ga.v + (h * ga.v_stride_head + tok * ga.v_stride_tok) * ga.elt_bytes + win_c * 16);
     }
@@ -1929,7 +1971,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
   // flight at a time.
   if (kept > 0 && small_seg) {
     __syncthreads();                                // sh_pos is complete
-    const int64_t tok0 = tab.tok_begin[seg], h = tab.head[seg], row0 = tab.out_off[seg];
+    const int64_t tok0 = sg.tok_begin, h = sg.head, row0 = tab.out_off(seg);
     const bool win_done = ranked && win_early;      // the window's pieces are in registers
     const int pieces = (win_done ? kk : kept) * lpr;
     const uint32_t magic = 0xffffffffu / (uint32_t)lpr + 1u;   // idx / lpr == umulhi(idx, magic) for idx < 2^16 (lpr > 1)
@@ -1983,15 +2025,16 @@ __global__ __launch_bounds__(256) void gather_kernel(const TAB tab, const Gather
   const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t rel = g / ga.lanes_per_row;
   const int c = (int)(g % ga.lanes_per_row);
-  const int64_t row0 = tab.out_off[0], row1 = tab.out_off[tab.nseg];
+  const int64_t row0 = tab.out_off(0), row1 = tab.out_off(tab.nseg);
   const int64_t row = row0 + rel;
   if (row >= row1) return;
-  const int seg = find_segment(tab.out_off, tab.nseg, (int)row);
-  if (!all_segments && tab.out_off[seg + 1] - tab.out_off[seg] <= kInlineGatherRows) return;   // done by the selection kernel
+  const int seg = find_segment(tab.nseg, (int)row, [&](int s) { return tab.out_off(s); });
+  if (!all_segments && tab.out_off(seg + 1) - tab.out_off(seg) <= kInlineGatherRows) return;   // done by the selection kernel
   // (a position outside the segment cannot come out of the selection; clamped all the same, so
   // that no input can turn into an out-of-bounds read here)
-  const int64_t tok = (int64_t)tab.tok_begin[seg] + min(max(kept_idx[row], 0), max(tab.n[seg] - 1, 0));
-  const int64_t h = tab.head[seg];
+  const SegShape sg = tab.shape(seg);
+  const int64_t tok = (int64_t)sg.tok_begin + min(max(kept_idx[row], 0), max(sg.n - 1, 0));
+  const int64_t h = sg.head;
   const uint4 kv = *reinterpret_cast<const uint4*>(ga.k + (h * ga.k_stride_head + tok * ga.k_stride_tok) * ga.elt_bytes + c * 16);
   const uint4 vv = *reinterpret_cast<const uint4*>(ga.v + (h * ga.v_stride_head + tok * ga.v_stride_tok) * ga.elt_bytes + c * 16);
   const int64_t o = (row * ga.lanes_per_row + c) * 16;
@@ -2000,25 +2043,13 @@ __global__ __launch_bounds__(256) void gather_kernel(const TAB tab, const Gather
   if (ga.pos_out && c == 0) ga.pos_out[row] = ga.pos_in[tok];
 }
 
-// Copies one kernel-argument table (up to kMaxSegPerLaunch segments starting at segment s0) into
-// the device-resident table.  The prefix arrays get one entry more.
-__global__ void table_write_kernel(const SegTable part, int s0, const SegTableDev dst) {
+// Words of a segment table that does not fit a kernel argument, on their way into the workspace.
+struct UploadWords {
+  int32_t w[kArgWords];
+};
+__global__ void upload_kernel(const UploadWords part, int count, int32_t* __restrict__ dst) {
   const int i = threadIdx.x;
-  if (i < part.nseg) {
-    dst.tok_begin[s0 + i] = part.tok_begin[i];
-    dst.n[s0 + i] = part.n[i];
-    dst.kkeep[s0 + i] = part.kkeep[i];
-    dst.head[s0 + i] = part.head[i];
-    dst.qrow_off[s0 + i] = part.qrow_off[i];
-    dst.score_off[s0 + i] = part.score_off[i];
-    dst.seg_global[s0 + i] = part.seg_global[i];
-    dst.hblk[s0 + i] = part.hblk[i];
-  }
-  if (i <= part.nseg) {
-    dst.out_off[s0 + i] = part.out_off[i];
-    dst.chunk_begin[s0 + i] = part.chunk_begin[i];
-    dst.blk_begin[s0 + i] = part.blk_begin[i];
-  }
+  if (i < count) dst[i] = part.w[i];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2037,6 +2068,9 @@ struct Seg {
 // What both entry points reduce to: common shape parameters plus the list of segments.
 struct Geometry {
   int dtype, Hq, Hkv, d, w, pool_kernel, pool;
+  bool ragged;
+  const int64_t* h_begin;   // B+1 token offsets, or (ragged) one row offset per segment and the end
+  const int32_t* h_caps;    // capacities of the KV heads
   int64_t k_stride_tok, k_stride_head, v_stride_tok, v_stride_head;
   int64_t score_elems;   // length of the importance / pooled arrays
   std::vector<Seg> segs;
@@ -2181,11 +2215,12 @@ static void make_plan(const Geometry& g, Plan& p) {
   p.off_table = p.off_hist + p.hist_bytes;
   // device-resident segment table: only for calls with more segments than one kernel argument holds
   const size_t S = g.segs.size();
-  p.table_bytes = S > (size_t)kMaxSegPerLaunch ? align((11 * S + 3) * sizeof(int32_t)) : 0;
+  p.table_bytes = S > (size_t)kMaxSegPerLaunch ? align((4 * S + 4 + (size_t)g.Hkv) * sizeof(int32_t)) : 0;
   p.total_bytes = p.off_table + p.table_bytes;
 }
 
 static void layer_geometry(const slkv_layer_desc* d, Geometry& g) {
+  g.ragged = false; g.h_begin = d->h_cu_seqlens; g.h_caps = d->h_budgets;
   g.dtype = d->dtype; g.Hq = d->Hq; g.Hkv = d->Hkv; g.d = d->d; g.w = d->w;
   g.pool_kernel = d->pool_kernel; g.pool = d->pool;
   g.k_stride_tok = d->k_stride_tok; g.k_stride_head = d->k_stride_head;
@@ -2208,6 +2243,7 @@ static void layer_geometry(const slkv_layer_desc* d, Geometry& g) {
 }
 
 static void ragged_geometry(const slkv_ragged_desc* d, Geometry& g) {
+  g.ragged = true; g.h_begin = d->h_in_offsets; g.h_caps = d->h_budgets;
   g.dtype = d->dtype; g.Hq = d->Hq; g.Hkv = d->Hkv; g.d = d->d; g.w = d->w;
   g.pool_kernel = d->pool_kernel; g.pool = d->pool;
   g.k_stride_tok = g.v_stride_tok = d->d;     // packed rows
@@ -2331,7 +2367,7 @@ static hipError_t raise_lds_limit() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_resident_kernel<RADIUS, EPT, SegTable>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLdsBytes);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&select_resident_kernel<RADIUS, EPT, SegTableDev>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&select_resident_kernel<RADIUS, EPT, SegTableBig>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLdsBytes);
 }
 
@@ -2362,7 +2398,7 @@ static hipError_t raise_score_limits() {
     for (const int dtype : {SLKV_F32, SLKV_BF16_KV_FP8}) {
       const hipError_t e = with_score_kind(d, dtype, [](auto dk, auto kind) {
         const hipError_t a = raise_score_limit<decltype(dk)::value, decltype(kind)::value, SegTable>();
-        return a != hipSuccess ? a : raise_score_limit<decltype(dk)::value, decltype(kind)::value, SegTableDev>();
+        return a != hipSuccess ? a : raise_score_limit<decltype(dk)::value, decltype(kind)::value, SegTableBig>();
       });
       if (e != hipSuccess) return e;
     }
@@ -2559,73 +2595,75 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     return SLKV_OK;
   };
 
-  // Few segments: the table travels as a kernel argument.  More: the per-64 tables are written
-  // to a device-resident table by a small kernel each, and one group of launches covers all segments.
-  const bool dev_table = S > kMaxSegPerLaunch;
-  SegTableDev dev;
-  std::memset(&dev, 0, sizeof(dev));
-  if (dev_table) {
-    int32_t* t = (int32_t*)(ws + p.off_table);
-    dev.tok_begin = t; t += S;
-    dev.n = t; t += S;
-    dev.kkeep = t; t += S;
-    dev.head = t; t += S;
-    dev.qrow_off = t; t += S;
-    dev.score_off = t; t += S;
-    dev.seg_global = t; t += S;
-    dev.hblk = t; t += S;
-    dev.out_off = t; t += S + 1;
-    dev.chunk_begin = t; t += S + 1;
-    dev.blk_begin = t;
-    dev.nseg = (int32_t)S;
-  }
-  // running totals over the call: output rows, key chunks, selection blocks, block histograms
-  int64_t out_run = 0, chunks = 0, max_chunks = 0, blocks = 0, hist_run = 0;
+  // The segment table, with the prefixes of output rows, key chunks and selection blocks over the segments.
+  int64_t out_run = 0, chunks = 0, max_chunks = 0, blocks = 0;
   bool any_large = false;
-  for (int64_t s0 = 0; s0 < S; s0 += kMaxSegPerLaunch) {
-    SegTable tab;
-    std::memset(&tab, 0, sizeof(tab));
-    const int ns = (int)std::min<int64_t>(kMaxSegPerLaunch, S - s0);
-    tab.nseg = ns;
-    for (int i = 0; i < ns; ++i) {
-      const Seg& sg = g.segs[(size_t)(s0 + i)];
-      tab.tok_begin[i] = (int32_t)sg.row_begin;
-      tab.n[i] = (int32_t)sg.n;
-      const bool all = sg.n <= g.w || sg.n <= sg.cap;
-      tab.kkeep[i] = all ? -1 : (int32_t)std::min<int64_t>(std::max<int64_t>(sg.cap - g.w, 0), sg.n - g.w);
-      tab.out_off[i] = (int32_t)out_run;
-      const int64_t kept = kept_rows(sg.n, g.w, sg.cap);
+  auto walk = [&](int32_t* out, int32_t* chunk, int32_t* blk) {   // (blk may be NULL)
+    for (int64_t i = 0; i < S; ++i) {
+      const Seg& sg = g.segs[(size_t)i];
+      out[i] = (int32_t)out_run;
+      chunk[i] = (int32_t)chunks;
+      if (blk) blk[i] = (int32_t)blocks;
+      const int64_t kept = kept_rows(sg.n, g.w, sg.cap), nc = seg_chunks(sg, g.w, p.CH);
       any_large |= kept > kInlineGatherRows;
       out_run += kept;
-      tab.head[i] = sg.head;
-      tab.qrow_off[i] = (int32_t)sg.qrow_off;
-      tab.score_off[i] = (int32_t)sg.score_off;
-      tab.seg_global[i] = (int32_t)(s0 + i);
-      const int64_t nc = seg_chunks(sg, g.w, p.CH), nb = seg_blocks(sg, g.w);
-      tab.chunk_begin[i] = (int32_t)chunks;
-      tab.blk_begin[i] = (int32_t)blocks;
-      tab.hblk[i] = (int32_t)hist_run;
       chunks += nc;
       max_chunks = std::max(max_chunks, nc);
-      blocks += nb;
-      hist_run += nb;
+      blocks += seg_blocks(sg, g.w);
     }
-    if (chunks >= (int64_t(1) << 31) || blocks >= (int64_t(1) << 31)) return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
-    // the remaining entries repeat the end values so that searches stay inside the table
-    for (int i = ns; i <= kMaxSegPerLaunch; ++i) {
-      tab.out_off[i] = (int32_t)out_run;
-      tab.chunk_begin[i] = (int32_t)chunks;
-      tab.blk_begin[i] = (int32_t)blocks;
+    out[S] = (int32_t)out_run;
+    chunk[S] = (int32_t)chunks;
+    if (blk) blk[S] = (int32_t)blocks;
+    return chunks < (int64_t(1) << 31) && blocks < (int64_t(1) << 31);
+  };
+  if (S <= kMaxSegPerLaunch) {
+    SegTable tab;
+    static_assert(sizeof(SegTable) + sizeof(GatherArgs) + 128 <= 4096, "kernel arguments are at most 4 KiB");
+    tab.nseg = (int32_t)S;
+    for (int64_t i = 0; i < S; ++i) {
+      const Seg& sg = g.segs[(size_t)i];
+      tab.tok_[i] = (int32_t)sg.row_begin;
+      tab.n_[i] = (int32_t)sg.n;
+      tab.head_[i] = sg.head;
+      const bool all = sg.n <= g.w || sg.n <= sg.cap;
+      tab.kk_[i] = all ? -1 : (int32_t)std::min<int64_t>(std::max<int64_t>(sg.cap - g.w, 0), sg.n - g.w);
+      tab.score_[i] = (int32_t)sg.score_off;
     }
-    tab.total_chunks = (int32_t)chunks;
-    if (dev_table) SLKV_LAUNCH(table_write_kernel, dim3(1), dim3(kMaxSegPerLaunch + 64), 0, st, tab, (int)s0, dev);
-    else return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
+    if (!walk(tab.out_, tab.chunk_, tab.blk_)) return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
+    return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
   }
-  if (dev_table) {
-    dev.total_chunks = (int32_t)chunks;
-    return launch_group(dev, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
+  SegTableBig tab;
+  static_assert(sizeof(SegTableBig) + sizeof(GatherArgs) + 128 <= 4096, "kernel arguments are at most 4 KiB");
+  const int nbeg = (int)(g.ragged ? S : S / g.Hkv) + 1;
+  tab.nseg = (int32_t)S;
+  tab.hkv = g.Hkv;
+  tab.w = g.w;
+  tab.ragged = g.ragged ? 1 : 0;
+  tab.off_cap = nbeg;
+  tab.off_out = tab.off_cap + g.Hkv;
+  tab.off_chunk = tab.off_out + (int32_t)S + 1;
+  tab.off_blk = tab.off_chunk + (int32_t)S + 1;            // (only the block-wise selection reads these)
+  const size_t count = (size_t)tab.off_blk + (resident_select ? 0 : (size_t)S + 1);
+  const bool in_arg = count <= (size_t)kArgWords;
+  std::vector<int32_t> spill;
+  if (!in_arg) spill.resize(count);
+  int32_t* const words = in_arg ? tab.words : spill.data();
+  for (int i = 0; i < nbeg; ++i) words[i] = (int32_t)g.h_begin[i];
+  for (int h = 0; h < g.Hkv; ++h) words[tab.off_cap + h] = g.h_caps[h];
+  if (!walk(words + tab.off_out, words + tab.off_chunk, resident_select ? nullptr : words + tab.off_blk))
+    return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
+  tab.mem = nullptr;
+  if (!in_arg) {
+    int32_t* const t = (int32_t*)(ws + p.off_table);
+    for (size_t i = 0; i < count; i += kArgWords) {
+      UploadWords part;
+      const int c = (int)std::min<size_t>(kArgWords, count - i);
+      std::memcpy(part.w, words + i, (size_t)c * sizeof(int32_t));
+      SLKV_LAUNCH(upload_kernel, dim3(1), dim3(1024), 0, st, part, c, t + i);
+    }
+    tab.mem = t;
   }
-  return SLKV_OK;
+  return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
 }
 
 }  // namespace slkv

@@ -10,7 +10,7 @@ namespace slkv {
 
 constexpr int kMaxRows = 512;         // (Hq/Hkv) * w rows scored per KV head
 constexpr int kMaxPool = 63;          // widest pooling window
-constexpr int kMaxSegPerLaunch = 64;  // (sequence, KV head) segments described per kernel launch
+constexpr int kMaxSegPerLaunch = 64;  // (sequence, KV head) segments whose every entry travels as a kernel argument
 
 // Sets the calling thread's error detail and returns `s`.
 slkv_status fail(slkv_status s, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
