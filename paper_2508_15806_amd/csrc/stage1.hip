@@ -48,7 +48,7 @@ __device__ __forceinline__ void store_cells(double* c, double WO, double WD, dou
 // are counted from the aligned address at or below the row's begin (`lead` floats before it).  The floats of the
 // first group that belong to the row before are taken out; those of a last group that is not whole (it may reach
 // past the tensor) are held one each by the first threads.
-// A lower bound of the K-th largest weight comes from the lane maxima of each wave (K distinct elements); the
+// A lower bound of the K-th largest weight comes from maxima per lane in each wave (K distinct elements); the
 // few weights at or above the bound are collected in LDS and ranked exactly (larger first, equal weights by
 // lower position).  Returns false, with nothing written, if a list overflows (many ties at the bound).
 // Bound: HBM.  32 x 32 heads x 16 rows of 16384 floats (1 GiB): 160-165 us, 6.6 TB/s.  Rows of 13867 floats went
@@ -84,7 +84,12 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
     for (int c = 0; c < 3; ++c)
       if (c < lead) v[0][c] = 0.f;
   }
-  float mx = -INFINITY;
+  // M maxima per lane (of its groups i, i + M, ...): enough disjoint subsets of the row that the K-th largest of
+  // their maxima lies close to the K-th largest weight
+  constexpr int M = NW == 1 ? 4 : NW == 2 ? 2 : 1;
+  float mx[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) mx[m] = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
     if (i * NT + tid < ngroups) {
@@ -97,28 +102,33 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
         for (int c = 0; c < 3; ++c)
           if (c < lead) v[0][c] = -INFINITY;
       }
-      mx = fmaxf(fmaxf(mx, fmaxf(v[i].x, v[i].y)), fmaxf(v[i].z, v[i].w));
+      mx[i % M] = fmaxf(fmaxf(mx[i % M], fmaxf(v[i].x, v[i].y)), fmaxf(v[i].z, v[i].w));
     }
   }
   if (!WHOLE) {
     tot += (double)vx;
-    if (have_x) mx = fmaxf(mx, vx);
+    if (have_x) mx[0] = fmaxf(mx[0], vx);
   }
   if (jn < ne) tnw = (double)nd;
   for (int32_t j = jn + NT; j < ne; j += NT) tnw += (double)W[j];
   tot = wave_sum<double>(tot);
   tnw = wave_sum<double>(tnw);
 
-  // Each wave finds a value at or below the ceil(K/NW)-th largest of its 64 lane maxima (bisection on the
+  // Each wave finds a value at or below the ceil(K/NW)-th largest of its 64 M maxima (bisection on the
   // upper 20 bits of the order-preserving key, with ballots).  At least K weights are >= the smallest of
   // the waves' values, so it bounds the K-th largest from below.
   const uint32_t want = (uint32_t)(topk + NW - 1) / NW;
-  const uint32_t mkey = tid < ngroups || have_x ? float_key(mx) : 0u;   // lanes without data never count
+  uint32_t mkey[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) mkey[m] = m * NT + tid < ngroups || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
   uint32_t tkey = 0;
 #pragma unroll
   for (int b = 31; b >= 12; --b) {
     const uint32_t trial = tkey | (1u << b);
-    if ((uint32_t)__popcll(__ballot(mkey >= trial)) >= want) tkey = trial;
+    uint32_t c = 0;
+#pragma unroll
+    for (int m = 0; m < M; ++m) c += (uint32_t)__popcll(__ballot(mkey[m] >= trial));
+    if (c >= want) tkey = trial;
   }
   // the float whose key is tkey (low bits cleared: not above the value found); 0 keys: -inf
   float bound = tkey == 0 ? -INFINITY : __uint_as_float((tkey & 0x80000000u) ? (tkey ^ 0x80000000u) : ~tkey);
