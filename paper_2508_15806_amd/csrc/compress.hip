@@ -147,8 +147,9 @@ __device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c
   const int nsub = rows < nt ? nt / rows : 1;
   const int row = nsub > 1 ? tid % rows : tid, sub = nsub > 1 ? tid / rows : 0;
   float mm = -INFINITY, ss = 0.f;
-  if (sub < nsub && row0 + row < Rpad) {
-    constexpr int NB = 16;
+  // batches of loads that are all in flight together: as large as the chunks ask for, since each costs a round trip
+  auto batches = [&](auto nb_c) __attribute__((always_inline)) {
+    constexpr int NB = decltype(nb_c)::value;
     for (int c = c0 + sub; c < c1; c += NB * nsub) {
       float v[NB];
 #pragma unroll
@@ -165,6 +166,10 @@ __device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c
       for (int u = 0; u < NB; ++u) ss += fast_exp2(v[u] - mu);
       mm = mn;
     }
+  };
+  if (sub < nsub && row0 + row < Rpad) {
+    if (c1 - c0 <= 16 * nsub) batches(std::integral_constant<int, 16>{});
+    else batches(std::integral_constant<int, 32>{});
   }
   if (nsub > 1) {
     fold[tid] = make_float2(mm, ss);
