@@ -459,29 +459,37 @@ __global__ __launch_bounds__(64 * kReduceHeads) void head_reduce_kernel(const do
 // from memory into the operand registers of the 32x32x16 bf16 MFMA (a lane: 16 bytes of one key
 // row per load; nothing is staged in LDS and the waves never wait for each other inside a chunk),
 // keeps two sub-tiles in flight, and multiplies it with both 32-row tiles of the queries, which
-// stay in registers.  A lane owns two query rows (one per row tile) and, per sub-tile, 16 keys of
+// stay in registers for a chunk.  A lane owns two query rows (one per row tile) and, per sub-tile, 16 keys of
 // each: it keeps the running softmax statistics and the needle mass of its rows.
-// Logits at or above the row's bound are appended to the row's candidate list in LDS.  The keys
-// are cut into chunks: the first kQkFirst keys, then chunks half as long as everything before
-// them.  After every chunk the waves meet, the bound of a row becomes the K-th largest entry of
-// its list (the K-th largest logit so far, resolved to its leading bits) and the list is cut back
-// to the entries at or above it; since a chunk holds at most half as many keys as came before, about K/2 new entries
-// join the K carried ones.  Only the first chunk, which has no bound to start from, is walked
-// twice: its first walk tracks 8 running maxima per lane and row, the 16 lanes of a row give 128
-// maxima of disjoint key subsets, and their K-th largest is a lower bound of the row's K-th
-// largest logit; its second walk collects.  So the keys are read 1 + kQkFirst/n times.
-// At the end a wave per row ranks its candidates exactly (larger logit first, equal logits by
-// lower position), turns the K winners into weights with the row's log-sum-exp and splits them
-// into WO / WD by needle membership.  A row whose list overflows (many equal logits at the top,
-// or logits that keep rising along the context) is flagged and redone by qk_fallback_kernel.
+// Logits at or above the row's bound are appended to the row's candidate list in LDS: a lane counts
+// its own ones of both row tiles first, so that a step waits for one pair of LDS atomics and not for one per entry.
+// The keys are cut into chunks: the first kQkFirst keys, then chunks as long as everything before
+// them.  After every chunk the waves meet, the bound of a row becomes a value at or a little below the K-th largest
+// entry of its list (the K-th largest logit so far) and the list is cut back to the entries at or above it;
+// since a chunk holds as many keys as came before, about K new entries join the K carried ones, and a
+// list of 256 has room for K = 64 and five standard deviations more, or for logits that rise along the
+// context.  The first two sub-tiles of every wave on the next chunk are in flight while the waves meet.
+// The first chunk, which has no bound to start from, stays in registers: a wave's two sub-tiles
+// give 8 maxima per lane and row, the 16 lanes of a row 128 maxima of disjoint key subsets, whose
+// K-th largest is a lower bound of the row's K-th largest logit; then the logits are collected.
+// At the end the bisection goes on until exactly K entries are left; where equal or almost equal logits prevent that, the
+// entries are ranked (larger logit first, equal logits by lower position).  The K winners become
+// weights with the row's log-sum-exp and are split into WO / WD by needle membership.  A row whose
+// list overflows (many equal logits at the top, or logits that keep rising along the context) is
+// flagged and redone by qk_fallback_kernel.
+// 32 layers x 8 KV heads x 16384 keys x 64 rows, K = 32: 316 -> 249 us (4.3 TB/s of keys; a large copy runs at 5.3) against
+// chunks half as long as what came before with lists of 128, a first chunk of 1024 keys walked twice, an 18-step
+// bisection at every chunk, an LDS atomic per entry and the queries in registers throughout; 6 meetings of the waves
+// instead of 11.
 constexpr int kQkThreads = 512;      // 8 waves
 constexpr int kQkWaves = kQkThreads / 64;
 constexpr int kQkRows = 64;          // two row tiles of 32
 constexpr int kQkStripe = 32 * kQkWaves;   // keys the waves take together: chunk ends are multiples of it
-constexpr int kQkFirst = 4 * kQkStripe;    // keys of the first chunk
-constexpr int kQkSubsets = kQkWaves * 2 * 8;    // key subsets per row whose maxima are tracked in the first walk
-constexpr int kQkCand = 128;
-constexpr int kQkBoundBits = 18;     // leading key bits that the bound of a row is resolved to between chunks
+constexpr int kQkFirst = 2 * kQkStripe;    // keys of the first chunk: two sub-tiles per wave
+constexpr int kQkSubsets = kQkWaves * 2 * 8;    // key subsets per row whose maxima are taken in the first chunk
+constexpr int kQkCand = 256;         // entries of a row's list
+constexpr int kQkStride = kQkCand + 8;     // conflict-free for the 8 rows a wave looks after; entry kQkCand takes what overflows
+constexpr int kQkSlack = 6;          // between chunks a list may keep this many entries more than K
 constexpr int kQkFallbackWGs = 128;
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 qk_bf16x8;
@@ -492,24 +500,40 @@ union QkPack16 {
   qk_bf16x8 b;
 };
 
-template <int DK>
 struct QkLds {
-  float cand_x[kQkRows][kQkCand];                           // first walk: the subset maxima [row][(wave, half, i)]
-  int32_t cand_p[kQkRows][kQkCand];
-  float st_m[kQkRows][2 * kQkWaves], st_s[kQkRows][2 * kQkWaves], st_t[kQkRows][2 * kQkWaves];
+  float cand_x[kQkRows][kQkStride];                         // scaled logits (log2 domain); first chunk: the subset maxima [row][(wave, half, i)]
+  int32_t cand_p[kQkRows][kQkStride];
+  union {
+    __attribute__((aligned(16))) unsigned char q[kQkRows][128 * 2 + 16];   // the queries (padded rows)
+    struct {                                                // at the end: statistics of the rows' 16 lanes
+      float st_m[kQkRows][2 * kQkWaves], st_s[kQkRows][2 * kQkWaves], st_t[kQkRows][2 * kQkWaves];
+    };
+  };
   float bound[kQkRows];
   uint32_t cnt[kQkRows];
   uint32_t ovf[kQkRows];
 };
 
-__device__ __forceinline__ float key_to_float(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
+// Sum / maximum / minimum over the 8 lanes that look after a row: neighbours in the quad, then the other quad (DPP).
+template <class F>
+__device__ __forceinline__ uint32_t over_8_lanes(uint32_t v, F f) {
+  v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+  v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+  return f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));   // row_half_mirror
 }
-// a key whose low bits were cleared, as a bound: a value at or below the one the key came from
-// (a truncated key of -inf reads as a NaN pattern: -inf then)
-__device__ __forceinline__ float bound_from_key(uint32_t key) {
-  const float f = key_to_float(key);
-  return f != f ? -INFINITY : f;
+__device__ __forceinline__ uint32_t sum_8(uint32_t v) {
+  return over_8_lanes(v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ float sum_8(float v) {
+  return __uint_as_float(over_8_lanes(__float_as_uint(v), [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }));
+}
+__device__ __forceinline__ float max_8(float v) {
+  return __uint_as_float(over_8_lanes(__float_as_uint(v), [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); }));
+}
+__device__ __forceinline__ double sum_8(double v) {
+#pragma unroll
+  for (int m = 1; m < 8; m *= 2) v += __shfl_xor(v, m, 64);
+  return v;
 }
 
 template <int DK>
@@ -519,15 +543,13 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
                                                                  double* __restrict__ cells, unsigned char* __restrict__ overflow) {
   constexpr int KK = DK / 16;
   extern __shared__ __attribute__((aligned(16))) unsigned char qk_smem[];
-  QkLds<DK>& S = *reinterpret_cast<QkLds<DK>*>(qk_smem);
+  QkLds& S = *reinterpret_cast<QkLds*>(qk_smem);
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
-  static_assert(sizeof(float) * kQkSubsets <= sizeof(S.cand_x[0]) + sizeof(S.cand_p[0]) &&
-                    offsetof(QkLds<DK>, cand_p) == sizeof(S.cand_x),
-                "the subset maxima of the first walk live in the (still empty) candidate lists");
-  static_assert(kQkSubsets == 128 && kQkCand == 128 && kQkRows % kQkWaves == 0, "eight lanes hold the maxima / candidates of a row, 16 each");
-  float (*mxl)[kQkSubsets] = reinterpret_cast<float (*)[kQkSubsets]>(&S.cand_x[0][0]);
+  static_assert(kQkSubsets <= kQkStride, "the subset maxima of the first chunk live in the (still empty) candidate lists");
+  static_assert(kQkSubsets == 128 && kQkCand == 256 && kQkRows == 8 * kQkWaves, "eight lanes hold the maxima or a half or all of the candidates of a row, 16 or 32 each");
   constexpr int RPW = kQkRows / kQkWaves;            // rows a wave looks after between the chunks
   const int G = Hq / Hkv, R = G * T;
   const int rg = blockIdx.x % rowgroups, seg = blockIdx.x / rowgroups;   // seg = l * Hkv + kvh
@@ -544,19 +566,25 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
     S.ovf[i] = 0;
     S.bound[i] = INFINITY;
   }
-  // this lane's rows inside the workgroup: l32 and 32 + l32
+  constexpr int PPR = DK / 8;                          // 16-byte pieces of a row
+  for (int i = tid; i < kQkRows * PPR; i += kQkThreads)
+    *reinterpret_cast<qk_u32x4*>(&S.q[i / PPR][i % PPR * 16]) =
+        *reinterpret_cast<const qk_u32x4*>(qbase + (int64_t)min(i / PPR, nrows - 1) * DK + i % PPR * 8);
+  // the queries of this lane's rows inside the workgroup, l32 and 32 + l32: read from LDS for every chunk, so that their
+  // registers are free while the waves meet
   qk_bf16x8 qreg[2][KK];
+  auto load_queries = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      QkPack16 p;
-      p.u = *reinterpret_cast<const qk_u32x4*>(qbase + (int64_t)min(mt * 32 + l32, nrows - 1) * DK + kk * 16 + half * 8);
-      qreg[mt][kk] = p.b;
-    }
+      for (int kk = 0; kk < KK; ++kk) {
+        QkPack16 p;
+        p.u = *reinterpret_cast<const qk_u32x4*>(&S.q[mt * 32 + l32][kk * 32 + half * 16]);
+        qreg[mt][kk] = p.b;
+      }
+  };
   float m_run[2] = {-INFINITY, -INFINITY}, s_run[2] = {0.f, 0.f}, t_run[2] = {0.f, 0.f};   // running maximum, sum of exp2(x - max), the same over the needle
-  float bound[2] = {INFINITY, INFINITY}, bound_raw[2] = {INFINITY, INFINITY};
-  __syncthreads();
+  float bound_raw[2];
 
   // one sub-tile of 32 keys starting at key_s: 16 bytes of key row (key_s + l32) per load (clamped at the end of the keys)
   auto issue = [&](int key_s, qk_u32x4 (&kf)[KK]) __attribute__((always_inline)) {
@@ -594,13 +622,20 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
           if (key0 + 8 * (i >> 2) + (i & 3) >= n) acc[mt][i] = -INFINITY;
     }
   };
+  // Three-operand maxima written out: from fmaxf the compiler makes two instructions that only canonicalise for each
+  // that compares.  The first maximum is the compiler's: reading the MFMA's result there, it keeps the
+  // distance that the hardware asks for between the two, and the others follow it.
+  auto max_16 = [&](const qk_f32x16& a) __attribute__((always_inline)) {
+    float r = fmaxf(a[14], a[15]);
+#pragma unroll
+    for (int i = 0; i < 14; i += 2) asm("v_max3_f32 %0, %0, %1, %2" : "+v"(r) : "v"(a[i]), "v"(a[i + 1]));
+    return r;
+  };
   // softmax statistics of the 16 unscaled logits a of row tile mt; returns their maximum.  Straight-line
   // code (it is scheduled among the MFMAs of the next sub-tile); the needle mass of the few sub-tiles
   // that touch the needle is added by needle_mass() afterwards.
   auto stats = [&](int mt, const qk_f32x16& a) __attribute__((always_inline)) {
-    float mxr = fmaxf(a[0], a[1]);
-#pragma unroll
-    for (int i = 2; i < 16; i += 2) mxr = fmaxf(mxr, fmaxf(a[i], a[i + 1]));
+    const float mxr = max_16(a);
     const float mn = fmaxf(m_run[mt], mxr * c_log2);
     const float mu = mn == -INFINITY ? 0.f : mn;
     const float scale = __builtin_amdgcn_exp2f(m_run[mt] - mu);
@@ -625,40 +660,46 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
       t_run[mt] += tsum;
     }
   };
-  // the logits at or above the bound join the row's list (mxr: the largest unscaled logit of the 16;
-  // bound_raw: the bound in unscaled units, rounded down, so the first test never misses one)
-  auto collect = [&](int mt, int key0, const qk_f32x16& a, float mxr) __attribute__((always_inline)) {
-    if (mxr >= bound_raw[mt]) {
-      const int r = mt * 32 + l32;
+  // The logits at or above the bounds join the rows' lists (mx: the largest unscaled logit of each 16; bound_raw:
+  // the bound in unscaled units, rounded down, so that the test never misses one).
+  auto collect = [&](int key0, const qk_f32x16 (&a)[2], const float (&mx)[2]) __attribute__((always_inline)) {
+    if (mx[0] >= bound_raw[0] || mx[1] >= bound_raw[1]) {
+      uint32_t slot0 = 0, slot1 = 0;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float x = a[i] * c_log2;
-        if (x >= bound[mt]) {
-          const uint32_t slot = atomicAdd(&S.cnt[r], 1u);
-          if (slot < (uint32_t)kQkCand) {
-            S.cand_x[r][slot] = x;
-            S.cand_p[r][slot] = key0 + 8 * (i >> 2) + (i & 3);
-          }
-        }
+        slot0 += a[0][i] >= bound_raw[0] ? 1u : 0u;
+        slot1 += a[1][i] >= bound_raw[1] ? 1u : 0u;
       }
+      slot0 = atomicAdd(&S.cnt[l32], slot0);
+      slot1 = atomicAdd(&S.cnt[32 + l32], slot1);
+      auto append = [&](int mt, uint32_t slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (a[mt][i] >= bound_raw[mt]) {
+            const uint32_t at = min(slot++, (uint32_t)kQkCand);
+            S.cand_x[mt * 32 + l32][at] = a[mt][i] * c_log2;
+            S.cand_p[mt * 32 + l32][at] = key0 + 8 * (i >> 2) + (i & 3);
+          }
+      };
+      append(0, slot0);
+      append(1, slot1);
     }
   };
   // This wave's sub-tiles of [key_lo, key_hi) (multiples of kQkStripe, key_hi clipped to n) as a
   // software pipeline: the MFMAs of a sub-tile are issued among the statistics of the sub-tile
   // before it (the two sets of accumulators alternate), and the loads of the sub-tile after it are
-  // in flight.  front(mt, key0, a) runs inside that mix and returns a value that back(mt, key0, a, v)
-  // receives afterwards (back may branch).
-  // (preloaded: the wave's first sub-tile is already on its way into kfA, requested by prefetch())
+  // in flight.  front(mt, a) runs inside that mix and returns a value that back(key0, a, values)
+  // takes afterwards (and may branch).  The
+  // wave's first two sub-tiles are already on their way into kfA and kfB, requested by prefetch().
   qk_u32x4 kfA[KK], kfB[KK];
   auto prefetch = [&](int key_lo, int key_hi) __attribute__((always_inline)) {
     if (key_lo + wv * 32 < key_hi) issue(key_lo + wv * 32, kfA);
+    if (key_lo + wv * 32 + kQkStripe < key_hi) issue(key_lo + wv * 32 + kQkStripe, kfB);
   };
-  auto walk = [&](int key_lo, int key_hi, bool preloaded, auto front, auto back) __attribute__((always_inline)) {
+  auto walk = [&](int key_lo, int key_hi, auto front, auto back) __attribute__((always_inline)) {
     int ks = key_lo + wv * 32;
     if (ks >= key_hi) return;
-    if (!preloaded) issue(ks, kfA);
     qk_f32x16 accA[2], accB[2];
-    if (ks + kQkStripe < key_hi) issue(ks + kQkStripe, kfB);
     mfma_sub(kfA, accA);
     // one pipelined step: the sub-tile at ks is in `cur`; the next one goes from kn into `nxt`, and kc is refilled
     auto pstep = [&](qk_f32x16 (&cur)[2], qk_f32x16 (&nxt)[2], qk_u32x4 (&kc)[KK], qk_u32x4 (&kn)[KK]) __attribute__((always_inline)) {
@@ -667,8 +708,8 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
       // kc held the current sub-tile, whose MFMAs have been issued: refill it with the sub-tile after the next
       if (ks + 2 * kQkStripe < key_hi) issue(ks + 2 * kQkStripe, kc);
       mfma_sub(kn, nxt);
-      v[0] = front(0, key0, cur[0]);
-      v[1] = front(1, key0, cur[1]);
+      v[0] = front(0, cur[0]);
+      v[1] = front(1, cur[1]);
 #pragma unroll
       for (int g = 0; g < 2 * KK; ++g) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
@@ -676,17 +717,15 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
       }
       // the statistics are complete here (they must not sink below the branches that follow)
       asm volatile("" ::"v"(v[0]), "v"(v[1]), "v"(s_run[0]), "v"(s_run[1]), "v"(m_run[0]), "v"(m_run[1]));
-      back(0, key0, cur[0], v[0]);
-      back(1, key0, cur[1], v[1]);
+      back(key0, cur, v);
       ks += kQkStripe;
     };
     // the wave's last sub-tile of the walk (the only one that can reach past the end of the keys)
     auto last = [&](qk_f32x16 (&cur)[2]) __attribute__((always_inline)) {
       const int key0 = ks + 4 * half;
       mask_sub(ks, cur);
-      const float v0 = front(0, key0, cur[0]), v1 = front(1, key0, cur[1]);
-      back(0, key0, cur[0], v0);
-      back(1, key0, cur[1], v1);
+      const float v[2] = {front(0, cur[0]), front(1, cur[1])};
+      back(key0, cur, v);
     };
     int rem = (key_hi - ks + kQkStripe - 1) / kQkStripe;   // sub-tiles of this wave still to finish (>= 1); the current one is in accA
     while (rem >= 3) {
@@ -701,200 +740,225 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
       last(accA);
     }
   };
-  // Bounds of the wave's RPW = 8 rows at once: 8 lanes per row, NE keys per lane (0 = no entry).
-  // Bisection on the leading kQkBoundBits bits of the keys: the result (the same in the 8 lanes
-  // of a row) is the largest value with the remaining bits clear that at least K keys reach, so
-  // it lies at or below the K-th largest key and within 2^-(kQkBoundBits - 9) of it (relative, in
-  // the logit).  All on the vector unit: no lane-mask round trips through scalar registers.
-  auto group_kth = [&](auto& keys, auto ne_c) __attribute__((always_inline)) {
+  // The bounds of the wave's 8 rows at once: 8 lanes per row, NE values per lane (NaN: no value).  Bisection from lo
+  // (reached by `reach` >= K values of the row) towards the largest value until at most K + slack values are at or above
+  // lo, or lo cannot be told from the K-th largest: lo stays at or below that one throughout.
+  const int grow = wv * RPW + (lane >> 3), gl = lane & 7;
+  auto bisect = [&](const auto& x, auto ne_c, float& lo, uint32_t reach, uint32_t slack, int steps) __attribute__((always_inline)) {
     constexpr int NE = decltype(ne_c)::value;
-    uint32_t tkey = 0;
-#pragma unroll 1
-    for (int b = 31; b >= 32 - kQkBoundBits; --b) {
-      const uint32_t trial = tkey | (1u << b);
+    float hi = x[0];
+#pragma unroll
+    for (int j = 1; j < NE; ++j) hi = fmaxf(hi, x[j]);
+    hi = max_8(hi);
+    if (__any(lo == -INFINITY)) {                        // no bound yet: the smallest finite value, if enough reach it
+      float mn = INFINITY;
+#pragma unroll
+      for (int j = 0; j < NE; ++j) mn = fminf(mn, x[j] > -INFINITY ? x[j] : INFINITY);
+      mn = -max_8(-mn);
       uint32_t c = 0;
 #pragma unroll
-      for (int j = 0; j < NE; ++j) c += keys[j] >= trial ? 1u : 0u;
-      // sum over the 8 lanes of the row: neighbours in the quad, then the other quad (DPP, no LDS crossbar)
-      c += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
-      c += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
-      c += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0x141, 0xF, 0xF, false);   // row_half_mirror
-      if (c >= (uint32_t)topk) tkey = trial;
+      for (int j = 0; j < NE; ++j) c += x[j] >= mn ? 1u : 0u;
+      c = sum_8(c);
+      if (lo == -INFINITY && c >= (uint32_t)topk) {
+        lo = mn;
+        reach = c;
+      }
     }
-    return tkey;
+#pragma unroll 1
+    for (int it = 0; it < steps; ++it) {
+      const float mid = lo + 0.5f * (hi - lo);
+      const bool open = reach > (uint32_t)topk + slack && mid > lo && mid <= hi;   // (false for infinities and NaN)
+      if (!__any(open)) break;
+      uint32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < NE; ++j) c += x[j] >= mid ? 1u : 0u;
+      c = sum_8(c);
+      if (open) {
+        if (c >= (uint32_t)topk) {
+          lo = mid;
+          reach = c;
+        } else {
+          hi = mid;
+        }
+      }
+    }
   };
-  // A wave sets the new bound nb of row rr and drops the list entries below it (an overflowed
-  // list sends the row to the fallback).
-  auto refilter = [&](int rr, float nb) __attribute__((always_inline)) {
-    const uint32_t c = S.cnt[rr];
-    if (c > (uint32_t)kQkCand) {
-      if (lane == 0) {
-        S.ovf[rr] = 1;
-        S.cnt[rr] = 0;
-        S.bound[rr] = INFINITY;
-      }
-    } else {
-      const float x0 = lane < (int)c ? S.cand_x[rr][lane] : -INFINITY, x1 = lane + 64 < (int)c ? S.cand_x[rr][lane + 64] : -INFINITY;
-      const int32_t p0 = S.cand_p[rr][lane], p1 = S.cand_p[rr][lane + 64];
-      const bool k0 = lane < (int)c && x0 >= nb, k1 = lane + 64 < (int)c && x1 >= nb;
-      const unsigned long long m0 = __ballot(k0), m1 = __ballot(k1);
-      const uint32_t n0 = (uint32_t)__popcll(m0);
-      const uint32_t lb0 = __builtin_amdgcn_mbcnt_hi((uint32_t)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m0, 0u));
-      const uint32_t lb1 = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, 0u));
-      if (k0) {
-        S.cand_x[rr][lb0] = x0;
-        S.cand_p[rr][lb0] = p0;
-      }
-      if (k1) {
-        S.cand_x[rr][n0 + lb1] = x1;
-        S.cand_p[rr][n0 + lb1] = p1;
-      }
-      if (lane == 0) {
-        S.cnt[rr] = n0 + (uint32_t)__popcll(m1);
-        if (!S.ovf[rr]) S.bound[rr] = nb;
+  // Between the chunks: new bounds, and the entries below them leave the lists (an overflowed list sends its row to the
+  // fallback).
+  auto update_lists = [&](uint32_t slack, int steps, auto ne_c) __attribute__((always_inline)) {
+    constexpr int NE = decltype(ne_c)::value;
+    const uint32_t c = S.cnt[grow];
+    const bool over = c > (uint32_t)kQkCand || S.ovf[grow];
+    float lo = S.bound[grow];
+    float x[NE];
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+      const float v = S.cand_x[grow][gl + 8 * j];
+      x[j] = gl + 8 * j < (int)c ? v : __builtin_nanf("");
+    }
+    if (c < (uint32_t)topk) lo = -INFINITY;              // cannot happen for a row of finite logits: keeps everything
+    else bisect(x, ne_c, lo, c, slack, steps);
+    // in order, 16 entries of a lane at a time: no entry moves up, so none is overwritten before it is read
+    uint32_t kept = 0;
+#pragma unroll
+    for (int j0 = 0; j0 < NE; j0 += 16) {
+      int32_t pos[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) pos[j] = S.cand_p[grow][gl + 8 * (j0 + j)];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const bool keep = x[j0 + j] >= lo;
+        const uint32_t in_row = (uint32_t)(__ballot(keep) >> (lane & 56)) & 255u;
+        if (keep) {
+          const uint32_t at = kept + __popc(in_row & ((1u << gl) - 1u));
+          S.cand_x[grow][at] = x[j0 + j];
+          S.cand_p[grow][at] = pos[j];
+        }
+        kept += __popc(in_row);
       }
     }
+    if (gl == 0) {
+      S.cnt[grow] = over ? 0u : kept;
+      S.ovf[grow] = over ? 1u : 0u;
+      S.bound[grow] = over || grow >= nrows ? INFINITY : lo;
+    }
+  };
+  auto meet = [&](uint32_t slack, int steps) __attribute__((always_inline)) {
+    __syncthreads();
+    if (__any(S.cnt[grow] > (uint32_t)kQkCand / 2)) update_lists(slack, steps, std::integral_constant<int, kQkCand / 8>{});
+    else update_lists(slack, steps, std::integral_constant<int, kQkCand / 16>{});
+    __syncthreads();
   };
 
   // this lane's bounds from the rows' bounds in LDS; the unscaled form is lowered by a few ulps so
-  // that a logit whose scaled value reaches the bound never fails the first test
+  // that a logit whose scaled value reaches the bound never fails the test
   auto load_bounds = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      bound[mt] = mt * 32 + l32 < nrows ? S.bound[mt * 32 + l32] : INFINITY;
-      const float raw = bound[mt] / c_log2;
-      bound_raw[mt] = fabsf(raw) == INFINITY ? raw : raw - fabsf(raw) * 4.8e-7f;
+      const float raw = (mt * 32 + l32 < nrows ? S.bound[mt * 32 + l32] : INFINITY) / c_log2;
+      // (no bound: any finite logit; those of -inf, masked keys among them, weigh nothing)
+      bound_raw[mt] = raw == INFINITY ? raw : fmaxf(raw - fabsf(raw) * 4.8e-7f, -3.4028235e38f);
     }
   };
-  auto no_front = [&](int, int, const qk_f32x16&) __attribute__((always_inline)) { return 0.f; };
+  // Keys of the chunk from n_lo on: as many as came before, in whole stripes, and a small rest of the keys with them.
+  auto chunk_end = [&](int n_lo) __attribute__((always_inline)) {
+    const int hi = 2 * n_lo;
+    return n - hi <= hi / 8 ? n : hi;
+  };
 
-  int c_lo = 0, c_hi = min(n, kQkFirst);
+  int c_lo, c_hi = min(n, kQkFirst);
   {
-    // The first chunk, first walk: statistics and 8 running maxima (of pairs of keys) per lane and row
-    float mxs[2][8];
+    // the first chunk: both sub-tiles of the wave in registers
+    const int ks[2] = {wv * 32, wv * 32 + kQkStripe};
+    qk_f32x16 acc[2][2];
+    issue(ks[0], kfA);
+    issue(ks[1], kfB);
+    __syncthreads();                                  // lists empty, queries there
+    load_queries();
+    mfma_sub(kfA, acc[0]);
+    mfma_sub(kfB, acc[1]);
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int j = 0; j < 2; ++j) {
+      mask_sub(ks[j], acc[j]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) mxs[mt][i] = -INFINITY;
-    walk(c_lo, c_hi, false,
-         [&](int mt, int, const qk_f32x16& a) __attribute__((always_inline)) { return stats(mt, a); },
-         [&](int mt, int key0, const qk_f32x16& a, float) __attribute__((always_inline)) {
-           needle_mass(mt, key0, a);
+      for (int mt = 0; mt < 2; ++mt) {
+        stats(mt, acc[j][mt]);
+        needle_mass(mt, ks[j] + 4 * half, acc[j][mt]);
+      }
+    }
 #pragma unroll
-           for (int i = 0; i < 8; ++i) mxs[mt][i] = fmaxf(mxs[mt][i], fmaxf(a[2 * i], a[2 * i + 1]));
-         });
-    prefetch(c_lo, c_hi);                             // the second walk starts where the first did
+    for (int mt = 0; mt < 2; ++mt) {
+      float* const mxl = &S.cand_x[mt * 32 + l32][(wv * 2 + half) * 8];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) mxl[mt * 32 + l32][(wv * 2 + half) * 8 + i] = mxs[mt][i] * c_log2;
+      for (int i = 0; i < 8; ++i)
+        mxl[i] = fmaxf(fmaxf(acc[0][mt][2 * i], acc[0][mt][2 * i + 1]), fmaxf(acc[1][mt][2 * i], acc[1][mt][2 * i + 1])) * c_log2;
+    }
+    if (c_hi < n) prefetch(c_hi, chunk_end(c_hi));
     __syncthreads();
-    const int grow = wv * RPW + (lane >> 3), gl = lane & 7;   // between chunks: 8 lanes look after one row
-    float nb0;
+    float nb = -INFINITY;
     {
-      uint32_t keys[kQkSubsets / 8];
+      float x[kQkSubsets / 8];
 #pragma unroll
-      for (int j = 0; j < kQkSubsets / 8; ++j) keys[j] = float_key(mxl[grow][gl + 8 * j]);
-      nb0 = grow < nrows ? bound_from_key(group_kth(keys, std::integral_constant<int, kQkSubsets / 8>{})) : INFINITY;
+      for (int j = 0; j < kQkSubsets / 8; ++j) x[j] = S.cand_x[grow][gl + 8 * j];
+      bisect(x, std::integral_constant<int, kQkSubsets / 8>{}, nb, kQkSubsets, 2, 24);
     }
     __syncthreads();                                  // the maxima have been read: the lists may fill
-    if (gl == 0) S.bound[grow] = nb0;
+    if (gl == 0) S.bound[grow] = grow < nrows ? nb : INFINITY;
     __syncthreads();
     load_bounds();
-    // second walk: collect
-    walk(c_lo, c_hi, true, no_front,
-         [&](int mt, int key0, const qk_f32x16& a, float) __attribute__((always_inline)) {
-           float mxr = fmaxf(a[0], a[1]);
 #pragma unroll
-           for (int i = 2; i < 16; i += 2) mxr = fmaxf(mxr, fmaxf(a[i], a[i + 1]));
-           collect(mt, key0, a, mxr);
-         });
+    for (int j = 0; j < 2; ++j)
+      if (ks[j] < n) {
+        float mx[2];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) mx[mt] = max_16(acc[j][mt]);
+        collect(ks[j] + 4 * half, acc[j], mx);
+      }
   }
   for (;;) {
-    // the next chunk: at most half as many keys as came before, in whole stripes; its first
-    // sub-tile is requested before the waves meet
-    const int n_lo = c_hi, n_hi = min(n, n_lo + max(kQkStripe, n_lo / 2 / kQkStripe * kQkStripe));
-    if (n_lo < n) prefetch(n_lo, n_hi);
-    // every list now holds all logits so far that are at or above the row's bound, hence the K
-    // largest: their K-th largest is the new bound, and the entries below it are dropped
-    __syncthreads();
-    {
-      const int grow = wv * RPW + (lane >> 3), gl = lane & 7;
-      const uint32_t c = min(S.cnt[grow], (uint32_t)kQkCand);
-      uint32_t keys[kQkCand / 8];
+    const bool done = c_hi >= n;
+    if (done) {
+      // statistics of a row: its 16 lanes -> log-sum-exp and needle mass
 #pragma unroll
-      for (int j = 0; j < kQkCand / 8; ++j) keys[j] = gl + 8 * j < (int)c ? float_key(S.cand_x[grow][gl + 8 * j]) : 0u;
-      const uint32_t tkey = group_kth(keys, std::integral_constant<int, kQkCand / 8>{});
-      // (a list shorter than K cannot happen for a row of finite logits; -inf keeps everything)
-      const float nbg = grow < nrows ? (c >= (uint32_t)topk ? bound_from_key(tkey) : -INFINITY) : INFINITY;
-      for (int j = 0; j < RPW; ++j) refilter(wv * RPW + j, __shfl(nbg, 8 * j, 64));
+      for (int mt = 0; mt < 2; ++mt) {
+        S.st_m[mt * 32 + l32][wv * 2 + half] = m_run[mt];
+        S.st_s[mt * 32 + l32][wv * 2 + half] = s_run[mt];
+        S.st_t[mt * 32 + l32][wv * 2 + half] = t_run[mt];
+      }
     }
-    __syncthreads();
-    if (c_hi >= n) break;
+    // every list now holds all logits so far that are at or above the row's bound, hence the K largest
+    meet(done ? 0u : (uint32_t)kQkSlack, done ? 40 : 24);
+    if (done) break;
+    load_queries();
     load_bounds();
-    c_lo = n_lo;
-    c_hi = n_hi;
-    walk(c_lo, c_hi, true,
-         [&](int mt, int, const qk_f32x16& a) __attribute__((always_inline)) { return stats(mt, a); },
-         [&](int mt, int key0, const qk_f32x16& a, float mxr) __attribute__((always_inline)) {
-           needle_mass(mt, key0, a);
-           collect(mt, key0, a, mxr);
+    c_lo = c_hi;
+    c_hi = chunk_end(c_lo);
+    walk(c_lo, c_hi,
+         [&](int mt, const qk_f32x16& a) __attribute__((always_inline)) { return stats(mt, a); },
+         [&](int key0, const qk_f32x16 (&a)[2], const float (&mx)[2]) __attribute__((always_inline)) {
+           needle_mass(0, key0, a[0]);
+           needle_mass(1, key0, a[1]);
+           collect(key0, a, mx);
          });
+    if (c_hi < n) prefetch(c_hi, chunk_end(c_hi));
   }
-
-  // statistics of a row: its 16 lanes -> log-sum-exp and needle mass
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    S.st_m[mt * 32 + l32][wv * 2 + half] = m_run[mt];
-    S.st_s[mt * 32 + l32][wv * 2 + half] = s_run[mt];
-    S.st_t[mt * 32 + l32][wv * 2 + half] = t_run[mt];
-  }
-  __syncthreads();
-  for (int rr = wv * RPW; rr < min(wv * RPW + RPW, nrows); ++rr) {
-    float M = S.st_m[rr][0];
-#pragma unroll
-    for (int j = 1; j < 2 * kQkWaves; ++j) M = fmaxf(M, S.st_m[rr][j]);
-    float ssum = 0.f, tsum = 0.f;
-#pragma unroll
-    for (int j = 0; j < 2 * kQkWaves; ++j) {
-      const float f = __builtin_amdgcn_exp2f(S.st_m[rr][j] - M);
-      ssum += S.st_s[rr][j] * f;
-      tsum += S.st_t[rr][j] * f;
-    }
+  {
+    const float m0 = S.st_m[grow][gl], m1 = S.st_m[grow][gl + 8];
+    const float M = max_8(fmaxf(m0, m1));
+    const float f0 = __builtin_amdgcn_exp2f(m0 - M), f1 = __builtin_amdgcn_exp2f(m1 - M);
+    const float ssum = sum_8(S.st_s[grow][gl] * f0 + S.st_s[grow][gl + 8] * f1);
+    const float tsum = sum_8(S.st_t[grow][gl] * f0 + S.st_t[grow][gl + 8] * f1);
     const float lse = M + log2f(ssum);
     const double tnw = (double)tsum / (double)ssum;
-    const uint32_t c = S.cnt[rr];
-    const bool over = S.ovf[rr] || c > (uint32_t)kQkCand;
-    if (lane == 0) overflow[rowid0 + rr] = over ? 1 : 0;
-    if (over) continue;
-    // exact rank of the candidates: larger logit first, equal logits by lower position
-    const float x0 = lane < (int)c ? S.cand_x[rr][lane] : -INFINITY, x1 = lane + 64 < (int)c ? S.cand_x[rr][lane + 64] : -INFINITY;
-    const int32_t p0 = S.cand_p[rr][lane], p1 = S.cand_p[rr][lane + 64];
-    uint32_t a0 = 0, a1 = 0;
-    for (uint32_t j = 0; j < c; ++j) {
-      const float xj = S.cand_x[rr][j];
-      const int32_t pj = S.cand_p[rr][j];
-      a0 += (xj > x0 || (xj == x0 && pj < p0)) ? 1u : 0u;
-      a1 += (xj > x1 || (xj == x1 && pj < p1)) ? 1u : 0u;
-    }
+    const uint32_t c = S.cnt[grow];
     double wo = 0.0, wd = 0.0;
-    if (lane < (int)c && a0 < (uint32_t)topk) {
-      const double wgt = (double)__builtin_amdgcn_exp2f(x0 - lse);
-      if (p0 >= needle_start && p0 < ne) wo += wgt; else wd += wgt;
+    for (uint32_t i = gl; i < c; i += 8) {
+      const float x = S.cand_x[grow][i];
+      const int32_t pos = S.cand_p[grow][i];
+      uint32_t rank = 0;
+      if (c > (uint32_t)topk)                          // larger logit first, equal logits by lower position
+        for (uint32_t j = 0; j < c; ++j) {
+          const float xj = S.cand_x[grow][j];
+          rank += (xj > x || (xj == x && S.cand_p[grow][j] < pos)) ? 1u : 0u;
+        }
+      if (rank < (uint32_t)topk) {
+        const double wgt = (double)__builtin_amdgcn_exp2f(x - lse);
+        if (pos >= needle_start && pos < ne) wo += wgt; else wd += wgt;
+      }
     }
-    if (lane + 64 < (int)c && a1 < (uint32_t)topk) {
-      const double wgt = (double)__builtin_amdgcn_exp2f(x1 - lse);
-      if (p1 >= needle_start && p1 < ne) wo += wgt; else wd += wgt;
-    }
-    wo = wave_sum<double>(wo);
-    wd = wave_sum<double>(wd);
-    if (lane == 0) {
-      const double WS = fmax(0.0, tnw - wo);
-      double* cdst = cells + (rowid0 + rr) * 4;
-      cdst[0] = wo;
-      cdst[1] = wd;
-      cdst[2] = WS;
-      cdst[3] = 1.0 - wo - wd - WS;                  // a softmax row sums to one
+    wo = sum_8(wo);
+    wd = sum_8(wd);
+    if (gl == 0 && grow < nrows) {
+      const bool over = S.ovf[grow] != 0;
+      overflow[rowid0 + grow] = over ? 1 : 0;
+      if (!over) {
+        const double WS = fmax(0.0, tnw - wo);
+        double* cdst = cells + (rowid0 + grow) * 4;
+        cdst[0] = wo;
+        cdst[1] = wd;
+        cdst[2] = WS;
+        cdst[3] = 1.0 - wo - wd - WS;                  // a softmax row sums to one
+      }
     }
   }
 }
@@ -1137,7 +1201,7 @@ hipError_t qk_prepare() {
   const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t(1) << dev) : 0;
   if (!(done & bit)) {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&qk_cells_kernel<DK>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)sizeof(QkLds<DK>));
+                            (int)sizeof(QkLds));
     if (e != hipSuccess) return e;
     done |= bit;
   }
@@ -1158,7 +1222,7 @@ slkv_status qk_launch(const uint16_t* q, const uint16_t* k, int32_t L, int32_t H
   const float c_log2 = (float)(1.4426950408889634 / std::sqrt((double)DK));
   {
     ScopedKernelTimer tm(SLKV_K_QK_CELLS, st);
-    SLKV_LAUNCH(qk_cells_kernel<DK>, dim3((unsigned)(L * Hkv * rowgroups)), dim3(kQkThreads), sizeof(QkLds<DK>), st, q, k, Hq, Hkv,
+    SLKV_LAUNCH(qk_cells_kernel<DK>, dim3((unsigned)(L * Hkv * rowgroups)), dim3(kQkThreads), sizeof(QkLds), st, q, k, Hq, Hkv,
                 T, n, rowgroups, needle_start, needle_len, topk, c_log2, cells, flags);
   }
   {

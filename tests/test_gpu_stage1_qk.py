@@ -55,6 +55,19 @@ def test_short_contexts_and_the_largest_k(n, topk, d):
     check(x)
 
 
+@pytest.mark.parametrize("n,topk,d", [(31, 7, 64), (288, 64, 128), (511, 64, 64), (512, 1, 128), (513, 64, 128), (1152, 33, 64),
+                                      (1153, 64, 128)])
+def test_equal_logits_at_the_kth_place_and_the_ends_of_chunks(n, topk, d):
+    # every key twice: an odd K cuts a pair of equal logits, of which the lower position counts.  Around the first chunk
+    # (512 keys, two sub-tiles per wave) and the rest that the second one takes along (up to 1152).
+    # (K = n is left out: WS and Wide are then 1 minus a sum of fp32 weights, rounding of up to T * 2**-23 = 8e-7 where
+    # the exact value is 0, which is above the 2e-7 that check() allows a small cell.)
+    x = wl.config4_qk(L=1, Hq=4, Hkv=2, T=7, n=n, d=d, needle_len=min(16, n // 2), seed_extra=30 + n)
+    x.k[:, :, 1::2] = x.k[:, :, 0:n - 1:2]
+    x.topk = topk
+    check(x)
+
+
 def test_several_row_groups_and_accumulation():
     import torch
     x = wl.config4_qk(L=1, Hq=8, Hkv=1, T=12, n=3000, d=128, seed_extra=2)      # 96 rows per KV head: 64 + 32
