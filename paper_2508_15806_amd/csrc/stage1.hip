@@ -477,6 +477,8 @@ __global__ __launch_bounds__(64 * kReduceHeads) void head_reduce_kernel(const do
 // weights with the row's log-sum-exp and are split into WO / WD by needle membership.  A row whose
 // list overflows (many equal logits at the top, or logits that keep rising along the context) is
 // flagged and redone by qk_fallback_kernel.
+// Calls with too few heads and rows for the chip, or a little more than it takes at once, cut the keys into `nsplit` ranges of
+// `range` keys: a workgroup then leaves its range's statistics and K largest logits per row to qk_merge_kernel.
 // 32 layers x 8 KV heads x 16384 keys x 64 rows, K = 32: 316 -> 249 us (4.3 TB/s of keys; a large copy runs at 5.3) against
 // chunks half as long as what came before with lists of 128, a first chunk of 1024 keys walked twice, an 18-step
 // bisection at every chunk, an LDS atomic per entry and the queries in registers throughout; 6 meetings of the waves
@@ -490,6 +492,7 @@ constexpr int kQkSubsets = kQkWaves * 2 * 8;    // key subsets per row whose max
 constexpr int kQkCand = 256;         // entries of a row's list
 constexpr int kQkStride = kQkCand + 8;     // conflict-free for the 8 rows a wave looks after; entry kQkCand takes what overflows
 constexpr int kQkSlack = 6;          // between chunks a list may keep this many entries more than K
+constexpr int kQkMaxSplit = 32;      // key ranges of a head
 constexpr int kQkFallbackWGs = 128;
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 qk_bf16x8;
@@ -513,6 +516,10 @@ struct QkLds {
   uint32_t cnt[kQkRows];
   uint32_t ovf[kQkRows];
 };
+
+// Floats of a (row, key range) record: largest logit, sum, needle sum, overflow flag; the K largest logits (NaN beyond the
+// range's keys); their positions.
+__host__ __device__ constexpr int qk_record(int topk) { return 4 + 2 * topk; }
 
 // Sum / maximum / minimum over the 8 lanes that look after a row: neighbours in the quad, then the other quad (DPP).
 template <class F>
@@ -538,9 +545,10 @@ __device__ __forceinline__ double sum_8(double v) {
 
 template <int DK>
 __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kmat,
-                                                                 int Hq, int Hkv, int T, int n, int rowgroups,
-                                                                 int needle_start, int needle_len, int topk, float c_log2,
-                                                                 double* __restrict__ cells, unsigned char* __restrict__ overflow) {
+                                                                 int Hq, int Hkv, int T, int n_keys, int rowgroups,
+                                                                 int nsplit, int range, int first_needle, int needle_len, int topk,
+                                                                 float c_log2, double* __restrict__ cells,
+                                                                 unsigned char* __restrict__ overflow, float* __restrict__ part) {
   constexpr int KK = DK / 16;
   extern __shared__ __attribute__((aligned(16))) unsigned char qk_smem[];
   QkLds& S = *reinterpret_cast<QkLds*>(qk_smem);
@@ -552,13 +560,16 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
   static_assert(kQkSubsets == 128 && kQkCand == 256 && kQkRows == 8 * kQkWaves, "eight lanes hold the maxima or a half or all of the candidates of a row, 16 or 32 each");
   constexpr int RPW = kQkRows / kQkWaves;            // rows a wave looks after between the chunks
   const int G = Hq / Hkv, R = G * T;
-  const int rg = blockIdx.x % rowgroups, seg = blockIdx.x / rowgroups;   // seg = l * Hkv + kvh
+  const int split = blockIdx.x % nsplit, group = blockIdx.x / nsplit;
+  const int rg = group % rowgroups, seg = group / rowgroups;             // seg = l * Hkv + kvh
+  // this workgroup's keys, and the needle, from here on counted from the start of its range
+  const int key_base = split * range, n = min(range, n_keys - key_base), needle_start = first_needle - key_base;
   const int l = seg / Hkv, kvh = seg % Hkv;
   const int row0 = rg * kQkRows;
   const int nrows = min(kQkRows, R - row0);
   const int64_t rowid0 = ((int64_t)l * Hq + (int64_t)kvh * G) * T + row0;   // first global row of this workgroup
   const uint16_t* qbase = q + rowid0 * DK;
-  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat + (int64_t)seg * n * DK);
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat + ((int64_t)seg * n_keys + key_base) * DK);
   const int ne = needle_start + needle_len;
 
   for (int i = tid; i < kQkRows; i += kQkThreads) {
@@ -925,12 +936,15 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
   {
     const float m0 = S.st_m[grow][gl], m1 = S.st_m[grow][gl + 8];
     const float M = max_8(fmaxf(m0, m1));
-    const float f0 = __builtin_amdgcn_exp2f(m0 - M), f1 = __builtin_amdgcn_exp2f(m1 - M);
+    const float mu = M == -INFINITY ? 0.f : M;
+    const float f0 = __builtin_amdgcn_exp2f(m0 - mu), f1 = __builtin_amdgcn_exp2f(m1 - mu);
     const float ssum = sum_8(S.st_s[grow][gl] * f0 + S.st_s[grow][gl + 8] * f1);
     const float tsum = sum_8(S.st_t[grow][gl] * f0 + S.st_t[grow][gl + 8] * f1);
     const float lse = M + log2f(ssum);
     const double tnw = (double)tsum / (double)ssum;
     const uint32_t c = S.cnt[grow];
+    const bool over = S.ovf[grow] != 0;
+    float* const rec = nsplit > 1 ? part + ((rowid0 + min(grow, nrows - 1)) * nsplit + split) * qk_record(topk) : nullptr;
     double wo = 0.0, wd = 0.0;
     for (uint32_t i = gl; i < c; i += 8) {
       const float x = S.cand_x[grow][i];
@@ -941,15 +955,32 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
           const float xj = S.cand_x[grow][j];
           rank += (xj > x || (xj == x && S.cand_p[grow][j] < pos)) ? 1u : 0u;
         }
-      if (rank < (uint32_t)topk) {
+      if (rec) {
+        if (c <= (uint32_t)topk) rank = i;
+        if (grow < nrows && rank < (uint32_t)topk) {
+          rec[4 + rank] = x;
+          rec[4 + topk + rank] = __int_as_float(pos + key_base);
+        }
+      } else if (rank < (uint32_t)topk) {
         const double wgt = (double)__builtin_amdgcn_exp2f(x - lse);
         if (pos >= needle_start && pos < ne) wo += wgt; else wd += wgt;
       }
     }
+    if (rec) {
+      if (grow < nrows) {
+        for (uint32_t i = c + gl; i < (uint32_t)topk; i += 8) rec[4 + i] = __builtin_nanf("");   // (fewer than K keys)
+        if (gl == 0) {
+          rec[0] = M;
+          rec[1] = ssum;
+          rec[2] = tsum;
+          rec[3] = over ? 1.f : 0.f;
+        }
+      }
+      return;
+    }
     wo = sum_8(wo);
     wd = sum_8(wd);
     if (gl == 0 && grow < nrows) {
-      const bool over = S.ovf[grow] != 0;
       overflow[rowid0 + grow] = over ? 1 : 0;
       if (!over) {
         const double WS = fmax(0.0, tnw - wo);
@@ -959,6 +990,103 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
         cdst[2] = WS;
         cdst[3] = 1.0 - wo - wd - WS;                  // a softmax row sums to one
       }
+    }
+  }
+}
+
+// The key ranges of a row put together, one wave per row: statistics, the K largest of the ranges' K largest logits (NE
+// of them per lane) and the row's cells.  Bound by the round trip of its loads; 512 rows x 32 ranges x 32 entries: 5 us.
+template <int NE>
+__global__ __launch_bounds__(256) void qk_merge_kernel(const float* __restrict__ part, int64_t rows, int nsplit, int topk,
+                                                       int needle_start, int needle_len, double* __restrict__ cells,
+                                                       unsigned char* __restrict__ overflow) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const int record = qk_record(topk);
+  const float* const rec = part + row * nsplit * record;
+  float x[NE];
+  int32_t pos[NE];
+  const int entries = nsplit * topk;
+#pragma unroll
+  for (int j = 0; j < NE; ++j) {
+    const int e = min(j * 64 + lane, entries - 1), sp = e / topk;
+    const float* const at = rec + sp * record + 4 + (e - sp * topk);
+    x[j] = at[0];
+    pos[j] = __float_as_int(at[topk]);
+  }
+  const float* const head = rec + min(lane, nsplit - 1) * record;
+  const float m = lane < nsplit ? head[0] : -INFINITY, sm = lane < nsplit ? head[1] : 0.f, tm = lane < nsplit ? head[2] : 0.f;
+  const bool over = __any(lane < nsplit && head[3] != 0.f);
+#pragma unroll
+  for (int j = 0; j < NE; ++j)
+    if (j * 64 + lane >= entries) x[j] = __builtin_nanf("");
+  auto wave_max = [](float v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
+    return v;
+  };
+  const float M = wave_max(m), mu = M == -INFINITY ? 0.f : M;
+  const float f = __builtin_amdgcn_exp2f(m - mu);
+  const float ssum = wave_sum<float>(sm * f), tsum = wave_sum<float>(tm * f);
+  const float lse = M + log2f(ssum);
+  const double tnw = (double)tsum / (double)ssum;
+
+  // a value that exactly K entries reach, if equal logits allow it, by bisection as in qk_cells_kernel
+  auto reaching = [&](float v) __attribute__((always_inline)) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) c += (uint32_t)__popcll(__ballot(x[j] >= v));
+    return c;
+  };
+  float hi = x[0], lo = INFINITY;
+#pragma unroll
+  for (int j = 0; j < NE; ++j) {
+    hi = fmaxf(hi, x[j]);
+    lo = fminf(lo, x[j] > -INFINITY ? x[j] : INFINITY);
+  }
+  hi = wave_max(hi);
+  lo = -wave_max(-lo);
+  uint32_t reach = reaching(lo);
+  if (reach < (uint32_t)topk) lo = -INFINITY;
+#pragma unroll 1
+  for (int it = 0; it < 48; ++it) {
+    const float mid = lo + 0.5f * (hi - lo);
+    if (!(reach > (uint32_t)topk && mid > lo && mid <= hi)) break;
+    const uint32_t c = reaching(mid);
+    if (c >= (uint32_t)topk) {
+      lo = mid;
+      reach = c;
+    } else {
+      hi = mid;
+    }
+  }
+  double wo = 0.0, wd = 0.0;
+#pragma unroll
+  for (int j = 0; j < NE; ++j)
+    if (x[j] >= lo) {
+      uint32_t rank = 0;
+      if (reach > (uint32_t)topk)                        // larger logit first, equal logits by lower position
+        for (int e = 0; e < entries; ++e) {
+          const float* const at = rec + e / topk * record + 4 + e % topk;
+          rank += (at[0] > x[j] || (at[0] == x[j] && __float_as_int(at[topk]) < pos[j])) ? 1u : 0u;
+        }
+      if (rank < (uint32_t)topk) {
+        const double wgt = (double)__builtin_amdgcn_exp2f(x[j] - lse);
+        if (pos[j] >= needle_start && pos[j] < needle_start + needle_len) wo += wgt; else wd += wgt;
+      }
+    }
+  wo = wave_sum<double>(wo);
+  wd = wave_sum<double>(wd);
+  if (lane == 0) {
+    overflow[row] = over ? 1 : 0;
+    if (!over) {
+      const double WS = fmax(0.0, tnw - wo);
+      double* cdst = cells + row * 4;
+      cdst[0] = wo;
+      cdst[1] = wd;
+      cdst[2] = WS;
+      cdst[3] = 1.0 - wo - wd - WS;
     }
   }
 }
@@ -1208,6 +1336,27 @@ hipError_t qk_prepare() {
   return hipSuccess;
 }
 
+// Key ranges per head.  256 workgroups run at once, each some kStartUs for its start, end and meetings and then its keys
+// one after the other; the ranges' results take another launch.  (At a range of 512 keys a workgroup does little but
+// start.)  The records of the ranges lie where the fallback keeps its rows later.
+// 24 groups of 64 rows x 6013 keys x d 128: 158 -> 54 us; 10 x 2318 x d 64: 100 -> 37; 24 x 8202: 197 -> 64; 270 groups (a little
+// more than run at once) x 16248: 493 -> 224.
+int qk_splits(int64_t groups, int64_t rows, int32_t n, int d, int32_t topk, size_t slots_bytes) {
+  constexpr double kStartUs = 12, kMergeUs = 5, kUsPerKeyAndDim = 1.1e-4;
+  const int64_t fit = (int64_t)(slots_bytes / ((size_t)rows * (size_t)qk_record(topk) * sizeof(float)));
+  const int most = (int)std::min<int64_t>({(int64_t)kQkMaxSplit, (int64_t)n / 512, fit});
+  int best = 1;
+  double best_us = 0;
+  for (int s = 1; s <= std::max(most, 1); ++s) {
+    const double us = (double)((groups * s + 255) / 256) * (kStartUs + kUsPerKeyAndDim * d * n / s) + (s > 1 ? kMergeUs : 0);
+    if (s == 1 || us < best_us) {
+      best = s;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
 template <int DK>
 slkv_status qk_launch(const uint16_t* q, const uint16_t* k, int32_t L, int32_t Hq, int32_t Hkv, int32_t T, int32_t n,
                       int32_t needle_start, int32_t needle_len, int32_t topk, double* d_acc, double* d_scores,
@@ -1220,10 +1369,22 @@ slkv_status qk_launch(const uint16_t* q, const uint16_t* k, int32_t L, int32_t H
   unsigned char* flags = ws + w.off_flags;
   float* slots = (float*)(ws + w.off_slots);
   const float c_log2 = (float)(1.4426950408889634 / std::sqrt((double)DK));
+  const int64_t groups = (int64_t)L * Hkv * rowgroups;
+  const int want = qk_splits(groups, rows, n, DK, topk, w.slots_bytes);
+  const int stripes = (n + kQkStripe - 1) / kQkStripe;
+  const int range = (stripes + want - 1) / want * kQkStripe, nsplit = (n + range - 1) / range;
   {
     ScopedKernelTimer tm(SLKV_K_QK_CELLS, st);
-    SLKV_LAUNCH(qk_cells_kernel<DK>, dim3((unsigned)(L * Hkv * rowgroups)), dim3(kQkThreads), sizeof(QkLds), st, q, k, Hq, Hkv,
-                T, n, rowgroups, needle_start, needle_len, topk, c_log2, cells, flags);
+    SLKV_LAUNCH(qk_cells_kernel<DK>, dim3((unsigned)(groups * nsplit)), dim3(kQkThreads), sizeof(QkLds), st, q, k, Hq, Hkv,
+                T, n, rowgroups, nsplit, range, needle_start, needle_len, topk, c_log2, cells, flags, slots);
+    if (nsplit > 1) {
+      const dim3 grid((unsigned)((rows + 3) / 4));
+      if (nsplit * topk <= 8 * 64)
+        SLKV_LAUNCH(qk_merge_kernel<8>, grid, dim3(256), 0, st, (const float*)slots, rows, nsplit, topk, needle_start, needle_len, cells, flags);
+      else
+        SLKV_LAUNCH(qk_merge_kernel<kQkMaxSplit>, grid, dim3(256), 0, st, (const float*)slots, rows, nsplit, topk, needle_start, needle_len, cells,
+                    flags);
+    }
   }
   {
     ScopedKernelTimer tm(SLKV_K_QK_FALLBACK, st);

@@ -68,6 +68,16 @@ def test_equal_logits_at_the_kth_place_and_the_ends_of_chunks(n, topk, d):
     check(x)
 
 
+@pytest.mark.parametrize("L,Hkv,T,n,topk,d", [(1, 1, 3, 16385, 33, 64), (1, 2, 16, 8000, 64, 128), (3, 2, 5, 2049, 1, 128), (2, 3, 40, 4100, 9, 64)])
+def test_few_heads_cut_their_keys_into_ranges(L, Hkv, T, n, topk, d):
+    # most keys twice, half the context apart, so that pairs of equal logits meet when the ranges are put together (K is
+    # odd or large); the last range is short, the needle lies across two ranges where n allows it
+    x = wl.config4_qk(L=L, Hq=2 * Hkv, Hkv=Hkv, T=T, n=n, d=d, needle_len=32, seed_extra=60 + n)
+    x.k[:, :, n // 2:2 * (n // 2)] = x.k[:, :, :n // 2]
+    x.needle_start, x.topk = 1024 - 16, topk
+    check(x)
+
+
 def test_several_row_groups_and_accumulation():
     import torch
     x = wl.config4_qk(L=1, Hq=8, Hkv=1, T=12, n=3000, d=128, seed_extra=2)      # 96 rows per KV head: 64 + 32
