@@ -629,6 +629,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 //   PASS 2: the segment's chunks are folded into the rows' log-sum-exp while the first keys are on their way;
 //           D[row][key]: a lane owns one key per tile -> sum over all rows of exp2(x - lse[row]).
 // A segment of a single chunk needs nobody else's rows: PASS 1 runs both passes over it.
+// rsplit waves may share a key group and take its query tiles in turn (one group per wave then); the second pass adds
+// their sums up in LDS.
 //
 // fp32 products run on the 32x32x2 fp32 MFMA: twice the rate of plain FMAs, and an operand is read from LDS once
 // for 32 products instead of once for each (4 heads x 1024 keys, d 64: 16.4 + 12.1 us with FMAs, 8.6 + 7.8 us).
@@ -650,7 +652,7 @@ struct ScoreCfg {
   static constexpr int PPR = DK * QB / 16;            // 16-byte pieces of a query row
   static constexpr int KK = PPR / 2;                  // operand pieces per lane and row
   static constexpr int RAW = DK * KB / 32;            // pieces per lane and key as they come from memory
-  static constexpr int KT = F32 && DK == 128 ? 1 : 2; // 32-key tiles of a group
+  static constexpr int KT = F32 ? 1 : 2;              // 32-key tiles of a group
   static constexpr int GK = 32 * KT;
   static constexpr int RBT = F32 && DK == 128 ? 4 : 8;   // query tiles per row block
 };
@@ -668,7 +670,7 @@ template <int DK, int KIND, int PASS, class TAB>
 __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab, const void* __restrict__ qmat, const void* __restrict__ kmat,
                                                        int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w,
                                                        int CH, float c_log2, float* __restrict__ part, float* __restrict__ imp,
-                                                       int grid2d) {
+                                                       int grid2d, int rsplit) {
   using C = ScoreCfg<DK, KIND>;
   constexpr int KK = C::KK, KT = C::KT, RAW = C::RAW, GK = C::GK, RBT = C::RBT, ROWB = C::ROWB, PPR = C::PPR;
   extern __shared__ __attribute__((aligned(16))) unsigned char score_smem[];
@@ -677,6 +679,8 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nthr = blockDim.x, NW = nthr >> 6;
   const int l32 = lane & 31, half = lane >> 5;
+  // wave: key groups kw, kw + KW, ..., query tiles rsub, rsub + rsplit, ...
+  const int KW = NW / rsplit, kw = wv % KW, rsub = wv / KW;
 
   // Which chunk of which segment.  With a two-dimensional grid (grid2d; the host chooses it when the
   // segments' chunk counts are alike enough) blockIdx.y is the segment and blockIdx.x the chunk, and
@@ -725,24 +729,24 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
       for (int i = 0; i < RAW; ++i) raw[kt][i] = *reinterpret_cast<const u32x4*>(row + i * 32);
     }
   };
-  // f(registers, group) over this wave's groups wv, wv + NW, ..., two in registers in turn.  The loads past
+  // f(registers, group) over this wave's groups kw, kw + KW, ..., two in registers in turn.  The loads past
   // the last group are issued too (of the chunk's last key): only so does the compiler know how many loads
   // follow those it waits for.  preloaded: the first two groups are on their way already.
   auto sweep = [&](bool preloaded, auto f) __attribute__((always_inline)) {
-    int g = wv;
+    int g = kw;
     if (g >= ngroups) return;
     if (!preloaded) {
       load(rawA, g);
-      load(rawB, g + NW);
+      load(rawB, g + KW);
     }
     for (;;) {
       f(rawA, g);
-      load(rawA, g + 2 * NW);
-      g += NW;
+      load(rawA, g + 2 * KW);
+      g += KW;
       if (g >= ngroups) break;
       f(rawB, g);
-      load(rawB, g + 2 * NW);
-      g += NW;
+      load(rawB, g + 2 * KW);
+      g += KW;
       if (g >= ngroups) break;
     }
   };
@@ -807,7 +811,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
   float* const lse_s = reinterpret_cast<float*>(stat + (size_t)NW * tiles0 * 64);             // [row of the block]
 
   bool preloaded = true;
-  load(rawA, wv);
+  load(rawA, kw);
   for (int rb0 = 0; rb0 < R; rb0 += RBT * 32) {
     const int rows = min(R - rb0, RBT * 32), rts = (rows + 31) >> 5;
     // queries of the block: memory -> LDS
@@ -829,7 +833,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
         }
       }
     }
-    if (preloaded) load(rawB, wv + NW);                // behind the queries: the first group does not wait for it
+    if (preloaded) load(rawB, kw + KW);                // behind the queries: the first group does not wait for it
 
     if (PASS == 1) {
       float2* const mine = stat + (size_t)wv * tiles0 * 64 + lane;
@@ -841,9 +845,9 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
         u32x4 op[KT][KK];
         widen(raw, op);
         const int key0 = key_begin + g * GK;
-        const bool first = g == wv, tail = key0 + GK > key_end;
+        const bool first = g == kw, tail = key0 + GK > key_end;
 #pragma unroll 1
-        for (int rt = 0; rt < rts; ++rt) {
+        for (int rt = rsub; rt < rts; rt += rsplit) {
           float2 st = mine[rt * 64];
           f32x16 acc[KT];
           logits(op, rt, std::true_type{}, acc);
@@ -891,7 +895,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
       for (int rt = 0; rt < rts; ++rt) bad = bad || !(mine[rt * 64].y < INFINITY);
       if (__syncthreads_or(bad ? 1 : 0)) {
         // a sum that left the fp32 range (logits far above the chunk's first ones); not taken for ordinary inputs
-        for (int g = wv; g < ngroups; g += NW) {
+        for (int g = kw; g < ngroups; g += KW) {
           load(rawA, g);
           stats_group(rawA, g, std::true_type{});
         }
@@ -930,6 +934,12 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
 
     // ---- importance of the chunk's keys: sum over the rows of exp2(x - lse)
     float* const dst = imp + se.score_off;
+    float* const col = reinterpret_cast<float*>(stat);   // [wave][lane]
+    if (rsplit > 1) col[tid] = 0.f;                      // (of a wave without keys)
+    auto put = [&](int g, float v) __attribute__((always_inline)) {
+      const int key = key_begin + g * GK + (KT == 2 ? lane : l32);
+      if (key < key_end && (KT == 2 || half == 0)) dst[key] = rb0 ? dst[key] + v : v;   // (a later row block adds to what this lane wrote)
+    };
     sweep(preloaded, [&](const u32x4 (&raw)[KT][RAW], int g) __attribute__((always_inline)) {
       u32x4 op[KT][KK];
       widen(raw, op);
@@ -937,7 +947,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) colsum[kt] = 0.f;
 #pragma unroll 1
-      for (int rt = 0; rt < rts; ++rt) {
+      for (int rt = rsub; rt < rts; rt += rsplit) {
         // lane: key l32 of tile kt, query rows rt*32 + 8*(i/4) + 4*half + i%4
         f32x16 acc[KT];
         logits(op, rt, std::false_type{}, acc);
@@ -952,9 +962,17 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) colsum[kt] += __shfl_xor(colsum[kt], 32, 64);
       const float v = KT == 2 && half ? colsum[KT - 1] : colsum[0];
-      const int key = key_begin + g * GK + (KT == 2 ? lane : l32);
-      if (key < key_end && (KT == 2 || half == 0)) dst[key] = rb0 ? dst[key] + v : v;   // (a later row block adds to what this lane wrote)
+      if (rsplit > 1) col[tid] = v;
+      else put(g, v);
     });
+    if (rsplit > 1) {                                    // one group per wave: the sums of its query tiles
+      __syncthreads();
+      if (rsub == 0 && kw < ngroups) {
+        float v = 0.f;
+        for (int r = 0; r < rsplit; ++r) v += col[(r * KW + kw) * 64 + lane];
+        put(kw, v);
+      }
+    }
     preloaded = false;
   }
 }
@@ -2085,6 +2103,7 @@ struct Plan {
   int R, Rpad, CH;
   int64_t hist_blocks;   // block histograms of the selection
   int waves;             // per workgroup of the scoring passes
+  int rsplit;            // of these, that share a key group's query tiles (score_k_resident_kernel)
   size_t part_bytes, score_bytes, hist_bytes, table_bytes;
   size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
 };
@@ -2114,13 +2133,23 @@ static auto with_score_kind(int d, int dtype, F f) {
   }
 }
 
-// Workgroup size and chunk length of score_k_resident_kernel.  A workgroup of 8 waves has a CU to itself (its waves
-// use all registers); two of 4 waves share one where their LDS fits twice, which deals the keys out in smaller
-// portions.  Of the chunk lengths, the one whose rounds of workgroups take the least time: a workgroup's start
-// and end (queries into LDS, first keys, row statistics: kStartUs) and its groups one after the other, each of
-// them R/32 query tiles long (kTileUs with both wave slots of a SIMD taken, so with 8 waves on the CU).
+// Workgroup size, chunk length and split of the query tiles of score_k_resident_kernel: what takes the least time by the
+// costs below, measured over calls of 2 to 56 segments of 104 to 16 K keys.
+//   kStartUs: a workgroup's start and end (queries into LDS, first keys, row statistics); kLaunchUs: from one pass to the
+//   next, saved where every segment is one chunk and the first pass completes it;
+//   tile: a key group against 32 query rows by a wave that has its SIMD to itself; `shared` times as long with two on it
+//   (8 waves on a CU, in one workgroup of 8 waves or in two of 4 where their LDS fits twice): fp32 MFMAs fill the
+//   matrix pipe alone, E4M3 keys leave gaps;
+//   kFoldUs: per chunk of a segment, its statistics read back by the second pass.
+// Waves that share a key group (rsplit of them take its query tiles in turn) shorten the chain of tiles of calls that
+// leave most SIMDs idle; with more keys than that they only repeat loads, so rsplit > 1 means one group per wave.
+// fp32: 4 heads x 1 K keys, d 64, one query tile 24.2 -> 19.7 us (groups of 32 keys instead of 64); 2 x 700, d 128, four tiles
+// 36.8 -> 25.3; 8 x 2 K, d 64, two tiles 28.0 -> 20.6; E4M3: 22 segments of 104 to 878 keys, four tiles 27.2 -> 19.9; 8 x 1.5 K 22.8 -> 19.4;
+// 56 segments of one chunk 27.7 -> 22.6 (no second pass); 8 x 32 K as before.
 static void plan_k_resident(const Geometry& g, Plan& p) {
-  constexpr double kStartUs = 4.0, kTileUs = 0.5;
+  constexpr double kLaunchUs = 3.7, kFoldUs = 0.03;
+  const bool f32 = g.dtype == SLKV_F32;
+  const double tile_us = f32 ? (g.d == 128 ? 2.1 : 1.25) : (g.d == 128 ? 0.64 : 0.4), shared = f32 ? 2.0 : 1.6;
   int gk = 0, tiles = 0, max_tiles = 0;
   size_t lds4 = 0;
   with_score_kind(g.d, g.dtype, [&](auto dk, auto kind) {
@@ -2130,35 +2159,57 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
     max_tiles = std::min(tiles, C::RBT);
     lds4 = score_lds_bytes<decltype(dk)::value, decltype(kind)::value>(max_tiles, 4);
   });
-  // ranked history lengths, equal ones together (a call has few different ones compared with its segments)
-  std::vector<std::pair<int64_t, int64_t>> hist;
+  // ranked history lengths (less one), equal neighbours together; in single precision, which a cost allows and which adds
+  // up 512 different ones in under a microsecond (this runs for every call)
+  std::vector<float> len;
+  std::vector<int> times;
+  int64_t longest = 1, ranked = 0;
   for (const Seg& s : g.segs)
     if (seg_ranked(s.n, g.w, s.cap)) {
-      if (!hist.empty() && hist.back().first == s.n - g.w) hist.back().second += 1;
-      else hist.emplace_back(s.n - g.w, 1);
+      const float m1 = (float)(s.n - g.w - 1);
+      if (!len.empty() && len.back() == m1) {
+        times.back() += 1;
+      } else {
+        len.push_back(m1);
+        times.push_back(1);
+      }
+      longest = std::max(longest, s.n - g.w);
+      ++ranked;
     }
-  int64_t longest = 1;
-  for (const auto& h : hist) longest = std::max(longest, h.first);
   double best = 0;
   p.waves = 8;
+  p.rsplit = 1;
   p.CH = 8 * gk;
   for (const int waves : {4, 8}) {
-    const bool pairs = waves == 4 && 2 * (lds4 + 256) <= 160 * 1024;
-    const int64_t slots = pairs ? 512 : 256;
-    const double tile_us = waves == 4 && !pairs ? 0.6 * kTileUs : kTileUs;
-    const int64_t unit = (int64_t)waves * gk, most = (longest + unit - 1) / unit;
-    for (int64_t gpw = 1;;) {
-      int64_t count = 0;
-      for (const auto& h : hist) count += h.second * ((h.first + gpw * unit - 1) / (gpw * unit));
-      const double rounds = (double)((count + slots - 1) / slots);
-      const double t = rounds * (kStartUs + (double)std::min(gpw, most) * tiles * tile_us);
-      if (best == 0 || t < best) {
-        best = t;
-        p.waves = waves;
-        p.CH = (int)(gpw * unit);
+    const double kStartUs = waves == 4 ? 5 : 5.75;
+    for (int rs = 1; rs <= waves && (rs == 1 || (rs < 2 * tiles && tiles == max_tiles)); rs *= 2) {
+      const bool pairs = waves == 4 && 2 * (lds4 + 256) <= 160 * 1024;
+      const int64_t unit = (int64_t)(waves / rs) * gk, most = (longest + unit - 1) / unit;
+      // chunks of gpw groups a wave; returns whether longer ones can only idle workgroups
+      auto consider = [&](int64_t gpw) {
+        const float per_chunk = 1.0f / (float)(gpw * unit);
+        int count = 0;
+        for (size_t i = 0; i < len.size(); ++i) count += times[i] * ((int)(len[i] * per_chunk) + 1);
+        const int64_t rounds = (count + (pairs ? 511 : 255)) / (pairs ? 512 : 256);
+        const double tile = tile_us * (waves == 8 || (pairs && count > 256) ? shared : 1.0);
+        const double sweep = (double)(std::min(gpw, most) * ((tiles + rs - 1) / rs)) * tile;
+        const double us = gpw >= most ? (double)rounds * (kStartUs + 2 * sweep)
+                                      : 2 * (double)rounds * (kStartUs + sweep) + kLaunchUs + kFoldUs * (double)((longest + gpw * unit - 1) / (gpw * unit));
+        // (more chunks than run at once only where the segments alone are that many: their statistics take workspace)
+        if (best == 0 || (us < best && (gpw >= most || count <= 512 + ranked))) {
+          best = us;
+          p.waves = waves;
+          p.rsplit = rs;
+          p.CH = (int)(gpw * unit);
+        }
+        return rounds <= 1;
+      };
+      if (rs > 1) {
+        consider(1);
+        continue;
       }
-      if (gpw >= most || rounds <= 1) break;           // longer chunks only idle workgroups from here on
-      gpw += std::max<int64_t>(1, gpw / 16);
+      for (int64_t gpw = 1; gpw < most && !consider(gpw); gpw += std::max<int64_t>(1, gpw / 16)) {}
+      consider(most);
     }
   }
 }
@@ -2194,6 +2245,7 @@ static void plan_q_resident(const Geometry& g, Plan& p) {
   }
   p.CH = (int)ch;
   p.waves = 4;
+  p.rsplit = 1;
 }
 
 static void make_plan(const Geometry& g, Plan& p) {
@@ -2303,10 +2355,10 @@ static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& 
     const size_t lds = score_lds_bytes<DK, KIND>(std::min((p.R + 31) / 32, ScoreCfg<DK, KIND>::RBT), p.waves);
     if (pass == 1)
       SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 1, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit);
     else
       SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 2, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit);
   }
 }
 
