@@ -2133,6 +2133,34 @@ static auto with_score_kind(int d, int dtype, F f) {
   }
 }
 
+// The ranked history lengths of a call (less one; equal neighbours together) and how many chunks they make: in single
+// precision, which a cost allows and which adds up 512 different ones in under a microsecond (this runs for every call).
+struct RankedLengths {
+  std::vector<float> len;
+  std::vector<int> times;
+  int64_t longest = 1, ranked = 0;
+  explicit RankedLengths(const Geometry& g) {
+    for (const Seg& s : g.segs)
+      if (seg_ranked(s.n, g.w, s.cap)) {
+        const float m1 = (float)(s.n - g.w - 1);
+        if (!len.empty() && len.back() == m1) {
+          times.back() += 1;
+        } else {
+          len.push_back(m1);
+          times.push_back(1);
+        }
+        longest = std::max(longest, s.n - g.w);
+        ++ranked;
+      }
+  }
+  int64_t chunks(int64_t ch) const {
+    const float per_chunk = 1.0f / (float)ch;
+    int count = 0;
+    for (size_t i = 0; i < len.size(); ++i) count += times[i] * ((int)(len[i] * per_chunk) + 1);
+    return count;
+  }
+};
+
 // Workgroup size, chunk length and split of the query tiles of score_k_resident_kernel: what takes the least time by the
 // costs below, measured over calls of 2 to 56 segments of 104 to 16 K keys.
 //   kStartUs: a workgroup's start and end (queries into LDS, first keys, row statistics); kLaunchUs: from one pass to the
@@ -2159,23 +2187,8 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
     max_tiles = std::min(tiles, C::RBT);
     lds4 = score_lds_bytes<decltype(dk)::value, decltype(kind)::value>(max_tiles, 4);
   });
-  // ranked history lengths (less one), equal neighbours together; in single precision, which a cost allows and which adds
-  // up 512 different ones in under a microsecond (this runs for every call)
-  std::vector<float> len;
-  std::vector<int> times;
-  int64_t longest = 1, ranked = 0;
-  for (const Seg& s : g.segs)
-    if (seg_ranked(s.n, g.w, s.cap)) {
-      const float m1 = (float)(s.n - g.w - 1);
-      if (!len.empty() && len.back() == m1) {
-        times.back() += 1;
-      } else {
-        len.push_back(m1);
-        times.push_back(1);
-      }
-      longest = std::max(longest, s.n - g.w);
-      ++ranked;
-    }
+  const RankedLengths lens(g);
+  const int64_t longest = lens.longest, ranked = lens.ranked;
   double best = 0;
   p.waves = 8;
   p.rsplit = 1;
@@ -2187,9 +2200,7 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
       const int64_t unit = (int64_t)(waves / rs) * gk, most = (longest + unit - 1) / unit;
       // chunks of gpw groups a wave; returns whether longer ones can only idle workgroups
       auto consider = [&](int64_t gpw) {
-        const float per_chunk = 1.0f / (float)(gpw * unit);
-        int count = 0;
-        for (size_t i = 0; i < len.size(); ++i) count += times[i] * ((int)(len[i] * per_chunk) + 1);
+        const int64_t count = lens.chunks(gpw * unit);
         const int64_t rounds = (count + (pairs ? 511 : 255)) / (pairs ? 512 : 256);
         const double tile = tile_us * (waves == 8 || (pairs && count > 256) ? shared : 1.0);
         const double sweep = (double)(std::min(gpw, most) * ((tiles + rs - 1) / rs)) * tile;
@@ -2214,36 +2225,35 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
   }
 }
 
-// Chunk length of score_q_resident_kernel.
+// Chunk length of score_q_resident_kernel: what takes the least time, by a workgroup's start and end and the time of a
+// 64-key tile for one workgroup on a CU (`alone`) and for two (`paired`; above 256 query rows its registers leave room
+// for one).  For 65 to 256 rows the arithmetic bounds either, two workgroups gain 10 % in the loop and pay 2 us for their
+// starts: 8 x 24 K keys of 256 rows 53.5 us with 504 chunks, 50.0 with 256; 32 K 62.6 and 59.8; 64 K 113 and 113; 128 K 183 and 187.
+// Up to 64 rows one workgroup's loads in flight do not keep the memory busy: 32 x 16 K keys 57.4 us with 512, 61.3 with 256.
+// 448 rows, 4 x 24 K: 88 us with 376 chunks, which run in two rounds, 60.7 with 252.  What does not fit at once runs in rounds.
+// Small calls take chunks down to two tiles: 8 x 2 K keys of 128 rows 22.5 us with 256 keys a chunk, 19.6 with 128.
 static void plan_q_resident(const Geometry& g, Plan& p) {
-  // keys to score over all ranked segments -> chunk length giving about 512 workgroups
-  int64_t keys = 0;
-  for (const Seg& s : g.segs)
-    if (seg_ranked(s.n, g.w, s.cap)) keys += s.n - g.w;
-  int64_t ch = (keys + 511) / 512;
-  ch = (ch + 127) / 128 * 128;                // pairs of 64-key tiles
-  ch = std::max<int64_t>(256, std::min<int64_t>(ch, 1 << 16));
-  // All chunks should be resident at once (two 256-thread workgroups per CU on 256 CUs): the
-  // partial last chunk of every segment can push the count a little over that, and the surplus
-  // workgroups would then run alone in a second round that doubles the kernel's time.  Lengthen
-  // the chunk, by up to a quarter, until the count fits.
-  {
-    constexpr int64_t kSlots = 512;
-    constexpr int64_t granule = 128;
-    auto count = [&](int64_t c) {
-      int64_t total = 0;
-      for (const Seg& s : g.segs)
-        if (seg_ranked(s.n, g.w, s.cap)) total += (s.n - g.w + c - 1) / c;
-      return total;
-    };
-    if (count(ch) > kSlots)
-      for (int64_t c = ch + granule; c <= ch + ch / 4 && c <= (1 << 16); c += granule)
-        if (count(c) <= kSlots) {
-          ch = c;
-          break;
-        }
+  const int cfg = p.R <= 64 ? 0 : p.R <= 128 ? 1 : p.R <= 256 ? 2 : 3;
+  const double dim = g.d == 128 ? 1.0 : 0.6;
+  const double alone = dim * (cfg == 0 ? 0.6 : cfg == 1 ? 0.6 : cfg == 2 ? 1.2 : 2.4), paired = dim * (cfg == 0 ? 0.75 : cfg == 1 ? 1.09 : 2.18);
+  constexpr double kStartUs = 6;
+  const double second = cfg == 0 ? 1.0 : 2.2;            // two workgroups of a CU that start together
+  const RankedLengths lens(g);
+  double best = 0;
+  p.CH = 128;
+  for (int64_t ch = 128;; ch += std::max<int64_t>(128, ch / 32 / 128 * 128)) {   // pairs of 64-key tiles
+    const int64_t count = lens.chunks(ch);
+    const double tiles = (double)(std::min(ch, (lens.longest + 127) / 128 * 128) / 64);
+    const double one = kStartUs + tiles * alone, two = kStartUs + second + tiles * paired;
+    const int64_t full = cfg == 3 ? count / 256 : count / 512, rest = cfg == 3 ? count % 256 : count % 512;
+    const double us = (double)full * (cfg == 3 ? one : two) + (rest == 0 ? 0 : rest <= 256 ? one : two);
+    // (more chunks than run at once only where the segments alone are that many: their statistics take workspace)
+    if (best == 0 || us < best || count > 512 + lens.ranked) {
+      best = us;
+      p.CH = (int)ch;
+    }
+    if (count <= 256 || ch >= lens.longest || ch >= (1 << 16)) break;
   }
-  p.CH = (int)ch;
   p.waves = 4;
   p.rsplit = 1;
 }

@@ -29,6 +29,14 @@ def test_many_chunks_per_segment(dtype, lens):
     check(lay, np.array([300, 90], dtype=np.int32))
 
 
+@pytest.mark.parametrize("Hq,Hkv,w,lens", [(4, 2, 32, [32 + 127, 32 + 128, 32 + 129, 2000]), (16, 2, 64, [500, 64 + 256]), (14, 2, 64, [3000, 90]),
+                                          (8, 8, 48, [4500])])
+def test_16_bit_chunks_of_two_tiles_and_more(Hq, Hkv, w, lens):
+    # 64, 512, 448 and 48 query rows; chunks of 128 keys, around whose ends the short histories lie
+    lay = wl.make_layer((304, Hq, w), lens, Hq, Hkv, 128, w, dtype="bf16", bias_frac=0.04)
+    check(lay, np.array([w + 30 + 11 * h for h in range(Hkv)], dtype=np.int32))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,Hkv", [(8, 8), (13, 5), (32, 8), (57, 8)])
 def test_segment_tables(dtype, B, Hkv):
