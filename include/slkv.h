@@ -219,8 +219,8 @@ slkv_status slkv_compacted_sizes(const slkv_layer_desc* desc, int64_t* h_out_off
                                  int64_t* total_kept);
 /* Device workspace slkv_compress_layer needs for this descriptor.
  * A workspace has to be ZERO-FILLED ONCE by the caller before the first call that uses it (its
- * first SLKV_WORKSPACE_HEADER_BYTES hold counters with which the workgroups of a kernel find
- * out which of them finishes a segment last); every call leaves them zero again, so the same
+ * first SLKV_WORKSPACE_HEADER_BYTES are kept for counters, of which the present kernels need
+ * none); every call leaves them zero, so the same
  * workspace serves any number of later calls, of any descriptor it is large enough for, also
  * from a replayed HIP graph.  Its other contents are scratch.  Two calls that may overlap in
  * time need a workspace each. */
