@@ -124,6 +124,23 @@ __device__ __forceinline__ int find_segment(int nseg, int x, F prefix) {
   return lo;
 }
 
+// The same for an x that is the same in all 64 lanes of a wave (all of them active): 64 prefixes are compared at a
+// time, so that a table of up to 64 segments costs one memory round trip and one of up to 4096 two, not one per
+// halving: these lookups come before a workgroup's first key.
+template <class F>
+__device__ __forceinline__ int find_segment_wave(int nseg, int x, F prefix) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, span = nseg;                             // the segment is one of lo .. lo + span - 1
+  while (span > 1) {
+    const int step = (span + 63) >> 6;
+    const bool below = lane * step < span && prefix(min(lo + lane * step, nseg - 1)) <= x;
+    const int last = max(__popcll(__ballot(below)) - 1, 0);
+    lo += last * step;
+    span = min(step, span - last * step);
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Merge two (max, sum) pairs of a running softmax in the log2 domain.
@@ -255,7 +272,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     if (bid >= se.chunk1) return;
   } else {
     bid = blockIdx.x;
-    seg = find_segment(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
+    seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
     se = entry_of(seg);
   }
   if (PASS == 1) SLKV_STAMP(256 + bid, 0);
@@ -705,7 +722,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
     if (bid >= se.chunk1) return;
   } else {
     bid = blockIdx.x;
-    seg = find_segment(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
+    seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
     se = entry_of(seg);
   }
   const int nchunks = se.chunk1 - se.chunk0;
@@ -1048,7 +1065,7 @@ __global__ __launch_bounds__(kSelThreads) void select_pool_kernel(const TAB tab,
   __shared__ float stage[kSelBlock + 2 * kSelHaloMax];
   const int tid = threadIdx.x;
   const int bid = blockIdx.x;
-  const int seg = find_segment(tab.nseg, bid, [&](int s) { return tab.blk_begin(s); });
+  const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.blk_begin(s); });
   const int blk = bid - tab.blk_begin(seg);
   const SegShape sg = tab.shape(seg);
   const int n = sg.n;
@@ -1329,7 +1346,7 @@ __global__ __launch_bounds__(kSelEmitThreads) void select_collect_kernel(const T
     blk = blockIdx.x;
     if (blk >= tab.blk_begin(seg + 1) - tab.blk_begin(seg)) return;
   } else {
-    seg = find_segment(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
+    seg = find_segment_wave(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
     blk = (int)blockIdx.x - tab.blk_begin(seg);
   }
   const SegShape sg = tab.shape(seg);
@@ -1388,7 +1405,7 @@ __global__ __launch_bounds__(kSelEmitThreads) void select_count_kernel(const TAB
     blk = blockIdx.x;
     if (blk >= tab.blk_begin(seg + 1) - tab.blk_begin(seg)) return;
   } else {
-    seg = find_segment(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
+    seg = find_segment_wave(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
     blk = (int)blockIdx.x - tab.blk_begin(seg);
   }
   const SegShape sg = tab.shape(seg);
@@ -1432,7 +1449,7 @@ __global__ __launch_bounds__(kSelEmitThreads) void select_emit_kernel(const TAB 
     blk = blockIdx.x;
     if (blk >= tab.blk_begin(seg + 1) - tab.blk_begin(seg)) return;
   } else {
-    seg = find_segment(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
+    seg = find_segment_wave(tab.nseg, (int)blockIdx.x, [&](int s) { return tab.blk_begin(s); });
     blk = (int)blockIdx.x - tab.blk_begin(seg);
   }
   const SegShape sg = tab.shape(seg);
