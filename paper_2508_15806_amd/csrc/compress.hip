@@ -113,19 +113,8 @@ __device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// Segment of a block / row: the largest s with prefix(s) <= x (prefix non-decreasing, prefix(nseg) > x).
-template <class F>
-__device__ __forceinline__ int find_segment(int nseg, int x, F prefix) {
-  int lo = 0, hi = nseg - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (prefix(mid) <= x) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-// The same for an x that is the same in all 64 lanes of a wave (all of them active): 64 prefixes are compared at a
-// time, so that a table of up to 64 segments costs one memory round trip and one of up to 4096 two, not one per
+// Segment of a block / row: the largest s with prefix(s) <= x (prefix non-decreasing, prefix(nseg) > x), for an x that is
+// the same in all 64 lanes of a wave (all of them active).  64 prefixes are compared at a time, so that a table of up to 64 segments costs one memory round trip and one of up to 4096 two, not one per
 // halving: these lookups come before a workgroup's first key.
 template <class F>
 __device__ __forceinline__ int find_segment_wave(int nseg, int x, F prefix) {
@@ -2059,28 +2048,59 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
 }
 
 // Copies kept rows of K and V (bit copies) into the packed output; one 16-byte lane per piece.
-template <class TAB>
+// Bound by HBM, after a chain of three loads (segment, kept position, row); the segment is looked up once per workgroup.
+// A call with more pieces than the chip has threads (kGatherThreads) gives each thread PIECES = 4, so that as many rows are in
+// flight at the end of one chain: re-compression of 256 segments, 64 K rows, 70.4 -> 68.0 us a call.  With fewer, 4 pieces a
+// thread only leave CUs idle (16 short prompts: 54.2 -> 58.5 us).
+constexpr int64_t kGatherThreads = 256 * 2048;
+template <int PIECES, class TAB>
 __global__ __launch_bounds__(256) void gather_kernel(const TAB tab, const GatherArgs ga,
                                                      const int32_t* __restrict__ kept_idx, int all_segments) {
-  const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t rel = g / ga.lanes_per_row;
-  const int c = (int)(g % ga.lanes_per_row);
-  const int64_t row0 = tab.out_off(0), row1 = tab.out_off(tab.nseg);
-  const int64_t row = row0 + rel;
-  if (row >= row1) return;
-  const int seg = find_segment(tab.nseg, (int)row, [&](int s) { return tab.out_off(s); });
-  if (!all_segments && tab.out_off(seg + 1) - tab.out_off(seg) <= kInlineGatherRows) return;   // done by the selection kernel
-  // (a position outside the segment cannot come out of the selection; clamped all the same, so
-  // that no input can turn into an out-of-bounds read here)
-  const SegShape sg = tab.shape(seg);
-  const int64_t tok = (int64_t)sg.tok_begin + min(max(kept_idx[row], 0), max(sg.n - 1, 0));
-  const int64_t h = sg.head;
-  const uint4 kv = *reinterpret_cast<const uint4*>(ga.k + (h * ga.k_stride_head + tok * ga.k_stride_tok) * ga.elt_bytes + c * 16);
-  const uint4 vv = *reinterpret_cast<const uint4*>(ga.v + (h * ga.v_stride_head + tok * ga.v_stride_tok) * ga.elt_bytes + c * 16);
-  const int64_t o = (row * ga.lanes_per_row + c) * 16;
-  *reinterpret_cast<uint4*>(ga.k_out + o) = kv;
-  *reinterpret_cast<uint4*>(ga.v_out + o) = vv;
-  if (ga.pos_out && c == 0) ga.pos_out[row] = ga.pos_in[tok];
+  const int shift = __builtin_ctz(ga.lanes_per_row);                  // 4 to 32 lanes per row: a power of two
+  const int64_t first = (int64_t)blockIdx.x * (256 * PIECES);
+  const int c = (int)threadIdx.x & (ga.lanes_per_row - 1);
+  const int row0 = tab.out_off(0), row1 = tab.out_off(tab.nseg);
+  // the segment of the workgroup's first row, and where the next three begin
+  const int seg0 = find_segment_wave(tab.nseg, min(row0 + (int)(first >> shift), row1 - 1), [&](int s) { return tab.out_off(s); });
+  int next[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) next[i] = tab.out_off(min(seg0 + 1 + i, tab.nseg));
+  int64_t row[PIECES], tok[PIECES], head[PIECES];
+  bool copy[PIECES];
+  u32x4 kv[PIECES], vv[PIECES];
+#pragma unroll
+  for (int u = 0; u < PIECES; ++u) {
+    row[u] = row0 + ((first + u * 256 + threadIdx.x) >> shift);
+    copy[u] = row[u] < row1;
+    const int r = (int)min(row[u], (int64_t)row1 - 1);
+    int seg = seg0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) seg += r >= next[i] ? 1 : 0;
+    while (r >= next[2] && tab.out_off(seg + 1) <= r) ++seg;
+    if (!all_segments && tab.out_off(seg + 1) - tab.out_off(seg) <= kInlineGatherRows) copy[u] = false;   // done by the selection kernel
+    // (a position outside the segment cannot come out of the selection; clamped all the same, so
+    // that no input can turn into an out-of-bounds read here)
+    const SegShape sg = tab.shape(seg);
+    const int kept = copy[u] ? kept_idx[r] : 0;
+    tok[u] = (int64_t)sg.tok_begin + min(max(kept, 0), max(sg.n - 1, 0));
+    head[u] = sg.head;
+  }
+#pragma unroll
+  for (int u = 0; u < PIECES; ++u)
+    if (copy[u]) {
+      kv[u] = *reinterpret_cast<const u32x4*>(ga.k + (head[u] * ga.k_stride_head + tok[u] * ga.k_stride_tok) * ga.elt_bytes + c * 16);
+      vv[u] = *reinterpret_cast<const u32x4*>(ga.v + (head[u] * ga.v_stride_head + tok[u] * ga.v_stride_tok) * ga.elt_bytes + c * 16);
+    } else {
+      kv[u] = vv[u] = u32x4{0, 0, 0, 0};
+    }
+#pragma unroll
+  for (int u = 0; u < PIECES; ++u)
+    if (copy[u]) {
+      const int64_t o = (row[u] * ga.lanes_per_row + c) * 16;
+      *reinterpret_cast<u32x4*>(ga.k_out + o) = kv[u];
+      *reinterpret_cast<u32x4*>(ga.v_out + o) = vv[u];
+      if (ga.pos_out && c == 0) ga.pos_out[row[u]] = ga.pos_in[tok[u]];
+    }
 }
 
 // Words of a segment table that does not fit a kernel argument, on their way into the workspace.
@@ -2671,8 +2691,10 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     if ((any_large || gather_all) && rows > 0) {
       ScopedKernelTimer tm(SLKV_K_GATHER, st);
       const int64_t threads = rows * lanes_per_row;
-      SLKV_LAUNCH(gather_kernel<TAB>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, tab, ga, d_kept_idx,
-                  gather_all ? 1 : 0);
+      if (threads > kGatherThreads)
+        SLKV_LAUNCH((gather_kernel<4, TAB>), dim3((unsigned)((threads + 1023) / 1024)), dim3(256), 0, st, tab, ga, d_kept_idx, gather_all ? 1 : 0);
+      else
+        SLKV_LAUNCH((gather_kernel<1, TAB>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, tab, ga, d_kept_idx, gather_all ? 1 : 0);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(SLKV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
