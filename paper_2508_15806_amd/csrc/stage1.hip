@@ -508,7 +508,7 @@ struct QkLds {
   int32_t cand_p[kQkRows][kQkStride];
   union {
     __attribute__((aligned(16))) unsigned char q[kQkRows][128 * 2 + 16];   // the queries (padded rows)
-    struct {                                                // at the end: statistics of the rows' 16 lanes
+    struct {                                                // in the last meeting, when the queries have been read: statistics of the rows' 16 lanes
       float st_m[kQkRows][2 * kQkWaves], st_s[kQkRows][2 * kQkWaves], st_t[kQkRows][2 * kQkWaves];
     };
   };
@@ -834,8 +834,22 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
       S.bound[grow] = over || grow >= nrows ? INFINITY : lo;
     }
   };
-  auto meet = [&](uint32_t slack, int steps) __attribute__((always_inline)) {
+  // After the first barrier of a meeting no wave reads its queries any more (each does so once per chunk, before its walk);
+  // only then may the statistics of the last one take their place in LDS.  Each wave writes its lanes' share of all rows
+  // there, and the second barrier stands before the rows are put together.
+  auto meet = [&](bool done) __attribute__((always_inline)) {
     __syncthreads();
+    if (done) {
+      // statistics of a row: its 16 lanes -> log-sum-exp and needle mass
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        S.st_m[mt * 32 + l32][wv * 2 + half] = m_run[mt];
+        S.st_s[mt * 32 + l32][wv * 2 + half] = s_run[mt];
+        S.st_t[mt * 32 + l32][wv * 2 + half] = t_run[mt];
+      }
+    }
+    const uint32_t slack = done ? 0u : (uint32_t)kQkSlack;
+    const int steps = done ? 40 : 24;
     if (__any(S.cnt[grow] > (uint32_t)kQkCand / 2)) update_lists(slack, steps, std::integral_constant<int, kQkCand / 8>{});
     else update_lists(slack, steps, std::integral_constant<int, kQkCand / 16>{});
     __syncthreads();
@@ -908,17 +922,8 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
   }
   for (;;) {
     const bool done = c_hi >= n;
-    if (done) {
-      // statistics of a row: its 16 lanes -> log-sum-exp and needle mass
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        S.st_m[mt * 32 + l32][wv * 2 + half] = m_run[mt];
-        S.st_s[mt * 32 + l32][wv * 2 + half] = s_run[mt];
-        S.st_t[mt * 32 + l32][wv * 2 + half] = t_run[mt];
-      }
-    }
     // every list now holds all logits so far that are at or above the row's bound, hence the K largest
-    meet(done ? 0u : (uint32_t)kQkSlack, done ? 40 : 24);
+    meet(done);
     if (done) break;
     load_queries();
     load_bounds();

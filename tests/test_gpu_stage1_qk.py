@@ -68,6 +68,18 @@ def test_equal_logits_at_the_kth_place_and_the_ends_of_chunks(n, topk, d):
     check(x)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("subtiles", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_last_chunks_in_which_some_waves_have_no_keys(subtiles, d):
+    # the chunk after the first 512 keys has one to eight sub-tiles of 32, so that waves without one meet the others at
+    # once: the queries that those still read and the statistics that these leave share one area of LDS.  With 1280
+    # keys before the last sub-tiles, d = 128 cuts a head into ranges of 768 keys and 512 + 32 * subtiles - 5.
+    for before, topk in ((512, 32), (1280, 33)):
+        x = wl.config4_qk(L=1, Hq=16, Hkv=4, T=16, n=before + 32 * subtiles - 5, d=d, needle_len=16, seed_extra=100 + subtiles)
+        x.topk = topk
+        check(x)
+
+
 @pytest.mark.parametrize("L,Hkv,T,n,topk,d", [(1, 1, 3, 16385, 33, 64), (1, 2, 16, 8000, 64, 128), (3, 2, 5, 2049, 1, 128), (2, 3, 40, 4100, 9, 64)])
 def test_few_heads_cut_their_keys_into_ranges(L, Hkv, T, n, topk, d):
     # most keys twice, half the context apart, so that pairs of equal logits meet when the ranges are put together (K is
