@@ -143,11 +143,14 @@ def _ptr(t):
 
 def _stream(stream):
     """The stream's handle; None: the current stream of the current device, read without the Stream object that
-    torch.cuda.current_stream() makes (3 us of a call's 16)."""
+    torch.cuda.current_stream() makes (3 us of a call's 16) where torch has the function for it, which is not a public one."""
     import torch
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 def slkv_version():

@@ -235,3 +235,14 @@ def test_score_heads_ex_rejects_bad_params_before_any_gpu_call():
     assert call(B.ScoreParams(C.sizeof(B.ScoreParams), 0, 1, 1, 1, 7)) == 2       # reserved
     assert call(good, rows=None) == 1                                             # NULL rows
     assert call(good, topk=0) == 2                                                # topk
+
+
+def test_current_stream_without_the_short_way(monkeypatch):
+    # a torch without the short way to the current stream's handle: the binding asks for the Stream object
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x1230))
+    assert B._stream(None) == 0x1230
+    assert B._stream(types.SimpleNamespace(cuda_stream=0x4560)) == 0x4560
