@@ -22,21 +22,23 @@ import numpy as np
 
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
 MFMA_BF16_PEAK_TFLOPS = 2500.0
-# HBM bytes per launch of the dominant kernel (the statistics pass): a counter reading (rocprofv3 --pmc
-# FETCH_SIZE / WRITE_SIZE runs of this same command), not something this script can measure.  It is read
-# from the table of the committed summary, so that it cannot go stale against it.
+# HBM bytes per launch of a scoring pass: a counter reading (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
+# of this same command), not something this script can measure.  It is read from the table of the committed
+# summary, under the kernel's present name: a summary of kernels that no longer exist gives None.
 PROFILE_SUMMARY = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles",
                                "compress_layer_c3_avg256_rocprofv3.md")
 
 
-def measured_traffic_bytes(path=PROFILE_SUMMARY):
-    """FETCH (scaled, KiB) + WRITE (KiB) of the pass-1 row of the summary's traffic table, in bytes; None if absent."""
+def measured_traffic_bytes(kernel, path=PROFILE_SUMMARY):
+    """FETCH (scaled, KiB) + WRITE (KiB) of the scoring pass `kernel` (score_stats: pass 1, score_accum: pass 2) in the
+    summary's traffic table, in bytes; None if absent."""
+    name = "score_q_resident_kernel<128,2,4,%d," % (1 if kernel == "score_stats" else 2)
     try:
         with open(path) as f:
             for line in f:
                 cells = [c.strip() for c in line.split("|")]
                 # | kernel | FETCH_SIZE | x 2.0 -> KiB read | WRITE_SIZE -> KiB written |
-                if len(cells) >= 6 and cells[1].startswith("score_bf16_kernel<128,2,4,1") and "MiB" in cells[3]:
+                if len(cells) >= 6 and cells[1].startswith(name) and "MiB" in cells[3]:
                     return (float(cells[3].split()[0]) + float(cells[4])) * 1024.0
     except (OSError, ValueError):
         pass
@@ -166,7 +168,7 @@ def main():
     flops_launch = float(np.mean(ranked_flops)) if ranked_flops else 0.0
     dom_ms = kernel_ms.get(dom, float("nan"))
     achieved_tflops = flops_launch / (dom_ms * 1e-3) / 1e12 if dom_ms > 0 else 0.0
-    traffic = measured_traffic_bytes()
+    traffic = measured_traffic_bytes(dom)
     roofline = {"kernel": dom, "bound": "mfma", "achieved": round(achieved_tflops, 2),
                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved_tflops / MFMA_BF16_PEAK_TFLOPS, 4),
