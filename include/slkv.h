@@ -17,9 +17,8 @@
  * Conventions
  *   - Pointers named d_* are DEVICE pointers, h_* are HOST pointers.  The caller owns every
  *     buffer; the library allocates no device memory.  What it keeps between calls: per device,
- *     that its one-time set-up has been done (slkv_init), the counters at the start of a
- *     workspace (see slkv_compress_layer), and the optional kernel-timing recorder at the end
- *     of this header.
+ *     that its one-time set-up has been done (slkv_init), and the optional kernel-timing
+ *     recorder at the end of this header.
  *   - slkv_score_heads, slkv_compress_layer and slkv_recompress_layer only enqueue work on `hip_stream` (a
  *     hipStream_t passed as void*, NULL = the default stream) and return without
  *     synchronising.  Host-side descriptors are consumed before the call returns.
@@ -60,7 +59,8 @@ typedef enum { SLKV_BUDGET_EXACT = 0, SLKV_BUDGET_PAPER_LITERAL = 1, SLKV_BUDGET
 const char* slkv_status_str(slkv_status s);
 /* Detail of the last error on the calling thread; valid until its next slkv call. */
 const char* slkv_last_error(void);
-/* ABI version: major * 1000 + minor. */
+/* ABI version: major * 1000 + minor.  slkv_score_heads_first and slkv_score_heads_qk_first joined 1.5 without a
+ * number of their own: a program that loads the library at run time looks these two symbols up. */
 int32_t slkv_version(void);
 /* One-time set-up on the CURRENT device (host pointer arguments: none): raises the LDS limit of
  * the selection kernels and looks up the scratch of slkv_compress_layer_static.  Optional: a
@@ -199,8 +199,8 @@ int32_t slkv_fixed_from_beta(int32_t avg_budget, double beta);
  */
 typedef struct {
   uint32_t struct_size;       /* sizeof(slkv_layer_desc) */
-  int32_t dtype;              /* slkv_dtype of Q, K, V: fp32 (plain FMA kernels), bf16, fp16, or bf16 queries with
-                                 E4M3 keys and values (MFMA kernels, products exact in the fp32 accumulators) */
+  int32_t dtype;              /* slkv_dtype of Q, K, V: fp32, bf16, fp16, or bf16 queries with E4M3 keys
+                                 and values (MFMA kernels; products of 16-bit and E4M3 inputs exact in the fp32 accumulators) */
   int32_t B, Hq, Hkv, d, w;   /* d in {64, 128}; w >= 1; Hq % Hkv == 0; (Hq/Hkv)*w <= 512 */
   int32_t pool_kernel;        /* odd, 1..63; 1 = no pooling */
   int32_t pool;               /* slkv_pool */
@@ -219,8 +219,8 @@ slkv_status slkv_compacted_sizes(const slkv_layer_desc* desc, int64_t* h_out_off
                                  int64_t* total_kept);
 /* Device workspace slkv_compress_layer needs for this descriptor.
  * A workspace has to be ZERO-FILLED ONCE by the caller before the first call that uses it (its
- * first SLKV_WORKSPACE_HEADER_BYTES are kept for counters, of which the present kernels need
- * none); every call leaves them zero, so the same
+ * first SLKV_WORKSPACE_HEADER_BYTES are a header that the present kernels do not use); every call leaves
+ * them zero, so the same
  * workspace serves any number of later calls, of any descriptor it is large enough for, also
  * from a replayed HIP graph.  Its other contents are scratch.  Two calls that may overlap in
  * time need a workspace each. */
@@ -320,7 +320,7 @@ slkv_status slkv_recompress_layer(const slkv_ragged_desc* desc, const void* d_qw
  */
 typedef enum {
   SLKV_K_SCORE_STATS = 0,   /* logits + per-row sum-exp of every key chunk */
-  SLKV_K_COMBINE = 1,       /* not launched any more: the statistics pass folds the chunks itself */
+  SLKV_K_COMBINE = 1,       /* not launched any more: SLKV_K_SCORE_ACCUM folds the chunks itself */
   SLKV_K_SCORE_ACCUM = 2,   /* logits + exp(logit - lse) summed down the rows */
   SLKV_K_SELECT = 3,        /* pooling + top-k (one record per launch: one launch for histories up to 32768 positions, six for longer ones) */
   SLKV_K_GATHER = 4,        /* K/V row gather */

@@ -51,8 +51,11 @@ __device__ __forceinline__ void store_cells(double* c, double WO, double WD, dou
 // A lower bound of the K-th largest weight comes from maxima per lane in each wave (K distinct elements); the
 // few weights at or above the bound are collected in LDS and ranked exactly (larger first, equal weights by
 // lower position).  Returns false, with nothing written, if a list overflows (many ties at the bound).
-// Bound: HBM.  32 x 32 heads x 16 rows of 16384 floats (1 GiB): 160-165 us, 6.6 TB/s.  Rows of 13867 floats went
-// through the general path, five sweeps over memory: 350 us for 227 MB; here 43 us, 5.2 TB/s.
+// Bound: HBM up to 32764 weights.  32 x 32 heads x 16 rows of 16384 floats (1 GiB): 160-165 us, 6.6 TB/s.  Rows of 13867
+// floats went through the general path, five sweeps over memory: 350 us for 227 MB; here 43 us, 5.2 TB/s.  Longer rows take
+// 1024 threads, whose 128 registers do not hold 16 groups and the rest (60 spilled), and such a workgroup fills its CU, so that
+// no row's loads run beside another's reduction: 2048 rows of 40000 weights 125 us, 2.6 TB/s (general path 627 us); 1024 of
+// 65532 79 us, 3.4 TB/s (512 us).  Above 65533 weights the general path is all there is: 512 rows of 131072 920 us, 0.3 TB/s.
 // WHOLE: every row is whole 16-byte groups (n % 4 == 0).
 template <int NT, int NG, bool WHOLE>
 __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, int32_t n, int32_t needle_start,
@@ -479,7 +482,9 @@ __global__ __launch_bounds__(64 * kReduceHeads) void head_reduce_kernel(const do
 // flagged and redone by qk_fallback_kernel.
 // Calls with too few heads and rows for the chip, or a little more than it takes at once, cut the keys into `nsplit` ranges of
 // `range` keys: a workgroup then leaves its range's statistics and K largest logits per row to qk_merge_kernel.
-// 32 layers x 8 KV heads x 16384 keys x 64 rows, K = 32: 316 -> 249 us (4.3 TB/s of keys; a large copy runs at 5.3) against
+// d = 64 spills no register; d = 128 takes all 256 and spills 23, LDS addresses mostly, which come back from scratch memory after
+// every meeting (11.5 MiB in the call below).
+// 32 layers x 8 KV heads x 16384 keys x 64 rows, K = 32: 316 -> 241 us (4.5 TB/s of keys; a large copy runs at 5.3) against
 // chunks half as long as what came before with lists of 128, a first chunk of 1024 keys walked twice, an 18-step
 // bisection at every chunk, an LDS atomic per entry and the queries in registers throughout; 6 meetings of the waves
 // instead of 11.
@@ -1211,7 +1216,8 @@ slkv_status run_score_heads(const float* d_rows, int32_t L, int32_t H, int32_t T
   hipStream_t st = (hipStream_t)hip_stream;
   double* cells = (double*)d_workspace;
   // Whole 16-byte groups of a row, up to three floats of the row before it included: the threads of a row
-  // hold them at 4, 8 or 16 a thread.
+  // hold them at 4, 8 or 16 a thread.  Up to K = kS1TopK the list of one wave has room for all of them and half as many
+  // again (2048 rows of 16384 weights: K = 64 35 us, K = 65 210 us).
   const int64_t groups = (n % 4 == 0 ? n : n + 3) / 4;
   {
     ScopedKernelTimer tm(SLKV_K_ROW_CELLS, st);

@@ -1,5 +1,5 @@
-"""Both selection kernels (one workgroup per segment; histories cut into blocks with a per-segment
-ticket) on the same shapes: SLKV_SELECT in the environment forces one of them, the library reads
+"""Both selection kernels (one workgroup per segment; histories cut into blocks, six launches)
+on the same shapes: SLKV_SELECT in the environment forces one of them, the library reads
 it at every call.  Same bar as the other parity tests; the two must also agree bit for bit."""
 
 import os
