@@ -1,5 +1,6 @@
 // Stage 2b of SurfaceLogicKV (Section 3.4, Eq. 7-8, Algorithm 3) on gfx950:
 //   pass 1  score_*<.., 1>  window-query x history-key logits, per-row log-sum-exp of every key chunk
+//   (long histories of 16-bit keys: score_sample, score_both, .. , one pass and exact scores only where they decide)
 //   pass 2  score_*<.., 2>  the chunks folded into the rows' log-sum-exp, logits again, exp(logit - lse) summed down
 //                            the G*w rows -> importance
 //   select                   1-D pooling + per-head top-k (radix select, ordered compaction)
@@ -44,6 +45,16 @@ struct SegShape {
   int score_off;   // offset of the segment in the importance / pooled arrays
 };
 
+// A history that keeps more than a fortieth of its positions: its threshold lies near the bulk of the scores, otherwise in their
+// thin upper tail (see OneScan).
+__device__ __host__ __forceinline__ bool many_kept(int m, int kk) { return kk >= m / 40; }
+// Positions per workgroup of the kernels that go over a sample of the keys or over the scores before the selection, CH: keys per chunk of the scoring pass.
+constexpr int kRangeMost = 6144, kRangeDense = 2560;
+__device__ __host__ __forceinline__ int range_len(int m, int kk, int CH) {
+  const int len = CH < 4096 ? CH : kRangeMost;
+  return many_kept(m, kk) && len > kRangeDense ? kRangeDense : len;
+}
+
 // Up to kMaxSegPerLaunch segments: everything per segment, in a kernel argument, so that one round of loads from
 // it (cold at every launch) answers a workgroup that knows its segment.
 struct SegTable {
@@ -52,9 +63,11 @@ struct SegTable {
   int32_t out_[kMaxSegPerLaunch + 1];     // first output row of the segment
   int32_t chunk_[kMaxSegPerLaunch + 1];   // prefix of key-chunk counts (0 chunks when not ranked)
   int32_t blk_[kMaxSegPerLaunch + 1];     // prefix of selection-block counts (no block when not ranked)
+  int32_t range_[kMaxSegPerLaunch + 1];   // prefix of range counts (see range_len)
   __device__ __forceinline__ int out_off(int s) const { return out_[s]; }
   __device__ __forceinline__ int chunk_begin(int s) const { return chunk_[s]; }
   __device__ __forceinline__ int blk_begin(int s) const { return blk_[s]; }
+  __device__ __forceinline__ int range_begin(int s) const { return range_[s]; }
   __device__ __forceinline__ SegShape shape(int s) const { return SegShape{n_[s], tok_[s], head_[s], kk_[s], score_[s]}; }
 };
 
@@ -104,6 +117,8 @@ union Pack16 {
   u32x4 u;
   bf16x8 b;
 };
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 // 32x32x16 MFMA on eight 16-bit elements per lane and operand: bfloat16, or IEEE half when F16
 // (the registers are typed bf16x8 either way; only the instruction reads them differently).
@@ -190,6 +205,42 @@ __device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c
         merge_stats(mm, ss, o.x, o.y);
       }
     __syncthreads();
+  }
+  return ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : INFINITY;
+}
+
+// As fold_rows, of the sample's ranges: a thread per row (tid < rows <= nt).  Of the ranges between the first and the last, which hold the keys
+// that are sampled one by one, the one with the largest sum is left out and stands at the mean of the others: a single
+// sampled key far above the rest (it stands for a hundred) would spoil the row's estimate, and one such row widens the bounds of all keys.
+__device__ __forceinline__ float fold_sample(const float* __restrict__ part, int c0, int c1, int Rpad, int rows) {
+  const int row = threadIdx.x;
+  float mm = -INFINITY, ss = 0.f, top = -INFINITY;
+  if (row < rows && row < Rpad) {
+    constexpr int NB = 32;
+    for (int c = c0; c < c1; c += NB) {
+      float v[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) v[u] = part[(int64_t)min(c + u, c1 - 1) * Rpad + row];
+      float bm = mm;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        if (c + u >= c1) v[u] = -INFINITY;
+        bm = fmaxf(bm, v[u]);
+        if (c + u > c0 && c + u < c1 - 1) top = fmaxf(top, v[u]);
+      }
+      const float mu = bm == -INFINITY ? 0.f : bm;
+      ss *= fast_exp2(mm - mu);
+#pragma unroll
+      for (int u = 0; u < NB; ++u) ss += fast_exp2(v[u] - mu);
+      mm = bm;
+    }
+    const int mid = c1 - c0 - 2;
+    if (mid >= 4) {
+      // sum of the first and last ranges, the others but the largest
+      const float ends = fast_exp2(part[(int64_t)c0 * Rpad + row] - mm) + fast_exp2(part[(int64_t)(c1 - 1) * Rpad + row] - mm);
+      const float rest = fmaxf(ss - ends - fast_exp2(top - mm), 0.f);
+      ss = ends + rest * ((float)mid / (float)(mid - 1));
+    }
   }
   return ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : INFINITY;
 }
@@ -301,7 +352,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       *reinterpret_cast<u32x4*>(&ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
     }
   };
-  static_assert(NPF == 2, "the tile loop below is written out for two register slots");
+  static_assert(kPrefetch == 2, "the tile loops below are written out for two register slots");
   issue_tile(0, pf0);   // the second tile is requested after the queries: the loop can start without it
 
   // query rows of this wave, kept in registers for the whole chunk
@@ -324,7 +375,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   if (PASS == 2) {
     float2* const fold = reinterpret_cast<float2*>(&ktile[0][0]);   // (no key has been stored yet)
 #pragma unroll
-    for (int j = 0; j < NLSE; ++j) lse_ld[j] = fold_rows(part, se.chunk0, se.chunk1, Rpad, j * 256, ROWS, 256, fold);
+    for (int j = 0; j < NLSE; ++j)
+      lse_ld[j] = fold_rows(part, se.chunk0, se.chunk1, Rpad, j * 256, ROWS, 256, fold);
   }
   float m_run[MT], s_run[MT];
 #pragma unroll
@@ -343,7 +395,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     store_tile(pf, buf);
     if (!ONLINE) issue_tile(t + NPF, pf);   // past the chunk end every piece comes from one clamped row
     __syncthreads();
-    if (PASS == 2 && t > 0 && tid < TK) {          // column sums of the previous tile
+    if (PASS == 2 && t > 0 && tid < TK) {   // column sums of the previous tile
       float v = 0.f;
 #pragma unroll
       for (int r = 0; r < RB; ++r) v += red[buf ^ 1][r][tid];
@@ -430,7 +482,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   __builtin_amdgcn_s_waitcnt(0x0F70 | LPT);   // vmcnt(LPT)
   __builtin_amdgcn_sched_barrier(0);
   if (PASS == 2) {
-    float* lse_s = reinterpret_cast<float*>(&comb[0][0]);   // comb is used by pass 1 only
+    float* lse_s = reinterpret_cast<float*>(&comb[0][0]);   // (comb is not used before the end)
     static_assert(sizeof(comb) >= NLSE * 256 * sizeof(float), "comb holds one value per thread and load");
 #pragma unroll
     for (int j = 0; j < NLSE; ++j) lse_s[tid + j * 256] = tid + j * 256 < R ? lse_ld[j] : INFINITY;
@@ -573,7 +625,19 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   }
 
   if (PASS == 1) SLKV_STAMP(256 + bid, 1);
-  if (PASS == 1) {
+  if (PASS == 2) {
+    __syncthreads();
+    if (tid < TK) {
+      const int t = ntiles - 1;
+      float v = 0.f;
+#pragma unroll
+      for (int r = 0; r < RB; ++r) v += red[t & 1][r][tid];
+      const int key = key_begin + t * TK + tid;
+      if (key < key_end) imp[se.score_off + key] = v;
+    }
+  }
+  if (PASS == 2) return;
+  {
     // A sum that left the fp32 range (logits far above the chunk's first ones): the whole
     // workgroup repeats the chunk with the running maximum.  Not taken for ordinary inputs.
     bool bad = false;
@@ -593,17 +657,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     }
   }
 
-  if (PASS == 2) {
-    __syncthreads();
-    if (tid < TK) {
-      const int t = ntiles - 1;
-      float v = 0.f;
-#pragma unroll
-      for (int r = 0; r < RB; ++r) v += red[t & 1][r][tid];
-      const int key = key_begin + t * TK + tid;
-      if (key < key_end) imp[se.score_off + key] = v;
-    }
-  } else {
+  {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       // (reference, sum) -> (log-sum-exp, 1): a sum referenced to early logits can be very large
@@ -624,6 +678,742 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       if (row < Rpad) part[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
     }
     SLKV_STAMP(256 + bid, 2);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Long histories of 16-bit keys: one pass over the keys instead of two, where no importance or pooled score is asked for
+// (which calls: plan_q_resident).
+//   score_sample_kernel     log-sum-exp of the rows over a sample of the keys: an estimate lse' of theirs
+//   score_both_kernel       over all keys e = e^(x - lse'[row]), added up along the keys (the rows' log-sum-exp, exact) and down the
+//                           rows (an approximate importance of every key)
+//   approx_hist_kernel      histogram of the pooled approximate importance
+//   one_scan_bounds_kernel  per segment: which keys can decide the selection
+//   select_chosen_kernel    the exact importance of these
+// and the selection as otherwise, from its exact values.
+//
+// The approximate importance of a key is I' = sum over the rows of e^(x - lse'[row]), the exact one
+// I = sum of rho[row] * e^(x - lse'[row]) with rho = e^(lse' - lse), so rho_min I' <= I <= rho_max I', and the same
+// holds for window maxima (averages: not built).  With tau' the k-th largest pooled I', known to a histogram bin [bin_lo, bin_hi),
+// the k-th largest pooled I, tau, lies in [rho_min bin_lo, rho_max bin_hi].  Hence
+//   a key with I' > bin_hi * rho_max / rho_min has I > tau: whatever its value, it only has to stay above tau;
+//   a key with I' < bin_lo * rho_min / max(rho_max, 1) has I < tau and I' < tau: it may keep I';
+//   the keys between get their exact importance, computed as PASS 2 does.
+// The selection on the array that holds these values keeps the same positions as on the exact importance.  A sample that misses what
+// matters only widens the range; at worst (rho not usable) every key is computed again.
+// Of 131072 keys, 256 rows, 2 per cent of the keys pulled towards a query, 2100 are sampled (8700 where 3395 positions are kept) and 70 to 200 (1200 to 1500) computed again.
+// 32 segments of 20 K to 128 K keys, 256 rows, two passes / this, us: passes 160 + 176 / sample 25, scan 184, histogram 12,
+// bounds 9, chosen keys 20 to 30; the block-wise selection 52 / 22 (pooled and listed by select_chosen_kernel); the call 407 / 278.
+constexpr int kDenseKeys = 128;      // so many of a history's first and last keys are all in the sample (attention sinks, recent tokens),
+constexpr int kSampleGroup = 8;      // of those between, groups of so many neighbours,
+// which make one of sample_step keys.  Near the bulk of the scores an uncertain one takes in many more of them: a finer sample there.
+__device__ __forceinline__ int sample_step(int m, int kk) { return max(many_kept(m, kk) ? m / 8192 : m / 2048, 4); }
+struct OneScan {
+  float* part0;        // log-sum-exp of the sample in every range, [range][Rpad]
+  uint32_t* hist;      // histogram of the approximate pooled scores, [segment][kHistBins]
+  float* lse;          // log-sum-exp of the rows, [segment][256]
+  uint32_t* bounds;    // [segment][4]: see one_scan_bounds_kernel
+  uint32_t* lists;     // [segment][kSelCandidates]
+};
+
+// 16 bytes per lane from base + off into LDS at lds (the same for the whole wave) + 16 * lane.  The caller waits for it (vmcnt);
+// the compiler does not know of it.
+__device__ __forceinline__ void load_to_lds16(const unsigned char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory", "m0");
+}
+
+// v of this lane and of the lane 32 away, added up, in both.
+__device__ __forceinline__ float sum_halves(float v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Log-sum-exp of every query row over a sample of a range's keys: an online softmax, 8 waves of 32 rows (wave (rb, ks) takes
+// the sub-tiles ks, ks + KS, .. of 32 keys of a tile).  Bound by round trips: a range has two to ten tiles.  (With the tile loop of
+// score_q_resident_kernel, 4 waves of 64 rows at 256 registers, 41 us where this takes 25.)
+template <int DK, int RB, int KIND>
+__global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
+                                                              int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w, int CH,
+                                                              float c_log2, const OneScan one) {
+  constexpr int NT = 512, KS = 8 / RB, TK = KS == 4 ? 128 : 64, NSUB = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2 + 16, CPR = DK * 2 / 16;
+  constexpr int LPT = TK * CPR / NT;
+  __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TK * ROWB];
+  __shared__ float2 comb[KS][RB * 32];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int rb = wv % RB, ks = wv / RB, l32 = lane & 31, half = lane >> 5;
+  const int bid = (int)(gridDim.x - 1 - blockIdx.x);     // (the last segments' first: short ones have the most to do)
+  const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.range_begin(s); });
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w, len = range_len(m, sg.kk, CH), r0 = tab.range_begin(seg), begin = (bid - r0) * len, keys = min(len, m - begin);
+  // key u of the sample: the range's first `head` keys, its last `tail`, then, of those between, kSampleGroup neighbours every `stride` keys, which
+  // stand for e^log_weight keys each
+  int head = keys, tail = 0, stride = 1, total = keys;
+  float log_weight = 0.f;
+  if (keys > 2 * kDenseKeys) {
+    head = bid == r0 ? kDenseKeys : 0;
+    tail = begin + keys == m ? kDenseKeys : 0;
+    const int between = keys - head - tail, groups = max(between / (kSampleGroup * sample_step(m, sg.kk)), 1);
+    stride = between / groups;
+    const int sampled = min(groups * kSampleGroup, between);
+    total = head + tail + sampled;
+    log_weight = sampled > 0 ? __builtin_amdgcn_logf((float)between / (float)sampled) : 0.f;
+  }
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat_v) +
+      ((int64_t)sg.head * k_stride_head + (int64_t)(sg.tok_begin + begin) * k_stride_tok) * 2;
+  const uint32_t row_bytes = (uint32_t)k_stride_tok * 2u, piece_off = (uint32_t)(tid % CPR) * 16u;
+  u32x4 pf0[LPT], pf1[LPT];
+  auto issue_tile = [&](int t, u32x4 (&pf)[LPT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+      const int u = min(t * TK + tid / CPR + i * (NT / CPR), total - 1);
+      const int x = u - head - tail;
+      const int key = u < head ? u : x < 0 ? x + keys : head + x / kSampleGroup * stride + x % kSampleGroup;
+      pf[i] = *reinterpret_cast<const u32x4*>(kbase + ((uint32_t)key * row_bytes + piece_off));
+    }
+  };
+  issue_tile(0, pf0);
+  bf16x8 qreg[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    Pack16 p;
+    p.u = *reinterpret_cast<const u32x4*>(q + ((int64_t)seg * R + min(rb * 32 + l32, R - 1)) * DK + kk * 16 + half * 8);
+    qreg[kk] = p.b;
+  }
+  issue_tile(1, pf1);
+  if (bid == r0)
+    for (int i = tid; i < kHistBins; i += NT) one.hist[(size_t)seg * kHistBins + i] = 0;
+  float m_run = -INFINITY, s_run = 0.f;
+  auto tile = [&](int t, u32x4 (&pf)[LPT], int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+      const int idx = i * NT + tid;
+      *reinterpret_cast<u32x4*>(&ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
+    }
+    issue_tile(t + 2, pf);
+    __syncthreads();
+#pragma unroll
+    for (int sb = 0; sb < NSUB; ++sb) {
+      const int sub = ks + sb * KS, u0 = t * TK + sub * 32;
+      f32x16 acc;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        Pack16 p;
+        p.u = *reinterpret_cast<const u32x4*>(&ktile[buf][(sub * 32 + l32) * ROWB + kk * 32 + half * 16]);
+        acc = mfma16<KIND == 1>(p.b, qreg[kk], acc);
+      }
+      if (u0 + 32 > total) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (u0 + 8 * (i >> 2) + 4 * half + (i & 3) >= total) acc[i] = -INFINITY;
+      }
+      const float lw = u0 >= head + tail ? log_weight : 0.f;   // (head and tail are multiples of 32 where other keys follow)
+      float mx = acc[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, acc[i]);
+      const float mn = fmaxf(m_run, fmaf(mx, c_log2, lw));
+      const float mu = mn == -INFINITY ? 0.f : mn;
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(acc[i], c_log2, lw - mu));
+      s_run = s_run * fast_exp2(m_run - mu) + sum;
+      m_run = mn;
+    }
+  };
+  const int ntiles = (total + TK - 1) / TK;
+  for (int t = 0; t < ntiles; t += 2) {
+    tile(t, pf0, 0);
+    if (t + 1 < ntiles) tile(t + 1, pf1, 1);
+  }
+  {
+    const float m2 = __shfl_xor(m_run, 32, 64), s2 = __shfl_xor(s_run, 32, 64);
+    merge_stats(m_run, s_run, m2, s2);
+    if (half == 0) comb[ks][rb * 32 + l32] = make_float2(m_run, s_run);
+  }
+  __syncthreads();
+  for (int row = tid; row < RB * 32; row += NT) {
+    float mm = comb[0][row].x, ss = comb[0][row].y;
+#pragma unroll
+    for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
+    if (row < Rpad) one.part0[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+  }
+}
+
+// One workgroup (4 waves) per chunk of keys, wave (rb, ks) with 32*MT query rows in registers, as in score_q_resident_kernel.
+// D[row][key]: a lane owns one key and 16 rows per product, and adds every exponential to its row's running sum and to its key's.
+//
+// Bound by the matrix cores and the vector units, which do 32 cycles of MFMA and 44 of fma, exp2 and two adds per 32x32x16 product, and by the
+// power both take (2.0 GHz under this load): the register-only loop takes 48 cycles a product, this one 72 of 2.5 M keys x 256 rows, 184 us = 0.9 PFLOP/s of products.
+//  - The unit of the software pipeline is one 32x32 product of 8 chained MFMAs: among them go the exponentials of the unit before, so
+//    two accumulators of 16 registers suffice, and the operand registers of the keys are refilled from LDS during their last use.  (16x16x32 MFMAs halve
+//    the registers of lse' and sums, but overlap worse with the vector units: 15.6 against 11.2 ns for the same work in a register-only loop; 215 us.)
+//  - Keys go from memory into LDS without passing registers, two tiles on their way: with them staged in registers
+//    the loop spilled, and a reload waits for every load in flight (249 us).
+//  - The tail mask is a second copy of the tile, not a branch between the units (20 us).
+template <int DK, int MT, int RB, int KIND>
+__global__ __launch_bounds__(256, 2) void score_both_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
+                                                            int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w, int CH,
+                                                            float c_log2, float* __restrict__ part, float* __restrict__ imp, int grid2d,
+                                                            const OneScan one) {
+  constexpr int KS = 4 / RB, TK = kTileKeys, NS = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2, CPR = ROWB / 16;
+  constexpr int LPT = TK * CPR / 256, RW = 32 * MT, ROWS = RB * RW;   // RW: rows of a wave
+  constexpr int NB = 4;                                  // tiles in LDS: the one at work, the next, two on their way
+  __shared__ __attribute__((aligned(16))) unsigned char ktile[NB][TK * ROWB];
+  __shared__ float red[NB][RB][TK];
+  __shared__ __attribute__((aligned(16))) float lse_s[256];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rb = wv % RB, ks = wv / RB, l32 = lane & 31, half = lane >> 5;
+
+  struct SegEntry {
+    int32_t n, tok_begin, head, score_off, chunk0, chunk1;
+  };
+  auto entry_of = [&](int s) {
+    const SegShape sg = tab.shape(s);
+    return SegEntry{sg.n, sg.tok_begin, sg.head, sg.score_off, tab.chunk_begin(s), tab.chunk_begin(s + 1)};
+  };
+  int seg = (int)blockIdx.y, bid;
+  SegEntry se = entry_of(seg);
+  if (grid2d) {
+    bid = se.chunk0 + (int)blockIdx.x;
+    if (bid >= se.chunk1) return;
+  } else {
+    bid = blockIdx.x;
+    seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
+    se = entry_of(seg);
+  }
+  const int key_begin = (bid - se.chunk0) * CH;
+  const int key_end = min(se.n - w, key_begin + CH);
+  const int ntiles = (key_end - key_begin + TK - 1) / TK;
+  const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat_v) +
+      ((int64_t)se.head * k_stride_head + (int64_t)se.tok_begin * k_stride_tok) * 2;
+  const uint32_t row_bytes = (uint32_t)k_stride_tok * 2u;
+  // Keys go straight from memory into LDS, 1 KiB (64 / CPR rows) per wave and instruction, no registers in between.  The 16-byte pieces of a
+  // row are permuted so that the lanes of an operand read, consecutive rows, meet different banks: piece p of row r lies in slot
+  // p ^ swz(r).
+  auto swz = [](int r) { return CPR == 16 ? r & 15 : (r >> 1) & 7; };
+  const int ld_row = wv * (64 / CPR) + lane / CPR;       // + 256 / CPR for each further instruction, which swz does not see
+  const uint32_t ld_piece = (uint32_t)((lane % CPR) ^ swz(ld_row)) * 16u;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)&ktile[0][0];
+  const uint32_t ld_first = (uint32_t)(key_begin + ld_row) * row_bytes + ld_piece, ld_last = (uint32_t)(key_end - 1) * row_bytes + ld_piece;
+  auto issue_tile = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i)                        // (past the end: the last key)
+      load_to_lds16(kbase, min(ld_first + (uint32_t)(t * TK + i * (256 / CPR)) * row_bytes, ld_last),
+                    lds_base + (uint32_t)((t % NB) * TK * ROWB + (i * 4 + wv) * 1024));
+  };
+  {
+    const float l = fold_sample(one.part0, tab.range_begin(seg), tab.range_begin(seg + 1), Rpad, ROWS);
+    lse_s[tid] = tid < R ? l : INFINITY;
+  }
+  __builtin_amdgcn_sched_barrier(0);                     // (the fold's loads and the queries together do not fit the registers)
+  bf16x8 qreg[MT][KK];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int row = min(rb * RW + mt * 32 + l32, R - 1);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      Pack16 p;
+      p.u = *reinterpret_cast<const u32x4*>(q + ((int64_t)seg * R + row) * DK + kk * 16 + half * 8);
+      qreg[mt][kk] = p.b;
+    }
+  }
+  __syncthreads();
+  issue_tile(0);
+  issue_tile(1);
+  issue_tile(2);
+  float lse_r[MT][16], row_sum[MT][16];
+  f32x16 accA, accB;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    accA[i] = accB[i] = -INFINITY;                       // (exp2 of "the products before the first" is 0)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      lse_r[mt][i] = lse_s[rb * RW + mt * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+      row_sum[mt][i] = 0.f;
+    }
+  }
+  bf16x8 kreg[KK];
+  uint32_t rd[KK];                                       // where in LDS they come from (first sub-tile of a tile)
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) rd[kk] = (uint32_t)((ks * NS * 32 + l32) * ROWB + ((kk * 2 + half) ^ swz(l32)) * 16);
+  auto lds_read = [&](int sub, int kk) __attribute__((always_inline)) {
+    Pack16 pk;
+    pk.u = *reinterpret_cast<const u32x4*>(&ktile[0][0] + (rd[kk] + (uint32_t)(sub * 32 * ROWB)));
+    kreg[kk] = pk.b;
+  };
+  // exponential of product i of row tile mt
+  auto one_exp = [&](const f32x16& a, int mt, int i, float& cs) __attribute__((always_inline)) {
+    const float x = fast_exp2(fmaf(a[i], c_log2, -lse_r[mt][i]));
+    row_sum[mt][i] += x;
+    cs += x;
+    asm volatile("" : "+v"(row_sum[mt][i]), "+v"(cs));   // here and not behind the next branch, where 16 exponentials would wait in registers
+  };
+  // The products of one row tile and 32 keys (kreg) into cur, a chain of MFMAs, and among them the exponentials of prev, the
+  // products before them, of row tile PM.  RELOAD: the last use of these keys, the operands of the next (sub-tile nsub of the tile
+  // that lies `ahead` bytes on) follow.
+  auto unit = [&](f32x16& cur, const f32x16& prev, auto mt_c, auto pm_c, auto reload_c, int ahead, int nsub, float& cs) __attribute__((always_inline)) {
+    constexpr int M = decltype(mt_c)::value, PM = decltype(pm_c)::value, EPS = 16 / KK;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      if (kk == 0) {
+        f32x16 z;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+        cur = mfma16<KIND == 1>(qreg[M][kk], kreg[kk], z);
+      } else {
+        cur = mfma16<KIND == 1>(qreg[M][kk], kreg[kk], cur);
+      }
+      if (decltype(reload_c)::value) {
+        if (nsub == 0) rd[kk] += (uint32_t)ahead;
+        lds_read(nsub, kk);
+      }
+#pragma unroll
+      for (int j = 0; j < EPS; ++j) one_exp(prev, PM, kk * EPS + j, cs);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto put = [&](float cs, int rbuf, int sub) __attribute__((always_inline)) {
+    red[rbuf][rb][ks * NS * 32 + sub * 32 + l32] = sum_halves(cs);   // (both halves write the same value)
+  };
+  // the sums of tile t's keys over the RB row blocks: a wave looks after 16 keys, RB neighbouring lanes after one
+  static_assert(16 * RB <= 64, "RB lanes per key");
+  auto read_sums = [&](int rbuf) __attribute__((always_inline)) { return red[rbuf][lane % RB][(wv * 16 + lane / RB) % TK]; };
+  auto store_sums = [&](float v, int t) __attribute__((always_inline)) {
+    v += dpp_move_f<0xb1>(v);                            // quad_perm: the neighbour
+    if (RB == 4) v += dpp_move_f<0x4e>(v);               // and the pair next to them
+    const int key = wv * 16 + lane / RB;
+    if (lane < 16 * RB && lane % RB == 0 && key < key_end - key_begin - t * TK) (imp + se.score_off + key_begin + t * TK)[(uint32_t)key] = v;
+  };
+  auto mask_keys = [&](f32x16& a, int t, int sub) __attribute__((always_inline)) {
+    if (key_begin + t * TK + (ks * NS + sub) * 32 + l32 >= key_end) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) a[i] = -INFINITY;
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  float cs = 0.f;                                        // of the keys whose products are in the accumulators
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  __builtin_amdgcn_s_waitcnt(0x0F70 | LPT);
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) lds_read(0, kk);
+  // tile t, in LDS since the barrier like tile t + 1; MASKED: it may reach past key_end
+  auto tile = [&](int t, auto masked_c) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    const int buf = t % NB, before = (t + NB - 1) % NB;
+    const int ahead = buf == NB - 1 ? -(NB - 1) * TK * ROWB : TK * ROWB;
+    tile_priority(t);
+    issue_tile(t + 3);                                   // into the buffer of tile t - 1, which every wave has read; past the end: the last key again
+    const float sums = read_sums((t + NB - 2) % NB);     // (complete since the barrier)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int nsub = s + 1 < NS ? s + 1 : 0;
+      unit(accA, accB, I0{}, std::integral_constant<int, MT - 1>{}, std::integral_constant<bool, MT == 1>{}, ahead, nsub, cs);
+      if (MASKED) mask_keys(accA, t, s);
+      put(cs, s > 0 ? buf : before, s > 0 ? s - 1 : NS - 1);
+      cs = 0.f;
+      if constexpr (MT == 2) {
+        unit(accB, accA, I1{}, I0{}, std::true_type{}, ahead, nsub, cs);
+        if (MASKED) mask_keys(accB, t, s);
+      } else {
+        accB = accA;
+      }
+    }
+    if (t > 1) store_sums(sums, t - 2);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | LPT);            // vmcnt: all but the tile issued above
+    __syncthreads();
+  };
+#pragma unroll 1
+  for (int t = 0; t < ntiles - 1; ++t) tile(t, std::false_type{});
+  tile(ntiles - 1, std::true_type{});
+  {
+    const int last = (ntiles - 1) % NB;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) one_exp(accB, MT - 1, i, cs);
+    put(cs, last, NS - 1);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                  // nothing is on its way into LDS any more
+    __syncthreads();
+    if (ntiles > 1) store_sums(read_sums((last + NB - 1) % NB), ntiles - 2);
+    store_sums(read_sums(last), ntiles - 1);
+  }
+  // the rows' sums over the 32 lanes that hold a row's keys, by row moves, into the last of them
+  bool bad = false;
+  float* const sums = reinterpret_cast<float*>(&ktile[0][0]);   // [KS][ROWS] (every wave is past its last read)
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float v = row_sum[mt][i];
+      v += dpp_move_f<kDppRowShr + 1>(v);
+      v += dpp_move_f<kDppRowShr + 2>(v);
+      v += dpp_move_f<kDppRowShr + 4>(v);
+      v += dpp_move_f<kDppRowShr + 8>(v);
+      v += dpp_move_f<kDppRowBcast15, 0xa>(v);
+      // (a row beyond R has lse' = inf and the sum 0; lse' = inf below R: no estimate, a sample of NaNs)
+      const int row = rb * RW + mt * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+      bad = bad || (l32 == 31 && (!(v < INFINITY) || (row < R && lse_r[mt][i] == INFINITY)));
+      if (l32 == 31) sums[ks * ROWS + row] = v;
+    }
+  if (__syncthreads_or(bad ? 1 : 0)) {
+    // A sum that left the fp32 range (logits far above the sample's) or is none: the chunk once more, with a running maximum, a tile at a time.
+    // Not taken for ordinary inputs.
+    int ln = l32;
+    asm volatile("" : "+v"(ln));                         // (no address of here is computed, and kept, before the loop above)
+    float m_run[MT], s_run[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      m_run[mt] = -INFINITY;
+      s_run[mt] = 0.f;
+    }
+    for (int t = 0; t < ntiles; ++t) {
+      __syncthreads();
+      for (int i = tid; i < TK * CPR; i += 256) {
+        const int r = i / CPR, key = min(key_begin + t * TK + r, key_end - 1);
+        *reinterpret_cast<u32x4*>(&ktile[0][r * ROWB + ((i % CPR) ^ swz(r)) * 16]) =
+            *reinterpret_cast<const u32x4*>(kbase + ((uint32_t)key * row_bytes + (uint32_t)(i % CPR) * 16u));
+      }
+      __syncthreads();
+      for (int s = 0; s < NS; ++s) {
+        const int r0 = (ks * NS + s) * 32, key0 = key_begin + t * TK + r0;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          f32x16 a;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) a[i] = 0.f;
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            Pack16 pk;
+            pk.u = *reinterpret_cast<const u32x4*>(&ktile[0][(r0 + ln) * ROWB + ((kk * 2 + half) ^ swz(ln)) * 16]);
+            a = mfma16<KIND == 1>(pk.b, qreg[mt][kk], a);
+          }
+          // lane: query row mt*32 + l32, keys key0 + 8*(i/4) + 4*half + i%4
+          float mx = -INFINITY;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            if (key0 + 8 * (i >> 2) + 4 * half + (i & 3) >= key_end) a[i] = -INFINITY;
+            mx = fmaxf(mx, a[i]);
+          }
+          const float mn = fmaxf(m_run[mt], mx * c_log2), mu = mn == -INFINITY ? 0.f : mn;
+          float sum = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(a[i], c_log2, -mu));
+          s_run[mt] = s_run[mt] * fast_exp2(m_run[mt] - mu) + sum;
+          m_run[mt] = mn;
+        }
+      }
+    }
+    float2* const comb = reinterpret_cast<float2*>(&ktile[1][0]);   // [KS][ROWS]
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const float m2 = __shfl_xor(m_run[mt], 32, 64), s2 = __shfl_xor(s_run[mt], 32, 64);
+      merge_stats(m_run[mt], s_run[mt], m2, s2);
+      if (half == 0) comb[ks * ROWS + rb * RW + mt * 32 + l32] = make_float2(m_run[mt], s_run[mt]);
+    }
+    __syncthreads();
+    for (int row = tid; row < ROWS; row += 256) {
+      float mm = comb[row].x, ss = comb[row].y;
+#pragma unroll
+      for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2 * ROWS + row].x, comb[k2 * ROWS + row].y);
+      if (row < Rpad) part[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+    }
+    return;
+  }
+  for (int row = tid; row < ROWS; row += 256) {
+    float v = sums[row];
+#pragma unroll
+    for (int k2 = 1; k2 < KS; ++k2) v += sums[k2 * ROWS + row];
+    if (row < Rpad) part[(int64_t)bid * Rpad + row] = v > 0.f ? lse_s[row] + __builtin_amdgcn_logf(v) : -INFINITY;
+  }
+}
+
+constexpr int kBinShift = 17;                        // 64 bins per octave,
+constexpr uint32_t kBinBase = 106u << (23 - kBinShift);   // from 2^-21 to 2^11; what lies outside counts in the first and last bin
+constexpr int kSelCandidates = 12288;                // scores that select_rank_kernel's list in LDS can hold
+constexpr float kAboveAll = 0x1p120f;                // stands for the importance of a key above tau
+
+__device__ __forceinline__ uint32_t importance_key(float v) {   // as score_key
+  const uint32_t u = __float_as_uint(v);
+  return u > 0x7f800000u ? 0x7f800000u : u;
+}
+
+// Histogram of the pooled approximate importance: a workgroup per block of 4096 positions (x) of a segment (y).
+constexpr int kApproxBlock = 4096;
+__global__ __launch_bounds__(256) void approx_hist_kernel(const SegTable tab, int w, int radius, const float* __restrict__ imp,
+                                                          uint32_t* __restrict__ hist) {
+  __shared__ uint32_t bins[kHistBins];
+  __shared__ uint32_t stage[kApproxBlock + kMaxPool];
+  const int tid = threadIdx.x, seg = blockIdx.y;
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w, p0 = (int)blockIdx.x * kApproxBlock;
+  if (!(sg.kk > 0 && sg.kk < m) || p0 >= m) return;
+  const float* I = imp + sg.score_off;
+  const int cnt = min(kApproxBlock, m - p0);
+  constexpr int PER = kApproxBlock / 256;
+  float v[PER + 1];
+#pragma unroll
+  for (int e = 0; e <= PER; ++e) {
+    const int j = p0 - radius + e * 256 + tid;
+    v[e] = I[min(max(j, 0), m - 1)];                 // (positions beyond either end: a neighbour inside the window or none)
+  }
+  for (int i = tid; i < kHistBins; i += 256) bins[i] = 0;
+#pragma unroll
+  for (int e = 0; e <= PER; ++e)
+    if (e * 256 + tid < kApproxBlock + 2 * radius) stage[e * 256 + tid] = importance_key(v[e]);
+  __syncthreads();
+#pragma unroll 4
+  for (int e = 0; e < PER; ++e) {
+    const int s = e * 256 + tid;
+    if (s < cnt) {
+      uint32_t a = stage[s];
+      for (int t = 1; t <= 2 * radius; ++t) a = max(a, stage[s + t]);
+      const uint32_t b = a >> kBinShift;
+      atomicAdd(&bins[b <= kBinBase ? 0u : min(b - kBinBase, (uint32_t)kHistBins - 1u)], 1u);
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < kHistBins; i += 256)
+    if (bins[i]) atomicAdd(&hist[(size_t)seg * kHistBins + i], bins[i]);
+}
+
+// A workgroup per segment: its rows' log-sum-exp, the range of rho, and what follows from them and the histogram:
+// bounds[0], [1]: keys whose I' lies between (bit patterns, inclusive) need their exact importance; above: kAboveAll stands for it;
+// bounds[2], [3]: the k-th largest pooled score lies between.
+// blockhist (block-wise selection): also the words that select_rank_kernel, phase 1, expects in the segment's first histogram row.
+__global__ __launch_bounds__(256) void one_scan_bounds_kernel(const SegTable tab, int w, int R, int Rpad, const float* __restrict__ part, const OneScan one,
+                                                              uint32_t* __restrict__ blockhist) {
+  __shared__ uint32_t bins[kHistBins];
+  __shared__ float2 fold[256];
+  __shared__ uint32_t sh_scan[4], res[2];
+  __shared__ float sh_rho[8];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, seg = blockIdx.x;
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w;
+  if (!(sg.kk > 0 && sg.kk < m)) return;
+#pragma unroll
+  for (int i = 0; i < kHistBins / 256; ++i) bins[i * 256 + tid] = one.hist[(size_t)seg * kHistBins + i * 256 + tid];
+  const int rows = Rpad <= 64 ? 64 : Rpad <= 128 ? 128 : 256;
+  const float lse = fold_rows(part, tab.chunk_begin(seg), tab.chunk_begin(seg + 1), Rpad, 0, rows, 256, fold);
+  const float lse0 = fold_sample(one.part0, tab.range_begin(seg), tab.range_begin(seg + 1), Rpad, rows);
+  one.lse[(size_t)seg * 256 + tid] = tid < R ? lse : INFINITY;
+  // the range of rho over the rows; anything that is not a positive number ends as 0 or inf
+  const float rho = fast_exp2(lse0 - lse);
+  float rmin = tid < R ? (rho > 0.f ? rho : 0.f) : INFINITY, rmax = tid < R ? (rho < INFINITY ? rho : INFINITY) : 0.f;
+#pragma unroll
+  for (int dlt = 32; dlt > 0; dlt >>= 1) {
+    rmin = fminf(rmin, __shfl_xor(rmin, dlt, 64));
+    rmax = fmaxf(rmax, __shfl_xor(rmax, dlt, 64));
+  }
+  if (lane == 0) {
+    sh_rho[wv] = rmin;
+    sh_rho[4 + wv] = rmax;
+  }
+  __syncthreads();
+  rmin = fminf(fminf(sh_rho[0], sh_rho[1]), fminf(sh_rho[2], sh_rho[3]));
+  rmax = fmaxf(fmaxf(sh_rho[4], sh_rho[5]), fmaxf(sh_rho[6], sh_rho[7]));
+  select_bin<256>(bins, (uint32_t)sg.kk, sh_scan, res);
+  if (tid == 0) {
+    const uint32_t b = res[0];
+    constexpr float kSlack = 1.f / 1024.f;               // far above the rounding of either side
+    const float ratio = rmax / rmin;
+    const bool usable = b > 0u && rmin > 0.f && ratio < 1e6f;   // (false for NaN, too)
+    const float bin_lo = __uint_as_float((b + kBinBase) << kBinShift);
+    const float bin_hi = b == (uint32_t)kHistBins - 1u ? INFINITY : __uint_as_float((b + 1u + kBinBase) << kBinShift);
+    uint32_t bd[4] = {0u, 0x7f800000u, 0u, 0x7f800000u};        // not usable: every key, any score
+    if (usable) {
+      bd[0] = __float_as_uint(bin_lo * (rmin / fmaxf(rmax, 1.f)) * (1.f - kSlack));
+      bd[1] = min(__float_as_uint(bin_hi * ratio * (1.f + kSlack)), 0x7f800000u);
+      bd[2] = __float_as_uint(bin_lo * rmin * (1.f - kSlack));
+      bd[3] = min(__float_as_uint(bin_hi * rmax * (1.f + kSlack)), 0x7f800000u);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) one.bounds[seg * 4 + i] = bd[i];
+    if (blockhist) {
+      uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
+      hdr[4] = bd[2];
+      hdr[5] = bd[3];
+      hdr[6] = 0;                                        // pooled scores above the range
+      hdr[7] = 0;                                        // scores listed (or counted, where they are more than a list holds)
+    }
+  }
+}
+
+// The exact importance of the keys that can decide the selection.  A workgroup (8 waves) per range of positions lists them
+// and takes them TK at a time through the loop of PASS 2; wave (rb, ks) holds 32 query rows.
+//   blockhist == NULL: the importance array is made fit for select_resident_kernel;
+//   otherwise the positions are pooled here (the keys of the neighbours' edges are done twice) and their scores between bounds[2] and [3] listed, so that the
+//   block-wise selection starts at phase 1 of select_rank_kernel.
+template <int DK, int RB, int KIND>
+__global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
+                                                               int64_t k_stride_tok, int64_t k_stride_head, int R, int w, int CH, int radius,
+                                                               float c_log2, const OneScan one, float* __restrict__ imp,
+                                                               float* __restrict__ pooled, uint32_t* __restrict__ blockhist) {
+  constexpr int NT = 512, KS = 8 / RB, TK = KS == 4 ? 128 : 64, NSUB = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2 + 16, CPR = DK * 2 / 16;
+  constexpr int LPT = TK * CPR / NT, MOST = kRangeMost + kMaxPool - 1, PER = (MOST + NT - 1) / NT;
+  __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TK * ROWB];
+  __shared__ float red[2][RB][TK];
+  __shared__ uint32_t val[MOST];                         // pooled scores; 0 where no key that matters is near
+  __shared__ uint16_t list[MOST];
+  __shared__ float lse_s[256];
+  __shared__ uint32_t nlist, nsure, nabove, nband, band0;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int rb = wv % RB, ks = wv / RB, l32 = lane & 31, half = lane >> 5;
+  const int bid = (int)(gridDim.x - 1 - blockIdx.x);     // (the last segments' first: short ones have the most to do)
+  const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.range_begin(s); });
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w, len = range_len(m, sg.kk, CH), begin = (bid - tab.range_begin(seg)) * len;
+  const int reach = blockhist ? radius : 0;
+  float* const I = imp + sg.score_off;
+  const uint32_t lo = one.bounds[seg * 4], hi = one.bounds[seg * 4 + 1];
+  const uint32_t lo2 = one.bounds[seg * 4 + 2], span2 = one.bounds[seg * 4 + 3] - lo2;
+  const int first = begin, end = min(begin + len, m);
+  const int p0 = max(first - reach, 0), cnt = min(end + reach, m) - p0;   // positions looked at here
+  float v[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) v[e] = I[p0 + min(e * NT + tid, cnt - 1)];
+  if (tid < 256) lse_s[tid] = one.lse[(size_t)seg * 256 + tid];
+  if (tid == 0) nlist = nsure = nabove = nband = 0;
+  if (blockhist)
+    for (int i = tid; i < cnt; i += NT) val[i] = 0;
+  // a key's score enters the windows that it lies in
+  auto pool = [&](int i, uint32_t u) __attribute__((always_inline)) {
+    for (int j = max(i - radius, 0); j <= min(i + radius, cnt - 1); ++j) atomicMax(&val[j], u);
+  };
+  bf16x8 qreg[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    Pack16 p;
+    p.u = *reinterpret_cast<const u32x4*>(q + ((int64_t)seg * R + min(rb * 32 + l32, R - 1)) * DK + kk * 16 + half * 8);
+    qreg[kk] = p.b;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int i = e * NT + tid;
+    const uint32_t u = importance_key(v[e]);
+    const bool valid = i < cnt, in = valid && u >= lo && u <= hi;
+    const unsigned long long mask = __ballot(in);
+    if (mask) {
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&nlist, (uint32_t)__popcll(mask));
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+      if (in) list[base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = (uint16_t)i;
+    }
+    if (valid && u > hi) {
+      if (blockhist) list[MOST - 1 - (int)atomicAdd(&nsure, 1u)] = (uint16_t)i;   // (few; the two lists together hold at most cnt entries)
+      else I[p0 + i] = kAboveAll;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < (int)nsure; i += NT) pool(list[MOST - 1 - i], __float_as_uint(kAboveAll));
+  const int nl = (int)nlist, ntiles = (nl + TK - 1) / TK;
+  if (nl > 0) {
+    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat_v) +
+        ((int64_t)sg.head * k_stride_head + (int64_t)(sg.tok_begin + p0) * k_stride_tok) * 2;
+    const uint32_t row_bytes = (uint32_t)k_stride_tok * 2u, piece_off = (uint32_t)(tid % CPR) * 16u;
+    const int piece_row = tid / CPR;
+    u32x4 pf0[LPT], pf1[LPT];
+    auto issue_tile = [&](int t, u32x4 (&pf)[LPT]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < LPT; ++i) {
+        const int key = list[min(t * TK + piece_row + i * (NT / CPR), nl - 1)];
+        pf[i] = *reinterpret_cast<const u32x4*>(kbase + ((uint32_t)key * row_bytes + piece_off));
+      }
+    };
+    issue_tile(0, pf0);
+    issue_tile(1, pf1);
+    float lse_r[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lse_r[i] = lse_s[rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+    auto tile = [&](int t, u32x4 (&pf)[LPT], int buf) __attribute__((always_inline)) {   // t == ntiles: only the sums of the tile before
+#pragma unroll
+      for (int i = 0; i < LPT; ++i) {
+        const int idx = i * NT + tid;
+        *reinterpret_cast<u32x4*>(&ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
+      }
+      issue_tile(t + 2, pf);
+      __syncthreads();
+      if (t > 0 && tid < TK) {                           // column sums of the previous tile
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) sum += red[buf ^ 1][r][tid];
+        const int li = (t - 1) * TK + tid;
+        if (li < nl) {
+          if (!blockhist) I[p0 + list[li]] = sum;
+          else if (importance_key(sum) >= lo2) pool(list[li], importance_key(sum));
+        }
+      }
+      if (t == ntiles) return;
+#pragma unroll
+      for (int sb = 0; sb < NSUB; ++sb) {
+        const int sub = ks + sb * KS;
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          Pack16 p;
+          p.u = *reinterpret_cast<const u32x4*>(&ktile[buf][(sub * 32 + l32) * ROWB + kk * 32 + half * 16]);
+          acc = mfma16<KIND == 1>(qreg[kk], p.b, acc);
+        }
+        float colsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) colsum += fast_exp2(fmaf(acc[i], c_log2, -lse_r[i]));
+        colsum += __shfl_xor(colsum, 32, 64);
+        if (half == 0) red[buf][rb][sub * 32 + l32] = colsum;
+      }
+    };
+    for (int t = 0; t <= ntiles; t += 2) {
+      tile(t, pf0, 0);
+      if (t < ntiles) tile(t + 1, pf1, 1);
+    }
+  }
+  if (!blockhist) return;
+  __syncthreads();
+  // pooled scores (exact from bounds[2] on) of positions first .. end - 1, those above the range counted, those in it listed
+  uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
+  constexpr int OWN = kRangeMost / NT;
+  uint32_t key[OWN];
+  uint32_t above = 0, in_band = 0;
+#pragma unroll
+  for (int e = 0; e < OWN; ++e) {
+    const int j = first + e * NT + tid;
+    const bool real = j < end;
+    key[e] = 0;
+    if (real) {
+      key[e] = val[j - p0];
+      pooled[sg.score_off + j] = __uint_as_float(key[e]);
+    }
+    above += (uint32_t)__popcll(__ballot(real && key[e] > lo2 + span2));
+    in_band += (uint32_t)__popcll(__ballot(real && key[e] - lo2 <= span2));
+  }
+  uint32_t base = 0;
+  if (lane == 0) {
+    if (above) atomicAdd(&nabove, above);
+    if (in_band) base = atomicAdd(&nband, in_band);
+  }
+  base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+  __syncthreads();
+  if (tid == 0) {
+    if (nabove) atomicAdd(&hdr[6], nabove);
+    band0 = nband ? atomicAdd(&hdr[7], nband) : 0u;
+  }
+  __syncthreads();
+  if (in_band) {
+    base += band0;
+    uint32_t* const L = one.lists + (size_t)seg * kSelCandidates;
+#pragma unroll
+    for (int e = 0; e < OWN; ++e) {
+      const bool in = first + e * NT + tid < end && key[e] - lo2 <= span2;
+      const unsigned long long mask = __ballot(in);
+      const uint32_t at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      if (in && at < (uint32_t)kSelCandidates) L[at] = key[e];
+      base += (uint32_t)__popcll(mask);
+    }
   }
 }
 
@@ -675,8 +1465,6 @@ template <int DK, int KIND>
 constexpr size_t score_lds_bytes(int tiles, int waves) {
   return (size_t)tiles * 32 * ScoreCfg<DK, KIND>::ROWB + (size_t)waves * tiles * 64 * sizeof(float2) + (size_t)tiles * 32 * sizeof(float);
 }
-
-typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 template <int DK, int KIND, int PASS, class TAB>
 __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab, const void* __restrict__ qmat, const void* __restrict__ kmat,
@@ -1035,7 +1823,6 @@ constexpr int kSelHaloMax = kMaxPool / 2;
 constexpr int kSelRankMax = 256;          // lists up to this length are ranked by direct counting
 constexpr int kSelTieGroups = 512;        // this many group maxima in the bound's digit switch the histograms to the pile-aware step
 constexpr int kSelTrackMax = 512;         // up to this many wanted keys the first level also tracks the largest and smallest key of every digit
-constexpr int kSelCandidates = 12288;     // scores of one first-level digit that the LDS list can hold
 constexpr int kDigitShift = 20;           // first-level digit = key >> 20: sign (0), 8 exponent and 3 mantissa bits
 constexpr uint32_t kKeyNone = 0xffffffffu;
 static_assert((0x7f800000u >> kDigitShift) < (uint32_t)kHistBins, "every key has a first-level digit inside the histogram");
@@ -1110,7 +1897,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
                                                                   uint32_t* __restrict__ blockhist,
                                                                   int32_t* __restrict__ kept_idx, int64_t* __restrict__ d_out_offsets,
                                                                   const GatherArgs ga, int split_emit,
-                                                                  const uint32_t* __restrict__ lists, int phase) {
+                                                                  const uint32_t* __restrict__ lists, int phase, int chosen) {
   constexpr int NT = kSelThreads, NW = kSelWaves, EPT = kSelEPT, ROUND = kSelRound;
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t cand[kSelCandidates];
@@ -1219,12 +2006,13 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
         for (int j = 0; j < EPT; ++j) f(key[j]);
       }
     };
-    uint32_t lo = hdr[4], hi = hdr[5], k = hdr[6], in_range = hdr[8];
-    const bool use_list = hdr[9] != 0u;
+    // (chosen: after select_chosen_kernel, word 6 counts the scores above the range instead)
+    uint32_t lo = hdr[4], hi = hdr[5], k = chosen ? (uint32_t)kk - hdr[6] : hdr[6], in_range = chosen ? hdr[7] : hdr[8];
+    const bool use_list = chosen ? in_range <= (uint32_t)kSelCandidates : hdr[9] != 0u;
     const uint32_t ncand = min(hdr[7], (uint32_t)kSelCandidates);   // (== in_range when the list is used)
     if (use_list) {
       // the scores of the chosen digit, listed by the blocks: into LDS
-      const uint32_t* L = lists + sg.score_off;
+      const uint32_t* L = lists + (chosen ? (int64_t)seg * kSelCandidates : (int64_t)sg.score_off);
       for (uint32_t i = tid; i < ncand; i += NT) cand[i] = L[i];
       __syncthreads();
     } else if (!multi) {
@@ -2150,11 +2938,19 @@ struct Plan {
   int rsplit;            // of these, that share a key group's query tiles (score_k_resident_kernel)
   size_t part_bytes, score_bytes, hist_bytes, table_bytes;
   size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
+  bool one_scan;         // the call may go over its keys once (see OneScan), if the workspace has these bytes as well
+  int64_t ranges;        // see range_len
+  size_t off_part0, off_bins, off_lse, off_bounds, off_lists, one_scan_bytes;
 };
 
 static bool seg_ranked(int64_t n, int64_t w, int64_t cap) { return n > w && n > cap && cap > w; }
 // key chunks of the scoring passes and blocks of the selection for one segment
 static int64_t seg_chunks(const Seg& s, int w, int64_t ch) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + ch - 1) / ch : 0; }
+static int64_t seg_ranges(const Seg& s, int w, int ch) {
+  if (!seg_ranked(s.n, w, s.cap)) return 0;
+  const int m = (int)(s.n - w), len = range_len(m, (int)(s.cap - w), ch);
+  return (m + len - 1) / len;
+}
 static int64_t seg_blocks(const Seg& s, int w) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + kSelBlock - 1) / kSelBlock : 0; }
 
 // f(head dimension, KIND) of a call, as integral constants.
@@ -2276,6 +3072,13 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
 // Up to 64 rows one workgroup's loads in flight do not keep the memory busy: 32 x 16 K keys 57.4 us with 512, 61.3 with 256.
 // 448 rows, 4 x 24 K: 88 us with 376 chunks, which run in two rounds, 60.7 with 252.  What does not fit at once runs in rounds.
 // Small calls take chunks down to two tiles: 8 x 2 K keys of 128 rows 22.5 us with 256 keys a chunk, 19.6 with 128.
+//
+// One pass over the keys instead of two (OneScan) where a pass takes this long by the costs above: it saves a pass, less a tenth, and
+// costs the sample, the histogram, the bounds and the chosen keys; where histories above 32768 positions are selected by blocks it
+// saves three of that selection's launches as well.  One pass / two, us: 8 x 64 K keys of 256 rows 121 / 119, 8 x 80 K 127 / 137, 8 x 128 K 158 / 189, c5's 2.5 M keys
+// 278 / 407; of 128 rows 8 x 96 K 115 / 114, 8 x 128 K 127 / 148; of 64 rows 8 x 128 K 126 / 121, 16 x 100 K 159 / 174; of 16 rows 32 x 75 K 204 / 239;
+// histories of at most 32768, 256 rows: 64 x 20 K 214 / 215, 48 x 30 K 224 / 249, 64 x 32 K 256 / 320, of 128 rows 64 x 32 K 208 / 212; more than 64 segments: 128 x 16 K 329 / 323.
+constexpr double kOneScanUs = 50, kOneScanFewRowsUs = 40, kOneScanResidentUs = 100;
 static void plan_q_resident(const Geometry& g, Plan& p) {
   const int cfg = p.R <= 64 ? 0 : p.R <= 128 ? 1 : p.R <= 256 ? 2 : 3;
   const double dim = g.d == 128 ? 1.0 : 0.6;
@@ -2300,9 +3103,12 @@ static void plan_q_resident(const Geometry& g, Plan& p) {
   }
   p.waves = 4;
   p.rsplit = 1;
+  const double worth = lens.longest <= kSelRound ? kOneScanResidentUs : cfg == 2 ? kOneScanUs : kOneScanFewRowsUs;
+  p.one_scan = best >= worth && (cfg == 2 || lens.longest > kSelRound) && p.R <= 256 && g.pool != SLKV_POOL_AVG && g.segs.size() <= (size_t)kMaxSegPerLaunch;
 }
 
 static void make_plan(const Geometry& g, Plan& p) {
+  p.one_scan = false;
   p.R = (g.Hq / g.Hkv) * g.w;
   p.Rpad = (p.R + 31) / 32 * 32;
   if (g.dtype == SLKV_BF16 || g.dtype == SLKV_F16) plan_q_resident(g, p);
@@ -2328,6 +3134,17 @@ static void make_plan(const Geometry& g, Plan& p) {
   const size_t S = g.segs.size();
   p.table_bytes = S > (size_t)kMaxSegPerLaunch ? align((4 * S + 4 + (size_t)g.Hkv) * sizeof(int32_t)) : 0;
   p.total_bytes = p.off_table + p.table_bytes;
+  p.one_scan_bytes = 0;
+  p.ranges = 0;
+  if (p.one_scan) {
+    for (const Seg& s : g.segs) p.ranges += seg_ranges(s, g.w, p.CH);
+    p.off_part0 = p.total_bytes;
+    p.off_bins = p.off_part0 + align((size_t)p.ranges * p.Rpad * sizeof(float));
+    p.off_lse = p.off_bins + S * kHistBins * sizeof(uint32_t);
+    p.off_bounds = p.off_lse + S * 256 * sizeof(float);
+    p.off_lists = p.off_bounds + align(S * 4 * sizeof(uint32_t));
+    p.one_scan_bytes = p.off_lists + S * kSelCandidates * sizeof(uint32_t) - p.total_bytes;
+  }
 }
 
 static void layer_geometry(const slkv_layer_desc* d, Geometry& g) {
@@ -2381,28 +3198,52 @@ struct ScoreGrid {
   int chunks, per_row, rows;
 };
 
+// The passes of a call: 1 and 2, or these three.
+constexpr int kPassSample = 0, kPassBoth = 3, kPassChosen = 4;
+
 template <int DK, int MT, int RB, int KIND, class TAB>
 static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                              const Geometry& g, const Plan& p, float c_log2, float* part, float* imp) {
+                              const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
+                              uint32_t* blockhist) {
   // segments with like chunk counts: one grid row per segment (see the kernel's first lines)
   const bool two = grid.rows > 0;
   const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
-  if (pass == 1)
-    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, 1, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
-                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
-  else
-    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, 2, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
-                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0);
+  auto scan = [&](auto pass_c, dim3 grid_c, float* part_c) {
+    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, decltype(pass_c)::value, KIND, TAB>), grid_c, dim3(256), 0, st, tab, (const uint16_t*)q, k,
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part_c, imp, two ? 1 : 0);
+  };
+  if (pass == 1) scan(std::integral_constant<int, 1>{}, gr, part);
+  if (pass == 2) scan(std::integral_constant<int, 2>{}, gr, part);
+  if constexpr (MT <= 2 && std::is_same_v<TAB, SegTable>) {
+    const unsigned S = (unsigned)g.segs.size();
+    if (pass == kPassSample)
+      SLKV_LAUNCH((score_sample_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, one);
+    if (pass == kPassBoth)
+      SLKV_LAUNCH((score_both_kernel<DK, MT, RB, KIND>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, one);
+    if (pass == kPassChosen) {
+      int64_t longest = 0;
+      for (const Seg& sg : g.segs)
+        if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
+      const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
+      SLKV_LAUNCH(approx_hist_kernel, dim3((unsigned)((longest + kApproxBlock - 1) / kApproxBlock), S), dim3(256), 0, st, tab, g.w, radius, imp, one.hist);
+      SLKV_LAUNCH(one_scan_bounds_kernel, dim3(S), dim3(256), 0, st, tab, g.w, p.R, p.Rpad, part, one, blockhist);
+      SLKV_LAUNCH((select_chosen_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab,
+                  (const uint16_t*)q, k, g.k_stride_tok, g.k_stride_head, p.R, g.w, p.CH, radius, c_log2, one, imp, pooled, blockhist);
+    }
+  }
 }
 
 template <int DK, int KIND, class TAB>
 static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                           const Geometry& g, const Plan& p, float c_log2, float* part, float* imp) {
+                           const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
+                              uint32_t* blockhist) {
   if constexpr (KIND <= 1) {
-    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
-    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
-    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
-    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
+    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
+    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
+    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
   } else {
     const bool two = grid.rows > 0;
     const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
@@ -2418,22 +3259,23 @@ static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& 
 
 template <class TAB>
 static void launch_score(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                         const Geometry& g, const Plan& p, float c_log2, float* part, float* imp) {
+                         const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
+                              uint32_t* blockhist) {
   with_score_kind(g.d, g.dtype, [&](auto dk, auto kind) {
-    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp);
+    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
   });
 }
 
 template <class TAB>
 static void launch_select(int nseg, int blocks, hipStream_t st, const TAB& tab, const Geometry& g, const float* imp,
                           float* pooled, uint32_t* blockhist, uint32_t* lists, int32_t* kept_idx, int64_t* d_out_offsets,
-                          const GatherArgs& ga) {
+                          const GatherArgs& ga, bool chosen) {
   const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
   const int pool_kernel = g.pool == SLKV_POOL_NONE ? 1 : g.pool_kernel;
 #define SLKV_POOL_LAUNCH(RAD)                                                                                          \
   SLKV_LAUNCH((select_pool_kernel<RAD, TAB>), dim3(blocks), dim3(kSelThreads), 0, st, tab, g.w, pool_kernel, g.pool, imp, \
               pooled, blockhist)
-  if (blocks > 0) {
+  if (blocks > 0 && !chosen) {                           // (chosen: select_chosen_kernel has pooled and listed the scores)
     switch (radius) {
       case 0: SLKV_POOL_LAUNCH(0); break;
       case 1: SLKV_POOL_LAUNCH(1); break;
@@ -2452,15 +3294,15 @@ static void launch_select(int nseg, int blocks, hipStream_t st, const TAB& tab, 
   // (one long history among many short ones) or more rows than a grid has
   const bool rows = nseg <= 65535 && longest * nseg <= 4 * (int64_t)blocks;
   const dim3 grid = rows ? dim3((unsigned)std::max<int64_t>(longest, 1), (unsigned)nseg) : dim3((unsigned)std::max(blocks, 1));
-  if (split) {
+  if (split && !chosen) {
     // first-level digit per segment, then the blocks list the scores of that digit
     SLKV_LAUNCH(select_rank_kernel<TAB>, dim3(nseg), dim3(kSelThreads), 0, st, tab, g.w, (const float*)pooled,
-                blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 0);
+                blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 0, 0);
     SLKV_LAUNCH(select_collect_kernel<TAB>, grid, dim3(kSelEmitThreads), 0, st, tab, g.w, (const float*)pooled, blockhist,
                 lists, rows ? 0 : -1);
   }
   SLKV_LAUNCH(select_rank_kernel<TAB>, dim3(nseg), dim3(kSelThreads), 0, st, tab, g.w, (const float*)pooled,
-              blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 1);
+              blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 1, chosen ? 1 : 0);
   if (split) {
     SLKV_LAUNCH(select_count_kernel<TAB>, grid, dim3(kSelEmitThreads), 0, st, tab, g.w, (const float*)pooled, blockhist,
                 rows ? 0 : -1);
@@ -2664,6 +3506,12 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   for (const Seg& sg : g.segs)
     if (seg_ranked(sg.n, g.w, sg.cap) && sg.n - g.w > kSelRound) resident_select = false;
   const int nseg = (int)S;
+  // one pass over the keys where no importance or pooled score is asked for: only the selection is exact there
+  const bool one_scan = p.one_scan && !d_importance && !d_pooled && workspace_bytes >= p.total_bytes + p.one_scan_bytes;
+  OneScan one{};
+  if (one_scan)
+    one = OneScan{(float*)(ws + p.off_part0), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
+                  (uint32_t*)(ws + p.off_lists)};
   auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, int64_t rows) -> slkv_status {
     using TAB = std::decay_t<decltype(tab)>;
     // one grid row per segment where that leaves at most a seventh of the grid empty (a segment with
@@ -2678,11 +3526,15 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     if (chunks > 0) {
       {
         ScopedKernelTimer tm(SLKV_K_SCORE_STATS, st);
-        launch_score(1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp);
+        launch_score(one_scan ? kPassSample : 1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
       }
-      if (max_chunks > 1 || !k_resident) {             // (score_k_resident_kernel completes segments of one chunk in its first pass)
+      if (one_scan) {
         ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
-        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp);
+        launch_score(kPassBoth, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
+        launch_score(kPassChosen, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
+      } else if (max_chunks > 1 || !k_resident) {             // (score_k_resident_kernel completes segments of one chunk in its first pass)
+        ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
+        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
       }
     }
     {
@@ -2691,7 +3543,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
         hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, imp, pooled, d_kept_idx, d_out_offsets, ga);
         if (se != hipSuccess) return fail(SLKV_ERR_HIP, "select launch setup failed: %s", hipGetErrorString(se));
       } else {
-        launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, lists, d_kept_idx, d_out_offsets, ga);
+        launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, one_scan ? one.lists : lists, d_kept_idx, d_out_offsets, ga, one_scan);
       }
     }
     const bool gather_all = !resident_select && blocks > 0;   // the block-wise selection copies no rows itself
@@ -2743,6 +3595,10 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       tab.score_[i] = (int32_t)sg.score_off;
     }
     if (!walk(tab.out_, tab.chunk_, tab.blk_)) return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
+    if (one_scan) {
+      tab.range_[0] = 0;
+      for (int64_t i = 0; i < S; ++i) tab.range_[i + 1] = tab.range_[i] + (int32_t)seg_ranges(g.segs[(size_t)i], g.w, p.CH);
+    }
     return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
   }
   SegTableBig tab;
@@ -2825,7 +3681,7 @@ extern "C" slkv_status slkv_workspace_bytes(const slkv_layer_desc* desc, size_t*
   layer_geometry(desc, g);
   Plan p;
   make_plan(g, p);
-  *bytes = p.total_bytes;
+  *bytes = p.total_bytes + p.one_scan_bytes;
   return SLKV_OK;
 }
 
@@ -2873,7 +3729,7 @@ extern "C" slkv_status slkv_recompress_workspace_bytes(const slkv_ragged_desc* d
   ragged_geometry(desc, g);
   Plan p;
   make_plan(g, p);
-  *bytes = p.total_bytes;
+  *bytes = p.total_bytes + p.one_scan_bytes;
   return SLKV_OK;
 }
 

@@ -17,6 +17,11 @@ template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ uint32_t dpp_move(uint32_t old, uint32_t src) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, CTRL, ROW_MASK, 0xf, false);
 }
+// The same for a float; 0 where there is no source.
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ float dpp_move_f(float src) {
+  return __uint_as_float(dpp_move<CTRL, ROW_MASK>(0u, __float_as_uint(src)));
+}
 constexpr int kDppRowShr = 0x110;       // + n: lane l reads lane l - n of its row
 constexpr int kDppRowBcast15 = 0x142;   // lane 15 of a row goes to every lane of the next row
 constexpr int kDppRowBcast31 = 0x143;   // lane 31 goes to every lane of rows 2 and 3

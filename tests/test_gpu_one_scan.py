@@ -1,0 +1,107 @@
+"""Long histories of 16-bit keys: the call that goes over its keys once keeps what the call keeps that goes over them twice
+(taken wherever importance or pooled scores are asked for, and compared with the oracle elsewhere), bit for bit, also where the
+sample of the keys says little about them."""
+
+import numpy as np
+import pytest
+
+from paper_2508_15806_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape="random", token_major=False, ragged=False):
+    """One call with and one without importance; the outputs of the second (one scan of the keys)."""
+    import torch
+    from paper_2508_15806_amd import api
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(len(lens) * 1000 + Hq * 10 + w)
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    T = int(cu[-1])
+    nseq = len(lens) if not ragged else len(lens) // Hkv
+    rows = T if ragged else Hkv * T
+    q = torch.randn(nseq, Hq, w, d, generator=gen, device="cuda")
+    k = torch.randn(rows, d, generator=gen, device="cuda")
+    if shape == "random":
+        pick = torch.rand(rows, generator=gen, device="cuda") < 0.02
+        to = q.reshape(-1, d)[torch.randint(0, q.numel() // d, (int(pick.sum()),), generator=gen, device="cuda")]
+        k[pick] += 4.0 * to / to.norm(dim=1, keepdim=True)
+    elif shape == "equal keys":
+        k[:] = k[:1]
+    elif shape == "zero queries":
+        q[:] = 0
+    elif shape == "few heavy keys":          # most of a row's weight on a few keys that the sample is unlikely to hold
+        at = torch.randint(0, rows, (64,), generator=gen, device="cuda")
+        to = q.reshape(-1, d)[torch.randint(0, q.numel() // d, (64,), generator=gen, device="cuda")]
+        k[at] = 13.0 * to / to.norm(dim=1, keepdim=True)
+    elif shape == "one overwhelming key":    # its exponential leaves the fp32 range of any estimate that does not know of it
+        q[:] = q[:, :, :1]
+        k[rows // 3] = 30.0 * q[0, 0, 0]
+        k[rows // 3 * 2] = 30.0 * q[-1, -1, 0]
+    k = k.to(dt)
+    v = torch.randn(rows, d, generator=gen, device="cuda").to(dt)
+    q = q.to(dt)
+    strides = None
+    if token_major:
+        k, v = (x.view(Hkv, T, d).transpose(0, 1).contiguous() for x in (k, v))
+        strides = (Hkv * d, d)
+    out = []
+    for debug in (True, False):
+        if ragged:
+            call = api.RaggedCall(dtype, nseq, Hq, Hkv, d, w, cu, caps, kernel, pool, debug_scores=debug)
+            call.run(q, k, v, torch.arange(T, dtype=torch.int32, device="cuda"))
+        else:
+            call = api.LayerCall(dtype, nseq, Hq, Hkv, d, w, cu, caps, kernel, pool, debug_scores=debug, k_strides=strides, v_strides=strides)
+            call.run(q, k, v)
+        torch.cuda.synchronize()
+        bits = torch.int16
+        out.append([call.kept_idx, call.out_offsets, call.k_out.view(bits), call.v_out.view(bits)])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    return call
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,w,lens,kernel,pool", [
+    # 256 rows; one range short of, at and past the ends of chunks, ranges and tiles; lengths at which a segment has one chunk or is not ranked
+    ("bf16", 32, 8, 128, 64, [131072 + 37, 64, 65, 128, 500, 6144 + 64], 7, B.SLKV_POOL_MAX),
+    ("f16", 32, 8, 128, 64, [98304 + 64 + 1, 40001], 13, B.SLKV_POOL_MAX),
+    ("bf16", 32, 8, 128, 63, [140001], 63, B.SLKV_POOL_MAX),                 # 252 rows, the widest window
+    ("bf16", 32, 8, 64, 64, [139999, 3000], 5, B.SLKV_POOL_MAX),
+    ("bf16", 28, 4, 128, 32, [140000, 139000], 1, B.SLKV_POOL_NONE),         # 224 rows
+    ("bf16", 32, 8, 128, 32, [131072, 300], 3, B.SLKV_POOL_MAX),             # 128 rows
+    ("f16", 32, 8, 128, 16, [131072, 70001], 7, B.SLKV_POOL_MAX),            # 64 rows
+    ("bf16", 32, 32, 128, 16, [74999], 7, B.SLKV_POOL_MAX),                  # 16 rows
+    ("bf16", 32, 8, 128, 64, [32768 + 64, 32000, 31999, 30000, 20001, 32001, 17], 7, B.SLKV_POOL_MAX),   # one workgroup per segment selects
+])
+def test_shapes(dtype, Hq, Hkv, d, w, lens, kernel, pool):
+    caps = np.array([w + 45 + 310 * (h % 5) * (1 + 4 * (h == 1)) for h in range(Hkv)], dtype=np.int32)
+    both(dtype, Hq, Hkv, d, w, lens, caps, kernel, pool)
+
+
+@pytest.mark.parametrize("shape", ["equal keys", "zero queries", "few heavy keys", "one overwhelming key"])
+@pytest.mark.parametrize("lens", [[131072 + 5, 2000], [32768, 32768, 32768, 32768, 32000, 31000, 32767]])
+def test_what_a_sample_says_little_about(shape, lens):
+    both("bf16", 32, 8, 128, 64, lens, np.array([200, 3000, 65, 64, 400, 1000, 90, 500], dtype=np.int32), shape=shape)
+
+
+def test_token_major_and_ragged():
+    caps = np.array([150, 4000, 100, 300, 64, 200, 90, 700], dtype=np.int32)
+    both("bf16", 32, 8, 128, 64, [120000, 999], caps, token_major=True)
+    both("f16", 32, 8, 128, 64, [90000, 131072, 70001, 100, 80000, 60, 99999, 100000], caps, ragged=True)
+
+
+def test_a_workspace_without_room_for_it():
+    # a workspace that holds the two passes only, as slkv_compress_layer_static's may: the call is made with them
+    import torch
+    from paper_2508_15806_amd import api
+    caps = np.array([150, 4000, 100, 300, 64, 200, 90, 700], dtype=np.int32)
+    call = both("bf16", 32, 8, 128, 64, [131072], caps)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q, k, v = (torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16) for s in ((1, 32, 64, 128), (8, 131072, 128), (8, 131072, 128)))
+    call.run(q, k, v)
+    want = call.kept_idx.clone()
+    call.workspace = call.workspace[:-256].clone()
+    call.run(q, k, v)
+    assert torch.equal(call.kept_idx, want)
