@@ -245,6 +245,23 @@ __device__ __forceinline__ float fold_sample(const float* __restrict__ part, int
   return ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : INFINITY;
 }
 
+// Largest importance of every group of kGroup keys, counted from the segment's first one, for the selection (see select_resident_kernel): where
+// a segment's groups begin.  Chunks begin at multiples of kGroup.
+constexpr int kGroup = 8;
+__device__ __forceinline__ int64_t group_off(int64_t score_off, int seg) { return (score_off >> 3) + seg; }
+// Key of a score: its bit pattern; anything that is not a non-negative number (cannot come out of finite inputs) ranks as +infinity,
+// so that every phase counts it the same way.
+__device__ __forceinline__ uint32_t score_key(float v) {
+  const uint32_t u = __float_as_uint(v);
+  return u > 0x7f800000u ? 0x7f800000u : u;
+}
+// Largest of v over each 8 neighbouring lanes, in all of them.
+__device__ __forceinline__ uint32_t max_8_lanes(uint32_t v) {
+  v = max(v, dpp_move<0xb1>(v, v));        // quad_perm: the neighbour,
+  v = max(v, dpp_move<0x4e>(v, v));        // the pair next to them,
+  return max(v, dpp_move<0x141>(v, v));    // row_half_mirror: the other four
+}
+
 // The two workgroups that share a CU would otherwise run one after the other: the scheduler
 // favours the older waves, the older workgroup finishes a third earlier and the younger one spends
 // the end of the kernel alone on the CU, one wave per SIMD, with nothing to overlap with.  Waves
@@ -278,7 +295,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
                                                          const void* __restrict__ kmat_v, int64_t k_stride_tok,
                                                          int64_t k_stride_head, int R, int Rpad, int w, int CH,
                                                          float c_log2, float* __restrict__ part,
-                                                         float* __restrict__ imp, int grid2d) {
+                                                         float* __restrict__ imp, int grid2d, uint32_t* __restrict__ gm) {
   constexpr int KS = 4 / RB;               // waves along the keys
   constexpr int TK = kTileKeys;
   constexpr int NSUB = TK / 32 / KS;       // 32-key sub-tiles per wave per tile
@@ -385,6 +402,14 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     s_run[mt] = 0.f;
   }
 
+  // importance of a key (the lanes of a wave have neighbouring ones) and, if asked for, of its group
+  auto put_sum = [&](int key, float v) __attribute__((always_inline)) {
+    if (key < key_end) imp[se.score_off + key] = v;
+    if (gm) {
+      const uint32_t top = max_8_lanes(key < key_end ? score_key(v) : 0u);
+      if (key < key_end && tid % kGroup == 0) gm[group_off(se.score_off, seg) + key / kGroup] = top;
+    }
+  };
   // one tile: registers -> LDS, refill the register slot, barrier, MFMAs + epilogue
   auto do_tile = [&](int t, u32x4 (&pf)[LPT], auto masked_c, auto online_c, auto first_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;   // the tile may reach past key_end
@@ -399,8 +424,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       float v = 0.f;
 #pragma unroll
       for (int r = 0; r < RB; ++r) v += red[buf ^ 1][r][tid];
-      const int key = key_begin + (t - 1) * TK + tid;
-      if (key < key_end) imp[se.score_off + key] = v;
+      put_sum(key_begin + (t - 1) * TK + tid, v);
     }
 #pragma unroll
     for (int sb = 0; sb < NSUB; ++sb) {
@@ -632,8 +656,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       float v = 0.f;
 #pragma unroll
       for (int r = 0; r < RB; ++r) v += red[t & 1][r][tid];
-      const int key = key_begin + t * TK + tid;
-      if (key < key_end) imp[se.score_off + key] = v;
+      put_sum(key_begin + t * TK + tid, v);
     }
   }
   if (PASS == 2) return;
@@ -1136,11 +1159,6 @@ constexpr uint32_t kBinBase = 106u << (23 - kBinShift);   // from 2^-21 to 2^11;
 constexpr int kSelCandidates = 12288;                // scores that select_rank_kernel's list in LDS can hold
 constexpr float kAboveAll = 0x1p120f;                // stands for the importance of a key above tau
 
-__device__ __forceinline__ uint32_t importance_key(float v) {   // as score_key
-  const uint32_t u = __float_as_uint(v);
-  return u > 0x7f800000u ? 0x7f800000u : u;
-}
-
 // Histogram of the pooled approximate importance: a workgroup per block of 4096 positions (x) of a segment (y).
 constexpr int kApproxBlock = 4096;
 __global__ __launch_bounds__(256) void approx_hist_kernel(const SegTable tab, int w, int radius, const float* __restrict__ imp,
@@ -1163,7 +1181,7 @@ __global__ __launch_bounds__(256) void approx_hist_kernel(const SegTable tab, in
   for (int i = tid; i < kHistBins; i += 256) bins[i] = 0;
 #pragma unroll
   for (int e = 0; e <= PER; ++e)
-    if (e * 256 + tid < kApproxBlock + 2 * radius) stage[e * 256 + tid] = importance_key(v[e]);
+    if (e * 256 + tid < kApproxBlock + 2 * radius) stage[e * 256 + tid] = score_key(v[e]);
   __syncthreads();
 #pragma unroll 4
   for (int e = 0; e < PER; ++e) {
@@ -1294,7 +1312,7 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
     const int i = e * NT + tid;
-    const uint32_t u = importance_key(v[e]);
+    const uint32_t u = score_key(v[e]);
     const bool valid = i < cnt, in = valid && u >= lo && u <= hi;
     const unsigned long long mask = __ballot(in);
     if (mask) {
@@ -1344,7 +1362,7 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
         const int li = (t - 1) * TK + tid;
         if (li < nl) {
           if (!blockhist) I[p0 + list[li]] = sum;
-          else if (importance_key(sum) >= lo2) pool(list[li], importance_key(sum));
+          else if (score_key(sum) >= lo2) pool(list[li], score_key(sum));
         }
       }
       if (t == ntiles) return;
@@ -1470,7 +1488,7 @@ template <int DK, int KIND, int PASS, class TAB>
 __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab, const void* __restrict__ qmat, const void* __restrict__ kmat,
                                                        int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w,
                                                        int CH, float c_log2, float* __restrict__ part, float* __restrict__ imp,
-                                                       int grid2d, int rsplit) {
+                                                       int grid2d, int rsplit, uint32_t* __restrict__ gm) {
   using C = ScoreCfg<DK, KIND>;
   constexpr int KK = C::KK, KT = C::KT, RAW = C::RAW, GK = C::GK, RBT = C::RBT, ROWB = C::ROWB, PPR = C::PPR;
   extern __shared__ __attribute__((aligned(16))) unsigned char score_smem[];
@@ -1738,7 +1756,13 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
     if (rsplit > 1) col[tid] = 0.f;                      // (of a wave without keys)
     auto put = [&](int g, float v) __attribute__((always_inline)) {
       const int key = key_begin + g * GK + (KT == 2 ? lane : l32);
-      if (key < key_end && (KT == 2 || half == 0)) dst[key] = rb0 ? dst[key] + v : v;   // (a later row block adds to what this lane wrote)
+      const bool mine = key < key_end && (KT == 2 || half == 0);
+      if (mine && rb0) v += dst[key];                    // (a later row block adds to what this lane wrote)
+      if (mine) dst[key] = v;
+      if (C::F8 && gm && rb0 + RBT * 32 >= R) {          // (the last row block; fp32: not asked for)
+        const uint32_t top = max_8_lanes(key < key_end ? score_key(v) : 0u);
+        if (mine && lane % kGroup == 0) gm[group_off(se.score_off, seg) + key / kGroup] = top;
+      }
     };
     sweep(preloaded, [&](const u32x4 (&raw)[KT][RAW], int g) __attribute__((always_inline)) {
       u32x4 op[KT][KK];
@@ -1826,13 +1850,6 @@ constexpr int kSelTrackMax = 512;         // up to this many wanted keys the fir
 constexpr int kDigitShift = 20;           // first-level digit = key >> 20: sign (0), 8 exponent and 3 mantissa bits
 constexpr uint32_t kKeyNone = 0xffffffffu;
 static_assert((0x7f800000u >> kDigitShift) < (uint32_t)kHistBins, "every key has a first-level digit inside the histogram");
-
-// Key of a pooled score: its bit pattern; anything that is not a non-negative number (cannot
-// come out of finite inputs) ranks as +infinity, so that both phases count it the same way.
-__device__ __forceinline__ uint32_t score_key(float v) {
-  const uint32_t u = __float_as_uint(v);
-  return u > 0x7f800000u ? 0x7f800000u : u;
-}
 
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -2325,7 +2342,7 @@ __device__ __forceinline__ int pad_idx(int i) { return i + i / EPT; }
 template <int RADIUS, int EPT_, class TAB>   // pooling radius known at compile time (0..3), or -1: any radius, window read from LDS;
                                              // EPT_: positions per thread (the history is at most 1024 * EPT_ positions)
 __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB tab, int w, int pool_kernel, int pool_mode,
-                                                                      int write_pooled, const float* __restrict__ imp,
+                                                                      int write_pooled, const float* __restrict__ imp, const uint32_t* __restrict__ gm,
                                                                       float* __restrict__ pooled, int32_t* __restrict__ kept_idx,
                                                                       int64_t* __restrict__ d_out_offsets, const GatherArgs ga) {
   constexpr int NT = kSelThreads, EPT = EPT_, ROUND = NT * EPT_;   // the history is at most ROUND positions
@@ -2380,10 +2397,209 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
   const float* I = imp + sg.score_off;
   float* P = pooled + sg.score_off;
   const int radius = RADIUS >= 0 ? RADIUS : pool_kernel / 2;
+  auto fetch_window = [&]() __attribute__((always_inline)) {
+    const int64_t tok = (int64_t)sg.tok_begin + m + win_row, h = sg.head;
+    win_k = *reinterpret_cast<const u32x4*>(ga.k + (h * ga.k_stride_head + tok * ga.k_stride_tok) * ga.elt_bytes + win_c * 16);
+    win_v = *reinterpret_cast<const u32x4*>(ga.v + (h * ga.v_stride_head + tok * ga.v_stride_tok) * ga.elt_bytes + win_c * 16);
+  };
+
+  // Window maxima (or no pooling), with the largest score of every group of 8 positions at hand: the k-th largest pooled score is found, and the kept
+  // positions written, from the few positions whose own score reaches a bound below it.
+  //   A score reaches the windows of min(radius + 1, 8) positions at least, of which no two groups' largest scores share more than
+  //   `slack` in all, so `need` groups whose largest score is >= L put the k-th largest pooled score at or above L.
+  //   Of the groups with a score >= L the scores >= L are listed in position order (others lie below every kept score).  The largest score
+  //   of a window (of equal ones the first) owns its position; the positions that a score owns are neighbours: right of the next score
+  //   before it that is at least as large, by more than the radius, left of the next one after it that is larger.
+  //   The k-th largest pooled score is then that of the listed scores, each counted as often as it owns a position.
+  // Returns false, in all threads, where the lists would not hold them; the positions are then ranked one by one below.
+  // 8 segments of 32704 positions, k from 43 to 1770: 15.3 -> 9 us (the call 68.2 -> 61.9); the passes over 32 positions a thread are what it saves.
+  auto select_by_groups = [&]() -> bool {
+    if (!gm) return false;
+    constexpr int kMostGroups = NT, kMostScores = 4 * NT;
+    const int cover = min(radius + 1, kGroup), slack = min(radius, kGroup - 1), need = (kk + slack + cover - 1) / cover;
+    const int ngroups = (m + kGroup - 1) / kGroup;
+    if (need > min(ngroups, kMostGroups) || ngroups > 4 * NT) return false;
+    uint32_t* const base = reinterpret_cast<uint32_t*>(stage);
+    uint32_t* const glist = base;                              // groups, in order
+    int32_t* const spos = (int32_t*)(base + kMostGroups);      // listed scores: position,
+    uint32_t* const skey = base + kMostGroups + kMostScores;   // key
+    uint32_t* const dhist = base + kMostGroups + 2 * kMostScores;   // of the positions owned, per digit; and the
+    uint32_t* const dmax = dhist + kHistBins;                  // largest and
+    uint32_t* const dmin = dmax + kHistBins;                   // smallest key of every digit
+    static_assert(kMostGroups + 2 * kMostScores + 3 * kHistBins <= (int)(kResLdsBytes / sizeof(uint32_t)), "the lists fit the staging area");
+    constexpr int kShift = 17;                                 // 64 bins per octave from 2^-21 on
+    constexpr uint32_t kFirst = 106u << (23 - kShift);
+    auto bin = [&](uint32_t u) { return (u >> kShift) <= kFirst ? 0u : min((u >> kShift) - kFirst, (uint32_t)kHistBins - 1u); };
+    uint32_t gk[4];
+    const uint32_t* const G = gm + group_off(sg.score_off, seg);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gk[c] = G[min(4 * tid + c, ngroups - 1)];
+    for (int i = tid; i < kHistBins; i += NT) {
+      hist[i] = 0;
+      dhist[i] = 0;
+      dmax[i] = 0;
+      dmin[i] = 0xffffffffu;
+    }
+    if (tid == 0) res[2] = 0;
+    __syncthreads();
+    uint32_t top = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (4 * tid + c >= ngroups) gk[c] = 0;
+      else atomicAdd(&hist[bin(gk[c])], 1u);
+      top = max(top, gk[c]);
+    }
+    top = wave_reduce_to_last(top, [](uint32_t a, uint32_t b) { return max(a, b); });
+    if (lane == 63) atomicMax(&res[2], top);
+    __syncthreads();
+    select_bin<NT>(hist, (uint32_t)need, sh_scan, res);
+    const uint32_t b = res[0], kmax = res[2];
+    if (b == 0u) return false;
+    const uint32_t L = (b + kFirst) << kShift;
+    // the groups that reach L
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cnt += gk[c] >= L ? 1u : 0u;
+    uint32_t at = block_incl_scan<NT>(cnt, sh_scan);
+    if (tid == NT - 1) res[3] = at;
+    at -= cnt;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (gk[c] >= L) {
+        if (at < (uint32_t)kMostGroups) glist[at] = (uint32_t)(4 * tid + c);
+        ++at;
+      }
+    __syncthreads();
+    const uint32_t ng = res[3];
+    if (ng > (uint32_t)kMostGroups) return false;
+    // their scores that do
+    uint32_t u[kGroup];
+    cnt = 0;
+    int p0 = 0;
+    if (tid < (int)ng) {
+      p0 = (int)glist[tid] * kGroup;
+      float v[kGroup];
+#pragma unroll
+      for (int e = 0; e < kGroup; ++e) v[e] = I[min(p0 + e, m - 1)];
+#pragma unroll
+      for (int e = 0; e < kGroup; ++e) {
+        u[e] = p0 + e < m ? score_key(v[e]) : 0u;
+        cnt += u[e] >= L ? 1u : 0u;
+      }
+    }
+    fetch_window();                                            // (behind the last loads that somebody waits for before the end)
+    at = block_incl_scan<NT>(cnt, sh_scan);
+    if (tid == NT - 1) res[3] = at;                            // (read by all before the barriers of the scan above)
+    at -= cnt;
+    if (tid < (int)ng) {
+#pragma unroll
+      for (int e = 0; e < kGroup; ++e)
+        if (u[e] >= L) {
+          if (at < (uint32_t)kMostScores) {
+            spos[at] = p0 + e;
+            skey[at] = u[e];
+          }
+          ++at;
+        }
+    }
+    __syncthreads();
+    const int ns = (int)res[3];
+    if (ns > kMostScores) return false;
+    // what each score owns: `per` consecutive ones per thread
+    const int per = (ns + NT - 1) / NT;
+    int from[4], own[4];
+    uint32_t sk[4];
+    const uint32_t span0 = kmax - L;
+    auto shift_of = [](uint32_t span) {
+      const int nbits = span ? 32 - __clz(span) : 0;
+      return nbits > 11 ? nbits - 11 : 0;
+    };
+    int shift = shift_of(span0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int i = tid * per + c;
+      own[c] = 0;
+      sk[c] = 0;
+      if (c < per && i < ns) {
+        const int p = spos[i];
+        const uint32_t k0 = skey[i];
+        int lo = max(p - radius, 0), hi = min(p + radius, m - 1);
+        for (int q = i - 1; q >= 0 && spos[q] >= p - 2 * radius; --q)
+          if (skey[q] >= k0) {
+            lo = max(lo, spos[q] + radius + 1);
+            break;
+          }
+        for (int q = i + 1; q < ns && spos[q] <= p + 2 * radius; ++q)
+          if (skey[q] > k0) {
+            hi = min(hi, spos[q] - radius - 1);
+            break;
+          }
+        from[c] = lo;
+        own[c] = max(hi - lo + 1, 0);
+        sk[c] = k0;
+        if (own[c]) {
+          const uint32_t d = (k0 - L) >> shift;
+          atomicAdd(&dhist[d], (uint32_t)own[c]);
+          atomicMax(&dmax[d], k0);
+          atomicMin(&dmin[d], k0);
+        }
+      }
+    }
+    // the k-th largest, 11 bits of the range at a time; as a rule the first digit holds one score
+    uint32_t lo = L, hi = kmax, k = (uint32_t)kk;
+    for (;;) {
+      __syncthreads();
+      select_bin<NT>(dhist, k, sh_scan, res);
+      const uint32_t d = res[0], big = dmax[d], small = dmin[d];
+      k = res[1];
+      lo += d << shift;
+      hi = min(hi, lo + ((1u << shift) - 1u));
+      if (big == small || shift == 0) {
+        lo = big;
+        break;
+      }
+      shift = shift_of(hi - lo);
+      __syncthreads();                                         // every thread has read the digit's keys
+      for (int i = tid; i < kHistBins; i += NT) {
+        dhist[i] = 0;
+        dmax[i] = 0;
+        dmin[i] = 0xffffffffu;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (own[c] && sk[c] >= lo && sk[c] <= hi) {
+          const uint32_t dd = (sk[c] - lo) >> shift;
+          atomicAdd(&dhist[dd], (uint32_t)own[c]);
+          atomicMax(&dmax[dd], sk[c]);
+          atomicMin(&dmin[dd], sk[c]);
+        }
+    }
+    // kept positions in order: slot = (#greater before) + min(#equal before, wanted)
+    uint32_t packed = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) packed += own[c] && sk[c] >= lo ? (uint32_t)own[c] << (sk[c] > lo ? 0 : 16) : 0u;
+    const uint32_t excl = block_incl_scan<NT, false>(packed, sh_scan) - packed;
+    uint32_t greater = excl & 0xffffu, equal = excl >> 16;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (own[c] && sk[c] >= lo) {
+        int take = own[c];
+        if (sk[c] == lo) take = equal < k ? min(take, (int)(k - equal)) : 0;
+        const int slot = (int)(greater + min(equal, k));
+        for (int e = 0; e < take; ++e) emit(slot + e, from[c] + e);
+        if (sk[c] > lo) greater += (uint32_t)own[c];
+        else equal += (uint32_t)own[c];
+      }
+    return true;
+  };
   const bool is_max = pool_mode != SLKV_POOL_AVG;
   const float fill = 0.f;                          // scores are >= 0, so zero padding leaves window maxima as they are
   const float inv_p = 1.f / (float)pool_kernel;
 
+  bool selected = false;
+  if constexpr (EPT == kSelEPT) selected = select_by_groups();
+  if (!selected) {
   // Keys: bit patterns of the pooled scores (>= 0, so monotone as unsigned integers); positions
   // past the end of the history get a key above every score.
   uint32_t key[EPT];
@@ -2410,12 +2626,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
       stage[pad_idx<EPT>(s)] = (j >= 0 && j < m) ? ld[EPT] : fill;
     }
     __syncthreads();
-    // (behind the barrier: every score has arrived, and nothing waits for these loads before the end)
-    {
-      const int64_t tok = (int64_t)sg.tok_begin + m + win_row, h = sg.head;
-      win_k = *reinterpret_cast<const u32x4*>(ga.k + (h * ga.k_stride_head + tok * ga.k_stride_tok) * ga.elt_bytes + win_c * 16);
-      win_v = *reinterpret_cast<const u32x4*>(ga.v + (h * ga.v_stride_head + tok * ga.v_stride_tok) * ga.elt_bytes + win_c * 16);
-    }
+    fetch_window();                                // (behind the barrier: every score has arrived, and nothing waits for these loads before the end)
     if (RADIUS >= 0) {
       constexpr int RR = RADIUS >= 0 ? RADIUS : 0;
       float v[EPT + 2 * RR];
@@ -2786,6 +2997,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
       sel &= sel - 1u;
     }
   }
+  }  // by the scores of all positions
   for (int j = tid; j < w; j += NT) emit(kk + j, m + j);
   SLKV_STAMP(128 + seg, 6);
   }  // ranked
@@ -3204,13 +3416,13 @@ constexpr int kPassSample = 0, kPassBoth = 3, kPassChosen = 4;
 template <int DK, int MT, int RB, int KIND, class TAB>
 static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
                               const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
-                              uint32_t* blockhist) {
+                              uint32_t* blockhist, uint32_t* gm) {
   // segments with like chunk counts: one grid row per segment (see the kernel's first lines)
   const bool two = grid.rows > 0;
   const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
   auto scan = [&](auto pass_c, dim3 grid_c, float* part_c) {
     SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, decltype(pass_c)::value, KIND, TAB>), grid_c, dim3(256), 0, st, tab, (const uint16_t*)q, k,
-                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part_c, imp, two ? 1 : 0);
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part_c, imp, two ? 1 : 0, gm);
   };
   if (pass == 1) scan(std::integral_constant<int, 1>{}, gr, part);
   if (pass == 2) scan(std::integral_constant<int, 2>{}, gr, part);
@@ -3238,31 +3450,31 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
 template <int DK, int KIND, class TAB>
 static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
                            const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
-                              uint32_t* blockhist) {
+                              uint32_t* blockhist, uint32_t* gm) {
   if constexpr (KIND <= 1) {
-    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
-    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
-    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
-    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
+    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
+    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
+    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
+    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
   } else {
     const bool two = grid.rows > 0;
     const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
     const size_t lds = score_lds_bytes<DK, KIND>(std::min((p.R + 31) / 32, ScoreCfg<DK, KIND>::RBT), p.waves);
     if (pass == 1)
       SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 1, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit, gm);
     else
       SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 2, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit, gm);
   }
 }
 
 template <class TAB>
 static void launch_score(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
                          const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
-                              uint32_t* blockhist) {
+                              uint32_t* blockhist, uint32_t* gm) {
   with_score_kind(g.d, g.dtype, [&](auto dk, auto kind) {
-    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist);
+    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
   });
 }
 
@@ -3376,44 +3588,44 @@ static hipError_t ensure_device_init() {
 }
 
 template <int RADIUS, int EPT, class TAB>
-static hipError_t launch_select_resident_e(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled,
+static hipError_t launch_select_resident_e(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                            const GatherArgs& ga) {
   const hipError_t e = ensure_device_init();
   if (e != hipSuccess) return e;
   const int pool_kernel = g.pool == SLKV_POOL_NONE ? 1 : g.pool_kernel;
   SLKV_LAUNCH((select_resident_kernel<RADIUS, EPT, TAB>), dim3(ns), dim3(kSelThreads), kResLdsBytes, st, tab, g.w,
-                     pool_kernel, g.pool, (int)write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
+                     pool_kernel, g.pool, (int)write_pooled, imp, gm, pooled, kept_idx, d_out_offsets, ga);
   return hipSuccess;
 }
 
 // Positions per thread: the fewest of 2, 8, 32 whose round holds the longest ranked history (every
 // wave runs through all of a thread's positions, whether or not the history reaches them).
 template <int RADIUS, class TAB>
-static hipError_t launch_select_resident_r(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled,
+static hipError_t launch_select_resident_r(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                            const GatherArgs& ga) {
   int64_t longest = 0;
   for (const Seg& sg : g.segs)
     if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
   if (longest <= kSelThreads * kSelEPTSmall)
-    return launch_select_resident_e<RADIUS, kSelEPTSmall>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
+    return launch_select_resident_e<RADIUS, kSelEPTSmall>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
   if (longest <= kSelThreads * kSelEPTMid)
-    return launch_select_resident_e<RADIUS, kSelEPTMid>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
-  return launch_select_resident_e<RADIUS, kSelEPT>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
+    return launch_select_resident_e<RADIUS, kSelEPTMid>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+  return launch_select_resident_e<RADIUS, kSelEPT>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
 }
 
 template <class TAB>
-static hipError_t launch_select_resident(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled,
+static hipError_t launch_select_resident(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                          const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                          const GatherArgs& ga) {
   const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
   switch (radius) {
-    case 0: return launch_select_resident_r<0>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
-    case 1: return launch_select_resident_r<1>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
-    case 2: return launch_select_resident_r<2>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
-    case 3: return launch_select_resident_r<3>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
-    default: return launch_select_resident_r<-1>(ns, st, tab, g, write_pooled, imp, pooled, kept_idx, d_out_offsets, ga);
+    case 0: return launch_select_resident_r<0>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    case 1: return launch_select_resident_r<1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    case 2: return launch_select_resident_r<2>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    case 3: return launch_select_resident_r<3>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    default: return launch_select_resident_r<-1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
   }
 }
 
@@ -3506,12 +3718,20 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   for (const Seg& sg : g.segs)
     if (seg_ranked(sg.n, g.w, sg.cap) && sg.n - g.w > kSelRound) resident_select = false;
   const int nseg = (int)S;
+  // The selection starts from the groups' largest scores where a thread would have 32 positions to go through otherwise (with 8 or 2 the shorter
+  // chain of phases wins: 8 x 8 K keys 25.7 us either way, 8 x 900 keys 22.4 us without, 24.8 with), and not for
+  // fp32, whose scoring kernel got slower by it on short calls (4 x 1 K 19.7 -> 20.1).  They lie in the pooled array, which nobody writes then.
+  int64_t longest = 0;
+  for (const Seg& sg : g.segs)
+    if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
+  const bool groups = resident_select && !d_pooled && g.pool != SLKV_POOL_AVG && g.dtype != SLKV_F32 && longest > kSelThreads * kSelEPTMid;
   // one pass over the keys where no importance or pooled score is asked for: only the selection is exact there
   const bool one_scan = p.one_scan && !d_importance && !d_pooled && workspace_bytes >= p.total_bytes + p.one_scan_bytes;
   OneScan one{};
   if (one_scan)
     one = OneScan{(float*)(ws + p.off_part0), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
                   (uint32_t*)(ws + p.off_lists)};
+  uint32_t* const gm = groups && !one_scan ? (uint32_t*)pooled : nullptr;
   auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, int64_t rows) -> slkv_status {
     using TAB = std::decay_t<decltype(tab)>;
     // one grid row per segment where that leaves at most a seventh of the grid empty (a segment with
@@ -3526,21 +3746,21 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     if (chunks > 0) {
       {
         ScopedKernelTimer tm(SLKV_K_SCORE_STATS, st);
-        launch_score(one_scan ? kPassSample : 1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
+        launch_score(one_scan ? kPassSample : 1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
       }
       if (one_scan) {
         ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
-        launch_score(kPassBoth, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
-        launch_score(kPassChosen, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
+        launch_score(kPassBoth, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
+        launch_score(kPassChosen, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
       } else if (max_chunks > 1 || !k_resident) {             // (score_k_resident_kernel completes segments of one chunk in its first pass)
         ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
-        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist);
+        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
       }
     }
     {
       ScopedKernelTimer tm(SLKV_K_SELECT, st);
       if (resident_select) {
-        hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, imp, pooled, d_kept_idx, d_out_offsets, ga);
+        hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, gm, imp, pooled, d_kept_idx, d_out_offsets, ga);
         if (se != hipSuccess) return fail(SLKV_ERR_HIP, "select launch setup failed: %s", hipGetErrorString(se));
       } else {
         launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, one_scan ? one.lists : lists, d_kept_idx, d_out_offsets, ga, one_scan);

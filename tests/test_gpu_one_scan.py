@@ -16,7 +16,8 @@ def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape
     from paper_2508_15806_amd import api
     gen = torch.Generator(device="cuda")
     gen.manual_seed(len(lens) * 1000 + Hq * 10 + w)
-    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    qt = {"f16": torch.float16, "f32": torch.float32}.get(dtype, torch.bfloat16)
+    cache = lambda x: x.to(torch.float8_e4m3fn).view(torch.uint8) if dtype == "bf16_kv8" else x.to(qt)
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     T = int(cu[-1])
     nseq = len(lens) if not ragged else len(lens) // Hkv
@@ -39,9 +40,9 @@ def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape
         q[:] = q[:, :, :1]
         k[rows // 3] = 30.0 * q[0, 0, 0]
         k[rows // 3 * 2] = 30.0 * q[-1, -1, 0]
-    k = k.to(dt)
-    v = torch.randn(rows, d, generator=gen, device="cuda").to(dt)
-    q = q.to(dt)
+    k = cache(k)
+    v = cache(torch.randn(rows, d, generator=gen, device="cuda"))
+    q = q.to(qt)
     strides = None
     if token_major:
         k, v = (x.view(Hkv, T, d).transpose(0, 1).contiguous() for x in (k, v))
@@ -55,7 +56,7 @@ def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape
             call = api.LayerCall(dtype, nseq, Hq, Hkv, d, w, cu, caps, kernel, pool, debug_scores=debug, k_strides=strides, v_strides=strides)
             call.run(q, k, v)
         torch.cuda.synchronize()
-        bits = torch.int16
+        bits = {4: torch.int32, 2: torch.int16, 1: torch.uint8}[k.element_size()]
         out.append([call.kept_idx, call.out_offsets, call.k_out.view(bits), call.v_out.view(bits)])
     for a, b in zip(*out):
         assert torch.equal(a, b)
