@@ -3724,7 +3724,9 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   int64_t longest = 0;
   for (const Seg& sg : g.segs)
     if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
-  const bool groups = resident_select && !d_pooled && g.pool != SLKV_POOL_AVG && g.dtype != SLKV_F32 && longest > kSelThreads * kSelEPTMid;
+  // (a group's place counts the segments before it, see group_off: with thousands of empty ones the array may be too short)
+  const bool groups = resident_select && !d_pooled && g.pool != SLKV_POOL_AVG && g.dtype != SLKV_F32 && longest > kSelThreads * kSelEPTMid &&
+                      g.score_elems / kGroup + S + 1 <= g.score_elems;
   // one pass over the keys where no importance or pooled score is asked for: only the selection is exact there
   const bool one_scan = p.one_scan && !d_importance && !d_pooled && workspace_bytes >= p.total_bytes + p.one_scan_bytes;
   OneScan one{};

@@ -42,3 +42,9 @@ def test_keys_of_32_and_8_bits(dtype, Hq, Hkv, d, w, lens):
 
 def test_decode_cache():
     both("bf16", 32, 8, 128, 32, [122, 929, 124, 134, 128, 10000, 140, 132] * 9, np.array([58, 865, 60, 70, 64, 60, 76, 68], dtype=np.int32), ragged=True)
+
+
+def test_more_empty_segments_than_scores():
+    # the groups of the last segment would lie behind the end of their array: such a call ranks every position
+    both("bf16", 2, 1, 64, 16, [0] * 9999 + [9000, 0], np.array([100], dtype=np.int32))
+    both("bf16", 2, 1, 64, 16, [0] * 6000 + [9000, 0], np.array([100], dtype=np.int32))     # (these fit)
