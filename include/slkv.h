@@ -223,7 +223,8 @@ slkv_status slkv_compacted_sizes(const slkv_layer_desc* desc, int64_t* h_out_off
  * them zero, so the same
  * workspace serves any number of later calls, of any descriptor it is large enough for, also
  * from a replayed HIP graph.  Its other contents are scratch.  Two calls that may overlap in
- * time need a workspace each. */
+ * time need a workspace each.  For calls with long histories the size includes room to go over the keys once instead of
+ * twice; they accept, with the same results, a workspace that lacks that room. */
 #define SLKV_WORKSPACE_HEADER_BYTES 65536
 slkv_status slkv_workspace_bytes(const slkv_layer_desc* desc, size_t* bytes);
 
@@ -251,8 +252,8 @@ slkv_status slkv_compress_layer(const slkv_layer_desc* desc, const void* d_qwin,
  * arguments, results and errors as slkv_compress_layer without the workspace: the scratch
  * (chunk statistics, log-sum-exp, importance, pooled scores, block histograms, segment table) lives in a buffer of
  * SLKV_STATIC_SCRATCH_BYTES that is part of the library's code object, one copy per GPU, held
- * until the process ends.  A call whose slkv_workspace_bytes() exceeds that size returns
- * SLKV_ERR_WORKSPACE and enqueues nothing.  The call allocates nothing (no hipMalloc / hipFree).
+ * until the process ends.  A call that needs more (slkv_workspace_bytes(), less the room it can
+ * do without) returns SLKV_ERR_WORKSPACE and enqueues nothing.  The call allocates nothing (no hipMalloc / hipFree).
  * All calls on one GPU share the buffer: calls that may overlap on one GPU (different streams
  * without ordering between them, or several host threads) race and must be serialised by the
  * caller.  The buffer's address is looked up on the first call on each device; make that call
