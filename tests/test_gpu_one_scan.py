@@ -10,6 +10,20 @@ from paper_2508_15806_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
+def takes_one_pass(dtype, Hq, Hkv, d, w, lens, caps, kernel, pool, ragged):
+    """Whether such a call goes over its keys once: its workspace is then larger than that of the call with average pooling, which never does."""
+    from paper_2508_15806_amd import api
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    dt, T = api.DTYPES[dtype][0], int(cu[-1])
+
+    def workspace(p):
+        if ragged:
+            return B.slkv_recompress_workspace_bytes(B.Ragged(dt, len(lens) // Hkv, Hq, Hkv, d, w, cu, caps, kernel, p))
+        return B.slkv_workspace_bytes(B.Layer(dt, len(lens), Hq, Hkv, d, w, cu, caps, (d, T * d), (d, T * d), kernel, p))
+
+    return workspace(pool) > workspace(B.SLKV_POOL_AVG)
+
+
 def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape="random", token_major=False, ragged=False):
     """One call with and one without importance; the outputs of the second (one scan of the keys)."""
     import torch
@@ -63,6 +77,11 @@ def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape
     return call
 
 
+def one_pass(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, ragged=False, **inputs):
+    assert takes_one_pass(dtype, Hq, Hkv, d, w, lens, caps, kernel, pool, ragged)
+    return both(dtype, Hq, Hkv, d, w, lens, caps, kernel, pool, ragged=ragged, **inputs)
+
+
 @pytest.mark.parametrize("dtype,Hq,Hkv,d,w,lens,kernel,pool", [
     # 256 rows; one range short of, at and past the ends of chunks, ranges and tiles; lengths at which a segment has one chunk or is not ranked
     ("bf16", 32, 8, 128, 64, [131072 + 37, 64, 65, 128, 500, 6144 + 64], 7, B.SLKV_POOL_MAX),
@@ -77,19 +96,20 @@ def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape
 ])
 def test_shapes(dtype, Hq, Hkv, d, w, lens, kernel, pool):
     caps = np.array([w + 45 + 310 * (h % 5) * (1 + 4 * (h == 1)) for h in range(Hkv)], dtype=np.int32)
-    both(dtype, Hq, Hkv, d, w, lens, caps, kernel, pool)
+    one_pass(dtype, Hq, Hkv, d, w, lens, caps, kernel, pool)
 
 
 @pytest.mark.parametrize("shape", ["equal keys", "zero queries", "few heavy keys", "one overwhelming key"])
 @pytest.mark.parametrize("lens", [[131072 + 5, 2000], [32768, 32768, 32768, 32768, 32000, 31000, 32767]])
 def test_what_a_sample_says_little_about(shape, lens):
-    both("bf16", 32, 8, 128, 64, lens, np.array([200, 3000, 65, 64, 400, 1000, 90, 500], dtype=np.int32), shape=shape)
+    one_pass("bf16", 32, 8, 128, 64, lens, np.array([200, 3000, 65, 64, 400, 1000, 90, 500], dtype=np.int32), shape=shape)
 
 
 def test_token_major_and_ragged():
     caps = np.array([150, 4000, 100, 300, 64, 200, 90, 700], dtype=np.int32)
-    both("bf16", 32, 8, 128, 64, [120000, 999], caps, token_major=True)
-    both("f16", 32, 8, 128, 64, [90000, 131072, 70001, 100, 80000, 60, 99999, 100000], caps, ragged=True)
+    one_pass("bf16", 32, 8, 128, 64, [120000, 999], caps, token_major=True)
+    lens = [90000, 131072, 70001, 100, 80000, 60, 99999, 100000, 131000, 120000, 65, 70000, 500, 33000, 90000, 140000]
+    one_pass("f16", 32, 8, 128, 64, lens, caps, ragged=True)
 
 
 def test_a_workspace_without_room_for_it():
@@ -97,7 +117,7 @@ def test_a_workspace_without_room_for_it():
     import torch
     from paper_2508_15806_amd import api
     caps = np.array([150, 4000, 100, 300, 64, 200, 90, 700], dtype=np.int32)
-    call = both("bf16", 32, 8, 128, 64, [131072], caps)
+    call = one_pass("bf16", 32, 8, 128, 64, [131072], caps)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(5)
     q, k, v = (torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16) for s in ((1, 32, 64, 128), (8, 131072, 128), (8, 131072, 128)))
