@@ -45,20 +45,25 @@ struct SegShape {
   int score_off;   // offset of the segment in the importance / pooled arrays
 };
 
-// A history that keeps more than a fortieth of its positions: its threshold lies near the bulk of the scores, otherwise in their
-// thin upper tail (see OneScan).
-__device__ __host__ __forceinline__ bool many_kept(int m, int kk) { return kk >= m / 40; }
-// Positions per workgroup of the kernels that go over a sample of the keys or over the scores before the selection, CH: keys per chunk of the scoring pass.
-constexpr int kRangeMost = 6144, kRangeDense = 2560;
-__device__ __host__ __forceinline__ int range_len(int m, int kk, int CH) {
-  const int len = CH < 4096 ? CH : kRangeMost;
-  return many_kept(m, kk) && len > kRangeDense ? kRangeDense : len;
+// The sample that the one pass over a long history starts from (see OneScan): kSampleGroup neighbours out of every kSampleGroup * sample_step keys, four
+// keys per position kept, 2048 to 8192 in all: the more are kept, the nearer the threshold lies to the bulk of the scores, where an uncertain one
+// takes in more keys.  32 segments of 20 K to 128 K keys, us of the sample and of the chosen keys: 170 kept 24 + 22 (8192 keys whatever is kept: 40 + 22);
+// 1500 kept 25 + 39 (2048 keys: 20 + 53; 8192: 39 + 39); 3300 kept 31 + 42 (2048: 19 + 89).
+// A workgroup of the kernels that go over the sample, and over the scores before the selection, takes a range of positions with `sampled` such keys (plan_ranges).
+constexpr int kSampleGroup = 8, kRangeMost = 6144;
+__device__ __host__ __forceinline__ int sample_step(int m, int kk) {
+  const int keys = 4 * kk < 2048 ? 2048 : 4 * kk > 8192 ? 8192 : 4 * kk;
+  return m / keys > 4 ? m / keys : 4;
+}
+__device__ __host__ __forceinline__ int range_len(int m, int kk, int sampled) {
+  const int len = sampled * sample_step(m, kk);
+  return len < 512 ? 512 : len > kRangeMost ? kRangeMost : len;
 }
 
 // Up to kMaxSegPerLaunch segments: everything per segment, in a kernel argument, so that one round of loads from
 // it (cold at every launch) answers a workgroup that knows its segment.
 struct SegTable {
-  int32_t nseg;
+  int32_t nseg, sampled;                  // (sampled: of range_len)
   int32_t tok_[kMaxSegPerLaunch], n_[kMaxSegPerLaunch], head_[kMaxSegPerLaunch], kk_[kMaxSegPerLaunch], score_[kMaxSegPerLaunch];
   int32_t out_[kMaxSegPerLaunch + 1];     // first output row of the segment
   int32_t chunk_[kMaxSegPerLaunch + 1];   // prefix of key-chunk counts (0 chunks when not ranked)
@@ -209,41 +214,47 @@ __device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c
   return ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : INFINITY;
 }
 
-// As fold_rows, of the sample's ranges: a thread per row (tid < rows <= nt).  Of the ranges between the first and the last, which hold the keys
-// that are sampled one by one, the one with the largest sum is left out and stands at the mean of the others: a single
-// sampled key far above the rest (it stands for a hundred) would spoil the row's estimate, and one such row widens the bounds of all keys.
-__device__ __forceinline__ float fold_sample(const float* __restrict__ part, int c0, int c1, int Rpad, int rows) {
+// As fold_rows, of the sample: a thread per row (tid < rows <= nt).  dense[0], [1] of a row: the keys at either end of the history, which are all in the
+// sample; part: the sampled keys of the ranges.  No range counts more than twice their geometric mean: a single sampled key far above the rest (it
+// stands for up to 64) would make the row's estimate several times too large, and one such row lowers the bound of all keys.
+__device__ __forceinline__ float fold_sample(const float* __restrict__ part, const float* __restrict__ dense, int c0, int c1, int Rpad, int rows) {
   const int row = threadIdx.x;
-  float mm = -INFINITY, ss = 0.f, top = -INFINITY;
+  float ss = 0.f, mu = 0.f;
   if (row < rows && row < Rpad) {
     constexpr int NB = 32;
-    for (int c = c0; c < c1; c += NB) {
-      float v[NB];
+    float v[NB];
+    const float d0 = dense[row], d1 = dense[Rpad + row];
+    auto load = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < NB; ++u) v[u] = part[(int64_t)min(c + u, c1 - 1) * Rpad + row];
-      float bm = mm;
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+        if (c + u >= c1) v[u] = -INFINITY;
+    };
+    float sum = 0.f, used = 0.f;
+    for (int c = c0; c < c1; c += NB) {
+      load(c);
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
-        if (c + u >= c1) v[u] = -INFINITY;
-        bm = fmaxf(bm, v[u]);
-        if (c + u > c0 && c + u < c1 - 1) top = fmaxf(top, v[u]);
+        sum += v[u] == -INFINITY ? 0.f : v[u];
+        used += v[u] == -INFINITY ? 0.f : 1.f;
       }
-      const float mu = bm == -INFINITY ? 0.f : bm;
-      ss *= fast_exp2(mm - mu);
-#pragma unroll
-      for (int u = 0; u < NB; ++u) ss += fast_exp2(v[u] - mu);
-      mm = bm;
     }
-    const int mid = c1 - c0 - 2;
-    if (mid >= 4) {
-      // sum of the first and last ranges, the others but the largest
-      const float ends = fast_exp2(part[(int64_t)c0 * Rpad + row] - mm) + fast_exp2(part[(int64_t)(c1 - 1) * Rpad + row] - mm);
-      const float rest = fmaxf(ss - ends - fast_exp2(top - mm), 0.f);
-      ss = ends + rest * ((float)mid / (float)(mid - 1));
+    const float cap = used > 0.f ? sum / used + 1.f : -INFINITY;
+    const float mm = fmaxf(cap, fmaxf(d0, d1));
+    mu = mm == -INFINITY ? 0.f : mm;
+    ss = fast_exp2(d0 - mu) + fast_exp2(d1 - mu);
+    for (int c = c0; c < c1; c += NB) {
+      if (c1 - c0 > NB) load(c);
+#pragma unroll
+      for (int u = 0; u < NB; ++u) ss += v[u] == v[u] ? fast_exp2(fminf(v[u], cap) - mu) : v[u];
     }
   }
-  return ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : INFINITY;
+  return ss > 0.f ? mu + __builtin_amdgcn_logf(ss) : INFINITY;
 }
+
+// Per segment: the words of OneScanBounds; smallest, largest and mean rho.
+constexpr int kBoundWords = 12, kBoundProbe = 4, kBoundWide = 5, kBoundRho = 6;
 
 // Largest importance of every group of kGroup keys, counted from the segment's first one, for the selection (see select_resident_kernel): where
 // a segment's groups begin.  Chunks begin at multiples of kGroup.
@@ -710,9 +721,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 //   score_sample_kernel     log-sum-exp of the rows over a sample of the keys: an estimate lse' of theirs
 //   score_both_kernel       over all keys e = e^(x - lse'[row]), added up along the keys (the rows' log-sum-exp, exact) and down the
 //                           rows (an approximate importance of every key)
-//   approx_hist_kernel      histogram of the pooled approximate importance
-//   one_scan_bounds_kernel  per segment: which keys can decide the selection
-//   select_chosen_kernel    the exact importance of these
+//   approx_hist_kernel      histograms of the approximate importance; the range of rho
+//   select_chosen_kernel    which keys can decide the selection; a probe, where that would be too many (first launch); their exact importance (second)
 // and the selection as otherwise, from its exact values.
 //
 // The approximate importance of a key is I' = sum over the rows of e^(x - lse'[row]), the exact one
@@ -720,22 +730,33 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 // holds for window maxima (averages: not built).  With tau' the k-th largest pooled I', known to a histogram bin [bin_lo, bin_hi),
 // the k-th largest pooled I, tau, lies in [rho_min bin_lo, rho_max bin_hi].  Hence
 //   a key with I' > bin_hi * rho_max / rho_min has I > tau: whatever its value, it only has to stay above tau;
-//   a key with I' < bin_lo * rho_min / max(rho_max, 1) has I < tau and I' < tau: it may keep I';
+//   a key with I' < bin_lo * rho_min / rho_max has I < tau: it may keep an I' below rho_min bin_lo, or stand at 0;
 //   the keys between get their exact importance, computed as PASS 2 does.
-// The selection on the array that holds these values keeps the same positions as on the exact importance.  A sample that misses what
-// matters only widens the range; at worst (rho not usable) every key is computed again.
-// Of 131072 keys, 256 rows, 2 per cent of the keys pulled towards a query, 2100 are sampled (8700 where 3395 positions are kept) and 70 to 200 (1200 to 1500) computed again.
-// 32 segments of 20 K to 128 K keys, 256 rows, two passes / this, us: passes 160 + 176 / sample 25, scan 184, histogram 12,
-// bounds 9, chosen keys 20 to 30; the block-wise selection 52 / 22 (pooled and listed by select_chosen_kernel); the call 407 / 278.
-constexpr int kDenseKeys = 128;      // so many of a history's first and last keys are all in the sample (attention sinks, recent tokens),
-constexpr int kSampleGroup = 8;      // of those between, groups of so many neighbours,
-// which make one of sample_step keys.  Near the bulk of the scores an uncertain one takes in many more of them: a finer sample there.
-__device__ __forceinline__ int sample_step(int m, int kk) { return max(many_kept(m, kk) ? m / 8192 : m / 2048, 4); }
+// The selection on the array that holds these values keeps the same positions as on the exact importance.
+//
+// That asks for every rho near 1, and one row that gives half its weight to one key that the sample does not hold has rho = 0.5: the keys between are then
+// up to all.  But such rows are few, or all alike, and I / I' is nearly the same for all keys.  So, where the range is wide, a probe comes first: the
+// exact importance of the keys that are the largest by I', and with them, however they were chosen, a lower bound t of tau, the k-th largest score of the
+// windows that they lie in.  Keys with I' < t / rho_max have I < tau; the others get their exact importance.  rho_max is kept near 1 by
+// fold_sample.  Whatever the sample misses, the selection is exact; it only costs time, at worst that of all keys one by one.
+//
+// Of 131072 keys, 256 rows, 2 per cent of the keys pulled towards a query, 170 (3395) positions kept: 2300 (8400) keys are sampled, 40 to 70
+// (1000) computed again.  With 1 row, or 16, that give half (0.9) of their weight to one key in the middle: 40 to 60 (800) in the probe and 30 to 60
+// (1000 to 2100) behind it, where all of them were computed again without a probe.
+// 32 segments of 20 K to 128 K keys, 256 rows, us: the two passes 160 + 176, their selection 52; sample 24, scan 184, histograms 13, bounds 6 (with a
+// probe 15), chosen keys 20, selection 22.  The call, two passes / this: 407 / 278; one row at 0.9 404 / 307 (531 without the
+// probe); 16 rows at 0.9 404 / 307 (528); 256 rows, a random share each 413 / 368; the queries 3 times as large 405 / 304 (481).  The worst found: the queries 5 times as
+// large, where the sample says nothing, 404 / 498; a tenth of the positions kept and 256 rows with a random share each 470 / 570.
+constexpr int kDenseKeys = 128;      // so many of a history's first and last keys are all in the sample (attention sinks, recent tokens);
+// of those between, groups of neighbours (sample_step).
+constexpr int kHists = 4, kHistPooled = 0, kHistKeys = 1;   // of I': pooled, and of a sample of the keys, not pooled;
+constexpr int kHistProbe = 2, kHistExact = 3;               // of pooled exact scores: after a probe, and at the end
 struct OneScan {
-  float* part0;        // log-sum-exp of the sample in every range, [range][Rpad]
-  uint32_t* hist;      // histogram of the approximate pooled scores, [segment][kHistBins]
-  float* lse;          // log-sum-exp of the rows, [segment][256]
-  uint32_t* bounds;    // [segment][4]: see one_scan_bounds_kernel
+  float* part0;        // log-sum-exp of the sample in every range, [range][Rpad],
+  float* dense;        // of all keys at either end, [segment][2][Rpad]
+  uint32_t* hist;      // histograms, [segment][kHists][kHistBins]
+  float* lse;          // log-sum-exp of the rows, [segment][2][256]: exact; of the sample
+  uint32_t* bounds;    // [segment][kBoundWords]
   uint32_t* lists;     // [segment][kSelCandidates]
 };
 
@@ -757,18 +778,18 @@ __device__ __forceinline__ float sum_halves(float v) {
 // score_q_resident_kernel, 4 waves of 64 rows at 256 registers, 41 us where this takes 25.)
 template <int DK, int RB, int KIND>
 __global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
-                                                              int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w, int CH,
+                                                              int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w,
                                                               float c_log2, const OneScan one) {
   constexpr int NT = 512, KS = 8 / RB, TK = KS == 4 ? 128 : 64, NSUB = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2 + 16, CPR = DK * 2 / 16;
   constexpr int LPT = TK * CPR / NT;
   __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TK * ROWB];
-  __shared__ float2 comb[KS][RB * 32];
+  __shared__ float2 comb[2][KS][RB * 32];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int rb = wv % RB, ks = wv / RB, l32 = lane & 31, half = lane >> 5;
-  const int bid = (int)(gridDim.x - 1 - blockIdx.x);     // (the last segments' first: short ones have the most to do)
+  const int bid = blockIdx.x;
   const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.range_begin(s); });
   const SegShape sg = tab.shape(seg);
-  const int m = sg.n - w, len = range_len(m, sg.kk, CH), r0 = tab.range_begin(seg), begin = (bid - r0) * len, keys = min(len, m - begin);
+  const int m = sg.n - w, len = range_len(m, sg.kk, tab.sampled), r0 = tab.range_begin(seg), begin = (bid - r0) * len, keys = min(len, m - begin);
   // key u of the sample: the range's first `head` keys, its last `tail`, then, of those between, kSampleGroup neighbours every `stride` keys, which
   // stand for e^log_weight keys each
   int head = keys, tail = 0, stride = 1, total = keys;
@@ -805,8 +826,8 @@ __global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab
   }
   issue_tile(1, pf1);
   if (bid == r0)
-    for (int i = tid; i < kHistBins; i += NT) one.hist[(size_t)seg * kHistBins + i] = 0;
-  float m_run = -INFINITY, s_run = 0.f;
+    for (int i = tid; i < kHists * kHistBins; i += NT) one.hist[(size_t)seg * kHists * kHistBins + i] = 0;
+  float m_run[2] = {-INFINITY, -INFINITY}, s_run[2] = {0.f, 0.f};   // the keys of head and tail; the others
   auto tile = [&](int t, u32x4 (&pf)[LPT], int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < LPT; ++i) {
@@ -832,17 +853,21 @@ __global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab
         for (int i = 0; i < 16; ++i)
           if (u0 + 8 * (i >> 2) + 4 * half + (i & 3) >= total) acc[i] = -INFINITY;
       }
-      const float lw = u0 >= head + tail ? log_weight : 0.f;   // (head and tail are multiples of 32 where other keys follow)
+      const bool sampled = u0 >= head + tail;            // (head and tail are multiples of 32 where other keys follow)
+      const float lw = sampled ? log_weight : 0.f, m_old = sampled ? m_run[1] : m_run[0];
       float mx = acc[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, acc[i]);
-      const float mn = fmaxf(m_run, fmaf(mx, c_log2, lw));
+      const float mn = fmaxf(m_old, fmaf(mx, c_log2, lw));
       const float mu = mn == -INFINITY ? 0.f : mn;
       float sum = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(acc[i], c_log2, lw - mu));
-      s_run = s_run * fast_exp2(m_run - mu) + sum;
-      m_run = mn;
+      sum += (sampled ? s_run[1] : s_run[0]) * fast_exp2(m_old - mu);
+      m_run[0] = sampled ? m_run[0] : mn;
+      s_run[0] = sampled ? s_run[0] : sum;
+      m_run[1] = sampled ? mn : m_run[1];
+      s_run[1] = sampled ? sum : s_run[1];
     }
   };
   const int ntiles = (total + TK - 1) / TK;
@@ -850,17 +875,26 @@ __global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab
     tile(t, pf0, 0);
     if (t + 1 < ntiles) tile(t + 1, pf1, 1);
   }
-  {
-    const float m2 = __shfl_xor(m_run, 32, 64), s2 = __shfl_xor(s_run, 32, 64);
-    merge_stats(m_run, s_run, m2, s2);
-    if (half == 0) comb[ks][rb * 32 + l32] = make_float2(m_run, s_run);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float m2 = __shfl_xor(m_run[i], 32, 64), s2 = __shfl_xor(s_run[i], 32, 64);
+    merge_stats(m_run[i], s_run[i], m2, s2);
+    if (half == 0) comb[i][ks][rb * 32 + l32] = make_float2(m_run[i], s_run[i]);
   }
   __syncthreads();
-  for (int row = tid; row < RB * 32; row += NT) {
-    float mm = comb[0][row].x, ss = comb[0][row].y;
+  const bool first = bid == r0, last = begin + keys == m;
+  for (int i = tid; i < 2 * RB * 32; i += NT) {
+    const int which = i / (RB * 32), row = i % (RB * 32);
+    float mm = comb[which][0][row].x, ss = comb[which][0][row].y;
 #pragma unroll
-    for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
-    if (row < Rpad) one.part0[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+    for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[which][k2][row].x, comb[which][k2][row].y);
+    const float l = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+    if (row >= Rpad) continue;
+    float* const ends = one.dense + (int64_t)seg * 2 * Rpad + row;
+    if (which == 1) one.part0[(int64_t)bid * Rpad + row] = l;
+    else if (first) ends[0] = l;
+    else if (last) ends[Rpad] = l;
+    if (which == 0 && first && last) ends[Rpad] = -INFINITY;
   }
 }
 
@@ -928,8 +962,9 @@ __global__ __launch_bounds__(256, 2) void score_both_kernel(const SegTable tab, 
                     lds_base + (uint32_t)((t % NB) * TK * ROWB + (i * 4 + wv) * 1024));
   };
   {
-    const float l = fold_sample(one.part0, tab.range_begin(seg), tab.range_begin(seg + 1), Rpad, ROWS);
+    const float l = fold_sample(one.part0, one.dense + (int64_t)seg * 2 * Rpad, tab.range_begin(seg), tab.range_begin(seg + 1), Rpad, ROWS);
     lse_s[tid] = tid < R ? l : INFINITY;
+    if (bid == se.chunk0) one.lse[(size_t)seg * 512 + 256 + tid] = l;   // (for approx_hist_kernel)
   }
   __builtin_amdgcn_sched_barrier(0);                     // (the fold's loads and the queries together do not fit the registers)
   bf16x8 qreg[MT][KK];
@@ -1158,17 +1193,56 @@ constexpr int kBinShift = 17;                        // 64 bins per octave,
 constexpr uint32_t kBinBase = 106u << (23 - kBinShift);   // from 2^-21 to 2^11; what lies outside counts in the first and last bin
 constexpr int kSelCandidates = 12288;                // scores that select_rank_kernel's list in LDS can hold
 constexpr float kAboveAll = 0x1p120f;                // stands for the importance of a key above tau
+constexpr float kProbeGain = 0.05f;                  // a probe has to save this share of a history's keys: it takes 10 us more than the bounds alone, all keys 220 us
+constexpr float kSlack = 1.f / 1024.f;               // of the bounds: far above the rounding of either side
 
-// Histogram of the pooled approximate importance: a workgroup per block of 4096 positions (x) of a segment (y).
+__device__ __forceinline__ uint32_t score_bin(uint32_t u) {
+  const uint32_t b = u >> kBinShift;
+  return b <= kBinBase ? 0u : min(b - kBinBase, (uint32_t)kHistBins - 1u);
+}
+
+// Histogram of the pooled approximate importance, and of that of every eighth run of 256 keys itself: a workgroup per block of 4096 positions
+// (x - 1) of a segment (y).  A block's two counts of a bin share a word.  Workgroup x == 0: the segment's rows, their log-sum-exp and the range of rho.
 constexpr int kApproxBlock = 4096;
-__global__ __launch_bounds__(256) void approx_hist_kernel(const SegTable tab, int w, int radius, const float* __restrict__ imp,
-                                                          uint32_t* __restrict__ hist) {
+__global__ __launch_bounds__(256) void approx_hist_kernel(const SegTable tab, int w, int radius, int R, int Rpad, const float* __restrict__ part,
+                                                          const float* __restrict__ imp, const OneScan one) {
   __shared__ uint32_t bins[kHistBins];
   __shared__ uint32_t stage[kApproxBlock + kMaxPool];
   const int tid = threadIdx.x, seg = blockIdx.y;
   const SegShape sg = tab.shape(seg);
-  const int m = sg.n - w, p0 = (int)blockIdx.x * kApproxBlock;
+  const int m = sg.n - w, p0 = ((int)blockIdx.x - 1) * kApproxBlock;
   if (!(sg.kk > 0 && sg.kk < m) || p0 >= m) return;
+  if (p0 < 0) {
+    const int lane = tid & 63, wv = tid >> 6;
+    const float lse0 = one.lse[(size_t)seg * 512 + 256 + tid];
+    const int rows = Rpad <= 64 ? 64 : Rpad <= 128 ? 128 : 256;
+    const float lse = fold_rows(part, tab.chunk_begin(seg), tab.chunk_begin(seg + 1), Rpad, 0, rows, 256, reinterpret_cast<float2*>(stage));
+    one.lse[(size_t)seg * 512 + tid] = tid < R ? lse : INFINITY;
+    // anything that is not a positive number ends as 0 or inf
+    const float rho = fast_exp2(lse0 - lse);
+    float rmin = tid < R ? (rho > 0.f ? rho : 0.f) : INFINITY, rmax = tid < R ? (rho < INFINITY ? rho : INFINITY) : 0.f;
+    float rsum = rmax;
+#pragma unroll
+    for (int dlt = 32; dlt > 0; dlt >>= 1) {
+      rmin = fminf(rmin, __shfl_xor(rmin, dlt, 64));
+      rmax = fmaxf(rmax, __shfl_xor(rmax, dlt, 64));
+      rsum += __shfl_xor(rsum, dlt, 64);
+    }
+    float* const sh = reinterpret_cast<float*>(bins);
+    if (lane == 0) {
+      sh[wv] = rmin;
+      sh[4 + wv] = rmax;
+      sh[8 + wv] = rsum;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      float* const out = reinterpret_cast<float*>(one.bounds + seg * kBoundWords + kBoundRho);
+      out[0] = fminf(fminf(sh[0], sh[1]), fminf(sh[2], sh[3]));
+      out[1] = fmaxf(fmaxf(sh[4], sh[5]), fmaxf(sh[6], sh[7]));
+      out[2] = (sh[8] + sh[9] + sh[10] + sh[11]) / (float)R;
+    }
+    return;
+  }
   const float* I = imp + sg.score_off;
   const int cnt = min(kApproxBlock, m - p0);
   constexpr int PER = kApproxBlock / 256;
@@ -1189,117 +1263,174 @@ __global__ __launch_bounds__(256) void approx_hist_kernel(const SegTable tab, in
     if (s < cnt) {
       uint32_t a = stage[s];
       for (int t = 1; t <= 2 * radius; ++t) a = max(a, stage[s + t]);
-      const uint32_t b = a >> kBinShift;
-      atomicAdd(&bins[b <= kBinBase ? 0u : min(b - kBinBase, (uint32_t)kHistBins - 1u)], 1u);
+      atomicAdd(&bins[score_bin(a)], 1u);
+      if (e % 8 == 0) atomicAdd(&bins[score_bin(stage[s + radius])], 1u << 16);
     }
   }
   __syncthreads();
-  for (int i = tid; i < kHistBins; i += 256)
-    if (bins[i]) atomicAdd(&hist[(size_t)seg * kHistBins + i], bins[i]);
+  uint32_t* const H = one.hist + (size_t)seg * kHists * kHistBins;
+  for (int i = tid; i < kHistBins; i += 256) {
+    const uint32_t c = bins[i];
+    if (c & 0xffffu) atomicAdd(&H[kHistPooled * kHistBins + i], c & 0xffffu);
+    if (c >> 16) atomicAdd(&H[kHistKeys * kHistBins + i], c >> 16);
+  }
 }
 
-// A workgroup per segment: its rows' log-sum-exp, the range of rho, and what follows from them and the histogram:
-// bounds[0], [1]: keys whose I' lies between (bit patterns, inclusive) need their exact importance; above: kAboveAll stands for it;
-// bounds[2], [3]: the k-th largest pooled score lies between.
-// blockhist (block-wise selection): also the words that select_rank_kernel, phase 1, expects in the segment's first histogram row.
-__global__ __launch_bounds__(256) void one_scan_bounds_kernel(const SegTable tab, int w, int R, int Rpad, const float* __restrict__ part, const OneScan one,
-                                                              uint32_t* __restrict__ blockhist) {
-  __shared__ uint32_t bins[kHistBins];
-  __shared__ float2 fold[256];
-  __shared__ uint32_t sh_scan[4], res[2];
-  __shared__ float sh_rho[8];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, seg = blockIdx.x;
-  const SegShape sg = tab.shape(seg);
-  const int m = sg.n - w;
-  if (!(sg.kk > 0 && sg.kk < m)) return;
+// What follows from the histograms and the range of rho, as every workgroup of a segment finds it (NT threads; ends with a barrier):
+//   word[0], [1]: keys whose I' lies between (bit patterns, inclusive) need their exact importance; above: kAboveAll stands for it;
+//   word[2], [3]: the k-th largest pooled score lies between;
+//   probe: the range of rho is too wide to tell much, a probe comes first.  word[0]: it computes the keys from here on;
+//   wide: the pooled scores between word[2] and [3] may be more than a list holds.
+struct OneScanBounds {
+  uint32_t word[4];
+  bool probe, wide;
+};
+template <int NT>
+__device__ __forceinline__ OneScanBounds one_scan_bounds(const uint32_t* __restrict__ H, const float* __restrict__ rho, int m, int kk,
+                                                         uint32_t* bins, uint32_t* sh_scan, uint32_t* res, uint32_t (*sh_count)[NT / 64]) {
+  constexpr int PER = kHistBins / NT;
+  const int tid = threadIdx.x;
+  uint32_t keys_in[PER];                                 // sampled keys of the bins
 #pragma unroll
-  for (int i = 0; i < kHistBins / 256; ++i) bins[i * 256 + tid] = one.hist[(size_t)seg * kHistBins + i * 256 + tid];
-  const int rows = Rpad <= 64 ? 64 : Rpad <= 128 ? 128 : 256;
-  const float lse = fold_rows(part, tab.chunk_begin(seg), tab.chunk_begin(seg + 1), Rpad, 0, rows, 256, fold);
-  const float lse0 = fold_sample(one.part0, tab.range_begin(seg), tab.range_begin(seg + 1), Rpad, rows);
-  one.lse[(size_t)seg * 256 + tid] = tid < R ? lse : INFINITY;
-  // the range of rho over the rows; anything that is not a positive number ends as 0 or inf
-  const float rho = fast_exp2(lse0 - lse);
-  float rmin = tid < R ? (rho > 0.f ? rho : 0.f) : INFINITY, rmax = tid < R ? (rho < INFINITY ? rho : INFINITY) : 0.f;
-#pragma unroll
-  for (int dlt = 32; dlt > 0; dlt >>= 1) {
-    rmin = fminf(rmin, __shfl_xor(rmin, dlt, 64));
-    rmax = fmaxf(rmax, __shfl_xor(rmax, dlt, 64));
+  for (int i = 0; i < PER; ++i) {
+    bins[i * NT + tid] = H[kHistPooled * kHistBins + i * NT + tid];
+    keys_in[i] = H[kHistKeys * kHistBins + i * NT + tid];
   }
-  if (lane == 0) {
-    sh_rho[wv] = rmin;
-    sh_rho[4 + wv] = rmax;
+  const float rmin = rho[0], rmax = rho[1], rmean = rho[2];
+  __syncthreads();
+  select_bin<NT>(bins, (uint32_t)kk, sh_scan, res);
+  const uint32_t b = res[0];
+  const float ratio = rmax / rmin;
+  const bool usable = b > 0u && rmin > 0.f && ratio < 1e6f;     // (false for NaN, too)
+  const float bin_lo = __uint_as_float((b + kBinBase) << kBinShift);
+  const float bin_hi = b == (uint32_t)kHistBins - 1u ? INFINITY : __uint_as_float((b + 1u + kBinBase) << kBinShift);
+  OneScanBounds r{{0u, 0x7f800000u, 0u, 0x7f800000u}, false, false};   // not usable: every key, any score
+  uint32_t guess = 0;                                           // about where the keys begin that follow a probe: I = rmean I' for most keys
+  if (usable) {
+    r.word[0] = __float_as_uint(bin_lo * (rmin / rmax) * (1.f - kSlack));
+    r.word[1] = min(__float_as_uint(bin_hi * ratio * (1.f + kSlack)), 0x7f800000u);
+    r.word[2] = __float_as_uint(bin_lo * rmin * (1.f - kSlack));
+    r.word[3] = min(__float_as_uint(bin_hi * rmax * (1.f + kSlack)), 0x7f800000u);
+    guess = __float_as_uint(bin_lo * (0.9f * rmean / rmax));
+  }
+  // positions whose pooled score probably lies between word[2] and [3], and sampled keys: between word[0] and [1], from the guess on, all
+  uint32_t count[4] = {0, 0, 0, 0};
+  const uint32_t lo_bin = score_bin(r.word[0]), hi_bin = score_bin(r.word[1]), guess_bin = score_bin(guess);
+  const uint32_t lo2_bin = usable ? score_bin(__float_as_uint(__uint_as_float(r.word[2]) / rmean * 0.95f)) : 0u;
+  const uint32_t hi2_bin = usable ? score_bin(__float_as_uint(__uint_as_float(r.word[3]) / rmean * 1.05f)) : (uint32_t)kHistBins - 1u;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const uint32_t at = (uint32_t)(i * NT + tid);
+    if (at >= lo2_bin && at <= hi2_bin) count[0] += bins[at];
+    if (at >= lo_bin && at <= hi_bin) count[1] += keys_in[i];
+    if (at >= guess_bin) count[2] += keys_in[i];
+    count[3] += keys_in[i];
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    count[c] = wave_sum(count[c]);
+    if ((tid & 63) == 0) sh_count[c][tid >> 6] = count[c];
   }
   __syncthreads();
-  rmin = fminf(fminf(sh_rho[0], sh_rho[1]), fminf(sh_rho[2], sh_rho[3]));
-  rmax = fmaxf(fmaxf(sh_rho[4], sh_rho[5]), fmaxf(sh_rho[6], sh_rho[7]));
-  select_bin<256>(bins, (uint32_t)sg.kk, sh_scan, res);
-  if (tid == 0) {
-    const uint32_t b = res[0];
-    constexpr float kSlack = 1.f / 1024.f;               // far above the rounding of either side
-    const float ratio = rmax / rmin;
-    const bool usable = b > 0u && rmin > 0.f && ratio < 1e6f;   // (false for NaN, too)
-    const float bin_lo = __uint_as_float((b + kBinBase) << kBinShift);
-    const float bin_hi = b == (uint32_t)kHistBins - 1u ? INFINITY : __uint_as_float((b + 1u + kBinBase) << kBinShift);
-    uint32_t bd[4] = {0u, 0x7f800000u, 0u, 0x7f800000u};        // not usable: every key, any score
-    if (usable) {
-      bd[0] = __float_as_uint(bin_lo * (rmin / fmaxf(rmax, 1.f)) * (1.f - kSlack));
-      bd[1] = min(__float_as_uint(bin_hi * ratio * (1.f + kSlack)), 0x7f800000u);
-      bd[2] = __float_as_uint(bin_lo * rmin * (1.f - kSlack));
-      bd[3] = min(__float_as_uint(bin_hi * rmax * (1.f + kSlack)), 0x7f800000u);
-    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) one.bounds[seg * 4 + i] = bd[i];
-    if (blockhist) {
-      uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
-      hdr[4] = bd[2];
-      hdr[5] = bd[3];
-      hdr[6] = 0;                                        // pooled scores above the range
-      hdr[7] = 0;                                        // scores listed (or counted, where they are more than a list holds)
-    }
+  for (int c = 0; c < 4; ++c) {
+    count[c] = 0;
+#pragma unroll
+    for (int v = 0; v < NT / 64; ++v) count[c] += sh_count[c][v];
   }
+  r.probe = usable && (float)count[2] + kProbeGain * (float)count[3] < (float)count[1];
+  r.wide = r.probe || count[0] > (uint32_t)kSelCandidates;
+  if (r.probe) {
+    // The keys that put half as many positions again as are wanted into this bin or above: the exact order differs, and from no more than
+    // kk positions their kk-th largest score would be a poor bound.
+    select_bin<NT>(bins, (uint32_t)min(kk + kk / 2, m), sh_scan, res);
+    r.word[0] = (max(res[0], 1u) + kBinBase) << kBinShift;
+  }
+  __syncthreads();
+  return r;
 }
 
 // The exact importance of the keys that can decide the selection.  A workgroup (8 waves) per range of positions lists them
-// and takes them TK at a time through the loop of PASS 2; wave (rb, ks) holds 32 query rows.
-//   blockhist == NULL: the importance array is made fit for select_resident_kernel;
-//   otherwise the positions are pooled here (the keys of the neighbours' edges are done twice) and their scores between bounds[2] and [3] listed, so that the
-//   block-wise selection starts at phase 1 of select_rank_kernel.
+// and takes them TK at a time through the loop of PASS 2; wave (rb, ks) holds 32 query rows.  Two launches:
+//   probe: the bounds of the segment, which the second one finds in memory; where they ask for a probe, the exact pooled scores that it gives, in a histogram;
+//   otherwise, blockhist == NULL: the importance array is made fit for select_resident_kernel;
+//   or the positions are pooled here (the keys of the neighbours' edges are done twice) and their scores between word[2] and [3] listed, or (wide) all of
+//   them counted in a histogram, so that the block-wise selection starts at phase 1 of select_rank_kernel.
 template <int DK, int RB, int KIND>
 __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
-                                                               int64_t k_stride_tok, int64_t k_stride_head, int R, int w, int CH, int radius,
+                                                               int64_t k_stride_tok, int64_t k_stride_head, int R, int w, int radius,
                                                                float c_log2, const OneScan one, float* __restrict__ imp,
-                                                               float* __restrict__ pooled, uint32_t* __restrict__ blockhist) {
+                                                               float* __restrict__ pooled, uint32_t* __restrict__ blockhist, int probe) {
   constexpr int NT = 512, KS = 8 / RB, TK = KS == 4 ? 128 : 64, NSUB = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2 + 16, CPR = DK * 2 / 16;
   constexpr int LPT = TK * CPR / NT, MOST = kRangeMost + kMaxPool - 1, PER = (MOST + NT - 1) / NT;
-  __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TK * ROWB];
+  constexpr int NB = KS == 4 ? 1 : 2;                    // up to 64 rows: one tile in LDS, or a CU would hold one workgroup only (32 heads x 58 K keys of 16 rows, two launches: 26 us instead of 17)
+  __shared__ __attribute__((aligned(16))) unsigned char ktile[NB][TK * ROWB];
   __shared__ float red[2][RB][TK];
-  __shared__ uint32_t val[MOST];                         // pooled scores; 0 where no key that matters is near
+  __shared__ uint32_t val[MOST];                         // pooled scores (dense: the keys' own); 0 where no key that matters is near
   __shared__ uint16_t list[MOST];
   __shared__ float lse_s[256];
   __shared__ uint32_t nlist, nsure, nabove, nband, band0;
+  __shared__ uint32_t sh_scan[NT / 64], res[2], sh_count[4][NT / 64];
+  uint32_t* const bins = reinterpret_cast<uint32_t*>(&ktile[0][0]);   // before and after the tiles
+  static_assert(sizeof(ktile) >= kHistBins * sizeof(uint32_t), "the bins fit the tiles' place");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int rb = wv % RB, ks = wv / RB, l32 = lane & 31, half = lane >> 5;
   const int bid = (int)(gridDim.x - 1 - blockIdx.x);     // (the last segments' first: short ones have the most to do)
   const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.range_begin(s); });
   const SegShape sg = tab.shape(seg);
-  const int m = sg.n - w, len = range_len(m, sg.kk, CH), begin = (bid - tab.range_begin(seg)) * len;
-  const int reach = blockhist ? radius : 0;
+  const int m = sg.n - w, len = range_len(m, sg.kk, tab.sampled), begin = (bid - tab.range_begin(seg)) * len;
+  const bool pools = blockhist || probe;
+  const int reach = pools ? radius : 0;
+  uint32_t* const H = one.hist + (size_t)seg * kHists * kHistBins;
+  uint32_t* const bd = one.bounds + seg * kBoundWords;
+  const float* const rho = reinterpret_cast<const float*>(bd + kBoundRho);
   float* const I = imp + sg.score_off;
-  const uint32_t lo = one.bounds[seg * 4], hi = one.bounds[seg * 4 + 1];
-  const uint32_t lo2 = one.bounds[seg * 4 + 2], span2 = one.bounds[seg * 4 + 3] - lo2;
   const int first = begin, end = min(begin + len, m);
   const int p0 = max(first - reach, 0), cnt = min(end + reach, m) - p0;   // positions looked at here
+  uint32_t lo, hi, lo2, hi2;
+  bool probed, wide;
+  if (probe) {
+    const OneScanBounds b = one_scan_bounds<NT>(H, rho, m, sg.kk, bins, sh_scan, res, sh_count);
+    if (begin == 0 && tid == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bd[i] = b.word[i];
+      bd[kBoundProbe] = b.probe ? 1u : 0u;
+      bd[kBoundWide] = b.wide ? 1u : 0u;
+      if (blockhist) {                                   // the words that select_rank_kernel, phase 1, expects
+        uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
+        hdr[4] = b.word[2];
+        hdr[5] = b.word[3];
+        hdr[6] = 0;                                      // pooled scores above the range
+        hdr[7] = 0;                                      // scores listed (or counted, where they are more than a list holds)
+      }
+    }
+    if (!b.probe) return;
+    probed = true;
+    wide = b.wide;
+    lo = b.word[0];
+    hi = hi2 = 0x7f800000u;
+    lo2 = 0;
+  } else {
+    probed = bd[kBoundProbe] != 0u;
+    wide = bd[kBoundWide] != 0u;
+    lo = bd[0];
+    hi = bd[1];
+    lo2 = bd[2];
+    hi2 = bd[3];
+  }
   float v[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) v[e] = I[p0 + min(e * NT + tid, cnt - 1)];
-  if (tid < 256) lse_s[tid] = one.lse[(size_t)seg * 256 + tid];
+  if (tid < 256) lse_s[tid] = one.lse[(size_t)seg * 512 + tid];
   if (tid == 0) nlist = nsure = nabove = nband = 0;
-  if (blockhist)
+  if (pools)
     for (int i = tid; i < cnt; i += NT) val[i] = 0;
-  // a key's score enters the windows that it lies in
+  // A key's score enters the windows that it lies in, or, where the list holds much of the range, its own place: the windows' maxima follow at the end
+  // (lists of all keys, call of 2.5 M: windows of 7 the same, of 13 467 -> 440 us, of 63 620 -> 480).
+  bool dense = false;
   auto pool = [&](int i, uint32_t u) __attribute__((always_inline)) {
-    for (int j = max(i - radius, 0); j <= min(i + radius, cnt - 1); ++j) atomicMax(&val[j], u);
+    if (dense) val[i] = u;
+    else for (int j = max(i - radius, 0); j <= min(i + radius, cnt - 1); ++j) atomicMax(&val[j], u);
   };
   bf16x8 qreg[KK];
 #pragma unroll
@@ -1308,6 +1439,16 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
     p.u = *reinterpret_cast<const u32x4*>(q + ((int64_t)seg * R + min(rb * 32 + l32, R - 1)) * DK + kk * 16 + half * 8);
     qreg[kk] = p.b;
   }
+  if (probed && !probe) {
+    // the probe's kk-th largest pooled score: what tau reaches at least
+    for (int i = tid; i < kHistBins; i += NT) bins[i] = H[kHistProbe * kHistBins + i];
+    __syncthreads();
+    select_bin<NT>(bins, (uint32_t)sg.kk, sh_scan, res);
+    lo2 = res[0] ? (res[0] + kBinBase) << kBinShift : 0u;
+    lo = __float_as_uint(__uint_as_float(lo2) / rho[1] * (1.f - kSlack));
+    hi = hi2 = 0x7f800000u;
+  }
+  const uint32_t span2 = hi2 - lo2;
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
@@ -1325,8 +1466,10 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
       if (blockhist) list[MOST - 1 - (int)atomicAdd(&nsure, 1u)] = (uint16_t)i;   // (few; the two lists together hold at most cnt entries)
       else I[p0 + i] = kAboveAll;
     }
+    if (!pools && valid && u >= lo2 && u < lo) I[p0 + i] = 0.f;   // (below tau, where its I' may be above)
   }
   __syncthreads();
+  dense = (int)nlist > cnt / 4;
   for (int i = tid; i < (int)nsure; i += NT) pool(list[MOST - 1 - i], __float_as_uint(kAboveAll));
   const int nl = (int)nlist, ntiles = (nl + TK - 1) / TK;
   if (nl > 0) {
@@ -1348,10 +1491,11 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
 #pragma unroll
     for (int i = 0; i < 16; ++i) lse_r[i] = lse_s[rb * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
     auto tile = [&](int t, u32x4 (&pf)[LPT], int buf) __attribute__((always_inline)) {   // t == ntiles: only the sums of the tile before
+      if (NB == 1) __syncthreads();                      // (every wave has read the tile before)
 #pragma unroll
       for (int i = 0; i < LPT; ++i) {
         const int idx = i * NT + tid;
-        *reinterpret_cast<u32x4*>(&ktile[buf][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
+        *reinterpret_cast<u32x4*>(&ktile[buf % NB][(idx / CPR) * ROWB + (idx % CPR) * 16]) = pf[i];
       }
       issue_tile(t + 2, pf);
       __syncthreads();
@@ -1361,8 +1505,8 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
         for (int r = 0; r < RB; ++r) sum += red[buf ^ 1][r][tid];
         const int li = (t - 1) * TK + tid;
         if (li < nl) {
-          if (!blockhist) I[p0 + list[li]] = sum;
-          else if (score_key(sum) >= lo2) pool(list[li], score_key(sum));
+          if (!pools) I[p0 + list[li]] = sum;
+          else if (score_key(sum) >= lo2) pool(list[li], max(score_key(sum), 1u));   // (1: not "no key that matters")
         }
       }
       if (t == ntiles) return;
@@ -1375,7 +1519,7 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
           Pack16 p;
-          p.u = *reinterpret_cast<const u32x4*>(&ktile[buf][(sub * 32 + l32) * ROWB + kk * 32 + half * 16]);
+          p.u = *reinterpret_cast<const u32x4*>(&ktile[buf % NB][(sub * 32 + l32) * ROWB + kk * 32 + half * 16]);
           acc = mfma16<KIND == 1>(qreg[kk], p.b, acc);
         }
         float colsum = 0.f;
@@ -1390,10 +1534,9 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
       if (t < ntiles) tile(t + 1, pf1, 1);
     }
   }
-  if (!blockhist) return;
+  if (!pools) return;
   __syncthreads();
-  // pooled scores (exact from bounds[2] on) of positions first .. end - 1, those above the range counted, those in it listed
-  uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
+  // pooled scores (exact from lo2 on) of positions first .. end - 1, those above the range counted, those in it listed
   constexpr int OWN = kRangeMost / NT;
   uint32_t key[OWN];
   uint32_t above = 0, in_band = 0;
@@ -1404,10 +1547,23 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
     key[e] = 0;
     if (real) {
       key[e] = val[j - p0];
-      pooled[sg.score_off + j] = __uint_as_float(key[e]);
+      if (dense)
+        for (int t = max(j - radius, p0); t <= min(j + radius, p0 + cnt - 1); ++t) key[e] = max(key[e], val[t - p0]);
+      if (!probe) pooled[sg.score_off + j] = __uint_as_float(key[e]);
     }
     above += (uint32_t)__popcll(__ballot(real && key[e] > lo2 + span2));
     in_band += (uint32_t)__popcll(__ballot(real && key[e] - lo2 <= span2));
+  }
+  if (probe || wide) {
+    for (int i = tid; i < kHistBins; i += NT) bins[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < OWN; ++e)
+      if (first + e * NT + tid < end && (key[e] || !probe)) atomicAdd(&bins[score_bin(key[e])], 1u);
+    __syncthreads();
+    for (int i = tid; i < kHistBins; i += NT)
+      if (bins[i]) atomicAdd(&H[(probe ? kHistProbe : kHistExact) * kHistBins + i], bins[i]);
+    return;
   }
   uint32_t base = 0;
   if (lane == 0) {
@@ -1417,6 +1573,7 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
   base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
   __syncthreads();
   if (tid == 0) {
+    uint32_t* const hdr = blockhist + (size_t)tab.blk_begin(seg) * kHistBins;
     if (nabove) atomicAdd(&hdr[6], nabove);
     band0 = nband ? atomicAdd(&hdr[7], nband) : 0u;
   }
@@ -1914,7 +2071,7 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
                                                                   uint32_t* __restrict__ blockhist,
                                                                   int32_t* __restrict__ kept_idx, int64_t* __restrict__ d_out_offsets,
                                                                   const GatherArgs ga, int split_emit,
-                                                                  const uint32_t* __restrict__ lists, int phase, int chosen) {
+                                                                  const uint32_t* __restrict__ lists, int phase, const OneScan one) {
   constexpr int NT = kSelThreads, NW = kSelWaves, EPT = kSelEPT, ROUND = kSelRound;
   __shared__ uint32_t hist[kHistBins];
   __shared__ uint32_t cand[kSelCandidates];
@@ -2024,10 +2181,36 @@ __global__ __launch_bounds__(kSelThreads) void select_rank_kernel(const TAB tab,
       }
     };
     // (chosen: after select_chosen_kernel, word 6 counts the scores above the range instead)
+    const bool chosen = one.hist != nullptr;
     uint32_t lo = hdr[4], hi = hdr[5], k = chosen ? (uint32_t)kk - hdr[6] : hdr[6], in_range = chosen ? hdr[7] : hdr[8];
-    const bool use_list = chosen ? in_range <= (uint32_t)kSelCandidates : hdr[9] != 0u;
-    const uint32_t ncand = min(hdr[7], (uint32_t)kSelCandidates);   // (== in_range when the list is used)
-    if (use_list) {
+    bool use_list = chosen ? in_range <= (uint32_t)kSelCandidates : hdr[9] != 0u;
+    uint32_t ncand = min(hdr[7], (uint32_t)kSelCandidates);   // (== in_range when the list is used)
+    if (chosen && one.bounds[seg * kBoundWords + kBoundWide]) {
+      // select_chosen_kernel has counted the scores per bin instead: those of the k-th largest one's bin, from the pooled array into the list
+      for (int i = tid; i < kHistBins; i += NT) hist[i] = one.hist[((size_t)seg * kHists + kHistExact) * kHistBins + i];
+      if (tid == 0) res[2] = 0;
+      __syncthreads();
+      select_bin<NT>(hist, (uint32_t)kk, sh_scan, res);
+      const uint32_t b = res[0];
+      k = res[1];
+      in_range = hist[b];
+      lo = b ? (b + kBinBase) << kBinShift : 0u;
+      hi = b == (uint32_t)kHistBins - 1u ? 0x7f800000u : ((b + 1u + kBinBase) << kBinShift) - 1u;
+      use_list = in_range <= (uint32_t)kSelCandidates;
+      ncand = in_range;
+      if (use_list || !multi)
+        for (int r = 0; r < rounds; ++r) {
+          load_round(r);
+          if (use_list)
+#pragma unroll
+            for (int j = 0; j < EPT; ++j)
+              if (key[j] >= lo && key[j] <= hi) {
+                const uint32_t slot = atomicAdd(&res[2], 1u);
+                if (slot < (uint32_t)kSelCandidates) cand[slot] = key[j];
+              }
+        }
+      __syncthreads();
+    } else if (use_list) {
       // the scores of the chosen digit, listed by the blocks: into LDS
       const uint32_t* L = lists + (chosen ? (int64_t)seg * kSelCandidates : (int64_t)sg.score_off);
       for (uint32_t i = tid; i < ncand; i += NT) cand[i] = L[i];
@@ -3151,16 +3334,17 @@ struct Plan {
   size_t part_bytes, score_bytes, hist_bytes, table_bytes;
   size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
   bool one_scan;         // the call may go over its keys once (see OneScan), if the workspace has these bytes as well
-  int64_t ranges;        // see range_len
-  size_t off_part0, off_bins, off_lse, off_bounds, off_lists, one_scan_bytes;
+  int sampled;           // see range_len
+  int64_t ranges;
+  size_t off_part0, off_dense, off_bins, off_lse, off_bounds, off_lists, one_scan_bytes;
 };
 
 static bool seg_ranked(int64_t n, int64_t w, int64_t cap) { return n > w && n > cap && cap > w; }
 // key chunks of the scoring passes and blocks of the selection for one segment
 static int64_t seg_chunks(const Seg& s, int w, int64_t ch) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + ch - 1) / ch : 0; }
-static int64_t seg_ranges(const Seg& s, int w, int ch) {
+static int64_t seg_ranges(const Seg& s, int w, int sampled) {
   if (!seg_ranked(s.n, w, s.cap)) return 0;
-  const int m = (int)(s.n - w), len = range_len(m, (int)(s.cap - w), ch);
+  const int m = (int)(s.n - w), len = range_len(m, (int)(s.cap - w), sampled);
   return (m + len - 1) / len;
 }
 static int64_t seg_blocks(const Seg& s, int w) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + kSelBlock - 1) / kSelBlock : 0; }
@@ -3286,10 +3470,13 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
 // Small calls take chunks down to two tiles: 8 x 2 K keys of 128 rows 22.5 us with 256 keys a chunk, 19.6 with 128.
 //
 // One pass over the keys instead of two (OneScan) where a pass takes this long by the costs above: it saves a pass, less a tenth, and
-// costs the sample, the histogram, the bounds and the chosen keys; where histories above 32768 positions are selected by blocks it
-// saves three of that selection's launches as well.  One pass / two, us: 8 x 64 K keys of 256 rows 121 / 119, 8 x 80 K 127 / 137, 8 x 128 K 158 / 189, c5's 2.5 M keys
-// 278 / 407; of 128 rows 8 x 96 K 115 / 114, 8 x 128 K 127 / 148; of 64 rows 8 x 128 K 126 / 121, 16 x 100 K 159 / 174; of 16 rows 32 x 75 K 204 / 239;
-// histories of at most 32768, 256 rows: 64 x 20 K 214 / 215, 48 x 30 K 224 / 249, 64 x 32 K 256 / 320, of 128 rows 64 x 32 K 208 / 212; more than 64 segments: 128 x 16 K 329 / 323.
+// costs the sample, the histograms, the bounds and the chosen keys; where histories above 32768 positions are selected by blocks it
+// saves three of that selection's launches as well.  One pass / two, us, on keys as in OneScan, and (in brackets) with 16 rows of every segment that give half
+// of their weight to one key each, for which the line has to leave room: 8 x 48 K keys of 256 rows 94 / 99 (110 / 99), 8 x 64 K 103 / 115 (118 / 116), 8 x 80 K
+// 112 / 132 (132 / 131), 8 x 128 K 142 / 189 (166 / 189); of 128 rows 8 x 64 K 85 / 89 (97 / 89), 8 x 96 K 94 / 113 (118 / 111), 8 x 128 K 110 / 138 (131 / 141);
+// of 64 rows 8 x 96 K 88 / 100 (93 / 100), 16 x 96 K 154 / 168 (159 / 170); of 16 rows 32 x 50 K 156 / 173, 32 x 75 K 201 / 245;
+// histories of at most 32768, 256 rows: 32 x 20 K 136 / 115, 32 x 32 K 177 / 170, 64 x 20 K 191 / 211 (1024 kept on average 238 / 234), 48 x 30 K 212 / 236,
+// 64 x 32 K 256 / 320, of 128 rows 64 x 32 K 200 / 216.  (More than 64 segments, before the probe: 128 x 16 K 329 / 323.)
 constexpr double kOneScanUs = 50, kOneScanFewRowsUs = 40, kOneScanResidentUs = 100;
 static void plan_q_resident(const Geometry& g, Plan& p) {
   const int cfg = p.R <= 64 ? 0 : p.R <= 128 ? 1 : p.R <= 256 ? 2 : 3;
@@ -3317,6 +3504,23 @@ static void plan_q_resident(const Geometry& g, Plan& p) {
   p.rsplit = 1;
   const double worth = lens.longest <= kSelRound ? kOneScanResidentUs : cfg == 2 ? kOneScanUs : kOneScanFewRowsUs;
   p.one_scan = best >= worth && (cfg == 2 || lens.longest > kSelRound) && p.R <= 256 && g.pool != SLKV_POOL_AVG && g.segs.size() <= (size_t)kMaxSegPerLaunch;
+}
+
+// Ranges of a call in one pass: the shortest that run at once, two workgroups on a CU, and that fold_sample reads in one round trip.
+// 32 segments of 20 K to 128 K keys: 511 ranges, chosen keys 20 us; 590 shorter ones, of which the last start when the first have ended, 28 us; 504, but those
+// of the short segments 6144 positions long, 24 to 55 us, by how many keys these list.  8 x 128 K: 64 ranges a segment and not 32, score_both 89 us and not 82.
+static void plan_ranges(const Geometry& g, Plan& p) {
+  for (const int sampled : {64, 96, 128, 192, 256, 288, 320, 384, 512}) {
+    p.sampled = sampled;
+    p.ranges = 0;
+    int64_t most = 0;
+    for (const Seg& s : g.segs) {
+      const int64_t n = seg_ranges(s, g.w, sampled);
+      p.ranges += n;
+      most = std::max(most, n);
+    }
+    if (p.ranges <= 512 && most <= 32) return;
+  }
 }
 
 static void make_plan(const Geometry& g, Plan& p) {
@@ -3349,12 +3553,13 @@ static void make_plan(const Geometry& g, Plan& p) {
   p.one_scan_bytes = 0;
   p.ranges = 0;
   if (p.one_scan) {
-    for (const Seg& s : g.segs) p.ranges += seg_ranges(s, g.w, p.CH);
+    plan_ranges(g, p);
     p.off_part0 = p.total_bytes;
-    p.off_bins = p.off_part0 + align((size_t)p.ranges * p.Rpad * sizeof(float));
-    p.off_lse = p.off_bins + S * kHistBins * sizeof(uint32_t);
-    p.off_bounds = p.off_lse + S * 256 * sizeof(float);
-    p.off_lists = p.off_bounds + align(S * 4 * sizeof(uint32_t));
+    p.off_dense = p.off_part0 + align((size_t)p.ranges * p.Rpad * sizeof(float));
+    p.off_bins = p.off_dense + align(S * 2 * p.Rpad * sizeof(float));
+    p.off_lse = p.off_bins + S * kHists * kHistBins * sizeof(uint32_t);
+    p.off_bounds = p.off_lse + S * 512 * sizeof(float);
+    p.off_lists = p.off_bounds + align(S * kBoundWords * sizeof(uint32_t));
     p.one_scan_bytes = p.off_lists + S * kSelCandidates * sizeof(uint32_t) - p.total_bytes;
   }
 }
@@ -3430,7 +3635,7 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
     const unsigned S = (unsigned)g.segs.size();
     if (pass == kPassSample)
       SLKV_LAUNCH((score_sample_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, one);
+                  g.k_stride_head, p.R, p.Rpad, g.w, c_log2, one);
     if (pass == kPassBoth)
       SLKV_LAUNCH((score_both_kernel<DK, MT, RB, KIND>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
                   g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, one);
@@ -3439,10 +3644,14 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
       for (const Seg& sg : g.segs)
         if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
       const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
-      SLKV_LAUNCH(approx_hist_kernel, dim3((unsigned)((longest + kApproxBlock - 1) / kApproxBlock), S), dim3(256), 0, st, tab, g.w, radius, imp, one.hist);
-      SLKV_LAUNCH(one_scan_bounds_kernel, dim3(S), dim3(256), 0, st, tab, g.w, p.R, p.Rpad, part, one, blockhist);
-      SLKV_LAUNCH((select_chosen_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab,
-                  (const uint16_t*)q, k, g.k_stride_tok, g.k_stride_head, p.R, g.w, p.CH, radius, c_log2, one, imp, pooled, blockhist);
+      SLKV_LAUNCH(approx_hist_kernel, dim3((unsigned)((longest + kApproxBlock - 1) / kApproxBlock + 1), S), dim3(256), 0, st, tab, g.w, radius, p.R, p.Rpad,
+                  part, imp, one);
+      auto exact = [&](int probe) {
+        SLKV_LAUNCH((select_chosen_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k,
+                    g.k_stride_tok, g.k_stride_head, p.R, g.w, radius, c_log2, one, imp, pooled, blockhist, probe);
+      };
+      exact(1);
+      exact(0);
     }
   }
 }
@@ -3481,7 +3690,8 @@ static void launch_score(int pass, ScoreGrid grid, hipStream_t st, const TAB& ta
 template <class TAB>
 static void launch_select(int nseg, int blocks, hipStream_t st, const TAB& tab, const Geometry& g, const float* imp,
                           float* pooled, uint32_t* blockhist, uint32_t* lists, int32_t* kept_idx, int64_t* d_out_offsets,
-                          const GatherArgs& ga, bool chosen) {
+                          const GatherArgs& ga, const OneScan& one) {
+  const bool chosen = one.hist != nullptr;
   const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
   const int pool_kernel = g.pool == SLKV_POOL_NONE ? 1 : g.pool_kernel;
 #define SLKV_POOL_LAUNCH(RAD)                                                                                          \
@@ -3509,12 +3719,12 @@ static void launch_select(int nseg, int blocks, hipStream_t st, const TAB& tab, 
   if (split && !chosen) {
     // first-level digit per segment, then the blocks list the scores of that digit
     SLKV_LAUNCH(select_rank_kernel<TAB>, dim3(nseg), dim3(kSelThreads), 0, st, tab, g.w, (const float*)pooled,
-                blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 0, 0);
+                blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 0, one);
     SLKV_LAUNCH(select_collect_kernel<TAB>, grid, dim3(kSelEmitThreads), 0, st, tab, g.w, (const float*)pooled, blockhist,
                 lists, rows ? 0 : -1);
   }
   SLKV_LAUNCH(select_rank_kernel<TAB>, dim3(nseg), dim3(kSelThreads), 0, st, tab, g.w, (const float*)pooled,
-              blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 1, chosen ? 1 : 0);
+              blockhist, kept_idx, d_out_offsets, ga, split, (const uint32_t*)lists, 1, one);
   if (split) {
     SLKV_LAUNCH(select_count_kernel<TAB>, grid, dim3(kSelEmitThreads), 0, st, tab, g.w, (const float*)pooled, blockhist,
                 rows ? 0 : -1);
@@ -3731,7 +3941,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   const bool one_scan = p.one_scan && !d_importance && !d_pooled && workspace_bytes >= p.total_bytes + p.one_scan_bytes;
   OneScan one{};
   if (one_scan)
-    one = OneScan{(float*)(ws + p.off_part0), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
+    one = OneScan{(float*)(ws + p.off_part0), (float*)(ws + p.off_dense), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
                   (uint32_t*)(ws + p.off_lists)};
   uint32_t* const gm = groups && !one_scan ? (uint32_t*)pooled : nullptr;
   auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, int64_t rows) -> slkv_status {
@@ -3765,7 +3975,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
         hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, gm, imp, pooled, d_kept_idx, d_out_offsets, ga);
         if (se != hipSuccess) return fail(SLKV_ERR_HIP, "select launch setup failed: %s", hipGetErrorString(se));
       } else {
-        launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, one_scan ? one.lists : lists, d_kept_idx, d_out_offsets, ga, one_scan);
+        launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, one_scan ? one.lists : lists, d_kept_idx, d_out_offsets, ga, one);
       }
     }
     const bool gather_all = !resident_select && blocks > 0;   // the block-wise selection copies no rows itself
@@ -3818,8 +4028,9 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     }
     if (!walk(tab.out_, tab.chunk_, tab.blk_)) return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
     if (one_scan) {
+      tab.sampled = p.sampled;
       tab.range_[0] = 0;
-      for (int64_t i = 0; i < S; ++i) tab.range_[i + 1] = tab.range_[i] + (int32_t)seg_ranges(g.segs[(size_t)i], g.w, p.CH);
+      for (int64_t i = 0; i < S; ++i) tab.range_[i + 1] = tab.range_[i] + (int32_t)seg_ranges(g.segs[(size_t)i], g.w, p.sampled);
     }
     return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
   }
