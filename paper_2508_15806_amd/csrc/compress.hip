@@ -671,48 +671,44 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     }
   }
   if (PASS == 2) return;
-  {
-    // A sum that left the fp32 range (logits far above the chunk's first ones): the whole
-    // workgroup repeats the chunk with the running maximum.  Not taken for ordinary inputs.
-    bool bad = false;
+  // A sum that left the fp32 range (logits far above the chunk's first ones): the whole
+  // workgroup repeats the chunk with the running maximum.  Not taken for ordinary inputs.
+  bool bad = false;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) bad = bad || !(s_run[mt] < INFINITY);
-    if (__syncthreads_or(bad ? 1 : 0)) {
+  for (int mt = 0; mt < MT; ++mt) bad = bad || !(s_run[mt] < INFINITY);
+  if (__syncthreads_or(bad ? 1 : 0)) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        m_run[mt] = -INFINITY;
-        s_run[mt] = 0.f;
-      }
-      for (int t = 0; t < ntiles; ++t) {          // plain loop, one tile in flight: this path is rare
-        issue_tile(t, pf0);
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-        do_tile(t, pf0, T{}, T{}, F{});
-      }
+    for (int mt = 0; mt < MT; ++mt) {
+      m_run[mt] = -INFINITY;
+      s_run[mt] = 0.f;
+    }
+    for (int t = 0; t < ntiles; ++t) {          // plain loop, one tile in flight: this path is rare
+      issue_tile(t, pf0);
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+      do_tile(t, pf0, T{}, T{}, F{});
     }
   }
 
-  {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      // (reference, sum) -> (log-sum-exp, 1): a sum referenced to early logits can be very large
-      // or small, and merging such pairs directly could lose it to an underflowing factor
-      m_run[mt] = s_run[mt] > 0.f ? m_run[mt] + __builtin_amdgcn_logf(s_run[mt]) : -INFINITY;
-      s_run[mt] = 1.f;
-      float m2 = __shfl_xor(m_run[mt], 32, 64);
-      float s2 = __shfl_xor(s_run[mt], 32, 64);
-      merge_stats(m_run[mt], s_run[mt], m2, s2);
-      if (half == 0) comb[ks][rb * 32 * MT + mt * 32 + l32] = make_float2(m_run[mt], s_run[mt]);
-    }
-    __syncthreads();
-    for (int row = tid; row < RB * 32 * MT; row += 256) {
-      float mm = comb[0][row].x, ss = comb[0][row].y;
-#pragma unroll
-      for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
-      // the chunk's log-sum-exp of the row (-inf: no key)
-      if (row < Rpad) part[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
-    }
-    SLKV_STAMP(256 + bid, 2);
+  for (int mt = 0; mt < MT; ++mt) {
+    // (reference, sum) -> (log-sum-exp, 1): a sum referenced to early logits can be very large
+    // or small, and merging such pairs directly could lose it to an underflowing factor
+    m_run[mt] = s_run[mt] > 0.f ? m_run[mt] + __builtin_amdgcn_logf(s_run[mt]) : -INFINITY;
+    s_run[mt] = 1.f;
+    float m2 = __shfl_xor(m_run[mt], 32, 64);
+    float s2 = __shfl_xor(s_run[mt], 32, 64);
+    merge_stats(m_run[mt], s_run[mt], m2, s2);
+    if (half == 0) comb[ks][rb * 32 * MT + mt * 32 + l32] = make_float2(m_run[mt], s_run[mt]);
   }
+  __syncthreads();
+  for (int row = tid; row < RB * 32 * MT; row += 256) {
+    float mm = comb[0][row].x, ss = comb[0][row].y;
+#pragma unroll
+    for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
+    // the chunk's log-sum-exp of the row (-inf: no key)
+    if (row < Rpad) part[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+  }
+  SLKV_STAMP(256 + bid, 2);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1054,8 +1050,6 @@ __global__ __launch_bounds__(256, 2) void score_both_kernel(const SegTable tab, 
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   float cs = 0.f;                                        // of the keys whose products are in the accumulators
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
   __builtin_amdgcn_s_waitcnt(0x0F70 | LPT);
   __syncthreads();
 #pragma unroll
@@ -3324,6 +3318,7 @@ struct Geometry {
   int64_t k_stride_tok, k_stride_head, v_stride_tok, v_stride_head;
   int64_t score_elems;   // length of the importance / pooled arrays
   std::vector<Seg> segs;
+  int64_t longest;       // ranked history (0: none)
 };
 
 struct Plan {
@@ -3346,6 +3341,12 @@ static int64_t seg_ranges(const Seg& s, int w, int sampled) {
   if (!seg_ranked(s.n, w, s.cap)) return 0;
   const int m = (int)(s.n - w), len = range_len(m, (int)(s.cap - w), sampled);
   return (m + len - 1) / len;
+}
+static int64_t longest_ranked(const Geometry& g) {
+  int64_t longest = 0;
+  for (const Seg& s : g.segs)
+    if (seg_ranked(s.n, g.w, s.cap)) longest = std::max(longest, s.n - g.w);
+  return longest;
 }
 static int64_t seg_blocks(const Seg& s, int w) { return seg_ranked(s.n, w, s.cap) ? (s.n - w + kSelBlock - 1) / kSelBlock : 0; }
 
@@ -3374,8 +3375,8 @@ static auto with_score_kind(int d, int dtype, F f) {
 struct RankedLengths {
   std::vector<float> len;
   std::vector<int> times;
-  int64_t longest = 1, ranked = 0;
-  explicit RankedLengths(const Geometry& g) {
+  int64_t longest, ranked = 0;
+  explicit RankedLengths(const Geometry& g) : longest(std::max<int64_t>(g.longest, 1)) {
     for (const Seg& s : g.segs)
       if (seg_ranked(s.n, g.w, s.cap)) {
         const float m1 = (float)(s.n - g.w - 1);
@@ -3385,7 +3386,6 @@ struct RankedLengths {
           len.push_back(m1);
           times.push_back(1);
         }
-        longest = std::max(longest, s.n - g.w);
         ++ranked;
       }
   }
@@ -3585,6 +3585,7 @@ static void layer_geometry(const slkv_layer_desc* d, Geometry& g) {
       s.score_off = (int64_t)d->Hkv * d->h_cu_seqlens[b] + (int64_t)h * n;
     }
   }
+  g.longest = longest_ranked(g);
 }
 
 static void ragged_geometry(const slkv_ragged_desc* d, Geometry& g) {
@@ -3607,6 +3608,7 @@ static void ragged_geometry(const slkv_ragged_desc* d, Geometry& g) {
     s.qrow_off = ((int64_t)b * d->Hq + (int64_t)h * G) * d->w;
     s.score_off = d->h_in_offsets[i] - d->h_in_offsets[0];
   }
+  g.longest = longest_ranked(g);
 }
 
 // Grid of a scoring launch: `chunks` workgroups in a row, or (rows > 0) one row of `per_row`
@@ -3618,37 +3620,42 @@ struct ScoreGrid {
 // The passes of a call: 1 and 2, or these three.
 constexpr int kPassSample = 0, kPassBoth = 3, kPassChosen = 4;
 
+// What the scoring passes write, for each other and for the selection.
+struct ScoreBuffers {
+  float *part, *imp;
+  uint32_t* gm;            // largest scores of the groups, or NULL
+  OneScan one;             // the rest is for one pass over the keys
+  float* pooled;
+  uint32_t* blockhist;     // or NULL: one workgroup per segment selects
+};
+
 template <int DK, int MT, int RB, int KIND, class TAB>
 static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                              const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
-                              uint32_t* blockhist, uint32_t* gm) {
+                              const Geometry& g, const Plan& p, float c_log2, const ScoreBuffers& buf) {
   // segments with like chunk counts: one grid row per segment (see the kernel's first lines)
   const bool two = grid.rows > 0;
   const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
-  auto scan = [&](auto pass_c, dim3 grid_c, float* part_c) {
-    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, decltype(pass_c)::value, KIND, TAB>), grid_c, dim3(256), 0, st, tab, (const uint16_t*)q, k,
-                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part_c, imp, two ? 1 : 0, gm);
+  auto scan = [&](auto pass_c) {
+    SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, decltype(pass_c)::value, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.gm);
   };
-  if (pass == 1) scan(std::integral_constant<int, 1>{}, gr, part);
-  if (pass == 2) scan(std::integral_constant<int, 2>{}, gr, part);
+  if (pass == 1) scan(std::integral_constant<int, 1>{});
+  if (pass == 2) scan(std::integral_constant<int, 2>{});
   if constexpr (MT <= 2 && std::is_same_v<TAB, SegTable>) {
     const unsigned S = (unsigned)g.segs.size();
     if (pass == kPassSample)
       SLKV_LAUNCH((score_sample_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, c_log2, one);
+                  g.k_stride_head, p.R, p.Rpad, g.w, c_log2, buf.one);
     if (pass == kPassBoth)
       SLKV_LAUNCH((score_both_kernel<DK, MT, RB, KIND>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, one);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.one);
     if (pass == kPassChosen) {
-      int64_t longest = 0;
-      for (const Seg& sg : g.segs)
-        if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
       const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
-      SLKV_LAUNCH(approx_hist_kernel, dim3((unsigned)((longest + kApproxBlock - 1) / kApproxBlock + 1), S), dim3(256), 0, st, tab, g.w, radius, p.R, p.Rpad,
-                  part, imp, one);
+      SLKV_LAUNCH(approx_hist_kernel, dim3((unsigned)((g.longest + kApproxBlock - 1) / kApproxBlock + 1), S), dim3(256), 0, st, tab, g.w, radius, p.R, p.Rpad,
+                  buf.part, buf.imp, buf.one);
       auto exact = [&](int probe) {
         SLKV_LAUNCH((select_chosen_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k,
-                    g.k_stride_tok, g.k_stride_head, p.R, g.w, radius, c_log2, one, imp, pooled, blockhist, probe);
+                    g.k_stride_tok, g.k_stride_head, p.R, g.w, radius, c_log2, buf.one, buf.imp, buf.pooled, buf.blockhist, probe);
       };
       exact(1);
       exact(0);
@@ -3658,32 +3665,30 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
 
 template <int DK, int KIND, class TAB>
 static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                           const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
-                              uint32_t* blockhist, uint32_t* gm) {
+                           const Geometry& g, const Plan& p, float c_log2, const ScoreBuffers& buf) {
   if constexpr (KIND <= 1) {
-    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
-    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
-    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
-    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
+    if (p.R <= 64) launch_q_resident<DK, 1, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, buf);
+    else if (p.R <= 128) launch_q_resident<DK, 2, 2, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, buf);
+    else if (p.R <= 256) launch_q_resident<DK, 2, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, buf);
+    else launch_q_resident<DK, 4, 4, KIND>(pass, grid, st, tab, q, k, g, p, c_log2, buf);
   } else {
     const bool two = grid.rows > 0;
     const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
     const size_t lds = score_lds_bytes<DK, KIND>(std::min((p.R + 31) / 32, ScoreCfg<DK, KIND>::RBT), p.waves);
     if (pass == 1)
       SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 1, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit, gm);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, p.rsplit, buf.gm);
     else
       SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 2, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, part, imp, two ? 1 : 0, p.rsplit, gm);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, p.rsplit, buf.gm);
   }
 }
 
 template <class TAB>
 static void launch_score(int pass, ScoreGrid grid, hipStream_t st, const TAB& tab, const void* q, const void* k,
-                         const Geometry& g, const Plan& p, float c_log2, float* part, float* imp, const OneScan& one, float* pooled,
-                              uint32_t* blockhist, uint32_t* gm) {
+                         const Geometry& g, const Plan& p, float c_log2, const ScoreBuffers& buf) {
   with_score_kind(g.d, g.dtype, [&](auto dk, auto kind) {
-    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, part, imp, one, pooled, blockhist, gm);
+    launch_score_k<decltype(dk)::value, decltype(kind)::value>(pass, grid, st, tab, q, k, g, p, c_log2, buf);
   });
 }
 
@@ -3710,8 +3715,7 @@ static void launch_select(int nseg, int blocks, hipStream_t st, const TAB& tab, 
   // with blocks, the ordered compaction runs per block (two short launches over the whole chip)
   // instead of per segment inside the ranking workgroup
   const int split = blocks > 0 ? 1 : 0;
-  int64_t longest = 0;
-  for (const Seg& sg : g.segs) longest = std::max<int64_t>(longest, seg_blocks(sg, g.w));
+  const int64_t longest = (g.longest + kSelBlock - 1) / kSelBlock;
   // block-wise launches: a grid row per segment unless that would launch mostly empty workgroups
   // (one long history among many short ones) or more rows than a grid has
   const bool rows = nseg <= 65535 && longest * nseg <= 4 * (int64_t)blocks;
@@ -3815,12 +3819,9 @@ template <int RADIUS, class TAB>
 static hipError_t launch_select_resident_r(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                            const GatherArgs& ga) {
-  int64_t longest = 0;
-  for (const Seg& sg : g.segs)
-    if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
-  if (longest <= kSelThreads * kSelEPTSmall)
+  if (g.longest <= kSelThreads * kSelEPTSmall)
     return launch_select_resident_e<RADIUS, kSelEPTSmall>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
-  if (longest <= kSelThreads * kSelEPTMid)
+  if (g.longest <= kSelThreads * kSelEPTMid)
     return launch_select_resident_e<RADIUS, kSelEPTMid>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
   return launch_select_resident_e<RADIUS, kSelEPT>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
 }
@@ -3924,18 +3925,13 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   // The kernels of the pass over the segments one table describes.
   // Selection kernel: if every history fits one round, the one-workgroup-per-segment kernel;
   // otherwise the histories are cut into blocks.
-  bool resident_select = select_mode() != 2;
-  for (const Seg& sg : g.segs)
-    if (seg_ranked(sg.n, g.w, sg.cap) && sg.n - g.w > kSelRound) resident_select = false;
+  const bool resident_select = select_mode() != 2 && g.longest <= kSelRound;
   const int nseg = (int)S;
   // The selection starts from the groups' largest scores where a thread would have 32 positions to go through otherwise (with 8 or 2 the shorter
   // chain of phases wins: 8 x 8 K keys 25.7 us either way, 8 x 900 keys 22.4 us without, 24.8 with), and not for
   // fp32, whose scoring kernel got slower by it on short calls (4 x 1 K 19.7 -> 20.1).  They lie in the pooled array, which nobody writes then.
-  int64_t longest = 0;
-  for (const Seg& sg : g.segs)
-    if (seg_ranked(sg.n, g.w, sg.cap)) longest = std::max<int64_t>(longest, sg.n - g.w);
   // (a group's place counts the segments before it, see group_off: with thousands of empty ones the array may be too short)
-  const bool groups = resident_select && !d_pooled && g.pool != SLKV_POOL_AVG && g.dtype != SLKV_F32 && longest > kSelThreads * kSelEPTMid &&
+  const bool groups = resident_select && !d_pooled && g.pool != SLKV_POOL_AVG && g.dtype != SLKV_F32 && g.longest > kSelThreads * kSelEPTMid &&
                       g.score_elems / kGroup + S + 1 <= g.score_elems;
   // one pass over the keys where no importance or pooled score is asked for: only the selection is exact there
   const bool one_scan = p.one_scan && !d_importance && !d_pooled && workspace_bytes >= p.total_bytes + p.one_scan_bytes;
@@ -3944,6 +3940,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     one = OneScan{(float*)(ws + p.off_part0), (float*)(ws + p.off_dense), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
                   (uint32_t*)(ws + p.off_lists)};
   uint32_t* const gm = groups && !one_scan ? (uint32_t*)pooled : nullptr;
+  const ScoreBuffers buf{part, imp, gm, one, pooled, resident_select ? nullptr : blockhist};
   auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, int64_t rows) -> slkv_status {
     using TAB = std::decay_t<decltype(tab)>;
     // one grid row per segment where that leaves at most a seventh of the grid empty (a segment with
@@ -3958,15 +3955,15 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     if (chunks > 0) {
       {
         ScopedKernelTimer tm(SLKV_K_SCORE_STATS, st);
-        launch_score(one_scan ? kPassSample : 1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
+        launch_score(one_scan ? kPassSample : 1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
       }
       if (one_scan) {
         ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
-        launch_score(kPassBoth, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
-        launch_score(kPassChosen, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
+        launch_score(kPassBoth, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
+        launch_score(kPassChosen, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
       } else if (max_chunks > 1 || !k_resident) {             // (score_k_resident_kernel completes segments of one chunk in its first pass)
         ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
-        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, part, imp, one, pooled, resident_select ? nullptr : blockhist, gm);
+        launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
       }
     }
     {
