@@ -317,13 +317,17 @@ slkv_status slkv_recompress_layer(const slkv_ragged_desc* desc, const void* d_qw
  * every kernel the library launches is bracketed by a HIP event pair on the call's stream.
  * slkv_profile_begin creates the events it needs (the only state the library ever keeps);
  * slkv_profile_end waits for the recorded events, writes up to `capacity` records in launch
- * order and sets *count to the number recorded.  Process-wide; not meant for production.
+ * order and sets *count to the number recorded.  A call of slkv_compress_layer or slkv_recompress_layer makes at most 9 records
+ * (two passes, long histories: 1 + 1 + 6 + 1; one pass: 1 + 4 + 3 + 1; histories up to 32768: 1 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1).
+ * Process-wide; not meant for production.
  */
 typedef enum {
-  SLKV_K_SCORE_STATS = 0,   /* logits + per-row sum-exp of every key chunk */
+  SLKV_K_SCORE_STATS = 0,   /* logits + per-row sum-exp of every key chunk; in one pass over the keys, the sample of them */
   SLKV_K_COMBINE = 1,       /* not launched any more: SLKV_K_SCORE_ACCUM folds the chunks itself */
-  SLKV_K_SCORE_ACCUM = 2,   /* logits + exp(logit - lse) summed down the rows */
-  SLKV_K_SELECT = 3,        /* pooling + top-k (one record per launch: one launch for histories up to 32768 positions, six for longer ones) */
+  SLKV_K_SCORE_ACCUM = 2,   /* logits + exp(logit - lse) summed down the rows (one launch); in one pass over the keys: the
+                               pass, the histograms, and two launches that compute some scores exactly (four records) */
+  SLKV_K_SELECT = 3,        /* pooling + top-k (one record per launch: one launch for histories up to 32768 positions, six for longer
+                               ones, three after one pass over the keys) */
   SLKV_K_GATHER = 4,        /* K/V row gather */
   SLKV_K_ROW_CELLS = 5,     /* Stage 1: per-row weight cells */
   SLKV_K_HEAD_REDUCE = 6,   /* Stage 1: per-head sums and scores */

@@ -222,3 +222,17 @@ def test_concentrated_attention_takes_no_longer(shape):
             torch.cuda.synchronize()
             best[name] = min(best.get(name, 1e9), start.elapsed_time(end) / 10)
     assert best["one"] < 1.05 * best["two"], best
+
+
+def test_records_of_a_call():
+    """Launches that the timing of a call records, as the header counts them."""
+    import torch
+    caps = np.array([233, 3459, 241, 280, 256, 240, 302, 271], dtype=np.int32)
+    for lens, one, two in (([131072], [0, 2, 2, 2, 2, 3, 3, 3, 4], [0, 2, 3, 3, 3, 3, 3, 3, 4]), ([32768] * 8, [0, 2, 2, 2, 2, 3, 4], [0, 2, 3, 4])):
+        call = one_pass("bf16", 32, 8, 128, 64, lens, caps)
+        for workspace, want in ((call.workspace, one), (call.workspace[:-256].clone(), two)):
+            call.workspace = workspace
+            B.slkv_profile_begin(16)
+            call.again()
+            torch.cuda.synchronize()
+            assert [k for k, _ in B.slkv_profile_end(16)] == [B.KERNEL_NAMES[x] for x in want]
