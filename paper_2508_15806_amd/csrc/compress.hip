@@ -50,7 +50,7 @@ struct SegShape {
 // takes in more keys.  32 segments of 20 K to 128 K keys, us of the sample and of the chosen keys: 170 kept 24 + 22 (8192 keys whatever is kept: 40 + 22);
 // 1500 kept 25 + 39 (2048 keys: 20 + 53; 8192: 39 + 39); 3300 kept 31 + 42 (2048: 19 + 89).
 // A workgroup of the kernels that go over the sample, and over the scores before the selection, takes a range of positions with `sampled` such keys (plan_ranges).
-constexpr int kSampleGroup = 8, kRangeMost = 6144;
+constexpr int kSampleGroup = 8, kRangeMost = 6144;   // (6144 positions: the scores and the list of two workgroups fit a CU's LDS)
 __device__ __host__ __forceinline__ int sample_step(int m, int kk) {
   const int keys = 4 * kk < 2048 ? 2048 : 4 * kk > 8192 ? 8192 : 4 * kk;
   return m / keys > 4 ? m / keys : 4;
@@ -63,7 +63,7 @@ __device__ __host__ __forceinline__ int range_len(int m, int kk, int sampled) {
 // Up to kMaxSegPerLaunch segments: everything per segment, in a kernel argument, so that one round of loads from
 // it (cold at every launch) answers a workgroup that knows its segment.
 struct SegTable {
-  int32_t nseg, sampled;                  // (sampled: of range_len)
+  int32_t nseg;
   int32_t tok_[kMaxSegPerLaunch], n_[kMaxSegPerLaunch], head_[kMaxSegPerLaunch], kk_[kMaxSegPerLaunch], score_[kMaxSegPerLaunch];
   int32_t out_[kMaxSegPerLaunch + 1];     // first output row of the segment
   int32_t chunk_[kMaxSegPerLaunch + 1];   // prefix of key-chunk counts (0 chunks when not ranked)
@@ -774,7 +774,7 @@ __device__ __forceinline__ float sum_halves(float v) {
 // score_q_resident_kernel, 4 waves of 64 rows at 256 registers, 41 us where this takes 25.)
 template <int DK, int RB, int KIND>
 __global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
-                                                              int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w,
+                                                              int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w, int sampled_keys,
                                                               float c_log2, const OneScan one) {
   constexpr int NT = 512, KS = 8 / RB, TK = KS == 4 ? 128 : 64, NSUB = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2 + 16, CPR = DK * 2 / 16;
   constexpr int LPT = TK * CPR / NT;
@@ -785,7 +785,7 @@ __global__ __launch_bounds__(512, 4) void score_sample_kernel(const SegTable tab
   const int bid = blockIdx.x;
   const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.range_begin(s); });
   const SegShape sg = tab.shape(seg);
-  const int m = sg.n - w, len = range_len(m, sg.kk, tab.sampled), r0 = tab.range_begin(seg), begin = (bid - r0) * len, keys = min(len, m - begin);
+  const int m = sg.n - w, len = range_len(m, sg.kk, sampled_keys), r0 = tab.range_begin(seg), begin = (bid - r0) * len, keys = min(len, m - begin);
   // key u of the sample: the range's first `head` keys, its last `tail`, then, of those between, kSampleGroup neighbours every `stride` keys, which
   // stand for e^log_weight keys each
   int head = keys, tail = 0, stride = 1, total = keys;
@@ -1352,7 +1352,7 @@ __device__ __forceinline__ OneScanBounds one_scan_bounds(const uint32_t* __restr
 //   them counted in a histogram, so that the block-wise selection starts at phase 1 of select_rank_kernel.
 template <int DK, int RB, int KIND>
 __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable tab, const uint16_t* __restrict__ q, const void* __restrict__ kmat_v,
-                                                               int64_t k_stride_tok, int64_t k_stride_head, int R, int w, int radius,
+                                                               int64_t k_stride_tok, int64_t k_stride_head, int R, int w, int sampled_keys, int radius,
                                                                float c_log2, const OneScan one, float* __restrict__ imp,
                                                                float* __restrict__ pooled, uint32_t* __restrict__ blockhist, int probe) {
   constexpr int NT = 512, KS = 8 / RB, TK = KS == 4 ? 128 : 64, NSUB = TK / 32 / KS, KK = DK / 16, ROWB = DK * 2 + 16, CPR = DK * 2 / 16;
@@ -1372,7 +1372,7 @@ __global__ __launch_bounds__(512, 4) void select_chosen_kernel(const SegTable ta
   const int bid = (int)(gridDim.x - 1 - blockIdx.x);     // (the last segments' first: short ones have the most to do)
   const int seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.range_begin(s); });
   const SegShape sg = tab.shape(seg);
-  const int m = sg.n - w, len = range_len(m, sg.kk, tab.sampled), begin = (bid - tab.range_begin(seg)) * len;
+  const int m = sg.n - w, len = range_len(m, sg.kk, sampled_keys), begin = (bid - tab.range_begin(seg)) * len;
   const bool pools = blockhist || probe;
   const int reach = pools ? radius : 0;
   uint32_t* const H = one.hist + (size_t)seg * kHists * kHistBins;
@@ -3645,7 +3645,7 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
     const unsigned S = (unsigned)g.segs.size();
     if (pass == kPassSample)
       SLKV_LAUNCH((score_sample_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, c_log2, buf.one);
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.sampled, c_log2, buf.one);
     if (pass == kPassBoth)
       SLKV_LAUNCH((score_both_kernel<DK, MT, RB, KIND>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k, g.k_stride_tok,
                   g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.one);
@@ -3655,7 +3655,7 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
                   buf.part, buf.imp, buf.one);
       auto exact = [&](int probe) {
         SLKV_LAUNCH((select_chosen_kernel<DK, MT * RB, KIND>), dim3((unsigned)p.ranges), dim3(512), 0, st, tab, (const uint16_t*)q, k,
-                    g.k_stride_tok, g.k_stride_head, p.R, g.w, radius, c_log2, buf.one, buf.imp, buf.pooled, buf.blockhist, probe);
+                    g.k_stride_tok, g.k_stride_head, p.R, g.w, p.sampled, radius, c_log2, buf.one, buf.imp, buf.pooled, buf.blockhist, probe);
       };
       exact(1);
       exact(0);
@@ -4025,7 +4025,6 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     }
     if (!walk(tab.out_, tab.chunk_, tab.blk_)) return fail(SLKV_ERR_BAD_ARG, "too many key chunks");
     if (one_scan) {
-      tab.sampled = p.sampled;
       tab.range_[0] = 0;
       for (int64_t i = 0; i < S; ++i) tab.range_[i + 1] = tab.range_[i] + (int32_t)seg_ranges(g.segs[(size_t)i], g.w, p.sampled);
     }
