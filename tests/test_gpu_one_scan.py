@@ -105,7 +105,8 @@ def both(dtype, Hq, Hkv, d, w, lens, caps, kernel=7, pool=B.SLKV_POOL_MAX, shape
         else:
             call = api.LayerCall(dtype, nseq, Hq, Hkv, d, w, cu, caps, kernel, pool, debug_scores=debug, k_strides=strides, v_strides=strides)
             call.run(q, k, v)
-            call.again = lambda c=call: c.run(q, k, v)
+            call.inputs = q, k, v
+            call.again = lambda c=call: c.run(*c.inputs)
         torch.cuda.synchronize()
         bits = {4: torch.int32, 2: torch.int16, 1: torch.uint8}[k.element_size()]
         out.append([call.kept_idx, call.out_offsets, call.k_out.view(bits), call.v_out.view(bits)])
@@ -236,3 +237,24 @@ def test_records_of_a_call():
             call.again()
             torch.cuda.synchronize()
             assert [k for k, _ in B.slkv_profile_end(16)] == [B.KERNEL_NAMES[x] for x in want]
+
+
+def test_replay_over_inputs_that_take_different_ways():
+    """One captured call, one workspace: diffuse keys, keys that ask for a probe, and keys whose scores are counted instead of listed, in turn."""
+    import torch
+    lens, caps = [131072, 20000], np.array([233, 3459, 241, 280, 256, 240, 302, 271], dtype=np.int32)
+    calls = []
+    for shape in ("random", (16, 0.9, 1.0), "equal keys"):
+        call = one_pass("bf16", 32, 8, 128, 64, lens, caps, shape=shape)
+        calls.append((call, call.inputs, call.kept_idx.clone(), call.k_out.clone()))
+    call, (q, k, v) = calls[0][0], [x.clone() for x in calls[0][1]]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call.run(q, k, v)
+    for i in (1, 0, 2, 1, 2, 0, 0):
+        for own, given in zip((q, k, v), calls[i][1]):
+            own.copy_(given)
+        call.kept_idx.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(call.kept_idx, calls[i][2]) and torch.equal(call.k_out, calls[i][3])
