@@ -739,8 +739,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 // Of 131072 keys, 256 rows, 2 per cent of the keys pulled towards a query, 170 (3395) positions kept: 2300 (8400) keys are sampled, 40 to 70
 // (1000) computed again.  With 1 row, or 16, that give half (0.9) of their weight to one key in the middle: 40 to 60 (800) in the probe and 30 to 60
 // (1000 to 2100) behind it, where all of them were computed again without a probe.
-// 32 segments of 20 K to 128 K keys, 256 rows, us: the two passes 160 + 176, their selection 52; sample 24, scan 184, histograms 13, bounds 6 (with a
-// probe 15), chosen keys 20, selection 22.  The call, two passes / this: 407 / 278; one row at 0.9 404 / 307 (531 without the
+// 32 segments of 20 K to 128 K keys, 256 rows, us: the two passes 160 + 176, their selection 52; sample 24, scan 184, histograms 13, bounds 7 (with a
+// probe 20), chosen keys 20 (30), selection 22 (33).  The call, two passes / this: 407 / 278; one row at 0.9 404 / 307 (531 without the
 // probe); 16 rows at 0.9 404 / 307 (528); 256 rows, a random share each 413 / 368; the queries 3 times as large 405 / 304 (481).  The worst found: the queries 5 times as
 // large, where the sample says nothing, 404 / 498; a tenth of the positions kept and 256 rows with a random share each 470 / 570.
 constexpr int kDenseKeys = 128;      // so many of a history's first and last keys are all in the sample (attention sinks, recent tokens);
