@@ -219,9 +219,8 @@ slkv_status slkv_compacted_sizes(const slkv_layer_desc* desc, int64_t* h_out_off
                                  int64_t* total_kept);
 /* Device workspace slkv_compress_layer needs for this descriptor.
  * A workspace has to be ZERO-FILLED ONCE by the caller before the first call that uses it (its
- * first SLKV_WORKSPACE_HEADER_BYTES are a header that the present kernels do not use); every call leaves
- * them zero, so the same
- * workspace serves any number of later calls, of any descriptor it is large enough for, also
+ * first SLKV_WORKSPACE_HEADER_BYTES are a header of counters through which the workgroups of a launch
+ * wait for each other); every call leaves them zero, so the same workspace serves any number of later calls, of any descriptor it is large enough for, also
  * from a replayed HIP graph.  Its other contents are scratch.  Two calls that may overlap in
  * time need a workspace each.  For calls with long histories the size includes room to go over the keys once instead of
  * twice; they accept, with the same results, a workspace that lacks that room. */
@@ -318,13 +317,14 @@ slkv_status slkv_recompress_layer(const slkv_ragged_desc* desc, const void* d_qw
  * slkv_profile_begin creates the events it needs (the only state the library ever keeps);
  * slkv_profile_end waits for the recorded events, writes up to `capacity` records in launch
  * order and sets *count to the number recorded.  A call of slkv_compress_layer or slkv_recompress_layer makes at most 9 records
- * (two passes, long histories: 1 + 1 + 6 + 1; one pass: 1 + 4 + 3 + 1; histories up to 32768: 1 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1).
+ * (two passes, long histories: 1 + 1 + 6 + 1; one pass: 1 + 4 + 3 + 1; histories up to 32768: 1 + 1 + 1 + 1, both passes in
+ * one launch 0 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1).
  * Process-wide; not meant for production.
  */
 typedef enum {
   SLKV_K_SCORE_STATS = 0,   /* logits + per-row sum-exp of every key chunk; in one pass over the keys, the sample of them */
   SLKV_K_COMBINE = 1,       /* not launched any more: SLKV_K_SCORE_ACCUM folds the chunks itself */
-  SLKV_K_SCORE_ACCUM = 2,   /* logits + exp(logit - lse) summed down the rows (one launch); in one pass over the keys: the
+  SLKV_K_SCORE_ACCUM = 2,   /* logits + exp(logit - lse) summed down the rows (one launch, which may hold the first pass too); in one pass over the keys: the
                                pass, the histograms, and two launches that compute some scores exactly (four records) */
   SLKV_K_SELECT = 3,        /* pooling + top-k (one record per launch: one launch for histories up to 32768 positions, six for longer
                                ones, three after one pass over the keys) */

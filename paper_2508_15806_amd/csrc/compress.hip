@@ -3,6 +3,7 @@
 //   (long histories of 16-bit keys: score_sample, score_both, .. , one pass and exact scores only where they decide)
 //   pass 2  score_*<.., 2>  the chunks folded into the rows' log-sum-exp, logits again, exp(logit - lse) summed down
 //                            the G*w rows -> importance
+//   (16-bit keys, where the workgroups fit the chip at once: both in one launch, score_q_resident_kernel<.., 3>)
 //   select                   1-D pooling + per-head top-k (radix select, ordered compaction)
 //   gather                   kept K/V rows -> compacted ragged cache
 // 16-bit keys: 32x32x16 MFMA, queries held in registers, key tiles staged in LDS (score_q_resident_kernel).  E4M3 keys
@@ -171,6 +172,7 @@ __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float 
 // key.  ROWS >= NT: a thread per row.  Every thread must call it; ends with a barrier if LDS was used.
 // (The chunk that arrives last at a per-segment ticket did this at the end of the first pass: 4 us there, against
 // 0.5 to 3 us here, where the loads travel with those of the keys and queries.)
+template <bool SHARED = false>   // SHARED: written by other workgroups of the same launch (see meet_chunks)
 __device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c0, int c1, int Rpad, int row0, int rows, int nt,
                                            float2* fold) {
   const int tid = threadIdx.x;
@@ -183,7 +185,10 @@ __device__ __forceinline__ float fold_rows(const float* __restrict__ part, int c
     for (int c = c0 + sub; c < c1; c += NB * nsub) {
       float v[NB];
 #pragma unroll
-      for (int u = 0; u < NB; ++u) v[u] = part[(int64_t)min(c + u * nsub, c1 - 1) * Rpad + row0 + row];
+      for (int u = 0; u < NB; ++u) {
+        const float* const p = part + ((int64_t)min(c + u * nsub, c1 - 1) * Rpad + row0 + row);
+        v[u] = SHARED ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+      }
 #pragma unroll
       for (int u = 0; u < NB; ++u) v[u] = c + u * nsub < c1 ? v[u] : -INFINITY;
       float bm = v[0];
@@ -253,6 +258,48 @@ __device__ __forceinline__ float fold_sample(const float* __restrict__ part, con
   return ss > 0.f ? mu + __builtin_amdgcn_logf(ss) : INFINITY;
 }
 
+// Where the workgroups of a segment that hold its chunks meet inside one launch: a 64-bit word per segment in the
+// workspace's header, 64 bytes apart, zero before the launch and cleared by the selection.  The upper 16 bits count the
+// chunks whose statistics are in memory, bit c of the others says that the workgroup of chunk c has left.
+//   A workgroup waits for the others a bounded time.  They may not be on the chip together (another stream's kernels hold
+// CUs, or such a launch of another call does and waits as well), so one that has waited `limit` says so in its chunk's
+// bit and leaves its place to those that wait for one; nobody depends on it any more.  The bits are set and the
+// count is raised in the same word, so the bits that stand when the count is full are all there will be: who sees it
+// full takes its own chunk, and then, one by one, those whose bits it clears.
+//   Statistics are stored and read past the caches of the XCDs (agent scope), each store complete before its chunk is
+// counted: 0.9 us to store and count, 0.6 to 1.2 for the others to see it, 1.3 to read 32 chunks of 256 rows.  (With a
+// release and an acquire fence at that scope, which write back and invalidate the L2s: 8 to 12 us each, 256 workgroups.)
+constexpr int kMeetMost = 48, kMeetWords = 8;
+constexpr int kMeetSegments = SLKV_WORKSPACE_HEADER_BYTES / (kMeetWords * 8);
+typedef unsigned long long meet_t;
+// The count of the other chunks has been seen full: the bits that stand; or kMeetLeft: somebody else completes this chunk.  In thread 0 alone.
+constexpr meet_t kMeetLeft = ~0ull;
+__device__ __forceinline__ meet_t meet_chunks(meet_t* word, int nchunks, int chunk, int limit) {
+  const meet_t full = (meet_t)nchunks, bit = 1ull << chunk, bits = (1ull << kMeetMost) - 1;
+  meet_t w = __hip_atomic_fetch_add(word, 1ull << kMeetMost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + (1ull << kMeetMost);
+  if (w >> kMeetMost == full) return w & bits;
+  const long long start = wall_clock64();
+  do {
+    __builtin_amdgcn_s_sleep(1);
+    w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (w >> kMeetMost == full) return w & bits;
+  } while (wall_clock64() - start < limit);
+  w = __hip_atomic_fetch_or(word, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (w >> kMeetMost != full) return kMeetLeft;
+  // full meanwhile: this chunk again, unless somebody has taken it
+  w = __hip_atomic_fetch_and(word, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return w & bit ? w & bits & ~bit : kMeetLeft;
+}
+// A chunk of those in `left` that nobody else completes, or -1.  In thread 0 alone.
+__device__ __forceinline__ int meet_take(meet_t* word, meet_t& left) {
+  while (left) {
+    const int c = __ffsll(left) - 1;
+    left &= left - 1;
+    if (__hip_atomic_fetch_and(word, ~(1ull << c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> c & 1) return c;
+  }
+  return -1;
+}
+
 // Per segment: the words of OneScanBounds; smallest, largest and mean rho.
 constexpr int kBoundWords = 12, kBoundProbe = 4, kBoundWide = 5, kBoundRho = 6;
 
@@ -295,9 +342,8 @@ __device__ __forceinline__ void tile_priority(int t) {
 // element at row 8*(i/4) + 4*(lane/32) + i%4, column lane%32.
 //   PASS 1: D[key][qrow]: a lane owns one query row per MFMA tile -> sum of exp2(x - reference).
 //   PASS 2: D[qrow][key]: a lane owns one key column -> sum over rows of exp2(x - lse[row]).
+//   PASS 3: both, in one launch: the workgroups of a segment meet in between (meet_chunks).
 // Rows beyond R and keys beyond the chunk are loaded from a clamped (valid) address and masked.
-// Segments of a single chunk take both passes as well (unlike in score_k_resident_kernel): pass 1 does not hold the
-// other operand order; not tried.  8 segments of 160 rows: 6.3 us and 6.6 us.
 constexpr int kTileKeys = 64;
 constexpr int kPrefetch = 2;
 
@@ -306,7 +352,9 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
                                                          const void* __restrict__ kmat_v, int64_t k_stride_tok,
                                                          int64_t k_stride_head, int R, int Rpad, int w, int CH,
                                                          float c_log2, float* __restrict__ part,
-                                                         float* __restrict__ imp, int grid2d, uint32_t* __restrict__ gm) {
+                                                         float* __restrict__ imp, int grid2d, uint32_t* __restrict__ gm,
+                                                         meet_t* __restrict__ meet, int limit) {
+  constexpr bool STATS = PASS != 2, BOTH = PASS == 3;
   constexpr int KS = 4 / RB;               // waves along the keys
   constexpr int TK = kTileKeys;
   constexpr int NSUB = TK / 32 / KS;       // 32-key sub-tiles per wave per tile
@@ -352,10 +400,14 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   if (PASS == 1) SLKV_STAMP(256 + bid, 0);
   const int chunk = bid - se.chunk0;
   const int m = se.n - w;
-  const int key_begin = chunk * CH;
-  const int key_end = min(m, key_begin + CH);
-  // tiles are processed in pairs (one per register slot); a surplus tile is fully masked
-  const int ntiles = ((key_end - key_begin + TK - 1) / TK + 1) & ~1;
+  int key_begin, key_end, ntiles;
+  auto set_chunk = [&](int c) __attribute__((always_inline)) {
+    key_begin = c * CH;
+    key_end = min(m, key_begin + CH);
+    // tiles are processed in pairs (one per register slot); a surplus tile is fully masked
+    ntiles = ((key_end - key_begin + TK - 1) / TK + 1) & ~1;
+  };
+  set_chunk(chunk);
   // uniform 64-bit base of the segment's keys + 32-bit byte offsets (the host checks the range)
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat_v) +
       ((int64_t)se.head * k_stride_head + (int64_t)se.tok_begin * k_stride_tok) * 2;
@@ -398,8 +450,20 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   // pass 2: log-sum-exp of the rows from that of the segment's chunks (see fold_rows), handed to the lanes
   // through LDS once the other loads have landed
   constexpr int ROWS = RB * 32 * MT, NLSE = (ROWS + 255) / 256;
-  float lse_ld[PASS == 2 ? NLSE : 1];
-  float lse_r[PASS == 2 ? MT : 1][16];
+  float lse_ld[NLSE];
+  float lse_r[MT][16];
+  auto share_lse = [&]() __attribute__((always_inline)) {
+    float* lse_s = reinterpret_cast<float*>(&comb[0][0]);
+    static_assert(sizeof(comb) >= NLSE * 256 * sizeof(float), "comb holds one value per thread and load");
+#pragma unroll
+    for (int j = 0; j < NLSE; ++j) lse_s[tid + j * 256] = tid + j * 256 < R ? lse_ld[j] : INFINITY;
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        lse_r[mt][i] = lse_s[rb * 32 * MT + mt * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
+  };
   if (PASS == 2) {
     float2* const fold = reinterpret_cast<float2*>(&ktile[0][0]);   // (no key has been stored yet)
 #pragma unroll
@@ -422,7 +486,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     }
   };
   // one tile: registers -> LDS, refill the register slot, barrier, MFMAs + epilogue
-  auto do_tile = [&](int t, u32x4 (&pf)[LPT], auto masked_c, auto online_c, auto first_c) __attribute__((always_inline)) {
+  auto do_tile = [&](auto pass_c, int t, u32x4 (&pf)[LPT], auto masked_c, auto online_c, auto first_c) __attribute__((always_inline)) {
+    constexpr int PS = decltype(pass_c)::value;        // (1 or 2: of which pass)
     constexpr bool MASKED = decltype(masked_c)::value;   // the tile may reach past key_end
     constexpr bool ONLINE = decltype(online_c)::value;   // pass 1: running maximum instead of a fixed reference
     constexpr bool FIRST = decltype(first_c)::value;     // pass 1: the chunk's first tile (fixes the reference)
@@ -431,7 +496,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     store_tile(pf, buf);
     if (!ONLINE) issue_tile(t + NPF, pf);   // past the chunk end every piece comes from one clamped row
     __syncthreads();
-    if (PASS == 2 && t > 0 && tid < TK) {   // column sums of the previous tile
+    if (PS == 2 && t > 0 && tid < TK) {   // column sums of the previous tile
       float v = 0.f;
 #pragma unroll
       for (int r = 0; r < RB; ++r) v += red[buf ^ 1][r][tid];
@@ -457,12 +522,12 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
         for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-          if (PASS == 1)
+          if (PS == 1)
             acc = mfma16<KIND == 1>(kreg[kk], qreg[mt][kk], acc);
           else
             acc = mfma16<KIND == 1>(qreg[mt][kk], kreg[kk], acc);
         }
-        if (PASS == 1) {
+        if (PS == 1) {
           // lane: query row mt*32 + l32, keys key0 + 8*(i/4) + 4*half + i%4
           if (MASKED && key0 + 32 > key_end) {
 #pragma unroll
@@ -502,7 +567,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
           for (int i = 0; i < 16; ++i) colsum += fast_exp2(fmaf(acc[i], c_log2, -lse_r[mt][i]));
         }
       }
-      if (PASS == 2) {
+      if (PS == 2) {
         colsum += __shfl_xor(colsum, 32, 64);
         if (half == 0) red[buf][rb][sub * 32 + l32] = colsum;
       }
@@ -516,26 +581,17 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   issue_tile(1, pf1);
   __builtin_amdgcn_s_waitcnt(0x0F70 | LPT);   // vmcnt(LPT)
   __builtin_amdgcn_sched_barrier(0);
-  if (PASS == 2) {
-    float* lse_s = reinterpret_cast<float*>(&comb[0][0]);   // (comb is not used before the end)
-    static_assert(sizeof(comb) >= NLSE * 256 * sizeof(float), "comb holds one value per thread and load");
-#pragma unroll
-    for (int j = 0; j < NLSE; ++j) lse_s[tid + j * 256] = tid + j * 256 < R ? lse_ld[j] : INFINITY;
-    __syncthreads();
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        lse_r[mt][i] = lse_s[rb * 32 * MT + mt * 32 + 8 * (i >> 2) + 4 * half + (i & 3)];
-  }
+  if (PASS == 2) share_lse();
   using T = std::true_type;
   using F = std::false_type;
+  using P1 = std::integral_constant<int, 1>;
+  using P2 = std::integral_constant<int, 2>;
   // Pass 1 with both sub-tiles of a tile in one wave (RB == 4; up to 64 rows per wave): software pipeline over sub-tiles.
   // The MFMAs of sub-tile s (two interleaved chains, one per row tile) are issued one per slot,
   // each slot also carrying the exponentials of two logits of sub-tile s-1 (read from the other
   // accumulator set), so the matrix pipe works in the shadow of the exponentials; the key operand
   // of the tile's second sub-tile is read from LDS during the first one's MFMAs.
-  if constexpr (PASS == 1 && NSUB == 2 && MT <= 2) {
+  if constexpr (STATS && NSUB == 2 && MT <= 2) {
     constexpr int NSLOT = KK * MT, EPS = (16 * MT + NSLOT - 1) / NSLOT;
     f32x16 accA[MT], accB[MT];
     bf16x8 kA[KK], kB[KK];
@@ -635,32 +691,30 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(accB[mt][i], c_log2, -m_run[mt]));
       s_run[mt] += sum;
     }
-  } else if (PASS == 1) {
+  } else if (STATS) {
     // the first tile fixes the reference of the exponentials; only the last pair can reach past the chunk end
     if (ntiles > NPF) {
-      do_tile(0, pf0, F{}, F{}, T{});
-      do_tile(1, pf1, F{}, F{}, F{});
+      do_tile(P1{}, 0, pf0, F{}, F{}, T{});
+      do_tile(P1{}, 1, pf1, F{}, F{}, F{});
       for (int t0 = NPF; t0 < ntiles - NPF; t0 += NPF) {
-        do_tile(t0, pf0, F{}, F{}, F{});
-        do_tile(t0 + 1, pf1, F{}, F{}, F{});
+        do_tile(P1{}, t0, pf0, F{}, F{}, F{});
+        do_tile(P1{}, t0 + 1, pf1, F{}, F{}, F{});
       }
-      do_tile(ntiles - 2, pf0, T{}, F{}, F{});
-      do_tile(ntiles - 1, pf1, T{}, F{}, F{});
+      do_tile(P1{}, ntiles - 2, pf0, T{}, F{}, F{});
+      do_tile(P1{}, ntiles - 1, pf1, T{}, F{}, F{});
     } else {
-      do_tile(0, pf0, T{}, F{}, T{});
-      do_tile(1, pf1, T{}, F{}, F{});
+      do_tile(P1{}, 0, pf0, T{}, F{}, T{});
+      do_tile(P1{}, 1, pf1, T{}, F{}, F{});
     }
-  } else {
-    for (int t0 = 0; t0 < ntiles - NPF; t0 += NPF) {
-      do_tile(t0, pf0, F{}, F{}, F{});
-      do_tile(t0 + 1, pf1, F{}, F{}, F{});
-    }
-    do_tile(ntiles - 2, pf0, T{}, F{}, F{});
-    do_tile(ntiles - 1, pf1, T{}, F{}, F{});
   }
-
-  if (PASS == 1) SLKV_STAMP(256 + bid, 1);
-  if (PASS == 2) {
+  // importance of the chunk's keys, whose first two tiles are on their way
+  auto accumulate = [&]() __attribute__((always_inline)) {
+    for (int t0 = 0; t0 < ntiles - NPF; t0 += NPF) {
+      do_tile(P2{}, t0, pf0, F{}, F{}, F{});
+      do_tile(P2{}, t0 + 1, pf1, F{}, F{}, F{});
+    }
+    do_tile(P2{}, ntiles - 2, pf0, T{}, F{}, F{});
+    do_tile(P2{}, ntiles - 1, pf1, T{}, F{}, F{});
     __syncthreads();
     if (tid < TK) {
       const int t = ntiles - 1;
@@ -669,8 +723,13 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       for (int r = 0; r < RB; ++r) v += red[t & 1][r][tid];
       put_sum(key_begin + t * TK + tid, v);
     }
+  };
+
+  if (STATS) SLKV_STAMP(256 + bid, 1);
+  if (PASS == 2) {
+    accumulate();
+    return;
   }
-  if (PASS == 2) return;
   // A sum that left the fp32 range (logits far above the chunk's first ones): the whole
   // workgroup repeats the chunk with the running maximum.  Not taken for ordinary inputs.
   bool bad = false;
@@ -685,7 +744,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     for (int t = 0; t < ntiles; ++t) {          // plain loop, one tile in flight: this path is rare
       issue_tile(t, pf0);
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-      do_tile(t, pf0, T{}, T{}, F{});
+      do_tile(P1{}, t, pf0, T{}, T{}, F{});
     }
   }
 
@@ -701,14 +760,65 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     if (half == 0) comb[ks][rb * 32 * MT + mt * 32 + l32] = make_float2(m_run[mt], s_run[mt]);
   }
   __syncthreads();
-  for (int row = tid; row < RB * 32 * MT; row += 256) {
-    float mm = comb[0][row].x, ss = comb[0][row].y;
+  const int nchunks = se.chunk1 - se.chunk0;
 #pragma unroll
-    for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
-    // the chunk's log-sum-exp of the row (-inf: no key)
-    if (row < Rpad) part[(int64_t)bid * Rpad + row] = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+  for (int j = 0; j < NLSE; ++j) {
+    const int row = tid + j * 256;
+    if (row < ROWS) {
+      float mm = comb[0][row].x, ss = comb[0][row].y;
+#pragma unroll
+      for (int k2 = 1; k2 < KS; ++k2) merge_stats(mm, ss, comb[k2][row].x, comb[k2][row].y);
+      // the chunk's log-sum-exp of the row (-inf: no key)
+      const float l = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
+      float* const p = part + ((int64_t)bid * Rpad + row);
+      if (!BOTH) {
+        if (row < Rpad) *p = l;
+      } else if (nchunks == 1) {
+        lse_ld[j] = l > -INFINITY ? l : INFINITY;
+      } else if (row < Rpad) {
+        __hip_atomic_store(p, l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
   }
   SLKV_STAMP(256 + bid, 2);
+  if constexpr (BOTH) {
+    // The second pass, its first keys on their way while the others' statistics are waited for.  As a rule over this
+    // chunk alone; `left`, in thread 0: those whose workgroups have left.
+    __shared__ int sh_next;
+    meet_t* const word = meet + (int64_t)seg * kMeetWords;
+    meet_t left = 0;
+    bool met = false;
+    for (;;) {
+      if (met || nchunks == 1) {
+        issue_tile(0, pf0);
+        issue_tile(1, pf1);
+        __syncthreads();                                 // (every thread has read comb and sh_next)
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the statistics are in memory
+        __syncthreads();
+        if (tid == 0) {
+          left = meet_chunks(word, nchunks, chunk, limit);
+          sh_next = left != kMeetLeft;
+        }
+        __syncthreads();
+        if (!sh_next) return;
+        issue_tile(0, pf0);                              // (before the wait they would delay what thread 0 reads)
+        issue_tile(1, pf1);
+        float2* const fold = reinterpret_cast<float2*>(&ktile[0][0]);
+#pragma unroll
+        for (int j = 0; j < NLSE; ++j)
+          lse_ld[j] = fold_rows<true>(part, se.chunk0, se.chunk1, Rpad, j * 256, ROWS, 256, fold);
+      }
+      if (!met) share_lse();
+      met = true;
+      accumulate();
+      if (nchunks == 1) break;
+      if (tid == 0) sh_next = meet_take(word, left);
+      __syncthreads();
+      if (sh_next < 0) break;
+      set_chunk(sh_next);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2521,7 +2631,8 @@ template <int RADIUS, int EPT_, class TAB>   // pooling radius known at compile 
 __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB tab, int w, int pool_kernel, int pool_mode,
                                                                       int write_pooled, const float* __restrict__ imp, const uint32_t* __restrict__ gm,
                                                                       float* __restrict__ pooled, int32_t* __restrict__ kept_idx,
-                                                                      int64_t* __restrict__ d_out_offsets, const GatherArgs ga) {
+                                                                      int64_t* __restrict__ d_out_offsets, const GatherArgs ga,
+                                                                      meet_t* __restrict__ meet) {
   constexpr int NT = kSelThreads, EPT = EPT_, ROUND = NT * EPT_;   // the history is at most ROUND positions
   extern __shared__ float stage[];
   __shared__ uint32_t hist[kHistBins];
@@ -2543,6 +2654,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
     d_out_offsets[seg] = tab.out_off(seg);
     if (seg == tab.nseg - 1) d_out_offsets[seg + 1] = tab.out_off(tab.nseg);
   }
+  if (meet && tid == 0) __hip_atomic_store(meet + (int64_t)seg * kMeetWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   auto emit = [&](int pos, int j) __attribute__((always_inline)) {   // kept position j goes to output slot pos
     if ((uint32_t)pos < (uint32_t)kept) {
       out[pos] = j;
@@ -3328,6 +3440,7 @@ struct Plan {
   int rsplit;            // of these, that share a key group's query tiles (score_k_resident_kernel)
   size_t part_bytes, score_bytes, hist_bytes, table_bytes;
   size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
+  bool together;         // both scoring passes in one launch (see meet_chunks), if its workgroups fit the chip
   bool one_scan;         // the call may go over its keys once (see OneScan), if the workspace has these bytes as well
   int sampled;           // see range_len
   int64_t ranges;
@@ -3469,6 +3582,12 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
 // 448 rows, 4 x 24 K: 88 us with 376 chunks, which run in two rounds, 60.7 with 252.  What does not fit at once runs in rounds.
 // Small calls take chunks down to two tiles: 8 x 2 K keys of 128 rows 22.5 us with 256 keys a chunk, 19.6 with 128.
 //
+// Both passes in one launch (PASS 3) up to an estimated pass time of kTogetherUs: it saves a launch, and the second start of every
+// workgroup: table, queries, first keys.  Two launches / one, us a call: 1 x 1.2 K 21.7 / 18.5, 1 x 2 K 23.9 / 20.6, 1 x 8 K 25.6 / 24.2, 16 prompts
+// of 150 to 5 K 56.0 / 47.7, a decode cache of 256 segments 67.7 / 60.5, 1 x 32 K of 256 rows 62.2 / 61.1, 2 x 32 K 98.0 / 94.9.  Above the
+// line the start is little of it, and the two workgroups of a CU, of which one is served first, wait for each other: 3 x 32 K 138.9 / 143.4.
+// On 2, 3 and 4 streams at once, 16 short prompts: 41.2 / 36.8, 37.4 / 35.4, 36.9 / 34.1; 1 x 32 K: 47.0 / 46.5, 44.1 / 46.0, 42.3 / 45.3.
+//
 // One pass over the keys instead of two (OneScan) where a pass takes this long by the costs above: it saves a pass, less a tenth, and
 // costs the sample, the histograms, the bounds and the chosen keys; where histories above 32768 positions are selected by blocks it
 // saves three of that selection's launches as well.  One pass / two, us, on keys as in OneScan, and (in brackets) with 16 rows of every segment that give half
@@ -3477,6 +3596,7 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
 // of 64 rows 8 x 96 K 88 / 100 (93 / 100), 16 x 96 K 154 / 168 (159 / 170); of 16 rows 32 x 50 K 156 / 173, 32 x 75 K 201 / 245;
 // histories of at most 32768, 256 rows: 32 x 20 K 136 / 115, 32 x 32 K 177 / 170, 64 x 20 K 191 / 211 (1024 kept on average 238 / 234), 48 x 30 K 212 / 236,
 // 64 x 32 K 256 / 320, of 128 rows 64 x 32 K 200 / 216.  (More than 64 segments, before the probe: 128 x 16 K 329 / 323.)
+constexpr double kTogetherUs = 50;
 constexpr double kOneScanUs = 50, kOneScanFewRowsUs = 40, kOneScanResidentUs = 100;
 static void plan_q_resident(const Geometry& g, Plan& p) {
   const int cfg = p.R <= 64 ? 0 : p.R <= 128 ? 1 : p.R <= 256 ? 2 : 3;
@@ -3502,6 +3622,7 @@ static void plan_q_resident(const Geometry& g, Plan& p) {
   }
   p.waves = 4;
   p.rsplit = 1;
+  p.together = best <= kTogetherUs;
   const double worth = lens.longest <= kSelRound ? kOneScanResidentUs : cfg == 2 ? kOneScanUs : kOneScanFewRowsUs;
   p.one_scan = best >= worth && (cfg == 2 || lens.longest > kSelRound) && p.R <= 256 && g.pool != SLKV_POOL_AVG && g.segs.size() <= (size_t)kMaxSegPerLaunch;
 }
@@ -3524,7 +3645,7 @@ static void plan_ranges(const Geometry& g, Plan& p) {
 }
 
 static void make_plan(const Geometry& g, Plan& p) {
-  p.one_scan = false;
+  p.one_scan = p.together = false;
   p.R = (g.Hq / g.Hkv) * g.w;
   p.Rpad = (p.R + 31) / 32 * 32;
   if (g.dtype == SLKV_BF16 || g.dtype == SLKV_F16) plan_q_resident(g, p);
@@ -3617,8 +3738,8 @@ struct ScoreGrid {
   int chunks, per_row, rows;
 };
 
-// The passes of a call: 1 and 2, or these three.
-constexpr int kPassSample = 0, kPassBoth = 3, kPassChosen = 4;
+// The passes of a call: 1 and 2, both in one launch, or three for one pass over the keys.
+constexpr int kPassSample = 0, kPassTogether = 3, kPassBoth = 4, kPassChosen = 5;
 
 // What the scoring passes write, for each other and for the selection.
 struct ScoreBuffers {
@@ -3627,6 +3748,8 @@ struct ScoreBuffers {
   OneScan one;             // the rest is for one pass over the keys
   float* pooled;
   uint32_t* blockhist;     // or NULL: one workgroup per segment selects
+  meet_t* meet;            // both passes in one launch: where their workgroups meet (see meet_chunks), or NULL
+  int limit;               // and how long they wait, in ticks of 10 ns
 };
 
 template <int DK, int MT, int RB, int KIND, class TAB>
@@ -3637,10 +3760,11 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
   const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
   auto scan = [&](auto pass_c) {
     SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, decltype(pass_c)::value, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
-                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.gm);
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.gm, buf.meet, buf.limit);
   };
   if (pass == 1) scan(std::integral_constant<int, 1>{});
   if (pass == 2) scan(std::integral_constant<int, 2>{});
+  if (pass == kPassTogether) scan(std::integral_constant<int, 3>{});
   if constexpr (MT <= 2 && std::is_same_v<TAB, SegTable>) {
     const unsigned S = (unsigned)g.segs.size();
     if (pass == kPassSample)
@@ -3784,15 +3908,23 @@ static hipError_t raise_score_limits() {
   return hipSuccess;
 }
 
-static hipError_t ensure_device_init() {
+// The set-up of the current device, whose number of CUs goes to `cus`.
+static hipError_t ensure_device_init(int* cus = nullptr) {
   static std::mutex mu;
   static uint64_t done = 0;                      // bit per device
-  int dev = 0;
+  static int cus_of[64];
+  int dev = 0, have = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   std::lock_guard<std::mutex> lk(mu);
   const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t(1) << dev) : 0;
-  if (done & bit) return hipSuccess;
+  if (done & bit) {
+    if (cus) *cus = cus_of[dev];
+    return hipSuccess;
+  }
+  if ((e = hipDeviceGetAttribute(&have, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+  if (cus) *cus = have;
+  if (bit) cus_of[dev] = have;
   if ((e = raise_score_limits()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPT>()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPTMid>()) != hipSuccess) return e;
@@ -3804,12 +3936,12 @@ static hipError_t ensure_device_init() {
 template <int RADIUS, int EPT, class TAB>
 static hipError_t launch_select_resident_e(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
-                                           const GatherArgs& ga) {
+                                           const GatherArgs& ga, meet_t* meet) {
   const hipError_t e = ensure_device_init();
   if (e != hipSuccess) return e;
   const int pool_kernel = g.pool == SLKV_POOL_NONE ? 1 : g.pool_kernel;
   SLKV_LAUNCH((select_resident_kernel<RADIUS, EPT, TAB>), dim3(ns), dim3(kSelThreads), kResLdsBytes, st, tab, g.w,
-                     pool_kernel, g.pool, (int)write_pooled, imp, gm, pooled, kept_idx, d_out_offsets, ga);
+                     pool_kernel, g.pool, (int)write_pooled, imp, gm, pooled, kept_idx, d_out_offsets, ga, meet);
   return hipSuccess;
 }
 
@@ -3818,25 +3950,25 @@ static hipError_t launch_select_resident_e(int ns, hipStream_t st, const TAB& ta
 template <int RADIUS, class TAB>
 static hipError_t launch_select_resident_r(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
-                                           const GatherArgs& ga) {
+                                           const GatherArgs& ga, meet_t* meet) {
   if (g.longest <= kSelThreads * kSelEPTSmall)
-    return launch_select_resident_e<RADIUS, kSelEPTSmall>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    return launch_select_resident_e<RADIUS, kSelEPTSmall>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
   if (g.longest <= kSelThreads * kSelEPTMid)
-    return launch_select_resident_e<RADIUS, kSelEPTMid>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
-  return launch_select_resident_e<RADIUS, kSelEPT>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    return launch_select_resident_e<RADIUS, kSelEPTMid>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+  return launch_select_resident_e<RADIUS, kSelEPT>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
 }
 
 template <class TAB>
 static hipError_t launch_select_resident(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                          const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
-                                         const GatherArgs& ga) {
+                                         const GatherArgs& ga, meet_t* meet) {
   const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
   switch (radius) {
-    case 0: return launch_select_resident_r<0>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
-    case 1: return launch_select_resident_r<1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
-    case 2: return launch_select_resident_r<2>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
-    case 3: return launch_select_resident_r<3>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
-    default: return launch_select_resident_r<-1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga);
+    case 0: return launch_select_resident_r<0>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 1: return launch_select_resident_r<1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 2: return launch_select_resident_r<2>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 3: return launch_select_resident_r<3>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    default: return launch_select_resident_r<-1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
   }
 }
 
@@ -3848,6 +3980,15 @@ static int select_mode() {
   if (!std::strcmp(e, "resident")) return 1;
   if (!std::strcmp(e, "blocks")) return 2;
   return 0;
+}
+
+// How long the workgroups of a launch that does both passes wait for each other, in ticks of 10 ns: several times what
+// they start and end apart (up to 10 us), and what another stream's selection keeps them from a CU (10 to 20 us).  SLKV_MEET_US in the
+// environment sets another limit (tests: 0, so that nearly all leave and the last ones complete their chunks).
+static int meet_limit() {
+  const char* e = std::getenv("SLKV_MEET_US");
+  const int us = e ? std::atoi(e) : 50;
+  return std::min(std::max(us, 0), 1000) * 100;
 }
 
 // Checks and launches shared by the two entry points.
@@ -3918,7 +4059,8 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   // (pooling has consumed the scores)
   uint32_t* lists = (uint32_t*)(ws + p.off_imp);
 
-  const hipError_t ie = ensure_device_init();
+  int cus = 0;
+  const hipError_t ie = ensure_device_init(&cus);
   if (ie != hipSuccess) return fail(SLKV_ERR_HIP, "device set-up failed: %s", hipGetErrorString(ie));
   const bool k_resident = g.dtype == SLKV_F32 || g.dtype == SLKV_BF16_KV_FP8;
 
@@ -3940,7 +4082,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     one = OneScan{(float*)(ws + p.off_part0), (float*)(ws + p.off_dense), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
                   (uint32_t*)(ws + p.off_lists)};
   uint32_t* const gm = groups && !one_scan ? (uint32_t*)pooled : nullptr;
-  const ScoreBuffers buf{part, imp, gm, one, pooled, resident_select ? nullptr : blockhist};
+  ScoreBuffers buf{part, imp, gm, one, pooled, resident_select ? nullptr : blockhist, nullptr, 0};
   auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, int64_t rows) -> slkv_status {
     using TAB = std::decay_t<decltype(tab)>;
     // one grid row per segment where that leaves at most a seventh of the grid empty (a segment with
@@ -3952,7 +4094,15 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       sgrid.per_row = max_chunks;
       sgrid.rows = tab.nseg;
     }
-    if (chunks > 0) {
+    // Both passes in one launch where all its workgroups fit the chip at once and the selection clears their meeting places.
+    if (p.together && !one_scan && resident_select && S <= kMeetSegments && max_chunks <= kMeetMost && chunks <= (p.R <= 256 ? 2 : 1) * cus) {
+      buf.meet = (meet_t*)ws;
+      buf.limit = meet_limit();
+    }
+    if (chunks > 0 && buf.meet) {
+      ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
+      launch_score(kPassTogether, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
+    } else if (chunks > 0) {
       {
         ScopedKernelTimer tm(SLKV_K_SCORE_STATS, st);
         launch_score(one_scan ? kPassSample : 1, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
@@ -3969,7 +4119,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     {
       ScopedKernelTimer tm(SLKV_K_SELECT, st);
       if (resident_select) {
-        hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, gm, imp, pooled, d_kept_idx, d_out_offsets, ga);
+        hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, gm, imp, pooled, d_kept_idx, d_out_offsets, ga, buf.meet);
         if (se != hipSuccess) return fail(SLKV_ERR_HIP, "select launch setup failed: %s", hipGetErrorString(se));
       } else {
         launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, one_scan ? one.lists : lists, d_kept_idx, d_out_offsets, ga, one);

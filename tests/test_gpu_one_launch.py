@@ -1,0 +1,107 @@
+"""Both scoring passes in one launch, whose workgroups meet in between: the same scores, bit for bit, as the two launches (which calls take
+that are selected by blocks), whether the workgroups of a segment wait for each other or leave and the last one completes their chunks."""
+
+import numpy as np
+import pytest
+
+from paper_2508_15806_amd import api
+from paper_2508_15806_amd import binding as B
+from paper_2508_15806_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+HEADER = 65536
+
+
+def results(call, run):
+    import torch
+    outs = [call.kept_idx, call.k_out, call.v_out, call.importance, call.pooled]
+    for x in outs:
+        x.zero_()
+    run()
+    torch.cuda.synchronize()
+    assert not bool(call.workspace[:HEADER].any())          # the meeting places are left as they were found
+    return [x.view(torch.uint8).clone() for x in outs]
+
+
+def launches(run):
+    import torch
+    B.slkv_profile_begin(16)
+    run()
+    torch.cuda.synchronize()
+    return [k for k, _ in B.slkv_profile_end(16)]
+
+
+def compare(monkeypatch, call, run, together=True):
+    import torch
+    monkeypatch.delenv("SLKV_MEET_US", raising=False)
+    monkeypatch.setenv("SLKV_SELECT", "blocks")
+    assert "score_stats" in launches(run)
+    two = results(call, run)
+    monkeypatch.delenv("SLKV_SELECT")
+    assert ("score_stats" not in launches(run)) == together
+    for limit in (None, "0", "0", "3", None):               # (0: nearly all leave; 3 us: some do)
+        if limit is not None:
+            monkeypatch.setenv("SLKV_MEET_US", limit)
+        else:
+            monkeypatch.delenv("SLKV_MEET_US", raising=False)
+        for _ in range(3):
+            for a, b in zip(results(call, run), two):
+                assert torch.equal(a, b)
+
+
+# 32 to 512 query rows, segments of one chunk, of one key more, of several; the ends of chunks and of tile pairs
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("Hq,Hkv,w,d,lens", [
+    (2, 2, 32, 128, [32 + 1, 32 + 128, 32 + 129, 700]), (8, 2, 16, 64, [5000]), (8, 2, 32, 128, [32 + 255, 1300, 90]),
+    (16, 4, 64, 64, [4000, 64 + 513]), (32, 8, 64, 128, [9000]), (14, 2, 64, 128, [3000, 200]), (16, 2, 64, 64, [2000])])
+def test_layer(monkeypatch, dtype, Hq, Hkv, w, d, lens):
+    lay = wl.make_layer((401, Hq, w, d), lens, Hq, Hkv, d, w, dtype=dtype, bias_frac=0.04)
+    call = api.LayerCall(dtype, len(lens), Hq, Hkv, d, w, lay.cu_seqlens, np.array([w + 20 + 31 * h for h in range(Hkv)], dtype=np.int32), debug_scores=True)
+    q, k, v = (api.to_device(x, dtype) for x in (lay.qwin, lay.k, lay.v))
+    compare(monkeypatch, call, lambda: call.run(q, k, v))
+
+
+def test_most_chunks_of_a_segment(monkeypatch):
+    # one KV head: as many chunks as a meeting place counts take one launch, more take two
+    for n, together in ((48 * 128 + 32, True), (48 * 128 + 33, False)):
+        lay = wl.make_layer((402, n), [n], 4, 1, 128, 32, dtype="bf16", bias_frac=0.02)
+        call = api.LayerCall("bf16", 1, 4, 1, 128, 32, lay.cu_seqlens, np.array([100], dtype=np.int32), debug_scores=True)
+        q, k, v = (api.to_device(x, "bf16") for x in (lay.qwin, lay.k, lay.v))
+        compare(monkeypatch, call, lambda: call.run(q, k, v), together)
+
+
+def test_cache_of_many_segments(monkeypatch):
+    # 256 segments of one to eight chunks: the table by sequence and head
+    import torch
+    caps = np.array([107, 1834, 111, 132, 119, 110, 143, 127], dtype=np.int32)
+    rng = np.random.default_rng(5)
+    lens = [int(c + t) for t in rng.integers(1, 129, size=32) for c in caps]
+    rc = wl.make_ragged_cache((403,), lens, 32, 32, 8, 128, 64, dtype="bf16", bias_frac=0.03)
+    call = api.RaggedCall("bf16", 32, 32, 8, 128, 64, rc.in_offsets, caps, debug_scores=True)
+    q, k, v = (api.to_device(x, "bf16") for x in (rc.qwin, rc.k_rows, rc.v_rows))
+    pos = torch.from_numpy(rc.pos_in).cuda()
+    compare(monkeypatch, call, lambda: call.run(q, k, v, pos))
+
+
+def test_three_streams():
+    # three calls of nearly as many workgroups as the chip holds, started together: none may wait for another
+    import torch
+    lens, caps = [4000] * 16, np.array([60, 300, 90, 80, 70, 200, 100, 64], dtype=np.int32)
+    lay = wl.make_layer((404,), lens, 32, 8, 128, 32, dtype="bf16", bias_frac=0.03)
+    calls = [api.LayerCall("bf16", 16, 32, 8, 128, 32, lay.cu_seqlens, caps) for _ in range(3)]
+    q, k, v = (api.to_device(x, "bf16") for x in (lay.qwin, lay.k, lay.v))
+    calls[0].run(q, k, v)
+    torch.cuda.synchronize()
+    want = calls[0].kept_idx.clone()
+    streams = [torch.cuda.Stream() for _ in calls]
+    for _ in range(5):
+        for call in calls:
+            call.kept_idx.zero_()
+        torch.cuda.synchronize()
+        for _ in range(4):
+            for call, s in zip(calls, streams):
+                call.run(q, k, v, stream=s)
+        torch.cuda.synchronize()
+        for call in calls:
+            assert torch.equal(call.kept_idx, want)
