@@ -318,7 +318,7 @@ slkv_status slkv_recompress_layer(const slkv_ragged_desc* desc, const void* d_qw
  * slkv_profile_end waits for the recorded events, writes up to `capacity` records in launch
  * order and sets *count to the number recorded.  A call of slkv_compress_layer or slkv_recompress_layer makes at most 9 records
  * (two passes, long histories: 1 + 1 + 6 + 1; one pass: 1 + 4 + 3 + 1; histories up to 32768: 1 + 1 + 1 + 1, both passes in
- * one launch 0 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1).
+ * one launch 0 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1, in each of these without the last one where the selection copies all rows).
  * Process-wide; not meant for production.
  */
 typedef enum {
@@ -328,7 +328,7 @@ typedef enum {
                                pass, the histograms, and two launches that compute some scores exactly (four records) */
   SLKV_K_SELECT = 3,        /* pooling + top-k (one record per launch: one launch for histories up to 32768 positions, six for longer
                                ones, three after one pass over the keys) */
-  SLKV_K_GATHER = 4,        /* K/V row gather */
+  SLKV_K_GATHER = 4,        /* K/V row gather, of the rows that the selection did not copy */
   SLKV_K_ROW_CELLS = 5,     /* Stage 1: per-row weight cells */
   SLKV_K_HEAD_REDUCE = 6,   /* Stage 1: per-head sums and scores */
   SLKV_K_QK_CELLS = 7,      /* Stage 1 from queries and keys: logits, top-K and cells of every row */

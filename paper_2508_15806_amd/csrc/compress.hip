@@ -2084,7 +2084,16 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
 // ranking workgroups and start tens of microseconds late.)
 // Keys are the bit patterns of the pooled scores (>= 0, so monotone).  While ranking, a wave owns
 // 2048 consecutive positions of a round, lane l the positions 64*j + l (j < 32).
-constexpr int kInlineGatherRows = 256;    // segments up to this many kept rows are gathered by the selection kernel
+// Slices: where the chip has CUs to spare, further workgroups of select_resident_kernel select again for a segment that keeps more than 64 rows (128
+// where only so few fit), each to write and copy that many of them.  The selection of a segment is a chain of phases that takes as
+// long on one CU as on ten; the copies, a few us where one workgroup holds 128 to 256 rows, and the gather launch (4 us) for those with more, are what
+// it saves.  us a call, without / slices of 32 / 64 / 128 / 256 rows: 8 x 32 K, 107 to 1834 kept 57.7 / - / 56.3 / 57.4 / 59.3; 8 x 21 K, 397 to 7655 kept
+// 59.6 / - / 55.3 / 56.6 / 58.7; 16 short prompts 45.4 / - / 45.0 / 43.4 / 44.7; one sequence's cache, 58 to 865 kept 20.7 / 18.9 / 19.1 / 19.5 / 20.5;
+// 8 x 8 K, 91 to 155 kept 25.5 / 24.6 / 24.8 / 25.5; 8 x 16 K, 220 kept 30.6 / 28.9 / 29.1 / 29.8; 4 x 1 K fp32, 105 to 137 kept 19.9 / - / 20.1: not
+// where the shortest form selects and nothing would be left to the gather.  Two workgroups to a CU (a decode cache of 256 segments, 480 slices
+// of 256) 60.8 / 60.5: not worth their LDS.
+constexpr int kSliceLog2Least = 6, kSliceLog2Most = 7;
+constexpr int kInlineGatherRows = 256;    // without slices: segments up to this many kept rows are gathered by the selection kernel
 
 struct GatherArgs {
   const unsigned char* k;
@@ -2632,7 +2641,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
                                                                       int write_pooled, const float* __restrict__ imp, const uint32_t* __restrict__ gm,
                                                                       float* __restrict__ pooled, int32_t* __restrict__ kept_idx,
                                                                       int64_t* __restrict__ d_out_offsets, const GatherArgs ga,
-                                                                      meet_t* __restrict__ meet) {
+                                                                      meet_t* __restrict__ meet, int slice_log2) {
   constexpr int NT = kSelThreads, EPT = EPT_, ROUND = NT * EPT_;   // the history is at most ROUND positions
   extern __shared__ float stage[];
   __shared__ uint32_t hist[kHistBins];
@@ -2642,34 +2651,58 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
   __shared__ uint32_t sh_mm[2 * (NT / 64)];
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int seg = blockIdx.x;
+  // Slices (slice_log2 > 0): the workgroups beyond the segments select once more for a segment that keeps more than a slice,
+  // each to write and copy the next 2^slice_log2 of its rows.
+  int seg = blockIdx.x, slice = 0;
+  if (seg >= tab.nseg) {
+    int more = seg - tab.nseg;
+    for (int s0 = 0; s0 < tab.nseg; s0 += 64) {
+      const int s = min(s0 + lane, tab.nseg - 1), rows = s0 + lane < tab.nseg ? tab.out_off(s + 1) - tab.out_off(s) : 0;
+      const int extra = max(rows - 1, 0) >> slice_log2, incl = (int)wave_incl_scan((uint32_t)extra);
+      const unsigned long long past = __builtin_amdgcn_ballot_w64(incl > more);
+      if (past) {
+        const int l = __builtin_ctzll(past);
+        seg = s0 + l;
+        slice = 1 + more - __builtin_amdgcn_readlane(incl - extra, l);
+        break;
+      }
+      more -= __builtin_amdgcn_readlane(incl, 63);
+    }
+    if (!slice) return;
+  }
   const SegShape sg = tab.shape(seg);
   const int n = sg.n;
   const int kk = sg.kk;
   const int m = n - w;
-  const int kept = tab.out_off(seg + 1) - tab.out_off(seg);
+  const int seg_kept = tab.out_off(seg + 1) - tab.out_off(seg);
+  const int first = slice << slice_log2, kept = slice_log2 ? min(seg_kept - first, 1 << slice_log2) : seg_kept;   // this workgroup's part of them
+  const int64_t row0 = tab.out_off(seg) + first;
   const bool small_seg = kept <= kInlineGatherRows;
-  int32_t* out = kept_idx + tab.out_off(seg);
-  if (d_out_offsets && tid == 0) {
-    d_out_offsets[seg] = tab.out_off(seg);
-    if (seg == tab.nseg - 1) d_out_offsets[seg + 1] = tab.out_off(tab.nseg);
+  int32_t* out = kept_idx + row0;
+  if (slice == 0 && tid == 0) {
+    if (d_out_offsets) {
+      d_out_offsets[seg] = tab.out_off(seg);
+      if (seg == tab.nseg - 1) d_out_offsets[seg + 1] = tab.out_off(tab.nseg);
+    }
+    if (meet) __hip_atomic_store(meet + (int64_t)seg * kMeetWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (meet && tid == 0) __hip_atomic_store(meet + (int64_t)seg * kMeetWords, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  auto emit = [&](int pos, int j) __attribute__((always_inline)) {   // kept position j goes to output slot pos
-    if ((uint32_t)pos < (uint32_t)kept) {
-      out[pos] = j;
-      if (small_seg) sh_pos[pos] = j;
+  auto emit = [&](int pos, int j) __attribute__((always_inline)) {   // kept position j goes to output slot pos of the segment
+    const int p = pos - first;
+    if ((uint32_t)p < (uint32_t)kept) {
+      out[p] = j;
+      if (small_seg) sh_pos[p] = j;
     }
   };
   SLKV_STAMP(128 + seg, 0);
   if (small_seg)
     for (int i = tid; i < kInlineGatherRows; i += NT) sh_pos[i] = 0;
   __syncthreads();
-  // The observation window is kept whatever the scores say: where this kernel also copies the rows
-  // (small segments) and the window is one 16-byte piece per thread at most, the pieces are
+  // The observation window is kept whatever the scores say: where this workgroup also copies its rows
+  // and the window is one 16-byte piece per thread at most, the pieces are
   // fetched right behind the scores and stored at the end, off the critical path.
   const int lpr = ga.lanes_per_row;
-  const bool win_early = small_seg && w * lpr <= NT;
+  const int win0 = kk - first;                                   // the window's place among this workgroup's rows
+  const bool win_early = small_seg && w * lpr <= NT && win0 >= 0 && win0 + w <= kept;
   const bool win_mine = win_early && tid < w * lpr;
   const int win_piece = min(tid, max(w * lpr - 1, 0));           // (threads past the window's pieces fetch its last one again: a load
   const int win_row = win_piece / lpr, win_c = win_piece % lpr;  //  under a condition would have to be waited for where the branches meet)
@@ -2685,6 +2718,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
   if (ranked) {
   const float* I = imp + sg.score_off;
   float* P = pooled + sg.score_off;
+  if (slice) write_pooled = 0;
   const int radius = RADIUS >= 0 ? RADIUS : pool_kernel / 2;
   auto fetch_window = [&]() __attribute__((always_inline)) {
     const int64_t tok = (int64_t)sg.tok_begin + m + win_row, h = sg.head;
@@ -3296,9 +3330,9 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
   // flight at a time.
   if (kept > 0 && small_seg) {
     __syncthreads();                                // sh_pos is complete
-    const int64_t tok0 = sg.tok_begin, h = sg.head, row0 = tab.out_off(seg);
+    const int64_t tok0 = sg.tok_begin, h = sg.head;
     const bool win_done = ranked && win_early;      // the window's pieces are in registers
-    const int pieces = (win_done ? kk : kept) * lpr;
+    const int pieces = (win_done ? win0 : kept) * lpr;
     const uint32_t magic = 0xffffffffu / (uint32_t)lpr + 1u;   // idx / lpr == umulhi(idx, magic) for idx < 2^16 (lpr > 1)
     struct Piece {
       u32x4 kq, vq;
@@ -3334,10 +3368,10 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
       put(base + 3 * NT, q3);
     }
     if (win_done && win_mine) {
-      const int64_t o = ((row0 + kk + win_row) * lpr + win_c) * 16;
+      const int64_t o = ((row0 + win0 + win_row) * lpr + win_c) * 16;
       *reinterpret_cast<u32x4*>(ga.k_out + o) = win_k;
       *reinterpret_cast<u32x4*>(ga.v_out + o) = win_v;
-      if (ga.pos_out && win_c == 0) ga.pos_out[row0 + kk + win_row] = ga.pos_in[tok0 + m + win_row];
+      if (ga.pos_out && win_c == 0) ga.pos_out[row0 + win0 + win_row] = ga.pos_in[tok0 + m + win_row];
     }
   }
   SLKV_STAMP(128 + seg, 7);
@@ -3933,42 +3967,47 @@ static hipError_t ensure_device_init(int* cus = nullptr) {
   return hipSuccess;
 }
 
+// Workgroups of select_resident_kernel: one per segment, or per slice of 2^slice_log2 kept rows of one.
+struct SelectGrid {
+  int workgroups, slice_log2;
+};
+
 template <int RADIUS, int EPT, class TAB>
-static hipError_t launch_select_resident_e(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
+static hipError_t launch_select_resident_e(SelectGrid sel, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                            const GatherArgs& ga, meet_t* meet) {
   const hipError_t e = ensure_device_init();
   if (e != hipSuccess) return e;
   const int pool_kernel = g.pool == SLKV_POOL_NONE ? 1 : g.pool_kernel;
-  SLKV_LAUNCH((select_resident_kernel<RADIUS, EPT, TAB>), dim3(ns), dim3(kSelThreads), kResLdsBytes, st, tab, g.w,
-                     pool_kernel, g.pool, (int)write_pooled, imp, gm, pooled, kept_idx, d_out_offsets, ga, meet);
+  SLKV_LAUNCH((select_resident_kernel<RADIUS, EPT, TAB>), dim3(sel.workgroups), dim3(kSelThreads), kResLdsBytes, st, tab, g.w,
+                     pool_kernel, g.pool, (int)write_pooled, imp, gm, pooled, kept_idx, d_out_offsets, ga, meet, sel.slice_log2);
   return hipSuccess;
 }
 
 // Positions per thread: the fewest of 2, 8, 32 whose round holds the longest ranked history (every
 // wave runs through all of a thread's positions, whether or not the history reaches them).
 template <int RADIUS, class TAB>
-static hipError_t launch_select_resident_r(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
+static hipError_t launch_select_resident_r(SelectGrid sel, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                            const GatherArgs& ga, meet_t* meet) {
   if (g.longest <= kSelThreads * kSelEPTSmall)
-    return launch_select_resident_e<RADIUS, kSelEPTSmall>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    return launch_select_resident_e<RADIUS, kSelEPTSmall>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
   if (g.longest <= kSelThreads * kSelEPTMid)
-    return launch_select_resident_e<RADIUS, kSelEPTMid>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
-  return launch_select_resident_e<RADIUS, kSelEPT>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    return launch_select_resident_e<RADIUS, kSelEPTMid>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+  return launch_select_resident_e<RADIUS, kSelEPT>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
 }
 
 template <class TAB>
-static hipError_t launch_select_resident(int ns, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
+static hipError_t launch_select_resident(SelectGrid sel, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                          const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                          const GatherArgs& ga, meet_t* meet) {
   const int radius = g.pool == SLKV_POOL_NONE ? 0 : g.pool_kernel / 2;
   switch (radius) {
-    case 0: return launch_select_resident_r<0>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
-    case 1: return launch_select_resident_r<1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
-    case 2: return launch_select_resident_r<2>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
-    case 3: return launch_select_resident_r<3>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
-    default: return launch_select_resident_r<-1>(ns, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 0: return launch_select_resident_r<0>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 1: return launch_select_resident_r<1>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 2: return launch_select_resident_r<2>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    case 3: return launch_select_resident_r<3>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+    default: return launch_select_resident_r<-1>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
   }
 }
 
@@ -4083,7 +4122,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
                   (uint32_t*)(ws + p.off_lists)};
   uint32_t* const gm = groups && !one_scan ? (uint32_t*)pooled : nullptr;
   ScoreBuffers buf{part, imp, gm, one, pooled, resident_select ? nullptr : blockhist, nullptr, 0};
-  auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, int64_t rows) -> slkv_status {
+  auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, const int64_t* slices, int64_t rows) -> slkv_status {
     using TAB = std::decay_t<decltype(tab)>;
     // one grid row per segment where that leaves at most a seventh of the grid empty (a segment with
     // fewer chunks than the longest leaves the surplus of its row empty; with more empty workgroups
@@ -4116,17 +4155,21 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
         launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
       }
     }
+    SelectGrid sel{nseg, 0};
+    const bool slice = resident_select && (any_large || g.longest > kSelThreads * kSelEPTSmall);
+    for (int l = kSliceLog2Least; slice && !sel.slice_log2 && l <= kSliceLog2Most; ++l)
+      if (slices[l - kSliceLog2Least] <= cus) sel = SelectGrid{(int)slices[l - kSliceLog2Least], l};
     {
       ScopedKernelTimer tm(SLKV_K_SELECT, st);
       if (resident_select) {
-        hipError_t se = launch_select_resident(nseg, st, tab, g, d_pooled != nullptr, gm, imp, pooled, d_kept_idx, d_out_offsets, ga, buf.meet);
+        hipError_t se = launch_select_resident(sel, st, tab, g, d_pooled != nullptr, gm, imp, pooled, d_kept_idx, d_out_offsets, ga, buf.meet);
         if (se != hipSuccess) return fail(SLKV_ERR_HIP, "select launch setup failed: %s", hipGetErrorString(se));
       } else {
         launch_select(nseg, blocks, st, tab, g, imp, pooled, blockhist, one_scan ? one.lists : lists, d_kept_idx, d_out_offsets, ga, one);
       }
     }
     const bool gather_all = !resident_select && blocks > 0;   // the block-wise selection copies no rows itself
-    if ((any_large || gather_all) && rows > 0) {
+    if ((any_large || gather_all) && !sel.slice_log2 && rows > 0) {
       ScopedKernelTimer tm(SLKV_K_GATHER, st);
       const int64_t threads = rows * lanes_per_row;
       if (threads > kGatherThreads)
@@ -4140,7 +4183,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   };
 
   // The segment table, with the prefixes of output rows, key chunks and selection blocks over the segments.
-  int64_t out_run = 0, chunks = 0, max_chunks = 0, blocks = 0;
+  int64_t out_run = 0, chunks = 0, max_chunks = 0, blocks = 0, slices[kSliceLog2Most - kSliceLog2Least + 1] = {};
   bool any_large = false;
   auto walk = [&](int32_t* out, int32_t* chunk, int32_t* blk) {   // (blk may be NULL)
     for (int64_t i = 0; i < S; ++i) {
@@ -4150,6 +4193,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       if (blk) blk[i] = (int32_t)blocks;
       const int64_t kept = kept_rows(sg.n, g.w, sg.cap), nc = seg_chunks(sg, g.w, p.CH);
       any_large |= kept > kInlineGatherRows;
+      for (int l = kSliceLog2Least; l <= kSliceLog2Most; ++l) slices[l - kSliceLog2Least] += 1 + (std::max<int64_t>(kept - 1, 0) >> l);
       out_run += kept;
       chunks += nc;
       max_chunks = std::max(max_chunks, nc);
@@ -4178,7 +4222,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       tab.range_[0] = 0;
       for (int64_t i = 0; i < S; ++i) tab.range_[i + 1] = tab.range_[i] + (int32_t)seg_ranges(g.segs[(size_t)i], g.w, p.sampled);
     }
-    return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
+    return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, slices, out_run);
   }
   SegTableBig tab;
   static_assert(sizeof(SegTableBig) + sizeof(GatherArgs) + 128 <= 4096, "kernel arguments are at most 4 KiB");
@@ -4211,7 +4255,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     }
     tab.mem = t;
   }
-  return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, out_run);
+  return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, slices, out_run);
 }
 
 }  // namespace slkv

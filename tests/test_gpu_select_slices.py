@@ -1,0 +1,53 @@
+"""GPU parity of the selection whose workgroups each copy a slice of 64 or 128 of a segment's kept rows: kept counts around the slices' ends,
+windows that lie across one, segments kept whole and empty ones, the numbers of slices from which on there are 128 rows to one, or no slices."""
+
+import numpy as np
+import pytest
+
+import parity
+from paper_2508_15806_amd import binding as B
+from paper_2508_15806_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def launches(call, *args):
+    import torch
+    B.slkv_profile_begin(16)
+    call.run(*args)
+    torch.cuda.synchronize()
+    return [k for k, _ in B.slkv_profile_end(16)]
+
+
+# the window (24 or 64 rows) before, on and behind the end of a slice; 2, 8 and 32 positions a thread; one history longer than its capacity's slices
+@pytest.mark.parametrize("dtype,d,pool", [("bf16", 128, "max"), ("f16", 64, "avg"), ("bf16_kv8", 64, "max"), ("f32", 128, "none")])
+@pytest.mark.parametrize("w,n", [(24, 1200), (64, 1500), (24, 5000), (64, 9000)])
+def test_layer(dtype, d, pool, w, n):
+    pools = {"max": B.SLKV_POOL_MAX, "avg": B.SLKV_POOL_AVG, "none": B.SLKV_POOL_NONE}
+    for caps in ([63, 64, 65, 88], [127, 128, 129, 152], [257, 640, 1000, 100000], [64 + w, 65 + w, 63 + w, 2]):
+        lay = wl.make_layer((501, n, w), [n], 4, 4, d, w, dtype=dtype, bias_frac=0.04)
+        budgets = np.array(caps, dtype=np.int32)
+        gpu = parity.run_gpu(lay, budgets, 1 if pool == "none" else 7, pools[pool], token_major=w == 64)
+        rep = parity.compare_layer(lay, budgets, gpu, 1 if pool == "none" else 7, pools[pool])
+        assert rep["ranked"] >= 2 and rep["tolerant"] == 0
+
+
+# tables of 64 segments and more, empty segments; slices of 64 rows, of 128, none: the gather copies
+@pytest.mark.parametrize("nseq,caps,sliced", [(16, [40, 300, 100, 16], True), (40, [40, 150, 100, 16], True), (32, [40, 300, 100, 16], True),
+                                              (64, [40, 300, 100, 16], False)])
+def test_ragged(nseq, caps, sliced):
+    w = 16
+    rng = np.random.default_rng(nseq)
+    lens = [0 if rng.random() < 0.1 else int(c + t) for t in rng.integers(1, 90, size=nseq) for c in caps]
+    lens[1] = 301                                            # (one segment that keeps more than 256 rows, or all of them)
+    rc = wl.make_ragged_cache((502, nseq), lens, nseq, 4, 4, 64, w, dtype="bf16", bias_frac=0.04)
+    budgets = np.array(caps, dtype=np.int32)
+    gpu = parity.run_gpu_ragged(rc, budgets)
+    rep = parity.compare_ragged(rc, budgets, gpu)
+    assert rep["ranked"] >= 20 and rep["tolerant"] == 0
+    import torch
+    from paper_2508_15806_amd import api
+    args = [api.to_device(x, "bf16") for x in (rc.qwin, rc.k_rows, rc.v_rows)] + [torch.from_numpy(rc.pos_in).cuda()]
+    slices = [sum(1 + (int(x) - 1 >> log2 if x else 0) for x in np.diff(gpu["offsets"])) for log2 in (6, 7)]
+    assert (min(slices) <= 256) == sliced
+    assert ("gather" in launches(gpu["call"], *args)) == (not sliced)
