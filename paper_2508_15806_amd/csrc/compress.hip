@@ -3,7 +3,7 @@
 //   (long histories of 16-bit keys: score_sample, score_both, .. , one pass and exact scores only where they decide)
 //   pass 2  score_*<.., 2>  the chunks folded into the rows' log-sum-exp, logits again, exp(logit - lse) summed down
 //                            the G*w rows -> importance
-//   (16-bit keys, where the workgroups fit the chip at once: both in one launch, score_q_resident_kernel<.., 3>)
+//   (where the workgroups fit the chip at once: both in one launch, score_*<.., 3>)
 //   select                   1-D pooling + per-head top-k (radix select, ordered compaction)
 //   gather                   kept K/V rows -> compacted ragged cache
 // 16-bit keys: 32x32x16 MFMA, queries held in registers, key tiles staged in LDS (score_q_resident_kernel).  E4M3 keys
@@ -1749,7 +1749,8 @@ template <int DK, int KIND, int PASS, class TAB>
 __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab, const void* __restrict__ qmat, const void* __restrict__ kmat,
                                                        int64_t k_stride_tok, int64_t k_stride_head, int R, int Rpad, int w,
                                                        int CH, float c_log2, float* __restrict__ part, float* __restrict__ imp,
-                                                       int grid2d, int rsplit, uint32_t* __restrict__ gm) {
+                                                       int grid2d, int rsplit, uint32_t* __restrict__ gm,
+                                                       meet_t* __restrict__ meet, int limit) {
   using C = ScoreCfg<DK, KIND>;
   constexpr int KK = C::KK, KT = C::KT, RAW = C::RAW, GK = C::GK, RBT = C::RBT, ROWB = C::ROWB, PPR = C::PPR;
   extern __shared__ __attribute__((aligned(16))) unsigned char score_smem[];
@@ -1789,9 +1790,14 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
   }
   const int nchunks = se.chunk1 - se.chunk0;
   if (PASS == 2 && nchunks == 1) return;               // done by pass 1
-  const int key_begin = (bid - se.chunk0) * CH;
-  const int key_end = min(se.n - w, key_begin + CH);
-  const int ngroups = (key_end - key_begin + GK - 1) / GK;
+  const int chunk = bid - se.chunk0;
+  int key_begin, key_end, ngroups;
+  auto set_chunk = [&](int c) __attribute__((always_inline)) {
+    key_begin = c * CH;
+    key_end = min(se.n - w, key_begin + CH);
+    ngroups = (key_end - key_begin + GK - 1) / GK;
+  };
+  set_chunk(chunk);
   // uniform 64-bit base of the segment's keys + 32-bit byte offsets (the host checks the range)
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(kmat) +
       ((int64_t)se.head * k_stride_head + (int64_t)se.tok_begin * k_stride_tok) * C::KB;
@@ -1809,8 +1815,8 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
     }
   };
   // f(registers, group) over this wave's groups kw, kw + KW, ..., two in registers in turn.  The loads past
-  // the last group are issued too (of the chunk's last key): only so does the compiler know how many loads
-  // follow those it waits for.  preloaded: the first two groups are on their way already.
+  // the last group are issued too (of the chunk's last key; PASS 3: of the first two groups, for the sweep to come): only so
+  // does the compiler know how many loads follow those it waits for.  preloaded: the first two groups are on their way already.
   auto sweep = [&](bool preloaded, auto f) __attribute__((always_inline)) {
     int g = kw;
     if (g >= ngroups) return;
@@ -1820,11 +1826,11 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
     }
     for (;;) {
       f(rawA, g);
-      load(rawA, g + 2 * KW);
+      load(rawA, PASS == 3 && g + 2 * KW >= ngroups ? kw : g + 2 * KW);
       g += KW;
       if (g >= ngroups) break;
       f(rawB, g);
-      load(rawB, g + 2 * KW);
+      load(rawB, PASS == 3 && g + 2 * KW >= ngroups ? kw + KW : g + 2 * KW);
       g += KW;
       if (g >= ngroups) break;
     }
@@ -1891,11 +1897,11 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
 
   bool preloaded = true;
   load(rawA, kw);
-  for (int rb0 = 0; rb0 < R; rb0 += RBT * 32) {
-    const int rows = min(R - rb0, RBT * 32), rts = (rows + 31) >> 5;
-    // queries of the block: memory -> LDS
-    if (rb0 > 0) __syncthreads();
-    {
+  int rb0 = 0, rows, rts;                                // the row block at hand
+  // queries of the block: memory -> LDS
+  auto stage_queries = [&]() __attribute__((always_inline)) {
+    rows = min(R - rb0, RBT * 32);
+    rts = (rows + 31) >> 5;
       const unsigned char* qsrc = reinterpret_cast<const unsigned char*>(qmat) + ((int64_t)se.qrow_off + rb0) * (DK * C::QB);
       const int pieces = rts * 32 * PPR;
       for (int i0 = tid; i0 < pieces; i0 += 8 * nthr) {
@@ -1911,10 +1917,9 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
           *reinterpret_cast<u32x4*>(qs + (i / PPR) * ROWB + (i % PPR) * 16) = t[u];
         }
       }
-    }
-    if (preloaded) load(rawB, kw + KW);                // behind the queries: the first group does not wait for it
-
-    if (PASS == 1) {
+  };
+  // row statistics of the chunk: to memory, or (a segment of one chunk) the rows' log-sum-exp to LDS
+  auto statistics = [&]() __attribute__((always_inline)) {
       float2* const mine = stat + (size_t)wv * tiles0 * 64 + lane;
       for (int rt = 0; rt < rts; ++rt) mine[rt * 64] = make_float2(0.f, 0.f);
       __syncthreads();
@@ -1981,7 +1986,7 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
         preloaded = false;
         __syncthreads();
       } else {
-        preloaded = false;
+        preloaded = PASS == 3;
       }
       // the chunk's log-sum-exp of every row of the block (-inf: no key)
       for (int row = tid; row < rts * 32; row += nthr) {
@@ -1998,20 +2003,17 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
         }
         const float l = ss > 0.f ? mm + __builtin_amdgcn_logf(ss) : -INFINITY;
         if (nchunks == 1) lse_s[row] = row < rows && ss > 0.f ? l : INFINITY;
+        else if (PASS == 3) __hip_atomic_store(part + ((int64_t)bid * Rpad + rb0 + row), l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else part[(int64_t)bid * Rpad + rb0 + row] = l;
       }
-      if (nchunks > 1) {
-        preloaded = false;
-        continue;
-      }
-      __syncthreads();
-    } else {
-      const float l = fold_rows(part, se.chunk0, se.chunk1, Rpad, rb0, rts * 32, nthr, stat);
-      if (tid < rts * 32) lse_s[tid] = tid < rows ? l : INFINITY;
-      __syncthreads();
-    }
-
-    // ---- importance of the chunk's keys: sum over the rows of exp2(x - lse)
+  };
+  auto fold = [&]() __attribute__((always_inline)) {
+    const float l = fold_rows<PASS == 3>(part, se.chunk0, se.chunk1, Rpad, rb0, rts * 32, nthr, stat);
+    if (tid < rts * 32) lse_s[tid] = tid < rows ? l : INFINITY;
+    __syncthreads();
+  };
+  // ---- importance of the chunk's keys: sum over the rows of exp2(x - lse)
+  auto importance = [&]() __attribute__((always_inline)) {
     float* const dst = imp + se.score_off;
     float* const col = reinterpret_cast<float*>(stat);   // [wave][lane]
     if (rsplit > 1) col[tid] = 0.f;                      // (of a wave without keys)
@@ -2058,7 +2060,54 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
         put(kw, v);
       }
     }
-    preloaded = false;
+    preloaded = PASS == 3;
+  };
+
+  for (; rb0 < R; rb0 += RBT * 32) {
+    if (rb0 > 0) __syncthreads();
+    stage_queries();
+    if (rb0 == 0) load(rawB, kw + KW);                 // behind the queries: the first group does not wait for it
+    if (PASS == 2) {
+      fold();
+    } else {
+      statistics();
+      if (nchunks > 1) continue;
+      __syncthreads();
+    }
+    importance();
+  }
+  if constexpr (PASS == 3) {
+    if (nchunks == 1) return;
+    // The second pass, with the first keys on their way and (one row block) the queries where they are.  As a rule over this chunk
+    // alone; `left`, in thread 0: those whose workgroups have left.
+    __shared__ int sh_next;
+    meet_t* const word = meet + (int64_t)seg * kMeetWords;
+    meet_t left = 0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the statistics are in memory
+    __syncthreads();
+    if (tid == 0) {
+      left = meet_chunks(word, nchunks, chunk, limit);
+      sh_next = left != kMeetLeft ? chunk : -1;
+    }
+    for (;;) {
+      __syncthreads();
+      const int next = sh_next;
+      if (next < 0) return;
+      if (next != chunk) {
+        set_chunk(next);
+        preloaded = false;
+      }
+      for (rb0 = 0; rb0 < R; rb0 += RBT * 32) {
+        if (R > RBT * 32) {
+          if (rb0 > 0) __syncthreads();
+          stage_queries();
+        }
+        fold();
+        importance();
+      }
+      __syncthreads();                                   // (every thread has read sh_next, and the sums in LDS)
+      if (tid == 0) sh_next = meet_take(word, left);
+    }
   }
 }
 
@@ -3474,7 +3523,8 @@ struct Plan {
   int rsplit;            // of these, that share a key group's query tiles (score_k_resident_kernel)
   size_t part_bytes, score_bytes, hist_bytes, table_bytes;
   size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
-  bool together;         // both scoring passes in one launch (see meet_chunks), if its workgroups fit the chip
+  int per_cu;            // workgroups of a scoring launch that a CU holds at least
+  int meet_most;         // chunks of a segment up to which both scoring passes take one launch (see meet_chunks), if its workgroups fit the chip
   bool one_scan;         // the call may go over its keys once (see OneScan), if the workspace has these bytes as well
   int sampled;           // see range_len
   int64_t ranges;
@@ -3557,6 +3607,12 @@ struct RankedLengths {
 // fp32: 4 heads x 1 K keys, d 64, one query tile 24.2 -> 19.7 us (groups of 32 keys instead of 64); 2 x 700, d 128, four tiles
 // 36.8 -> 25.3; 8 x 2 K, d 64, two tiles 28.0 -> 20.6; E4M3: 22 segments of 104 to 878 keys, four tiles 27.2 -> 19.9; 8 x 1.5 K 22.8 -> 19.4;
 // 56 segments of one chunk 27.7 -> 22.6 (no second pass); 8 x 32 K as before.
+//
+// Both passes in one launch (PASS 3): the queries stay in LDS, up to two groups of keys a wave in registers (the second pass then reads no key).  Two launches
+// / one, us a call: E4M3 8 x 32 K 57.8 / 55.1, 16 x 32 K 90.4 / 84.2, 128 x 3 K 64.0 / 58.0, 192 x 1.7 to 9 K of 64 rows 99.1 / 84.2, 4 x 20 K of 448 rows 62.9 / 58.3,
+// 8 x 2 K 21.6 / 20.5, a decode cache of 256 segments 35.3 / 34.6, of 8 22.9 / 20.3; fp32 4 x 1 K 20.6 / 19.4, 32 x 0.6 K 23.9 / 22.7.  Not with many short
+// chunks to a segment, for which everybody waits and which everybody reads back: E4M3 8 x 12 K in 47 each 27.8 / 28.5; fp32 8 x 4 K in 31 29.6 / 29.8, 8 x 2 K in 32
+// 31.5 / 31.7.  (Planned for, by its lower cost, one launch takes fewer, longer chunks: 8 x 8 K fp32 46.3 -> 47.5.)
 static void plan_k_resident(const Geometry& g, Plan& p) {
   constexpr double kLaunchUs = 3.7, kFoldUs = 0.03;
   const bool f32 = g.dtype == SLKV_F32;
@@ -3573,6 +3629,7 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
   const RankedLengths lens(g);
   const int64_t longest = lens.longest, ranked = lens.ranked;
   double best = 0;
+  p.per_cu = 1;
   p.waves = 8;
   p.rsplit = 1;
   p.CH = 8 * gk;
@@ -3595,6 +3652,7 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
           p.waves = waves;
           p.rsplit = rs;
           p.CH = (int)(gpw * unit);
+          p.per_cu = pairs ? 2 : 1;
         }
         return rounds <= 1;
       };
@@ -3606,6 +3664,7 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
       consider(most);
     }
   }
+  p.meet_most = f32 ? 16 : 32;
 }
 
 // Chunk length of score_q_resident_kernel: what takes the least time, by a workgroup's start and end and the time of a
@@ -3656,7 +3715,8 @@ static void plan_q_resident(const Geometry& g, Plan& p) {
   }
   p.waves = 4;
   p.rsplit = 1;
-  p.together = best <= kTogetherUs;
+  p.per_cu = cfg == 3 ? 1 : 2;
+  p.meet_most = best <= kTogetherUs ? kMeetMost : 0;
   const double worth = lens.longest <= kSelRound ? kOneScanResidentUs : cfg == 2 ? kOneScanUs : kOneScanFewRowsUs;
   p.one_scan = best >= worth && (cfg == 2 || lens.longest > kSelRound) && p.R <= 256 && g.pool != SLKV_POOL_AVG && g.segs.size() <= (size_t)kMaxSegPerLaunch;
 }
@@ -3679,7 +3739,7 @@ static void plan_ranges(const Geometry& g, Plan& p) {
 }
 
 static void make_plan(const Geometry& g, Plan& p) {
-  p.one_scan = p.together = false;
+  p.one_scan = false;
   p.R = (g.Hq / g.Hkv) * g.w;
   p.Rpad = (p.R + 31) / 32 * 32;
   if (g.dtype == SLKV_BF16 || g.dtype == SLKV_F16) plan_q_resident(g, p);
@@ -3833,12 +3893,13 @@ static void launch_score_k(int pass, ScoreGrid grid, hipStream_t st, const TAB& 
     const bool two = grid.rows > 0;
     const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
     const size_t lds = score_lds_bytes<DK, KIND>(std::min((p.R + 31) / 32, ScoreCfg<DK, KIND>::RBT), p.waves);
-    if (pass == 1)
-      SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 1, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, p.rsplit, buf.gm);
-    else
-      SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, 2, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
-                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, p.rsplit, buf.gm);
+    auto scan = [&](auto pass_c) {
+      SLKV_LAUNCH((score_k_resident_kernel<DK, KIND, decltype(pass_c)::value, TAB>), gr, dim3(64 * p.waves), lds, st, tab, q, k, g.k_stride_tok,
+                  g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, p.rsplit, buf.gm, buf.meet, buf.limit);
+    };
+    if (pass == 1) scan(std::integral_constant<int, 1>{});
+    if (pass == 2) scan(std::integral_constant<int, 2>{});
+    if (pass == kPassTogether) scan(std::integral_constant<int, 3>{});
   }
 }
 
@@ -3922,11 +3983,12 @@ template <int DK, int KIND, class TAB>
 static hipError_t raise_score_limit() {
   if constexpr (KIND <= 1) return hipSuccess;          // (score_q_resident_kernel has static LDS)
   else {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 1, TAB>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 2, TAB>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    for (const void* kernel : {reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 1, TAB>), reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 2, TAB>),
+                               reinterpret_cast<const void*>(&score_k_resident_kernel<DK, KIND, 3, TAB>)}) {
+      const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
 }
 
@@ -4134,7 +4196,8 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       sgrid.rows = tab.nseg;
     }
     // Both passes in one launch where all its workgroups fit the chip at once and the selection clears their meeting places.
-    if (p.together && !one_scan && resident_select && S <= kMeetSegments && max_chunks <= kMeetMost && chunks <= (p.R <= 256 ? 2 : 1) * cus) {
+    if (!one_scan && resident_select && S <= kMeetSegments && max_chunks > (k_resident ? 1 : 0) && max_chunks <= p.meet_most &&
+        chunks <= p.per_cu * cus) {
       buf.meet = (meet_t*)ws;
       buf.limit = meet_limit();
     }

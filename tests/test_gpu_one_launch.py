@@ -62,6 +62,20 @@ def test_layer(monkeypatch, dtype, Hq, Hkv, w, d, lens):
     compare(monkeypatch, call, lambda: call.run(q, k, v))
 
 
+# fp32 and E4M3 keys: one and several blocks of query rows, key groups that all stay in registers and more of them, waves that share a
+# group, segments of one chunk among longer ones
+@pytest.mark.parametrize("dtype,Hq,Hkv,w,d,lens,together", [
+    ("f32", 4, 4, 32, 64, [1024], True), ("f32", 2, 2, 32, 128, [32 + 1, 32 + 33, 700], True), ("f32", 8, 2, 64, 128, [64 + 31, 1300], True),
+    ("f32", 16, 2, 64, 64, [900, 300], True), ("f32", 8, 8, 64, 64, [3000], False), ("bf16_kv8", 8, 2, 16, 64, [2000], True),
+    ("bf16_kv8", 32, 8, 64, 128, [20000], True), ("bf16_kv8", 14, 2, 64, 128, [3000, 200], True), ("bf16_kv8", 16, 2, 32, 128, [32 + 1, 32 + 64, 32 + 65, 1500], True),
+    ("bf16_kv8", 32, 8, 32, 128, [20000, 31000, 9000], True), ("bf16_kv8", 32, 8, 32, 128, [8192], False)])
+def test_keys_in_registers(monkeypatch, dtype, Hq, Hkv, w, d, lens, together):
+    lay = wl.make_layer((404, Hq, w, d), lens, Hq, Hkv, d, w, dtype=dtype, bias_frac=0.04)
+    call = api.LayerCall(dtype, len(lens), Hq, Hkv, d, w, lay.cu_seqlens, np.array([w + 20 + 31 * h for h in range(Hkv)], dtype=np.int32), debug_scores=True)
+    q, k, v = (api.to_device(x, dtype) for x in (lay.qwin, lay.k, lay.v))
+    compare(monkeypatch, call, lambda: call.run(q, k, v), together)
+
+
 def test_most_chunks_of_a_segment(monkeypatch):
     # one KV head: as many chunks as a meeting place counts take one launch, more take two
     for n, together in ((48 * 128 + 32, True), (48 * 128 + 33, False)):
