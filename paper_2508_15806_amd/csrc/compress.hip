@@ -282,10 +282,10 @@ __device__ __forceinline__ meet_t meet_chunks(meet_t* word, int nchunks, int chu
   do {
     __builtin_amdgcn_s_sleep(1);
     w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (w >> kMeetMost == full) return w & bits;
+    if (w >> kMeetMost >= full) return w & bits;         // (more: some have scored a chunk already, see meet_scores)
   } while (wall_clock64() - start < limit);
   w = __hip_atomic_fetch_or(word, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (w >> kMeetMost != full) return kMeetLeft;
+  if (w >> kMeetMost < full) return kMeetLeft;
   // full meanwhile: this chunk again, unless somebody has taken it
   w = __hip_atomic_fetch_and(word, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return w & bit ? w & bits & ~bit : kMeetLeft;
@@ -298,6 +298,29 @@ __device__ __forceinline__ int meet_take(meet_t* word, meet_t& left) {
     if (__hip_atomic_fetch_and(word, ~(1ull << c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> c & 1) return c;
   }
   return -1;
+}
+
+// The segment finished in the launch that scores it (PASS 4).  Behind the second pass a workgroup counts the chunks it has scored in the same
+// word, up to twice their number, and waits for the others as before.  Whoever sees all scored selects, each the whole segment, and takes slices
+// of the kept rows from the next word, of which there are as many as chunks, until none is left.  One that has waited `limit` leaves, without a
+// word: the one that counts the last chunk does not wait.  A third word counts the workgroups that touch these words no more; the last one clears them.
+__device__ __forceinline__ bool meet_scores(meet_t* word, int nchunks, int scored, int limit) {
+  const meet_t full = 2 * (meet_t)nchunks, add = (meet_t)scored << kMeetMost;
+  if ((__hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add) >> kMeetMost == full) return true;
+  const long long start = wall_clock64();
+  do {
+    __builtin_amdgcn_s_sleep(1);
+    if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kMeetMost == full) return true;
+  } while (wall_clock64() - start < limit);
+  return false;
+}
+__device__ __forceinline__ int meet_slice(meet_t* word) {
+  return (int)__hip_atomic_fetch_add(word + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void meet_leave(meet_t* word, int nchunks) {
+  if (__hip_atomic_fetch_add(word + 2, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != (meet_t)nchunks) return;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) __hip_atomic_store(word + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Per segment: the words of OneScanBounds; smallest, largest and mean rho.
@@ -332,6 +355,280 @@ __device__ __forceinline__ void tile_priority(int t) {
   else __builtin_amdgcn_s_setprio(1);
 }
 
+struct GatherArgs {
+  const unsigned char* k;
+  const unsigned char* v;
+  unsigned char* k_out;
+  unsigned char* v_out;
+  int64_t k_stride_tok, k_stride_head, v_stride_tok, v_stride_head;   // elements
+  int lanes_per_row, elt_bytes;
+  const int32_t* pos_in;   // optional: original position of every input row (ragged input)
+  int32_t* pos_out;        // optional: pos_in at the kept rows
+};
+
+constexpr int kSelHaloMax = kMaxPool / 2;
+constexpr uint32_t kKeyNone = 0xffffffffu;
+
+// What a scoring launch that also selects and copies (PASS 4) needs beside the scores.
+struct FinishArgs {
+  GatherArgs ga;
+  float* pooled;
+  int32_t* kept_idx;
+  int64_t* out_offsets;    // or NULL
+  int pool_kernel, pool_mode, write_pooled;
+  int chunks;              // workgroups of chunks; those behind them copy segments that are not ranked
+};
+
+// Rows of a segment to output rows row0 .. row0 + rows - 1, of which pos(i) gives the i-th one's position: four 16-byte pieces of K and V in flight a thread.
+template <class F>
+__device__ __forceinline__ void copy_rows(const GatherArgs& ga, const SegShape& sg, int64_t row0, int rows, int nthr, F pos) {
+  const int lpr = ga.lanes_per_row, shift = __builtin_ctz(lpr), pieces = rows << shift;   // (4 to 32 lanes per row: a power of two)
+  const int64_t h = sg.head;
+  for (int base = (int)threadIdx.x; base < pieces; base += 4 * nthr) {
+    u32x4 kq[4], vq[4];
+    int64_t tok[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int idx = min(base + u * nthr, pieces - 1), c = idx & (lpr - 1);
+      tok[u] = (int64_t)sg.tok_begin + pos(idx >> shift);
+      kq[u] = *reinterpret_cast<const u32x4*>(ga.k + (h * ga.k_stride_head + tok[u] * ga.k_stride_tok) * ga.elt_bytes + c * 16);
+      vq[u] = *reinterpret_cast<const u32x4*>(ga.v + (h * ga.v_stride_head + tok[u] * ga.v_stride_tok) * ga.elt_bytes + c * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int idx = base + u * nthr;
+      if (idx < pieces) {
+        const int64_t row = row0 + (idx >> shift), o = (row << shift) * 16 + (idx & (lpr - 1)) * 16;
+        *reinterpret_cast<u32x4*>(ga.k_out + o) = kq[u];
+        *reinterpret_cast<u32x4*>(ga.v_out + o) = vq[u];
+        if (ga.pos_out && (idx & (lpr - 1)) == 0) ga.pos_out[row] = ga.pos_in[tok[u]];
+      }
+    }
+  }
+}
+
+// Workgroup `more` of those that copy segments that are not ranked: kFinishRows rows of one, or (kk == 0) of its window.
+constexpr int kFinishRowsLog2 = 7;
+template <class TAB>
+__device__ __forceinline__ void copy_unranked(const TAB& tab, const FinishArgs& fin, int w, int more, int nthr) {
+  const int lane = threadIdx.x & 63;
+  for (int s0 = 0; s0 < tab.nseg; s0 += 64) {
+    const int s = min(s0 + lane, tab.nseg - 1);
+    const SegShape sh = tab.shape(s);
+    const bool unranked = s0 + lane < tab.nseg && !(sh.kk > 0 && sh.kk < sh.n - w);
+    const int rows = unranked ? tab.out_off(s + 1) - tab.out_off(s) : 0;
+    const int parts = unranked ? 1 + (max(rows - 1, 0) >> kFinishRowsLog2) : 0, incl = (int)wave_incl_scan((uint32_t)parts);
+    const unsigned long long past = __builtin_amdgcn_ballot_w64(incl > more);
+    if (past) {
+      const int l = __builtin_ctzll(past), seg = s0 + l, first = (more - __builtin_amdgcn_readlane(incl - parts, l)) << kFinishRowsLog2;
+      const SegShape sg = tab.shape(seg);
+      const int64_t row0 = tab.out_off(seg) + first;
+      const int cnt = min(tab.out_off(seg + 1) - tab.out_off(seg) - first, 1 << kFinishRowsLog2), at = first + (sg.kk < 0 ? 0 : sg.n - w);
+      if (first == 0 && threadIdx.x == 0 && fin.out_offsets) {
+        fin.out_offsets[seg] = tab.out_off(seg);
+        if (seg == tab.nseg - 1) fin.out_offsets[seg + 1] = tab.out_off(tab.nseg);
+      }
+      for (int i = threadIdx.x; i < cnt; i += nthr) fin.kept_idx[row0 + i] = at + i;
+      if (cnt > 0) copy_rows(fin.ga, sg, row0, cnt, nthr, [&](int i) { return at + i; });
+      return;
+    }
+    more -= __builtin_amdgcn_readlane(incl, 63);
+  }
+}
+
+// Pooling, top-k and copy (as select_resident_kernel, with the same keys and order) of a segment of at most kFinishMost positions by a workgroup that has
+// scored some of them; in `smem`, LDS that nobody reads any more.  The phases take a few us whatever they are spread over, so every workgroup of
+// the segment goes through them all and copies a slice of the rows; rows of one segment travel while another is still scored or selected.
+//   It takes the place of a selection with one workgroup per CU and of a gather, where both would be launched.  Three launches / one, us a call, 16-bit keys:
+// a decode cache of 256 segments, 107 to 1834 kept, 56.6 / 51.1; of 128 40.4 / 38.5; 192 segments, 500 kept on average, 512 new, averages 79.2 / 65.0; 384 heads of
+// 300 55.7 / 45.0; 24 prompts of 500 to 1000 48.4 / 39.5; at worst 256 segments of 300 kept each, 128 rows 35.6 / 36.1.
+//   Bound by the chain of its phases, and 256 threads go through it more slowly than the 1024 of the selection kernel, so not where no gather follows: scoring and
+// selection / one launch: 8 x 2 K 18.2 / 21.1, one sequence's cache 18.6 / 21.6, 16 prompts of 1 to 1.7 K 40.3 / 49.3; nor up to 64 segments (64 x 1000 kept 35.8 / 35.7);
+// nor fp32 and E4M3 keys, whose kernel keeps one workgroup on a CU (E4M3 cache of 256 segments 74.1 / 74.2; fp32 4 x 1 K 19.3 / 22.6).
+constexpr int kFinishMost = 2048;
+constexpr int kFinishRank = 256;          // keys of a digit that are ranked by counting
+constexpr int kFinishStage = (kFinishMost + 2 * kSelHaloMax) / 4 * 5 + 16;   // padded for 4 positions a thread; then a list, then the kept positions
+constexpr int kFinishWords = kFinishStage + kHistBins + 48;
+template <int NT, class TAB>
+__device__ __forceinline__ void finish_segment(uint32_t* smem, const TAB& tab, const FinishArgs& fin, int seg, int w, const float* imp, meet_t* word,
+                                               int nchunks) {
+  constexpr int EPT = kFinishMost / NT;
+  static_assert(EPT >= 4 && EPT <= 32 && kFinishRank <= NT, "padding of the stage; a thread per listed key");
+  float* const stage = reinterpret_cast<float*>(smem);
+  int32_t* const at = reinterpret_cast<int32_t*>(smem);
+  uint32_t* const hist = smem + kFinishStage;
+  uint32_t* const sh_scan = hist + kHistBins;                  // 16
+  uint32_t* const sh_mm = sh_scan + 16;                        // 2 * NT / 64
+  uint32_t* const res = sh_mm + 16;                            // [0], [1]: digit search and ranking; [2]: length of the list; [3]: slice
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  auto pad = [](int i) { return i + i / EPT; };
+  const SegShape sg = tab.shape(seg);
+  const int m = sg.n - w, kk = sg.kk, radius = fin.pool_kernel / 2;
+  const int out0 = tab.out_off(seg), kept = tab.out_off(seg + 1) - out0, per = (kept + nchunks - 1) / nchunks;
+  const float* const I = imp + sg.score_off;
+  if (tid == 0) {
+    res[2] = 0;
+    res[3] = nchunks > 1 ? (uint32_t)meet_slice(word) : 0u;
+  }
+  auto score_at = [&](int j) __attribute__((always_inline)) {
+    return __hip_atomic_load(I + min(max(j, 0), m - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  float ld[EPT + 1];
+#pragma unroll
+  for (int c = 0; c <= EPT; ++c) ld[c] = score_at((c < EPT ? c * NT + tid : kFinishMost + min(tid, 2 * radius)) - radius);
+  for (int i = tid; i < kHistBins; i += NT) hist[i] = 0;
+#pragma unroll
+  for (int c = 0; c <= EPT; ++c) {
+    const int i = c * NT + tid, j = i - radius;
+    if (c < EPT || tid < 2 * radius) stage[pad(i)] = j >= 0 && j < m ? ld[c] : 0.f;
+  }
+  __syncthreads();
+  // pooled scores of this thread's positions, in the order of select_resident_kernel (up to a radius of 3 maxima of the keys)
+  const int j0 = EPT * tid;
+  uint32_t key[EPT];
+  {
+    float a[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      a[e] = stage[pad(j0 + e)];
+      key[e] = score_key(a[e]);
+    }
+    const bool is_max = fin.pool_mode != SLKV_POOL_AVG, by_key = is_max && radius <= 3;
+    for (int t = 1; t <= 2 * radius; ++t) {
+      float x[EPT];
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) x[e] = stage[pad(j0 + e + t)];
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        if (by_key) key[e] = max(key[e], score_key(x[e]));
+        else a[e] = is_max ? fmaxf(a[e], x[e]) : a[e] + x[e];
+      }
+    }
+    const float inv_p = 1.f / (float)fin.pool_kernel;
+    if (!by_key)
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) key[e] = score_key(is_max ? a[e] : a[e] * inv_p);
+  }
+  uint32_t kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    if (j0 + e < m) {
+      kmin = min(kmin, key[e]);
+      kmax = max(kmax, key[e]);
+    } else {
+      key[e] = kKeyNone;
+    }
+  }
+  kmin = wave_reduce_to_last(kmin, [](uint32_t a, uint32_t b) { return min(a, b); });
+  kmax = wave_reduce_to_last(kmax, [](uint32_t a, uint32_t b) { return max(a, b); });
+  if (lane == 63) {
+    sh_mm[wv] = kmin;
+    sh_mm[NT / 64 + wv] = kmax;
+  }
+  __syncthreads();
+  int slice = (int)res[3];
+  uint32_t lo = sh_mm[0], hi = sh_mm[NT / 64], k = (uint32_t)kk;
+#pragma unroll
+  for (int i = 1; i < NT / 64; ++i) {
+    lo = min(lo, sh_mm[i]);
+    hi = max(hi, sh_mm[NT / 64 + i]);
+  }
+  // the k-th largest key: 11 bits of the range at a time, until the digit's keys are few enough to be ranked by counting
+  while (hi != lo) {
+    const uint32_t span = hi - lo;
+    const int nbits = 32 - __clz(span), shift = nbits > 11 ? nbits - 11 : 0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const uint32_t dk = key[e] - lo;                         // (a key below lo wraps to a difference above any span)
+      if (dk <= span) atomicAdd(&hist[dk >> shift], 1u);
+    }
+    __syncthreads();
+    select_bin<NT>(hist, k, sh_scan, res);
+    const uint32_t d = res[0], cnt = hist[d];
+    k = res[1];
+    lo += d << shift;
+    hi = min(hi, lo + ((1u << shift) - 1u));
+    if (shift == 0) break;
+    if (cnt <= (uint32_t)kFinishRank) {
+      uint32_t* const list = smem;                             // (the scores are in registers)
+#pragma unroll
+      for (int e = 0; e < EPT; ++e)
+        if (key[e] - lo <= hi - lo) list[atomicAdd(&res[2], 1u)] = key[e];
+      __syncthreads();
+      if ((uint32_t)tid < cnt) {
+        const uint32_t kv = list[tid];
+        uint32_t gt = 0, ge = 0;
+        for (uint32_t i = 0; i < cnt; i += 4) {
+#pragma unroll
+          for (uint32_t u = 0; u < 4; ++u) {
+            const uint32_t o = list[i + u];
+            const bool live = i + u < cnt;
+            gt += live && o > kv ? 1u : 0u;
+            ge += live && o >= kv ? 1u : 0u;
+          }
+        }
+        if (gt < k && k <= ge) {                               // (every thread that holds the k-th largest value writes the same pair)
+          res[0] = kv;
+          res[1] = k - gt;
+        }
+      }
+      __syncthreads();
+      lo = res[0];
+      k = res[1];
+      break;
+    }
+    __syncthreads();                                           // every thread has read the digit's count
+    for (int i = tid; i < kHistBins; i += NT) hist[i] = 0;
+    __syncthreads();
+  }
+  const uint32_t tau = lo, need_eq = k;
+  // ordered compaction: slot = (#greater before) + min(#equal before, need_eq)
+  uint32_t gmask = 0, emask = 0;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    gmask |= key[e] > tau && key[e] != kKeyNone ? 1u << e : 0u;
+    emask |= key[e] == tau ? 1u << e : 0u;
+  }
+  const uint32_t ce = __popc(emask), packed = ce << 16 | __popc(gmask);
+  const uint32_t excl = block_incl_scan<NT, false>(packed, sh_scan) - packed, e_before = excl >> 16;   // (its barrier: the list has been read)
+  // (taken as the smaller first: of `e < need ? min(need - e, n) : 0` beside min(e, need) this compiler drops the comparison and the minimum)
+  const uint32_t equal0 = min(e_before, need_eq);
+  uint32_t kept_here = gmask, em = emask;
+  for (uint32_t take = min(need_eq - equal0, ce); take > 0; --take) {
+    kept_here |= em & (0u - em);
+    em &= em - 1u;
+  }
+  const int slot0 = (int)((excl & 0xffffu) + equal0);
+  while (slice < nchunks) {
+    const int first = slice * per, rows = max(min(kept - first, per), 0);
+    int slot = slot0 - first;
+    for (uint32_t sel = kept_here; sel; sel &= sel - 1u, ++slot)
+      if ((uint32_t)slot < (uint32_t)rows) at[slot] = j0 + __ffs(sel) - 1;
+    if (slice == 0) {
+      if (tid == 0 && fin.out_offsets) {
+        fin.out_offsets[seg] = out0;
+        if (seg == tab.nseg - 1) fin.out_offsets[seg + 1] = tab.out_off(tab.nseg);
+      }
+      if (fin.write_pooled) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+          if (j0 + e < m) fin.pooled[sg.score_off + j0 + e] = __uint_as_float(key[e]);
+      }
+    }
+    int next = nchunks;
+    if (tid == 0 && nchunks > 1) next = meet_slice(word);      // (on its way while the rows are copied)
+    __syncthreads();
+    auto pos = [&](int i) __attribute__((always_inline)) { return first + i < kk ? min(max(at[i], 0), m - 1) : m + first + i - kk; };   // (clamped as in gather_kernel)
+    for (int i = tid; i < rows; i += NT) fin.kept_idx[out0 + first + i] = pos(i);
+    if (rows > 0) copy_rows(fin.ga, sg, (int64_t)out0 + first, rows, NT, pos);
+    if (nchunks == 1) break;
+    if (tid == 0) res[3] = (uint32_t)next;
+    __syncthreads();                                           // (and the positions have been read)
+    slice = (int)res[3];
+  }
+  if (nchunks > 1 && tid == 0) meet_leave(word, nchunks);
+}
+
 // ------------------------------------------------------------------------------------------
 // MFMA scoring of 16-bit inputs (bfloat16 or half).  One workgroup (4 waves) owns one chunk of history keys of one segment.
 // K is staged in LDS in tiles of 64 keys (two buffers); up to kPrefetch further tiles are in
@@ -343,6 +640,7 @@ __device__ __forceinline__ void tile_priority(int t) {
 //   PASS 1: D[key][qrow]: a lane owns one query row per MFMA tile -> sum of exp2(x - reference).
 //   PASS 2: D[qrow][key]: a lane owns one key column -> sum over rows of exp2(x - lse[row]).
 //   PASS 3: both, in one launch: the workgroups of a segment meet in between (meet_chunks).
+//   PASS 4: as 3, and they select and copy as well (finish_segment).
 // Rows beyond R and keys beyond the chunk are loaded from a clamped (valid) address and masked.
 constexpr int kTileKeys = 64;
 constexpr int kPrefetch = 2;
@@ -353,8 +651,8 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
                                                          int64_t k_stride_head, int R, int Rpad, int w, int CH,
                                                          float c_log2, float* __restrict__ part,
                                                          float* __restrict__ imp, int grid2d, uint32_t* __restrict__ gm,
-                                                         meet_t* __restrict__ meet, int limit) {
-  constexpr bool STATS = PASS != 2, BOTH = PASS == 3;
+                                                         meet_t* __restrict__ meet, int limit, const FinishArgs fin) {
+  constexpr bool STATS = PASS != 2, BOTH = PASS >= 3, FINISH = PASS == 4;
   constexpr int KS = 4 / RB;               // waves along the keys
   constexpr int TK = kTileKeys;
   constexpr int NSUB = TK / 32 / KS;       // 32-key sub-tiles per wave per tile
@@ -364,7 +662,9 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
   constexpr int LPT = TK * CPR / 256;      // pieces per thread per tile
   constexpr int NPF = kPrefetch;
   static_assert(TK * CPR % 256 == 0 && LPT < 16, "tile must divide over the workgroup; LPT is or-ed into a wait count");
-  __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TK * ROWB];
+  constexpr int KTILES = 2 * TK * ROWB, FINW = FINISH ? kFinishWords * 4 : 0;
+  __shared__ __attribute__((aligned(16))) unsigned char ktile_s[KTILES > FINW ? KTILES : FINW];   // (PASS 4: the selection's as well)
+  unsigned char (*const ktile)[TK * ROWB] = reinterpret_cast<unsigned char (*)[TK * ROWB]>(ktile_s);
   __shared__ float red[2][RB][TK];
   __shared__ float2 comb[KS][RB * 32 * MT];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -394,6 +694,10 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     if (bid >= se.chunk1) return;
   } else {
     bid = blockIdx.x;
+    if (FINISH && bid >= fin.chunks) {
+      copy_unranked(tab, fin, w, bid - fin.chunks, 256);
+      return;
+    }
     seg = find_segment_wave(tab.nseg, bid, [&](int s) { return tab.chunk_begin(s); });
     se = entry_of(seg);
   }
@@ -479,6 +783,10 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
 
   // importance of a key (the lanes of a wave have neighbouring ones) and, if asked for, of its group
   auto put_sum = [&](int key, float v) __attribute__((always_inline)) {
+    if (FINISH) {
+      if (key < key_end) __hip_atomic_store(imp + se.score_off + key, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
     if (key < key_end) imp[se.score_off + key] = v;
     if (gm) {
       const uint32_t top = max_8_lanes(key < key_end ? score_key(v) : 0u);
@@ -788,6 +1096,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
     meet_t* const word = meet + (int64_t)seg * kMeetWords;
     meet_t left = 0;
     bool met = false;
+    int scored = 0;
     for (;;) {
       if (met || nchunks == 1) {
         issue_tile(0, pf0);
@@ -799,6 +1108,7 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
         if (tid == 0) {
           left = meet_chunks(word, nchunks, chunk, limit);
           sh_next = left != kMeetLeft;
+          if (FINISH && left == kMeetLeft) meet_leave(word, nchunks);
         }
         __syncthreads();
         if (!sh_next) return;
@@ -812,11 +1122,26 @@ __global__ __launch_bounds__(256, (MT <= 2 ? 2 : 1)) void score_q_resident_kerne
       if (!met) share_lse();
       met = true;
       accumulate();
+      ++scored;
       if (nchunks == 1) break;
       if (tid == 0) sh_next = meet_take(word, left);
       __syncthreads();
       if (sh_next < 0) break;
       set_chunk(sh_next);
+    }
+    if constexpr (FINISH) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the scores are in memory
+      __syncthreads();
+      if (nchunks > 1) {
+        if (tid == 0) {
+          const bool all = meet_scores(word, nchunks, scored, limit);
+          if (!all) meet_leave(word, nchunks);
+          sh_next = all;
+        }
+        __syncthreads();
+        if (!sh_next) return;
+      }
+      finish_segment<256>(reinterpret_cast<uint32_t*>(ktile_s), tab, fin, seg, w, imp, word, nchunks);
     }
   }
 }
@@ -2144,17 +2469,6 @@ __global__ __launch_bounds__(512, 2) void score_k_resident_kernel(const TAB tab,
 constexpr int kSliceLog2Least = 6, kSliceLog2Most = 7;
 constexpr int kInlineGatherRows = 256;    // without slices: segments up to this many kept rows are gathered by the selection kernel
 
-struct GatherArgs {
-  const unsigned char* k;
-  const unsigned char* v;
-  unsigned char* k_out;
-  unsigned char* v_out;
-  int64_t k_stride_tok, k_stride_head, v_stride_tok, v_stride_head;   // elements
-  int lanes_per_row, elt_bytes;
-  const int32_t* pos_in;   // optional: original position of every input row (ragged input)
-  int32_t* pos_out;        // optional: pos_in at the kept rows
-};
-
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelBlock = 4096;           // history positions per phase-A block
@@ -2162,12 +2476,10 @@ constexpr int kSelEmitThreads = 256;      // workgroup of the block-wise count /
 constexpr int kSelEPT = 32;
 constexpr int kSelEPTMid = 8, kSelEPTSmall = 2;   // shorter histories: fewer positions per thread in the one-workgroup kernel
 constexpr int kSelRound = kSelThreads * kSelEPT;
-constexpr int kSelHaloMax = kMaxPool / 2;
 constexpr int kSelRankMax = 256;          // lists up to this length are ranked by direct counting
 constexpr int kSelTieGroups = 512;        // this many group maxima in the bound's digit switch the histograms to the pile-aware step
 constexpr int kSelTrackMax = 512;         // up to this many wanted keys the first level also tracks the largest and smallest key of every digit
 constexpr int kDigitShift = 20;           // first-level digit = key >> 20: sign (0), 8 exponent and 3 mantissa bits
-constexpr uint32_t kKeyNone = 0xffffffffu;
 static_assert((0x7f800000u >> kDigitShift) < (uint32_t)kHistBins, "every key has a first-level digit inside the histogram");
 
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
@@ -3832,8 +4144,8 @@ struct ScoreGrid {
   int chunks, per_row, rows;
 };
 
-// The passes of a call: 1 and 2, both in one launch, or three for one pass over the keys.
-constexpr int kPassSample = 0, kPassTogether = 3, kPassBoth = 4, kPassChosen = 5;
+// The passes of a call: 1 and 2, both in one launch, these with the selection and the copy, or three for one pass over the keys.
+constexpr int kPassSample = 0, kPassTogether = 3, kPassFinish = 4, kPassBoth = 5, kPassChosen = 6;
 
 // What the scoring passes write, for each other and for the selection.
 struct ScoreBuffers {
@@ -3844,6 +4156,7 @@ struct ScoreBuffers {
   uint32_t* blockhist;     // or NULL: one workgroup per segment selects
   meet_t* meet;            // both passes in one launch: where their workgroups meet (see meet_chunks), or NULL
   int limit;               // and how long they wait, in ticks of 10 ns
+  FinishArgs fin;          // kPassFinish: the rest of the call
 };
 
 template <int DK, int MT, int RB, int KIND, class TAB>
@@ -3854,11 +4167,14 @@ static void launch_q_resident(int pass, ScoreGrid grid, hipStream_t st, const TA
   const dim3 gr = two ? dim3((unsigned)grid.per_row, (unsigned)grid.rows) : dim3((unsigned)grid.chunks);
   auto scan = [&](auto pass_c) {
     SLKV_LAUNCH((score_q_resident_kernel<DK, MT, RB, decltype(pass_c)::value, KIND, TAB>), gr, dim3(256), 0, st, tab, (const uint16_t*)q, k,
-                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.gm, buf.meet, buf.limit);
+                g.k_stride_tok, g.k_stride_head, p.R, p.Rpad, g.w, p.CH, c_log2, buf.part, buf.imp, two ? 1 : 0, buf.gm, buf.meet, buf.limit, buf.fin);
   };
   if (pass == 1) scan(std::integral_constant<int, 1>{});
   if (pass == 2) scan(std::integral_constant<int, 2>{});
   if (pass == kPassTogether) scan(std::integral_constant<int, 3>{});
+  if constexpr (std::is_same_v<TAB, SegTableBig>) {
+    if (pass == kPassFinish) scan(std::integral_constant<int, 4>{});
+  }
   if constexpr (MT <= 2 && std::is_same_v<TAB, SegTable>) {
     const unsigned S = (unsigned)g.segs.size();
     if (pass == kPassSample)
@@ -4074,7 +4390,7 @@ static hipError_t launch_select_resident(SelectGrid sel, hipStream_t st, const T
 }
 
 // SLKV_SELECT=resident|blocks in the environment forces one selection kernel (tests run both on
-// every shape the resident one covers); default: chosen per call.  0 auto, 1 resident, 2 blocks.
+// every shape the resident one covers); default: chosen per call, or none where the scoring launch selects.  0 auto, 1 resident, 2 blocks.
 static int select_mode() {
   const char* e = std::getenv("SLKV_SELECT");
   if (!e) return 0;
@@ -4183,7 +4499,8 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     one = OneScan{(float*)(ws + p.off_part0), (float*)(ws + p.off_dense), (uint32_t*)(ws + p.off_bins), (float*)(ws + p.off_lse), (uint32_t*)(ws + p.off_bounds),
                   (uint32_t*)(ws + p.off_lists)};
   uint32_t* const gm = groups && !one_scan ? (uint32_t*)pooled : nullptr;
-  ScoreBuffers buf{part, imp, gm, one, pooled, resident_select ? nullptr : blockhist, nullptr, 0};
+  ScoreBuffers buf{part, imp, gm, one, pooled, resident_select ? nullptr : blockhist, nullptr, 0, FinishArgs{}};
+  int64_t unranked = 0;                              // workgroups that copy segments that are not ranked, where one launch does everything
   auto launch_group = [&](const auto& tab, int chunks, int max_chunks, int blocks, bool any_large, const int64_t* slices, int64_t rows) -> slkv_status {
     using TAB = std::decay_t<decltype(tab)>;
     // one grid row per segment where that leaves at most a seventh of the grid empty (a segment with
@@ -4200,6 +4517,20 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
         chunks <= p.per_cu * cus) {
       buf.meet = (meet_t*)ws;
       buf.limit = meet_limit();
+    }
+    SelectGrid sel{nseg, 0};
+    const bool slice = resident_select && (any_large || g.longest > kSelThreads * kSelEPTSmall);
+    for (int l = kSliceLog2Least; slice && !sel.slice_log2 && l <= kSliceLog2Most; ++l)
+      if (slices[l - kSliceLog2Least] <= cus) sel = SelectGrid{(int)slices[l - kSliceLog2Least], l};
+    // The selection and the copy in the same launch too, where a gather would follow (both sides: finish_segment).
+    if (std::is_same_v<TAB, SegTableBig> && !k_resident && buf.meet && any_large && !sel.slice_log2 && g.longest <= kFinishMost && select_mode() == 0) {
+      buf.fin = FinishArgs{ga, pooled, d_kept_idx, d_out_offsets, g.pool == SLKV_POOL_NONE ? 1 : g.pool_kernel, g.pool, d_pooled != nullptr, chunks};
+      sgrid.chunks = chunks + (int)unranked;
+      if (unranked > 0) sgrid.rows = 0;
+      ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
+      launch_score(kPassFinish, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
+      const hipError_t e = hipGetLastError();
+      return e == hipSuccess ? SLKV_OK : fail(SLKV_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
     }
     if (chunks > 0 && buf.meet) {
       ScopedKernelTimer tm(SLKV_K_SCORE_ACCUM, st);
@@ -4218,10 +4549,6 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
         launch_score(2, sgrid, st, tab, d_qwin, d_k, g, p, c_log2, buf);
       }
     }
-    SelectGrid sel{nseg, 0};
-    const bool slice = resident_select && (any_large || g.longest > kSelThreads * kSelEPTSmall);
-    for (int l = kSliceLog2Least; slice && !sel.slice_log2 && l <= kSliceLog2Most; ++l)
-      if (slices[l - kSliceLog2Least] <= cus) sel = SelectGrid{(int)slices[l - kSliceLog2Least], l};
     {
       ScopedKernelTimer tm(SLKV_K_SELECT, st);
       if (resident_select) {
@@ -4257,6 +4584,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
       const int64_t kept = kept_rows(sg.n, g.w, sg.cap), nc = seg_chunks(sg, g.w, p.CH);
       any_large |= kept > kInlineGatherRows;
       for (int l = kSliceLog2Least; l <= kSliceLog2Most; ++l) slices[l - kSliceLog2Least] += 1 + (std::max<int64_t>(kept - 1, 0) >> l);
+      if (nc == 0) unranked += 1 + (std::max<int64_t>(kept - 1, 0) >> kFinishRowsLog2);
       out_run += kept;
       chunks += nc;
       max_chunks = std::max(max_chunks, nc);

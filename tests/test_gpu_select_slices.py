@@ -35,7 +35,8 @@ def test_layer(dtype, d, pool, w, n):
 # tables of 64 segments and more, empty segments; slices of 64 rows, of 128, none: the gather copies
 @pytest.mark.parametrize("nseq,caps,sliced", [(16, [40, 300, 100, 16], True), (40, [40, 150, 100, 16], True), (32, [40, 300, 100, 16], True),
                                               (64, [40, 300, 100, 16], False)])
-def test_ragged(nseq, caps, sliced):
+def test_ragged(monkeypatch, nseq, caps, sliced):
+    monkeypatch.setenv("SLKV_SELECT", "resident")         # (not all in one launch)
     w = 16
     rng = np.random.default_rng(nseq)
     lens = [0 if rng.random() < 0.1 else int(c + t) for t in rng.integers(1, 90, size=nseq) for c in caps]
