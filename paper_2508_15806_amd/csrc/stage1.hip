@@ -871,8 +871,13 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
     }
   };
   // Keys of the chunk from n_lo on: as many as came before, in whole stripes, and a small rest of the keys with them.
+  // With d = 128 every second workgroup of an XCD (they are dealt to 8 in turn) has its chunk ends half an octave before the others': while one
+  // half of the chip meets, the other has the memory to itself.  32 x 8 heads, us: 2600 keys 77.8 -> 76.0, 6000 119.6 -> 116.6, 16384 237.8 -> 231.6, 8 x 8
+  // heads x 40000 189.3 -> 184.6.  It costs a meeting more: 1000 keys 42.0 -> 43.2.  Four groups instead of two: 16384 the same, 3000 2 % slower than one.
+  // d = 64, 10123 keys: 121.7 -> 122.7.
+  const bool half_octave = DK == 128 && n >= 5 * kQkFirst && (blockIdx.x >> 3 & 1);
   auto chunk_end = [&](int n_lo) __attribute__((always_inline)) {
-    const int hi = 2 * n_lo;
+    const int hi = half_octave && n_lo == kQkFirst ? n_lo + kQkStripe : 2 * n_lo;
     return n - hi <= hi / 8 ? n : hi;
   };
 
