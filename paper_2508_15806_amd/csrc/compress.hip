@@ -2474,7 +2474,7 @@ constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelBlock = 4096;           // history positions per phase-A block
 constexpr int kSelEmitThreads = 256;      // workgroup of the block-wise count / emit kernels (16 positions per thread)
 constexpr int kSelEPT = 32;
-constexpr int kSelEPTMid = 8, kSelEPTSmall = 2;   // shorter histories: fewer positions per thread in the one-workgroup kernel
+constexpr int kSelEPTLong = 24, kSelEPTMore = 16, kSelEPTMid = 8, kSelEPTLess = 4, kSelEPTSmall = 2;   // shorter histories: fewer positions per thread in the one-workgroup kernel
 constexpr int kSelRound = kSelThreads * kSelEPT;
 constexpr int kSelRankMax = 256;          // lists up to this length are ranked by direct counting
 constexpr int kSelTieGroups = 512;        // this many group maxima in the bound's digit switch the histograms to the pile-aware step
@@ -3282,7 +3282,7 @@ __global__ __launch_bounds__(kSelThreads) void select_resident_kernel(const TAB 
   const float inv_p = 1.f / (float)pool_kernel;
 
   bool selected = false;
-  if constexpr (EPT == kSelEPT) selected = select_by_groups();
+  if constexpr (EPT > kSelEPTMid) selected = select_by_groups();
   if (!selected) {
   // Keys: bit patterns of the pooled scores (>= 0, so monotone as unsigned integers); positions
   // past the end of the history get a key above every score.
@@ -4339,6 +4339,9 @@ static hipError_t ensure_device_init(int* cus = nullptr) {
   if (bit) cus_of[dev] = have;
   if ((e = raise_score_limits()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPT>()) != hipSuccess) return e;
+  if ((e = raise_lds_limits<kSelEPTLong>()) != hipSuccess) return e;
+  if ((e = raise_lds_limits<kSelEPTMore>()) != hipSuccess) return e;
+  if ((e = raise_lds_limits<kSelEPTLess>()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPTMid>()) != hipSuccess) return e;
   if ((e = raise_lds_limits<kSelEPTSmall>()) != hipSuccess) return e;
   done |= bit;
@@ -4362,16 +4365,25 @@ static hipError_t launch_select_resident_e(SelectGrid sel, hipStream_t st, const
   return hipSuccess;
 }
 
-// Positions per thread: the fewest of 2, 8, 32 whose round holds the longest ranked history (every
-// wave runs through all of a thread's positions, whether or not the history reaches them).
+// Positions per thread: the fewest of 2, 4, 8, 16, 24, 32 whose round holds the longest ranked history (every
+// wave runs through all of a thread's positions, whether or not the history reaches them).  Without 4, 16 and 24 / with them, us a call:
+// averages, 8 x 9 K 34.2 / 29.6, 8 x 16 K 37.1 / 33.1, 8 x 20 K 39.8 / 37.6, of 13 and 700 kept, 8 x 12 K 62.6 / 45.6; 21 K fp16, budgets of 1024 59.5 / 56.8; maxima,
+// budgets of 1024, 8 x 12 K 38.6 / 33.2; fp32 4 x 10 K 40.5 / 37.2; 8 x 4 K 22.2 / 21.5, averages 21.9 / 20.9; 8 prompts of 2 to 4 K 42.4 / 41.3.  (Window maxima
+// above 8192 positions mostly go by groups, whatever the form.)
 template <int RADIUS, class TAB>
 static hipError_t launch_select_resident_r(SelectGrid sel, hipStream_t st, const TAB& tab, const Geometry& g, bool write_pooled, const uint32_t* gm,
                                            const float* imp, float* pooled, int32_t* kept_idx, int64_t* d_out_offsets,
                                            const GatherArgs& ga, meet_t* meet) {
   if (g.longest <= kSelThreads * kSelEPTSmall)
     return launch_select_resident_e<RADIUS, kSelEPTSmall>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+  if (g.longest <= kSelThreads * kSelEPTLess)
+    return launch_select_resident_e<RADIUS, kSelEPTLess>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
   if (g.longest <= kSelThreads * kSelEPTMid)
     return launch_select_resident_e<RADIUS, kSelEPTMid>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+  if (g.longest <= kSelThreads * kSelEPTMore)
+    return launch_select_resident_e<RADIUS, kSelEPTMore>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
+  if (g.longest <= kSelThreads * kSelEPTLong)
+    return launch_select_resident_e<RADIUS, kSelEPTLong>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
   return launch_select_resident_e<RADIUS, kSelEPT>(sel, st, tab, g, write_pooled, gm, imp, pooled, kept_idx, d_out_offsets, ga, meet);
 }
 
