@@ -14,7 +14,6 @@
 namespace slkv {
 
 constexpr int kS1Threads = 256;   // workgroup of the general row path
-constexpr int kS1Groups = 16;     // 16-byte groups per thread that the resident row path holds in registers, at most
 constexpr int kS1TopK = 64;       // largest K of the resident row path
 
 // LDS of the row paths with NT threads: the candidate lists of the resident path (per wave; a needle's
@@ -372,9 +371,9 @@ __device__ __forceinline__ void row_cells_general(const float* __restrict__ W, i
   if (tid == 0) store_cells(c_out, wo + (double)tau_val * (double)take_needle, wd + (double)tau_val * (double)(need_eq - take_needle), tot, tnw);
 }
 
-// One workgroup per row; cells[row] = (WO, WD, WS, Wide).  NG = 0: the general path.
-template <int NT, int NG, bool WHOLE>
-__global__ __launch_bounds__(NT, 4) void row_cells_kernel(const float* __restrict__ rows, int32_t n, int32_t needle_start,
+// One workgroup per row; cells[row] = (WO, WD, WS, Wide).  NG = 0: the general path.  MW: wavefronts of a SIMD that the registers leave room for.
+template <int NT, int NG, bool WHOLE, int MW>
+__global__ __launch_bounds__(NT, MW) void row_cells_kernel(const float* __restrict__ rows, int32_t n, int32_t needle_start,
                                                           int32_t needle_len, int32_t topk, double* __restrict__ cells) {
   __shared__ RowLds<NT> S;
   const float* W = rows + (int64_t)blockIdx.x * n;
@@ -1221,29 +1220,43 @@ slkv_status run_score_heads(const float* d_rows, int32_t L, int32_t H, int32_t T
   hipStream_t st = (hipStream_t)hip_stream;
   double* cells = (double*)d_workspace;
   // Whole 16-byte groups of a row, up to three floats of the row before it included: the threads of a row
-  // hold them at 4, 8 or 16 a thread.  Up to K = kS1TopK the list of one wave has room for all of them and half as many
+  // hold them.  Up to K = kS1TopK the list of one wave has room for all of them and half as many
   // again (2048 rows of 16384 weights: K = 64 35 us, K = 65 210 us).
+  //   The form is the smallest that holds the row: slots beyond its end cost as much as others, and so do waves beyond those that
+  // four workgroups to a CU need to read while they rank: above 4096 groups three workgroups of 256 threads with 18 to 28 groups each, not two of 512, and up to
+  // 11264 groups two of 512 threads, not one of 1024.  512 MiB of rows, us, with 4, 8 or 16 groups a thread alone / with all forms: 1030 weights 236 / 217, 2052
+  // 146 / 136, 4100 127 / 99, 6000 96 / 88, 8196 128 / 95, 9000 119 / 92, 12000 96 / 84, 16390 172 / 88, 20000 144 / 95, 24000 125 / 93, 26000 120 / 107,
+  // 33000 235 / 106, 40000 202 / 96, 45000 188 / 97; 4096 90, 8192 85, 16384 88, 32760 104 (the same form).  Below 2000 weights the time is that of the instructions
+  // of a row (bound, list, ranks), which one wave executes.
   const int64_t groups = (n % 4 == 0 ? n : n + 3) / 4;
   {
     ScopedKernelTimer tm(SLKV_K_ROW_CELLS, st);
-    auto launch = [&](auto nt, auto ng) {
-      constexpr int NT = decltype(nt)::value, NG = decltype(ng)::value;
+    bool launched = false;
+    auto launch = [&](auto nt, auto ng, auto mw) {
+      constexpr int NT = decltype(nt)::value, NG = decltype(ng)::value, MW = decltype(mw)::value;
+      if (launched || (NG && (topk > kS1TopK || n < 4 || groups > NT * NG))) return;
+      launched = true;
       if (n % 4 == 0)
-        SLKV_LAUNCH((row_cells_kernel<NT, NG, true>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
+        SLKV_LAUNCH((row_cells_kernel<NT, NG, true, MW>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
                     (int32_t)needle_start, needle_len, topk, cells);
       else
-        SLKV_LAUNCH((row_cells_kernel<NT, NG, false>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
+        SLKV_LAUNCH((row_cells_kernel<NT, NG, false, MW>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
                     (int32_t)needle_start, needle_len, topk, cells);
     };
-    using std::integral_constant;
-    if (topk > kS1TopK || n < 4 || groups > 1024 * kS1Groups) launch(integral_constant<int, kS1Threads>{}, integral_constant<int, 0>{});
-    else if (groups <= 64 * 4) launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
-    else if (groups <= 64 * 8) launch(integral_constant<int, 64>{}, integral_constant<int, 8>{});
-    else if (groups <= 64 * 16) launch(integral_constant<int, 64>{}, integral_constant<int, 16>{});
-    else if (groups <= 128 * 16) launch(integral_constant<int, 128>{}, integral_constant<int, 16>{});
-    else if (groups <= 256 * 16) launch(integral_constant<int, 256>{}, integral_constant<int, 16>{});
-    else if (groups <= 512 * 16) launch(integral_constant<int, 512>{}, integral_constant<int, 16>{});
-    else launch(integral_constant<int, 1024>{}, integral_constant<int, 16>{});
+    auto forms = [&](auto nt, auto mw, auto... ng) { (launch(nt, ng, mw), ...); };   // by groups a thread
+#define SLKV_C(x) std::integral_constant<int, x>{}
+    forms(SLKV_C(64), SLKV_C(4), SLKV_C(4));
+    forms(SLKV_C(64), SLKV_C(5), SLKV_C(6), SLKV_C(8));
+    forms(SLKV_C(64), SLKV_C(4), SLKV_C(10), SLKV_C(12), SLKV_C(16));
+    forms(SLKV_C(128), SLKV_C(5), SLKV_C(10), SLKV_C(12));
+    forms(SLKV_C(128), SLKV_C(4), SLKV_C(14), SLKV_C(16));
+    forms(SLKV_C(256), SLKV_C(5), SLKV_C(10), SLKV_C(12));
+    forms(SLKV_C(256), SLKV_C(4), SLKV_C(14), SLKV_C(16));
+    forms(SLKV_C(256), SLKV_C(3), SLKV_C(18), SLKV_C(20), SLKV_C(24), SLKV_C(28));
+    forms(SLKV_C(512), SLKV_C(4), SLKV_C(16), SLKV_C(18), SLKV_C(20), SLKV_C(22));
+    forms(SLKV_C(1024), SLKV_C(4), SLKV_C(16));
+    forms(SLKV_C(kS1Threads), SLKV_C(4), SLKV_C(0));
+#undef SLKV_C
   }
   const int heads = L * H;
   {

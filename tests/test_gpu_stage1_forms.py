@@ -1,0 +1,35 @@
+"""Stage 1 over rows whose length is the most that a form of the row kernel holds, or one form further: rows of whole 16-byte groups, and others."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2508_15806_amd import api
+from paper_2508_15806_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+GROUPS = [384, 512, 640, 768, 1280, 1536, 1792, 2560, 3072, 3584, 4608, 5120, 6144, 7168, 9216, 10240, 11264]
+
+
+@pytest.mark.parametrize("n", [4 * g + d for g in GROUPS for d in (0, -3, -2, 4)])
+def test_most_groups_of_a_form(n):
+    import torch
+    topk = 64 if n % 8 else 17
+    nr = wl.config4(L=1, H=2, T=5, n=n, needle_len=27, seed_extra=2000 + n)
+    acc, sc = api.score_heads(torch.from_numpy(nr.rows).cuda(), nr.needle_start, nr.needle_len, topk)
+    racc, rsc = oracle.score_heads(nr.rows, nr.needle_start, nr.needle_len, topk)
+    np.testing.assert_allclose(acc.cpu().numpy(), racc, rtol=1e-12, atol=1e-15)      # the order of double sums
+    np.testing.assert_allclose(sc.cpu().numpy(), rsc, rtol=1e-11, atol=1e-15)
+
+
+@pytest.mark.parametrize("n", [2400, 5002, 17001, 20480, 28671, 33001, 45056])
+def test_ties_at_the_cut(n):
+    # quantised weights: the candidate lists overflow and the general path takes the row
+    import torch
+    rng = np.random.default_rng(n)
+    q = rng.integers(0, 4, size=(1, 2, 3, n)).astype(np.float32)
+    q /= q.sum(-1, keepdims=True)
+    acc, _ = api.score_heads(torch.from_numpy(q).cuda(), n - 40, 40, 40)
+    racc, _ = oracle.score_heads(q, n - 40, 40, 40)
+    np.testing.assert_allclose(acc.cpu().numpy(), racc, rtol=1e-12, atol=1e-15)
