@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace slkv {
 
 constexpr int kWave = 64;
@@ -61,6 +63,29 @@ __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
   for (int dlt = kWave / 2; dlt > 0; dlt >>= 1) v += __shfl_xor(v, dlt, kWave);
   return v;
+}
+
+// Of doubles: 6 steps through DPP moves and one lane read back, in every lane the same value.  (Through shuffles, two LDS round trips a step, the sums were a third
+// of a short attention row's time.)
+template <>
+__device__ __forceinline__ double wave_sum<double>(double v) {
+  auto add = [&](auto ctrl_c, auto mask_c) __attribute__((always_inline)) {
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = dpp_move<decltype(ctrl_c)::value, decltype(mask_c)::value>(0u, (uint32_t)b);
+    const uint32_t hi = dpp_move<decltype(ctrl_c)::value, decltype(mask_c)::value>(0u, (uint32_t)((unsigned long long)b >> 32));
+    v += __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+  };
+  using std::integral_constant;
+  add(integral_constant<int, kDppRowShr + 1>{}, integral_constant<int, 0xf>{});
+  add(integral_constant<int, kDppRowShr + 2>{}, integral_constant<int, 0xf>{});
+  add(integral_constant<int, kDppRowShr + 4>{}, integral_constant<int, 0xf>{});
+  add(integral_constant<int, kDppRowShr + 8>{}, integral_constant<int, 0xf>{});
+  add(integral_constant<int, kDppRowBcast15>{}, integral_constant<int, 0xa>{});
+  add(integral_constant<int, kDppRowBcast31>{}, integral_constant<int, 0xc>{});
+  const long long b = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, kWave - 1);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)b >> 32), kWave - 1);
+  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
 }
 
 // Inclusive scan over the NT threads of the block in thread order.  `sh` holds NT/64 values.

@@ -68,12 +68,17 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   const int32_t ngroups = end >> 2;                    // whole groups (at least one: n >= 4)
   const f32x4* W4 = reinterpret_cast<const f32x4*>(W - lead);
 
-  // group i of this thread: i * NT + tid; all loads are issued first.  The rows are read exactly once:
+  // group i of this thread: i * NT + tid.  Rows of a multiple of 16 KiB begin at the same memory channel, and the workgroups that start together would all read
+  // it: in two forms each begins with another i (1 GiB of rows, K = 32, us without / with: 8192 weights 162 / 157, 16384 168 / 162.5; in the other forms
+  // it costs registers or more than it gives: 4096 163 / 165.5, 20480 169.5 / 175, 32768 170 / 175); all loads are issued first.  The rows are read exactly once:
   // non-temporal loads (they do not displace anything in the caches) stream about 13 % faster than plain
   // ones on this part.
+  constexpr bool TURN = WHOLE && NG == 16 && (NT == 128 || NT == 256);
+  const int turn = TURN && n % 4096 == 0 ? (int)(blockIdx.x % NG) : 0;
+  auto group = [&](int i) __attribute__((always_inline)) { return (TURN && i + turn >= NG ? i + turn - NG : i + turn) * NT + tid; };
   f32x4 v[NG];
 #pragma unroll
-  for (int i = 0; i < NG; ++i) v[i] = __builtin_nontemporal_load(W4 + min(i * NT + tid, ngroups - 1));   // past the end: loaded again, never used
+  for (int i = 0; i < NG; ++i) v[i] = __builtin_nontemporal_load(W4 + min(group(i), ngroups - 1));   // past the end: loaded again, never used
   const int32_t jx = 4 * ngroups + tid - lead;         // position of this thread's float of the last group
   const bool have_x = !WHOLE && tid < (end & 3) && jx >= 0;
   const float vx = have_x ? W[jx] : 0.f;
@@ -90,11 +95,13 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   // their maxima lies close to the K-th largest weight
   constexpr int M = NW == 1 ? 4 : NW == 2 ? 2 : 1;
   float mx[M];
+  uint32_t seen = 0;                       // bit m: subset m has data
 #pragma unroll
   for (int m = 0; m < M; ++m) mx[m] = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
-    if (i * NT + tid < ngroups) {
+    if (group(i) < ngroups) {
+      seen |= 1u << i % M;
       tot += (double)v[i].x;
       tot += (double)v[i].y;
       tot += (double)v[i].z;
@@ -122,15 +129,36 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   const uint32_t want = (uint32_t)(topk + NW - 1) / NW;
   uint32_t mkey[M];
 #pragma unroll
-  for (int m = 0; m < M; ++m) mkey[m] = m * NT + tid < ngroups || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
-  uint32_t tkey = 0;
-#pragma unroll
-  for (int b = 31; b >= 12; --b) {
-    const uint32_t trial = tkey | (1u << b);
+  for (int m = 0; m < M; ++m) mkey[m] = seen >> m & 1u || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
+  auto reach = [&](uint32_t t) __attribute__((always_inline)) {
     uint32_t c = 0;
 #pragma unroll
-    for (int m = 0; m < M; ++m) c += (uint32_t)__popcll(__ballot(mkey[m] >= trial));
-    if (c >= want) tkey = trial;
+    for (int m = 0; m < M; ++m) c += (uint32_t)__popcll(__ballot(mkey[m] >= t));
+    return c;
+  };
+  // (it starts below the bits that all maxima share and ends where exactly as many as wanted reach the value)
+  uint32_t tkey = 0;
+  {
+    uint32_t least = 0xffffffffu, most = 0u;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      least = min(least, mkey[m] ? mkey[m] : 0xffffffffu);
+      most = max(most, mkey[m]);
+    }
+    least = wave_reduce_to_last(least, [](uint32_t a, uint32_t b) { return min(a, b); });
+    most = wave_reduce_to_last(most, [](uint32_t a, uint32_t b) { return max(a, b); });
+    least = (uint32_t)__builtin_amdgcn_readlane((int)least, kWave - 1);
+    most = (uint32_t)__builtin_amdgcn_readlane((int)most, kWave - 1);
+    int b = 31;
+    if (reach(1u) >= want) {
+      b = 31 - __clz((int)(least ^ most));                     // (-1: all equal)
+      tkey = b < 12 ? least & 0xfffff000u : b < 31 ? least & (0xfffffffeu << b) : 0u;
+    }
+    for (; b >= 12; --b) {
+      const uint32_t trial = tkey | (1u << b), c = reach(trial);
+      if (c >= want) tkey = trial;
+      if (c == want) break;
+    }
   }
   // the float whose key is tkey (low bits cleared: not above the value found); 0 keys: -inf
   float bound = tkey == 0 ? -INFINITY : __uint_as_float((tkey & 0x80000000u) ? (tkey ^ 0x80000000u) : ~tkey);
@@ -170,7 +198,7 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   };
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
-    const int32_t g = i * NT + tid;
+    const int32_t g = group(i);
     const float bnd = g < ngroups ? bound : INFINITY;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -223,6 +251,24 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
       candidate(q * kWave + lane, mine[q], x[q]);
       ahead[q] = 0;
     }
+    // More than one candidate a lane: first a value that exactly K of them reach, by bisection; only where equal weights
+    // stand at the cut there is none, and each is ranked.
+    bool exact = false;
+    uint32_t cut = 0;
+    if (PER > 1) {
+      for (int b = 31; b >= 0 && !exact; --b) {
+        const uint32_t trial = cut | (1u << b);
+        uint32_t c = 0;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) c += (uint32_t)__popcll(__ballot((uint32_t)(mine[q] >> 32) >= trial));
+        if (c >= (uint32_t)topk) cut = trial;
+        exact = c == (uint32_t)topk;
+      }
+    }
+    if (exact) {
+#pragma unroll
+      for (int q = 0; q < PER; ++q) ahead[q] = (uint32_t)(mine[q] >> 32) >= cut ? 0u : (uint32_t)topk;
+    } else
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       const int cnt = min((int)nc - p * kWave, kWave);
