@@ -30,9 +30,9 @@ PROFILE_SUMMARY = os.path.join(os.path.dirname(os.path.abspath(__file__)), "prof
 
 
 def measured_traffic_bytes(kernel, path=PROFILE_SUMMARY):
-    """FETCH (scaled, KiB) + WRITE (KiB) of the scoring pass `kernel` (score_stats: pass 1, score_accum: pass 2) in the
-    summary's traffic table, in bytes; None if absent."""
-    name = "score_q_resident_kernel<128,2,4,%d," % (1 if kernel == "score_stats" else 2)
+    """FETCH (scaled, KiB) + WRITE (KiB) of the scoring pass `kernel` (score_stats: pass 1, score_accum: pass 2, together: both
+    in one launch) in the summary's traffic table, in bytes; None if absent."""
+    name = "score_q_resident_kernel<128,2,4,%d," % {"score_stats": 1, "score_accum": 2, "together": 3}[kernel]
     try:
         with open(path) as f:
             for line in f:
@@ -169,7 +169,7 @@ def main():
     flops_launch = (2.0 if together else 1.0) * float(np.mean(ranked_flops)) if ranked_flops else 0.0
     dom_ms = kernel_ms.get(dom, float("nan"))
     achieved_tflops = flops_launch / (dom_ms * 1e-3) / 1e12 if dom_ms > 0 else 0.0
-    traffic = None if together else measured_traffic_bytes(dom)
+    traffic = measured_traffic_bytes("together" if together else dom)
     roofline = {"kernel": dom, "bound": "mfma", "achieved": round(achieved_tflops, 2),
                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved_tflops / MFMA_BF16_PEAK_TFLOPS, 4),

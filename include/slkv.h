@@ -318,7 +318,8 @@ slkv_status slkv_recompress_layer(const slkv_ragged_desc* desc, const void* d_qw
  * slkv_profile_end waits for the recorded events, writes up to `capacity` records in launch
  * order and sets *count to the number recorded.  A call of slkv_compress_layer or slkv_recompress_layer makes at most 9 records
  * (two passes, long histories: 1 + 1 + 6 + 1; one pass: 1 + 4 + 3 + 1; histories up to 32768: 1 + 1 + 1 + 1, both passes in
- * one launch 0 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1, in each of these without the last one where the selection copies all rows).
+ * one launch 0 + 1 + 1 + 1, one pass 1 + 4 + 1 + 1, in each of these without the last one where the selection copies all rows; ragged
+ * caches and batches of many short histories: one SLKV_K_SCORE_ACCUM record in all, where the scoring launch selects and copies too).
  * Process-wide; not meant for production.
  */
 typedef enum {
