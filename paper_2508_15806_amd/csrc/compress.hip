@@ -3837,6 +3837,7 @@ struct Plan {
   size_t off_part, off_imp, off_pooled, off_hist, off_table, total_bytes;
   int per_cu;            // workgroups of a scoring launch that a CU holds at least
   int meet_most;         // chunks of a segment up to which both scoring passes take one launch (see meet_chunks), if its workgroups fit the chip
+  double passes_us;      // estimate of both scoring passes together
   bool one_scan;         // the call may go over its keys once (see OneScan), if the workspace has these bytes as well
   int sampled;           // see range_len
   int64_t ranges;
@@ -3977,6 +3978,7 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
     }
   }
   p.meet_most = f32 ? 16 : 32;
+  p.passes_us = best;
 }
 
 // Chunk length of score_q_resident_kernel: what takes the least time, by a workgroup's start and end and the time of a
@@ -4029,6 +4031,7 @@ static void plan_q_resident(const Geometry& g, Plan& p) {
   p.rsplit = 1;
   p.per_cu = cfg == 3 ? 1 : 2;
   p.meet_most = best <= kTogetherUs ? kMeetMost : 0;
+  p.passes_us = 2 * best;
   const double worth = lens.longest <= kSelRound ? kOneScanResidentUs : cfg == 2 ? kOneScanUs : kOneScanFewRowsUs;
   p.one_scan = best >= worth && (cfg == 2 || lens.longest > kSelRound) && p.R <= 256 && g.pool != SLKV_POOL_AVG && g.segs.size() <= (size_t)kMaxSegPerLaunch;
 }
@@ -4411,13 +4414,16 @@ static int select_mode() {
   return 0;
 }
 
-// How long the workgroups of a launch that does both passes wait for each other, in ticks of 10 ns: several times what
-// they start and end apart (up to 10 us), and what another stream's selection keeps them from a CU (10 to 20 us).  SLKV_MEET_US in the
-// environment sets another limit (tests: 0, so that nearly all leave and the last ones complete their chunks).
-static int meet_limit() {
+// How long the workgroups of a launch that does both passes wait for each other, in ticks of 10 ns.  Alone they start and end up to 10 us apart, but other
+// streams' workgroups hold CUs for the time of a pass of their own, and a short last chunk waits for a whole one of the others.  Who leaves too early costs much: the few
+// that come last complete the chunks of all others, one by one.  So it is twice the time of both passes by the plan, and some for what else keeps them.  us a call on 1, 2,
+// 3 and 4 streams, limits of 50 us / of this / two launches: E4M3 32 x 32 K 152 146 425 405 / 152 146 148 150 / 159 149 151 151; 64 x 32 K 280 276 498 470 / 278 276 282 283 /
+// 283 285 284 284; six prompts of 2 to 32 K 151 143 314 356 / 151 141 144 144 / 163 144 145 143.  (Least that avoids it: 100, 200 and 75 us; 8 x 32 K 35 us, 16-bit keys 50.)
+// SLKV_MEET_US in the environment sets another limit (tests: 0, so that nearly all leave and the last ones complete their chunks).
+static int meet_limit(const Plan& p) {
   const char* e = std::getenv("SLKV_MEET_US");
-  const int us = e ? std::atoi(e) : 50;
-  return std::min(std::max(us, 0), 1000) * 100;
+  const double us = e ? (double)std::atoi(e) : 20 + 2 * p.passes_us;
+  return (int)(std::min(std::max(us, 0.0), 10000.0) * 100);
 }
 
 // Checks and launches shared by the two entry points.
@@ -4528,7 +4534,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     if (!one_scan && resident_select && S <= kMeetSegments && max_chunks > (k_resident ? 1 : 0) && max_chunks <= p.meet_most &&
         chunks <= p.per_cu * cus) {
       buf.meet = (meet_t*)ws;
-      buf.limit = meet_limit();
+      buf.limit = meet_limit(p);
     }
     SelectGrid sel{nseg, 0};
     const bool slice = resident_select && (any_large || g.longest > kSelThreads * kSelEPTSmall);

@@ -119,3 +119,32 @@ def test_three_streams():
         torch.cuda.synchronize()
         for call in calls:
             assert torch.equal(call.kept_idx, want)
+
+
+def test_streams_long_passes():
+    # passes of 140 us, on more streams than the chip has room for: workgroups that left each other before a pass was over would leave nearly all
+    # chunks to the few that come last (three times as long)
+    import time
+    import torch
+    lens, caps = [32768] * 8, np.array([107, 1834, 111, 132, 119, 110, 143, 127], dtype=np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q = torch.randn(8, 32, 64, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    kv = [torch.randn(2, 8, sum(lens), 128, generator=gen, device="cuda").to(torch.float8_e4m3fn).view(torch.uint8) for _ in range(4)]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    calls = [api.LayerCall("bf16_kv8", 8, 32, 8, 128, 64, cu, caps) for _ in range(4)]
+    assert "score_stats" not in launches(lambda: calls[0].run(q, *kv[0]))
+
+    def us_a_call(streams):
+        took = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(15):
+                for call, x, s in zip(calls, kv, streams):
+                    call.run(q, *x, stream=s)
+            torch.cuda.synchronize()
+            took.append((time.perf_counter() - t0) / (15 * len(calls)) * 1e6)
+        return float(np.median(took))
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    us = [us_a_call([streams[i % n] for i in range(4)]) for n in (1, 2, 3, 4)]
+    assert max(us) < 1.35 * us[0], us
