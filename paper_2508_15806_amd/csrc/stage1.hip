@@ -50,11 +50,11 @@ __device__ __forceinline__ void store_cells(double* c, double WO, double WD, dou
 // A lower bound of the K-th largest weight comes from maxima per lane in each wave (K distinct elements); the
 // few weights at or above the bound are collected in LDS and ranked exactly (larger first, equal weights by
 // lower position).  Returns false, with nothing written, if a list overflows (many ties at the bound).
-// Bound: HBM up to 32764 weights.  32 x 32 heads x 16 rows of 16384 floats (1 GiB): 160-165 us, 6.6 TB/s.  Rows of 13867
-// floats went through the general path, five sweeps over memory: 350 us for 227 MB; here 43 us, 5.2 TB/s.  Longer rows take
+// Bound: HBM up to 45052 weights.  32 x 32 heads x 16 rows of 16384 floats (1 GiB): 160-165 us, 6.6 TB/s.  Rows of 13867
+// floats went through the general path, five sweeps over memory: 350 us for 227 MB; here 42 us, 5.4 TB/s.  Longer rows take
 // 1024 threads, whose 128 registers do not hold 16 groups and the rest (60 spilled), and such a workgroup fills its CU, so that
-// no row's loads run beside another's reduction: 2048 rows of 40000 weights 125 us, 2.6 TB/s (general path 627 us); 1024 of
-// 65532 79 us, 3.4 TB/s (512 us).  Above 65533 weights the general path is all there is: 512 rows of 131072 920 us, 0.3 TB/s.
+// no row's loads run beside another's reduction: 1024 rows of 65532 weights 79 us, 3.4 TB/s (general path 512 us).  Above 65533 weights the
+// general path is all there is: 512 rows of 131072 920 us, 0.3 TB/s.
 // WHOLE: every row is whole 16-byte groups (n % 4 == 0).
 template <int NT, int NG, bool WHOLE>
 __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, int32_t n, int32_t needle_start,
@@ -68,14 +68,12 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   const int32_t ngroups = end >> 2;                    // whole groups (at least one: n >= 4)
   const f32x4* W4 = reinterpret_cast<const f32x4*>(W - lead);
 
-  // group i of this thread: i * NT + tid.  Rows of a multiple of 16 KiB begin at the same memory channel, and the workgroups that start together would all read
-  // it: in two forms each begins with another i (1 GiB of rows, K = 32, us without / with: 8192 weights 162 / 157, 16384 168 / 162.5; in the other forms
-  // it costs registers or more than it gives: 4096 163 / 165.5, 20480 169.5 / 175, 32768 170 / 175); all loads are issued first.  The rows are read exactly once:
+  // group i of this thread: i * NT + tid, whatever the row's place in the call: its double sums have one order.  (Rows of a multiple of 16 KiB begin at the same memory
+  // channel.  Workgroups that begin with another i each read 16384 weights in 158 to 166 us a GiB instead of 161 to 167, and sum them in another order each; begun in four or sixteen
+  // orders that are summed alike, 162 to 169.)  All loads are issued first.  The rows are read exactly once:
   // non-temporal loads (they do not displace anything in the caches) stream about 13 % faster than plain
   // ones on this part.
-  constexpr bool TURN = WHOLE && NG == 16 && (NT == 128 || NT == 256);
-  const int turn = TURN && n % 4096 == 0 ? (int)(blockIdx.x % NG) : 0;
-  auto group = [&](int i) __attribute__((always_inline)) { return (TURN && i + turn >= NG ? i + turn - NG : i + turn) * NT + tid; };
+  auto group = [&](int i) __attribute__((always_inline)) { return i * NT + tid; };
   f32x4 v[NG];
 #pragma unroll
   for (int i = 0; i < NG; ++i) v[i] = __builtin_nontemporal_load(W4 + min(group(i), ngroups - 1));   // past the end: loaded again, never used
@@ -95,13 +93,11 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   // their maxima lies close to the K-th largest weight
   constexpr int M = NW == 1 ? 4 : NW == 2 ? 2 : 1;
   float mx[M];
-  uint32_t seen = 0;                       // bit m: subset m has data
 #pragma unroll
   for (int m = 0; m < M; ++m) mx[m] = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
     if (group(i) < ngroups) {
-      seen |= 1u << i % M;
       tot += (double)v[i].x;
       tot += (double)v[i].y;
       tot += (double)v[i].z;
@@ -129,7 +125,7 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   const uint32_t want = (uint32_t)(topk + NW - 1) / NW;
   uint32_t mkey[M];
 #pragma unroll
-  for (int m = 0; m < M; ++m) mkey[m] = seen >> m & 1u || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
+  for (int m = 0; m < M; ++m) mkey[m] = group(m) < ngroups || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
   auto reach = [&](uint32_t t) __attribute__((always_inline)) {
     uint32_t c = 0;
 #pragma unroll
@@ -1272,7 +1268,9 @@ slkv_status run_score_heads(const float* d_rows, int32_t L, int32_t H, int32_t T
   // four workgroups to a CU need to read while they rank: above 4096 groups three workgroups of 256 threads with 18 to 28 groups each, not two of 512, and up to
   // 11264 groups two of 512 threads, not one of 1024.  512 MiB of rows, us, with 4, 8 or 16 groups a thread alone / with all forms: 1030 weights 236 / 217, 2052
   // 146 / 136, 4100 127 / 99, 6000 96 / 88, 8196 128 / 95, 9000 119 / 92, 12000 96 / 84, 16390 172 / 88, 20000 144 / 95, 24000 125 / 93, 26000 120 / 107,
-  // 33000 235 / 106, 40000 202 / 96, 45000 188 / 97; 4096 90, 8192 85, 16384 88, 32760 104 (the same form).  Below 2000 weights the time is that of the instructions
+  // 33000 235 / 106, 40000 202 / 96, 45000 188 / 97; 4096 90, 8192 85, 16384 88, 32760 104 (the same form).  Each form against the next larger one, at its longest rows less 256
+  // weights: 64 threads x 6 154 / 161, x 8 124 / 137, x 10 113 / 115 (rows of no whole groups 117 / 122), x 12 99 / 105, x 16 86 / 97; 128 x 10 81 / 84, x 12 80 / 87, x 14 79 / 83, x 16
+  // 79 / 88; 256 x 10 78 / 80, x 12 81 / 87, x 14 80 / 83, x 16 80 / 83, x 18 80 / 92, x 20 87 / 93, x 24 84 / 88, x 28 83 / 97; 512 x 16 91 / 93, x 18 91 / 97, x 20 85 / 87, x 22 84 / 151.  Below 2000 weights the time is that of the instructions
   // of a row (bound, list, ranks), which one wave executes.
   const int64_t groups = (n % 4 == 0 ? n : n + 3) / 4;
   {

@@ -33,3 +33,18 @@ def test_ties_at_the_cut(n):
     acc, _ = api.score_heads(torch.from_numpy(q).cuda(), n - 40, 40, 40)
     racc, _ = oracle.score_heads(q, n - 40, 40, 40)
     np.testing.assert_allclose(acc.cpu().numpy(), racc, rtol=1e-12, atol=1e-15)
+
+
+@pytest.mark.parametrize("n", [4096, 8192, 12288, 16384, 20480, 32768])
+def test_multiples_of_16_kib_at_any_place(n):
+    # weights of many magnitudes, whose double sums are rounded: a head scored alone and at each of 40 places of a call gives the same bits
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    one = torch.softmax(12 * torch.randn(1, 1, 3, n, generator=gen, device="cuda"), -1)
+    start, topk = n // 3, 21
+    alone, sc_alone = api.score_heads(one, start, 27, topk)
+    acc, sc = api.score_heads(one.expand(2, 20, 3, n).contiguous(), start, 27, topk)
+    assert torch.equal(acc, alone.expand(2, 20, 5)) and torch.equal(sc, sc_alone.expand(2, 20, 3))
+    racc, rsc = oracle.score_heads(one.cpu().numpy(), start, 27, topk)
+    np.testing.assert_allclose(alone.cpu().numpy(), racc, rtol=1e-12, atol=1e-15)
+    np.testing.assert_allclose(sc_alone.cpu().numpy(), rsc, rtol=1e-11, atol=1e-15)
