@@ -528,7 +528,7 @@ __global__ __launch_bounds__(64 * kReduceHeads) void head_reduce_kernel(const do
 // 32 layers x 8 KV heads x 16384 keys x 64 rows, K = 32: 316 -> 241 us (4.5 TB/s of keys; a large copy runs at 5.3) against
 // chunks half as long as what came before with lists of 128, a first chunk of 1024 keys walked twice, an 18-step
 // bisection at every chunk, an LDS atomic per entry and the queries in registers throughout; 6 meetings of the waves
-// instead of 11.
+// instead of 11.  With the meetings of half of the workgroups (7 then) between those of the others 231 (4.65 TB/s).
 constexpr int kQkThreads = 512;      // 8 waves
 constexpr int kQkWaves = kQkThreads / 64;
 constexpr int kQkRows = 64;          // two row tiles of 32
@@ -915,7 +915,8 @@ __global__ __launch_bounds__(kQkThreads) void qk_cells_kernel(const uint16_t* __
   // With d = 128 every second workgroup of an XCD (they are dealt to 8 in turn) has its chunk ends half an octave before the others': while one
   // half of the chip meets, the other has the memory to itself.  32 x 8 heads, us: 2600 keys 77.8 -> 76.0, 6000 119.6 -> 116.6, 16384 237.8 -> 231.6, 8 x 8
   // heads x 40000 189.3 -> 184.6.  It costs a meeting more: 1000 keys 42.0 -> 43.2.  Four groups instead of two: 16384 the same, 3000 2 % slower than one.
-  // d = 64, 10123 keys: 121.7 -> 122.7.
+  // d = 64, 10123 keys: 121.7 -> 122.7.  A row's result does not depend on which half it falls to: chunks end at whole stripes, so that a wave has the same sub-tiles in the same order, and
+  // the lists end with the same K entries.  (Only a row whose list overflows in one half alone would come from the fallback there, with other last digits.)
   const bool half_octave = DK == 128 && n >= 5 * kQkFirst && (blockIdx.x >> 3 & 1);
   auto chunk_end = [&](int n_lo) __attribute__((always_inline)) {
     const int hi = half_octave && n_lo == kQkFirst ? n_lo + kQkStripe : 2 * n_lo;

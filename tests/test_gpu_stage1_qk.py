@@ -133,3 +133,23 @@ def test_needle_run_shape_sampled_heads():
         np.testing.assert_allclose(got_sc[l, kv * 4:kv * 4 + 4], rsc[0], rtol=5 * RTOL, atol=1e-6)
     # every row's cells sum to one row of mass
     np.testing.assert_allclose(got_acc[..., :4].sum(axis=-1), 16.0, rtol=1e-6)
+
+
+@pytest.mark.parametrize("equal", [False, True])
+@pytest.mark.parametrize("n", [2559, 2560, 2561, 3455, 3456, 3457, 4609, 5001, 6911, 6913, 10123])
+def test_chunk_ends_of_both_schedules(n, equal):
+    # d = 128, 256 heads that are not cut into ranges: from 2560 keys on half of the workgroups have their chunk ends half an octave earlier than the others (768, 1536, 3072,
+    # 6144; an eighth more keys join the chunk before them: 3456, 6912).  The same two heads of queries and keys at every place give the same bits, those of the oracle;
+    # `equal`: every key twice, and an odd K cuts a pair
+    import torch
+    x = wl.config4_qk(L=1, Hq=2, Hkv=2, T=9, n=n, d=128, needle_len=16, seed_extra=200 + n)
+    if equal:
+        x.k[:, :, 1::2] = x.k[:, :, 0:n - 1:2]
+    x.topk = 33
+    q, k = api.to_device(x.q, "bf16"), api.to_device(x.k, "bf16")
+    racc, rsc = oracle.score_heads_from_qk(x.q, x.k, x.needle_start, x.needle_len, x.topk)
+    acc, sc = api.score_heads_qk(q.repeat(32, 4, 1, 1), k.repeat(32, 4, 1, 1), x.needle_start, x.needle_len, x.topk)
+    acc, sc = acc.view(128, 2, 5), sc.view(128, 2, 3)
+    np.testing.assert_allclose(acc[0].cpu().numpy(), racc[0], rtol=RTOL, atol=ATOL)
+    np.testing.assert_allclose(sc[0].cpu().numpy(), rsc[0], rtol=5 * RTOL, atol=1e-6)
+    assert torch.equal(acc, acc[:1].expand_as(acc)) and torch.equal(sc, sc[:1].expand_as(sc))
