@@ -98,27 +98,45 @@ def test_cache_of_many_segments(monkeypatch):
     compare(monkeypatch, call, lambda: call.run(q, k, v, pos))
 
 
-def test_three_streams():
+# finish: the launch also selects and copies (more than 64 segments, histories of at most 2048, some that keep more than 256 rows)
+@pytest.mark.parametrize("finish", [False, True])
+def test_three_streams(monkeypatch, finish):
     # three calls of nearly as many workgroups as the chip holds, started together: none may wait for another
     import torch
-    lens, caps = [4000] * 16, np.array([60, 300, 90, 80, 70, 200, 100, 64], dtype=np.int32)
-    lay = wl.make_layer((404,), lens, 32, 8, 128, 32, dtype="bf16", bias_frac=0.03)
-    calls = [api.LayerCall("bf16", 16, 32, 8, 128, 32, lay.cu_seqlens, caps) for _ in range(3)]
-    q, k, v = (api.to_device(x, "bf16") for x in (lay.qwin, lay.k, lay.v))
-    calls[0].run(q, k, v)
-    torch.cuda.synchronize()
-    want = calls[0].kept_idx.clone()
+    if finish:
+        caps = np.array([107, 1834, 111, 132, 119, 110, 143, 127], dtype=np.int32)
+        lens = [int(c + t) for t in np.random.default_rng(6).integers(1, 129, size=32) for c in caps]
+        rc = wl.make_ragged_cache((406,), lens, 32, 32, 8, 128, 64, dtype="bf16", bias_frac=0.03)
+        calls = [api.RaggedCall("bf16", 32, 32, 8, 128, 64, rc.in_offsets, caps) for _ in range(3)]
+        args = [api.to_device(x, "bf16") for x in (rc.qwin, rc.k_rows, rc.v_rows)] + [torch.from_numpy(rc.pos_in).cuda()]
+    else:
+        lens, caps = [4000] * 16, np.array([60, 300, 90, 80, 70, 200, 100, 64], dtype=np.int32)
+        lay = wl.make_layer((404,), lens, 32, 8, 128, 32, dtype="bf16", bias_frac=0.03)
+        calls = [api.LayerCall("bf16", 16, 32, 8, 128, 32, lay.cu_seqlens, caps) for _ in range(3)]
+        args = [api.to_device(x, "bf16") for x in (lay.qwin, lay.k, lay.v)]
+
+    def outs(call):
+        return [call.kept_idx, call.k_out, call.v_out, call.out_offsets] + ([call.pos_out] if finish else [])
+    monkeypatch.setenv("SLKV_SELECT", "blocks")
+    assert "score_stats" in launches(lambda: calls[0].run(*args))
+    want = [x.view(torch.uint8).clone() for x in outs(calls[0])]
+    monkeypatch.delenv("SLKV_SELECT")
+    took = launches(lambda: calls[0].run(*args))
+    assert "score_stats" not in took and ("select" in took) != finish
     streams = [torch.cuda.Stream() for _ in calls]
     for _ in range(5):
         for call in calls:
-            call.kept_idx.zero_()
+            for x in outs(call):
+                x.zero_()
         torch.cuda.synchronize()
         for _ in range(4):
             for call, s in zip(calls, streams):
-                call.run(q, k, v, stream=s)
+                call.run(*args, stream=s)
         torch.cuda.synchronize()
         for call in calls:
-            assert torch.equal(call.kept_idx, want)
+            assert not bool(call.workspace[:HEADER].any())
+            for x, y in zip(outs(call), want):
+                assert torch.equal(x.view(torch.uint8), y)
 
 
 def test_streams_long_passes():

@@ -48,3 +48,22 @@ def test_multiples_of_16_kib_at_any_place(n):
     racc, rsc = oracle.score_heads(one.cpu().numpy(), start, 27, topk)
     np.testing.assert_allclose(alone.cpu().numpy(), racc, rtol=1e-12, atol=1e-15)
     np.testing.assert_allclose(sc_alone.cpu().numpy(), rsc, rtol=1e-11, atol=1e-15)
+
+
+@pytest.mark.parametrize("n", [777, 1800, 3000, 5002, 8192, 12000, 16384, 28000, 40001, 60000])
+@pytest.mark.parametrize("topk,above,equal", [(64, 61, 2), (64, 63, 2), (64, 60, 9), (62, 0, 66), (40, 39, 7), (33, 20, 30)])
+def test_few_equal_weights_at_the_cut(n, topk, above, equal):
+    # `equal` equal weights behind the `above` largest ones, all of them in lists of at most 256: no value is reached by exactly K of them, each is ranked, and the lower positions
+    # count.  (Above 64 candidates four to a lane, which K = 62 and 64 make sure of.)
+    import torch
+    rng = np.random.default_rng(n + topk + equal)
+    rows = rng.random((1, 2, 8, n)).astype(np.float32)
+    for row in rows.reshape(-1, n):
+        order = np.argsort(-row)
+        row[order[above:above + equal]] = row[order[above]]
+    rows /= n
+    start = n // 4
+    acc, sc = api.score_heads(torch.from_numpy(rows).cuda(), start, n // 2, topk)
+    racc, rsc = oracle.score_heads(rows, start, n // 2, topk)
+    np.testing.assert_allclose(acc.cpu().numpy(), racc, rtol=1e-12, atol=1e-15)
+    np.testing.assert_allclose(sc.cpu().numpy(), rsc, rtol=1e-11, atol=1e-15)
