@@ -222,7 +222,8 @@ slkv_status slkv_compacted_sizes(const slkv_layer_desc* desc, int64_t* h_out_off
  * first SLKV_WORKSPACE_HEADER_BYTES are a header of counters through which the workgroups of a launch
  * wait for each other); every call leaves them zero, so the same workspace serves any number of later calls, of any descriptor it is large enough for, also
  * from a replayed HIP graph.  Its other contents are scratch.  Two calls that may overlap in
- * time need a workspace each.  For calls with long histories the size includes room to go over the keys once instead of
+ * time need a workspace each.  After SLKV_ERR_HIP, or after two calls that overlapped on one workspace all the same, the header
+ * has to be cleared again before the next call: what stands there would be taken for chunks of that call.  For calls with long histories the size includes room to go over the keys once instead of
  * twice; they accept, with the same results, a workspace that lacks that room. */
 #define SLKV_WORKSPACE_HEADER_BYTES 65536
 slkv_status slkv_workspace_bytes(const slkv_layer_desc* desc, size_t* bytes);
@@ -255,8 +256,8 @@ slkv_status slkv_compress_layer(const slkv_layer_desc* desc, const void* d_qwin,
  * do without) returns SLKV_ERR_WORKSPACE and enqueues nothing.  The call allocates nothing (no hipMalloc / hipFree).
  * All calls on one GPU share the buffer: calls that may overlap on one GPU (different streams
  * without ordering between them, or several host threads) race and must be serialised by the
- * caller.  The buffer's address is looked up on the first call on each device; make that call
- * outside stream capture.
+ * caller.  The buffer's address is looked up, and its header cleared, on the first call on each device and on the next one after
+ * SLKV_ERR_HIP; make these calls outside stream capture, or slkv_init() before them.
  */
 #define SLKV_STATIC_SCRATCH_BYTES (8u << 20)
 slkv_status slkv_compress_layer_static(const slkv_layer_desc* desc, const void* d_qwin,

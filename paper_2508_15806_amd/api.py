@@ -35,7 +35,33 @@ def to_host(t):
     return t.cpu().numpy()
 
 
-class LayerCall:
+class _Buffers:
+    """What the two kinds of call share: a workspace whose header has to be zero before every call."""
+
+    def _made(self):
+        """The buffers are allocated, and filled by the stream that is current now: another stream waits for that before its first call."""
+        self._filled = None
+        if self.workspace.is_cuda and not torch.cuda.is_current_stream_capturing():
+            s = torch.cuda.current_stream(self.workspace.device)
+            self._filled, self._ordered = s.record_event(), {s.cuda_stream}
+
+    def _enqueue(self, function, *args, stream=None):
+        if self._filled is not None and B._stream(stream) not in self._ordered:
+            s = stream if stream is not None else torch.cuda.current_stream()
+            with torch.cuda.stream(s):
+                if not torch.cuda.is_current_stream_capturing():      # (a capture begins after what it uses has been filled)
+                    s.wait_event(self._filled)
+                    self._ordered.add(s.cuda_stream)
+        try:
+            function(*args, stream)
+        except B.SlkvError as e:
+            if e.status == B.SLKV_ERR_HIP:      # some of its launches may have run: the next call finds the header clear all the same
+                with torch.cuda.stream(stream):
+                    self.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].zero_()
+            raise
+
+
+class LayerCall(_Buffers):
     """Device buffers + descriptor for repeated calls on one layer's shapes."""
 
     def __init__(self, dtype, B_, Hq, Hkv, d, w, cu_seqlens, budgets, pool_kernel=7, pool=B.SLKV_POOL_MAX,
@@ -58,13 +84,14 @@ class LayerCall:
         if debug_scores:
             self.importance = torch.zeros((max(Hkv * T, 1),), dtype=torch.float32, device=device)
             self.pooled = torch.zeros((max(Hkv * T, 1),), dtype=torch.float32, device=device)
+        self._made()
 
     def run(self, qwin, k, v, stream=None):
-        B.slkv_compress_layer(self.layer, qwin, k, v, self.k_out, self.v_out, self.kept_idx, self.workspace,
-                              self.out_offsets, self.importance, self.pooled, stream)
+        self._enqueue(B.slkv_compress_layer, self.layer, qwin, k, v, self.k_out, self.v_out, self.kept_idx, self.workspace,
+                      self.out_offsets, self.importance, self.pooled, stream=stream)
 
 
-class RaggedCall:
+class RaggedCall(_Buffers):
     """Device buffers + descriptor for repeated re-compression calls on one ragged cache shape."""
 
     def __init__(self, dtype, B_, Hq, Hkv, d, w, in_offsets, budgets, pool_kernel=7, pool=B.SLKV_POOL_MAX,
@@ -85,11 +112,12 @@ class RaggedCall:
         if debug_scores:
             self.importance = torch.zeros((max(rows_in, 1),), dtype=torch.float32, device=device)
             self.pooled = torch.zeros((max(rows_in, 1),), dtype=torch.float32, device=device)
+        self._made()
 
     def run(self, qwin, k_in, v_in, pos_in=None, stream=None):
-        B.slkv_recompress_layer(self.rag, qwin, k_in, v_in, self.k_out, self.v_out, self.kept_idx, self.workspace,
-                                pos_in, self.pos_out if pos_in is not None else None, self.out_offsets,
-                                self.importance, self.pooled, stream)
+        self._enqueue(B.slkv_recompress_layer, self.rag, qwin, k_in, v_in, self.k_out, self.v_out, self.kept_idx, self.workspace,
+                      pos_in, self.pos_out if pos_in is not None else None, self.out_offsets,
+                      self.importance, self.pooled, stream=stream)
 
 
 def score_heads(rows, needle_start, needle_len, topk, acc=None, stream=None):

@@ -30,6 +30,9 @@ EXPORTS = ["slkv_status_str", "slkv_last_error", "slkv_version", "slkv_init", "s
            "slkv_recompress_sizes", "slkv_recompress_workspace_bytes", "slkv_recompress_layer",
            "slkv_profile_begin", "slkv_profile_end"]
 
+SLKV_ERR_HIP = 7
+SLKV_WORKSPACE_HEADER_BYTES = 65536
+
 KERNEL_NAMES = ["score_stats", "combine", "score_accum", "select", "gather", "row_cells", "head_reduce", "qk_cells",
                 "qk_fallback"]
 

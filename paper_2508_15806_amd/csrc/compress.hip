@@ -275,7 +275,7 @@ typedef unsigned long long meet_t;
 // The count of the other chunks has been seen full: the bits that stand; or kMeetLeft: somebody else completes this chunk.  In thread 0 alone.
 constexpr meet_t kMeetLeft = ~0ull;
 __device__ __forceinline__ meet_t meet_chunks(meet_t* word, int nchunks, int chunk, int limit) {
-  const meet_t full = (meet_t)nchunks, bit = 1ull << chunk, bits = (1ull << kMeetMost) - 1;
+  const meet_t full = (meet_t)nchunks, bit = 1ull << chunk, bits = (1ull << nchunks) - 1;   // (a word that was not zero names no chunk that is not there)
   meet_t w = __hip_atomic_fetch_add(word, 1ull << kMeetMost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + (1ull << kMeetMost);
   if (w >> kMeetMost == full) return w & bits;
   const long long start = wall_clock64();
@@ -315,7 +315,7 @@ __device__ __forceinline__ bool meet_scores(meet_t* word, int nchunks, int score
   return false;
 }
 __device__ __forceinline__ int meet_slice(meet_t* word) {
-  return (int)__hip_atomic_fetch_add(word + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (int)min(__hip_atomic_fetch_add(word + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), (meet_t)kMeetMost);
 }
 __device__ __forceinline__ void meet_leave(meet_t* word, int nchunks) {
   if (__hip_atomic_fetch_add(word + 2, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != (meet_t)nchunks) return;
@@ -4674,8 +4674,9 @@ using namespace slkv;
 // Scratch of slkv_compress_layer_static: one copy per GPU, held until the process ends.
 static __device__ __align__(256) unsigned char scratch[SLKV_STATIC_SCRATCH_BYTES];
 
-// Device address of `scratch` on the current device (looked up once per device).
-static slkv_status static_scratch(void** out) {
+// Device address of `scratch` on the current device, looked up, and its header cleared, once per device and again after a call that failed
+// between its launches (failed: nothing is returned).
+static slkv_status static_scratch(void** out, bool failed = false) {
   constexpr int kMaxDev = 64;
   static std::mutex mu;
   static void* ptrs[kMaxDev] = {};
@@ -4684,11 +4685,15 @@ static slkv_status static_scratch(void** out) {
   if (e != hipSuccess) return fail(SLKV_ERR_HIP, "hipGetDevice failed: %s", hipGetErrorString(e));
   if (dev < 0 || dev >= kMaxDev) return fail(SLKV_ERR_UNSUPPORTED, "device index %d outside 0..%d", dev, kMaxDev - 1);
   std::lock_guard<std::mutex> lk(mu);
+  if (failed) {
+    ptrs[dev] = nullptr;
+    return SLKV_OK;
+  }
   if (!ptrs[dev]) {
     void* ptr = nullptr;
     e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess || !ptr) return fail(SLKV_ERR_HIP, "hipGetSymbolAddress(scratch) failed: %s", hipGetErrorString(e));
-    e = hipMemset(ptr, 0, SLKV_WORKSPACE_HEADER_BYTES);      // the header of a workspace is zero (once; not under capture)
+    e = hipMemset(ptr, 0, SLKV_WORKSPACE_HEADER_BYTES);      // the header of a workspace is zero (not under capture)
     if (e != hipSuccess) return fail(SLKV_ERR_HIP, "clearing the static scratch failed: %s", hipGetErrorString(e));
     ptrs[dev] = ptr;
   }
@@ -4748,8 +4753,10 @@ extern "C" slkv_status slkv_compress_layer_static(const slkv_layer_desc* desc, c
   void* ws = nullptr;
   vs = static_scratch(&ws);
   if (vs != SLKV_OK) return vs;
-  return run_geometry(g, d_qwin, d_k, d_v, nullptr, d_k_out, d_v_out, d_kept_idx, nullptr, d_out_offsets, d_importance,
-                      d_pooled, out_capacity_rows, ws, (size_t)SLKV_STATIC_SCRATCH_BYTES, hip_stream);
+  vs = run_geometry(g, d_qwin, d_k, d_v, nullptr, d_k_out, d_v_out, d_kept_idx, nullptr, d_out_offsets, d_importance,
+                    d_pooled, out_capacity_rows, ws, (size_t)SLKV_STATIC_SCRATCH_BYTES, hip_stream);
+  if (vs == SLKV_ERR_HIP) (void)static_scratch(&ws, true);
+  return vs;
 }
 
 extern "C" slkv_status slkv_recompress_workspace_bytes(const slkv_ragged_desc* desc, size_t* bytes) {
