@@ -4615,7 +4615,6 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   };
   if (S <= kMaxSegPerLaunch) {
     SegTable tab;
-    static_assert(sizeof(SegTable) + sizeof(GatherArgs) + 128 <= 4096, "kernel arguments are at most 4 KiB");
     tab.nseg = (int32_t)S;
     for (int64_t i = 0; i < S; ++i) {
       const Seg& sg = g.segs[(size_t)i];
@@ -4634,7 +4633,6 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
     return launch_group(tab, (int)chunks, (int)max_chunks, (int)blocks, any_large, slices, out_run);
   }
   SegTableBig tab;
-  static_assert(sizeof(SegTableBig) + sizeof(GatherArgs) + 128 <= 4096, "kernel arguments are at most 4 KiB");
   const int nbeg = (int)(g.ragged ? S : S / g.Hkv) + 1;
   tab.nseg = (int32_t)S;
   tab.hkv = g.Hkv;
