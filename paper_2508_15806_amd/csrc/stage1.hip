@@ -55,12 +55,14 @@ __device__ __forceinline__ void store_cells(double* c, double WO, double WD, dou
 // 1024 threads, whose 128 registers do not hold 16 groups and the rest (60 spilled), and such a workgroup fills its CU, so that
 // no row's loads run beside another's reduction: 1024 rows of 65532 weights 79 us, 3.4 TB/s (general path 512 us).  Above 65533 weights the
 // general path is all there is: 512 rows of 131072 920 us, 0.3 TB/s.
-// WHOLE: every row is whole 16-byte groups (n % 4 == 0).
-template <int NT, int NG, bool WHOLE>
+// Rows of a call: of any length; of whole 16-byte groups (n % 4 == 0); of a multiple of 16 KiB (n % 4096 == 0).
+constexpr int kRowsAny = 0, kRowsWhole = 1, kRowsAligned = 2;
+template <int NT, int NG, int ROWS>
 __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, int32_t n, int32_t needle_start,
                                                    int32_t needle_len, int32_t topk, double* __restrict__ c_out, RowLds<NT>& S) {
   constexpr int NW = NT / kWave, kWaveCand = RowLds<NT>::kWaveCand;
   typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr bool WHOLE = ROWS != kRowsAny, ALIGNED = ROWS == kRowsAligned;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int32_t ne = needle_start + needle_len;
   const int32_t lead = WHOLE ? 0 : (int32_t)((reinterpret_cast<uintptr_t>(W) >> 2) & 3u);
@@ -68,15 +70,28 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   const int32_t ngroups = end >> 2;                    // whole groups (at least one: n >= 4)
   const f32x4* W4 = reinterpret_cast<const f32x4*>(W - lead);
 
-  // group i of this thread: i * NT + tid, whatever the row's place in the call: its double sums have one order.  (Rows of a multiple of 16 KiB begin at the same memory
-  // channel.  Workgroups that begin with another i each read 16384 weights in 158 to 166 us a GiB instead of 161 to 167, and sum them in another order each; begun in four or sixteen
-  // orders that are summed alike, 162 to 169.)  All loads are issued first.  The rows are read exactly once:
+  // group i of this thread: i * NT + tid; all loads are issued first.  The rows are read exactly once:
   // non-temporal loads (they do not displace anything in the caches) stream about 13 % faster than plain
   // ones on this part.
+  //   ALIGNED: such rows all begin at the same memory channel.  Workgroups therefore begin 0, 8, 16 or 24 KiB into their row, and all add up from 24 KiB on, when what they
+  // have read first is there: a row's sums have one order, wherever it stands in the call.
   auto group = [&](int i) __attribute__((always_inline)) { return i * NT + tid; };
+  constexpr int STEP = ALIGNED ? 8192 / (16 * NT) : 0;
+  static_assert(3 * STEP < NG, "four places to begin at");
   f32x4 v[NG];
+  auto load_from = [&](auto first_c) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < NG; ++i) v[i] = __builtin_nontemporal_load(W4 + min(group(i), ngroups - 1));   // past the end: loaded again, never used
+    for (int u = 0; u < NG; ++u) {
+      const int i = (u + decltype(first_c)::value) % NG;
+      v[i] = __builtin_nontemporal_load(W4 + min(group(i), ngroups - 1));   // past the end: loaded again, never used
+    }
+  };
+  switch (ALIGNED ? blockIdx.x & 3 : 0) {
+    case 0: load_from(std::integral_constant<int, 0>{}); break;
+    case 1: load_from(std::integral_constant<int, STEP>{}); break;
+    case 2: load_from(std::integral_constant<int, 2 * STEP>{}); break;
+    default: load_from(std::integral_constant<int, 3 * STEP>{});
+  }
   const int32_t jx = 4 * ngroups + tid - lead;         // position of this thread's float of the last group
   const bool have_x = !WHOLE && tid < (end & 3) && jx >= 0;
   const float vx = have_x ? W[jx] : 0.f;
@@ -93,11 +108,14 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   // their maxima lies close to the K-th largest weight
   constexpr int M = NW == 1 ? 4 : NW == 2 ? 2 : 1;
   float mx[M];
+  uint32_t seen = 0;                       // bit m: subset m has data
 #pragma unroll
   for (int m = 0; m < M; ++m) mx[m] = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < NG; ++i) {
+  for (int u = 0; u < NG; ++u) {
+    const int i = (u + 3 * STEP) % NG;
     if (group(i) < ngroups) {
+      seen |= 1u << i % M;
       tot += (double)v[i].x;
       tot += (double)v[i].y;
       tot += (double)v[i].z;
@@ -125,7 +143,7 @@ __device__ __forceinline__ bool row_cells_resident(const float* __restrict__ W, 
   const uint32_t want = (uint32_t)(topk + NW - 1) / NW;
   uint32_t mkey[M];
 #pragma unroll
-  for (int m = 0; m < M; ++m) mkey[m] = group(m) < ngroups || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
+  for (int m = 0; m < M; ++m) mkey[m] = seen >> m & 1u || (m == 0 && have_x) ? float_key(mx[m]) : 0u;   // subsets without data never count
   auto reach = [&](uint32_t t) __attribute__((always_inline)) {
     uint32_t c = 0;
 #pragma unroll
@@ -413,15 +431,16 @@ __device__ __forceinline__ void row_cells_general(const float* __restrict__ W, i
   if (tid == 0) store_cells(c_out, wo + (double)tau_val * (double)take_needle, wd + (double)tau_val * (double)(need_eq - take_needle), tot, tnw);
 }
 
-// One workgroup per row; cells[row] = (WO, WD, WS, Wide).  NG = 0: the general path.  MW: wavefronts of a SIMD that the registers leave room for.
-template <int NT, int NG, bool WHOLE, int MW>
-__global__ __launch_bounds__(NT, MW) void row_cells_kernel(const float* __restrict__ rows, int32_t n, int32_t needle_start,
+// One workgroup per row; cells[row] = (WO, WD, WS, Wide).  NG = 0: the general path.  MW: wavefronts of a SIMD that the registers leave room for; with rows of a
+// multiple of 16 KiB no more than 4 (5 where MW is) run there, though fewer registers would do: 16384 weights 170 us a GiB with 5 workgroups to a CU, 159 with 4.
+template <int NT, int NG, int ROWS, int MW>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MW, ROWS == kRowsAligned ? (MW < 4 ? 4 : MW) : 8))) void row_cells_kernel(const float* __restrict__ rows, int32_t n, int32_t needle_start,
                                                           int32_t needle_len, int32_t topk, double* __restrict__ cells) {
   __shared__ RowLds<NT> S;
   const float* W = rows + (int64_t)blockIdx.x * n;
   double* c = cells + (int64_t)blockIdx.x * 4;
   if constexpr (NG > 0) {
-    if (row_cells_resident<NT, NG, WHOLE>(W, n, needle_start, needle_len, topk, c, S)) return;
+    if (row_cells_resident<NT, NG, ROWS>(W, n, needle_start, needle_len, topk, c, S)) return;
     __syncthreads();                     // the candidate lists have been read
   }
   row_cells_general<NT, (NG > 0)>(W, n, needle_start, needle_len, topk, c, S);
@@ -1281,12 +1300,16 @@ slkv_status run_score_heads(const float* d_rows, int32_t L, int32_t H, int32_t T
       constexpr int NT = decltype(nt)::value, NG = decltype(ng)::value, MW = decltype(mw)::value;
       if (launched || (NG && (topk > kS1TopK || n < 4 || groups > NT * NG))) return;
       launched = true;
-      if (n % 4 == 0)
-        SLKV_LAUNCH((row_cells_kernel<NT, NG, true, MW>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
+      auto rows = [&](auto rows_c) {
+        SLKV_LAUNCH((row_cells_kernel<NT, NG, decltype(rows_c)::value, MW>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
                     (int32_t)needle_start, needle_len, topk, cells);
-      else
-        SLKV_LAUNCH((row_cells_kernel<NT, NG, false, MW>), dim3((unsigned)nrows), dim3(NT), 0, st, d_rows, (int32_t)n,
-                    (int32_t)needle_start, needle_len, topk, cells);
+      };
+      // 512 MiB to 1 GiB of rows of a multiple of 16 KiB, us a GiB, in one order / four: 8192 weights 157 / 152, 12288 158.5 / 154.5, 16384 164.5 / 159, 20480 164 / 154.5; not
+      // 4096 157 / 157, 24576 157 / 158.5, 28672 156 / 156, 32768 166 / 170.5, 36864 163 / 166.5, 40960 159 / 161, 45056 158.5 / 160.
+      constexpr bool kAligned = (NT == 128 || NT == 256) && NG > 0 && NG <= 20 && NT * NG % 1024 == 0;   // (such rows fill their form)
+      if (n % 4 != 0) rows(std::integral_constant<int, kRowsAny>{});
+      else if (kAligned && n % 4096 == 0) rows(std::integral_constant<int, (kAligned ? kRowsAligned : kRowsWhole)>{});
+      else rows(std::integral_constant<int, kRowsWhole>{});
     };
     auto forms = [&](auto nt, auto mw, auto... ng) { (launch(nt, ng, mw), ...); };   // by groups a thread
 #define SLKV_C(x) std::integral_constant<int, x>{}
