@@ -41,24 +41,31 @@ class _Buffers:
     def _made(self):
         """The buffers are allocated, and filled by the stream that is current now: another stream waits for that before its first call."""
         self._filled = None
-        if self.workspace.is_cuda and not torch.cuda.is_current_stream_capturing():
-            s = torch.cuda.current_stream(self.workspace.device)
-            self._filled, self._ordered = s.record_event(), {s.cuda_stream}
+        if self.workspace.is_cuda:
+            with torch.cuda.device(self.workspace.device):
+                if not torch.cuda.is_current_stream_capturing():
+                    self._filled, self._ordered = torch.cuda.Event(), {B._stream(None)}
+                    self._filled.record()
 
-    def _enqueue(self, function, *args, stream=None):
-        if self._filled is not None and B._stream(stream) not in self._ordered:
-            s = stream if stream is not None else torch.cuda.current_stream()
-            with torch.cuda.stream(s):
-                if not torch.cuda.is_current_stream_capturing():      # (a capture begins after what it uses has been filled)
-                    s.wait_event(self._filled)
-                    self._ordered.add(s.cuda_stream)
+    def _enqueue(self, function, args, stream):
+        handle = stream
+        if self._filled is not None:
+            handle = B._stream(stream)
+            if handle not in self._ordered:
+                self._wait_for_fill(handle, stream)
         try:
-            function(*args, stream)
+            function(*args, handle)
         except B.SlkvError as e:
             if e.status == B.SLKV_ERR_HIP:      # some of its launches may have run: the next call finds the header clear all the same
                 with torch.cuda.stream(stream):
                     self.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].zero_()
             raise
+
+    def _wait_for_fill(self, handle, stream):
+        with torch.cuda.stream(stream):
+            if not torch.cuda.is_current_stream_capturing():      # (a capture begins after what it uses has been filled)
+                torch.cuda.current_stream().wait_event(self._filled)
+                self._ordered.add(handle)
 
 
 class LayerCall(_Buffers):
@@ -87,8 +94,8 @@ class LayerCall(_Buffers):
         self._made()
 
     def run(self, qwin, k, v, stream=None):
-        self._enqueue(B.slkv_compress_layer, self.layer, qwin, k, v, self.k_out, self.v_out, self.kept_idx, self.workspace,
-                      self.out_offsets, self.importance, self.pooled, stream=stream)
+        self._enqueue(B.slkv_compress_layer, (self.layer, qwin, k, v, self.k_out, self.v_out, self.kept_idx, self.workspace,
+                                              self.out_offsets, self.importance, self.pooled), stream)
 
 
 class RaggedCall(_Buffers):
@@ -115,9 +122,9 @@ class RaggedCall(_Buffers):
         self._made()
 
     def run(self, qwin, k_in, v_in, pos_in=None, stream=None):
-        self._enqueue(B.slkv_recompress_layer, self.rag, qwin, k_in, v_in, self.k_out, self.v_out, self.kept_idx, self.workspace,
-                      pos_in, self.pos_out if pos_in is not None else None, self.out_offsets,
-                      self.importance, self.pooled, stream=stream)
+        self._enqueue(B.slkv_recompress_layer, (self.rag, qwin, k_in, v_in, self.k_out, self.v_out, self.kept_idx, self.workspace,
+                                                pos_in, self.pos_out if pos_in is not None else None, self.out_offsets,
+                                                self.importance, self.pooled), stream)
 
 
 def score_heads(rows, needle_start, needle_len, topk, acc=None, stream=None):
