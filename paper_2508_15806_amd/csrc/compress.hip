@@ -3921,11 +3921,12 @@ struct RankedLengths {
 // 36.8 -> 25.3; 8 x 2 K, d 64, two tiles 28.0 -> 20.6; E4M3: 22 segments of 104 to 878 keys, four tiles 27.2 -> 19.9; 8 x 1.5 K 22.8 -> 19.4;
 // 56 segments of one chunk 27.7 -> 22.6 (no second pass); 8 x 32 K as before.
 //
-// Both passes in one launch (PASS 3): the queries stay in LDS, up to two groups of keys a wave in registers (the second pass then reads no key).  Two launches
+// Both passes in one launch (PASS 3): the queries stay in LDS, up to two groups of keys a wave in registers (the second pass then waits for no key, though it requests them again).  Two launches
 // / one, us a call: E4M3 8 x 32 K 57.8 / 55.1, 16 x 32 K 90.4 / 84.2, 128 x 3 K 64.0 / 58.0, 192 x 1.7 to 9 K of 64 rows 99.1 / 84.2, 4 x 20 K of 448 rows 62.9 / 58.3,
 // 8 x 2 K 21.6 / 20.5, a decode cache of 256 segments 35.3 / 34.6, of 8 22.9 / 20.3; fp32 4 x 1 K 20.6 / 19.4, 32 x 0.6 K 23.9 / 22.7.  Not with many short
 // chunks to a segment, for which everybody waits and which everybody reads back: E4M3 8 x 12 K in 47 each 27.8 / 28.5; fp32 8 x 4 K in 31 29.6 / 29.8, 8 x 2 K in 32
-// 31.5 / 31.7.  (Planned for, by its lower cost, one launch takes fewer, longer chunks: 8 x 8 K fp32 46.3 -> 47.5.)
+// 31.5 / 31.7.  (Planned for, by its lower cost, one launch takes fewer, longer chunks: 8 x 8 K fp32 46.3 -> 47.5.)  Long passes gain as well, unlike those of 16-bit keys (kTogetherUs): one
+// workgroup has a CU to itself.  E4M3 32 x 32 K 159 / 152, 64 x 32 K 283 / 278, six prompts of 2 to 32 K 163 / 151 (on several streams: meet_limit).
 static void plan_k_resident(const Geometry& g, Plan& p) {
   constexpr double kLaunchUs = 3.7, kFoldUs = 0.03;
   const bool f32 = g.dtype == SLKV_F32;
@@ -3993,7 +3994,9 @@ static void plan_k_resident(const Geometry& g, Plan& p) {
 // workgroup: table, queries, first keys.  Two launches / one, us a call: 1 x 1.2 K 21.7 / 18.5, 1 x 2 K 23.9 / 20.6, 1 x 8 K 25.6 / 24.2, 16 prompts
 // of 150 to 5 K 56.0 / 47.7, a decode cache of 256 segments 67.7 / 60.5, 1 x 32 K of 256 rows 62.2 / 61.1, 2 x 32 K 98.0 / 94.9.  Above the
 // line the start is little of it, and the two workgroups of a CU, of which one is served first, wait for each other: 3 x 32 K 138.9 / 143.4.
-// On 2, 3 and 4 streams at once, 16 short prompts: 41.2 / 36.8, 37.4 / 35.4, 36.9 / 34.1; 1 x 32 K: 47.0 / 46.5, 44.1 / 46.0, 42.3 / 45.3.
+// On 1 to 4 streams at once, 16 short prompts 59.0 43.5 38.8 37.8 / 47.8 37.8 36.6 36.4; a decode cache of 256 segments 70.2 50.4 55.9 45.5 / 55.2 40.8 46.5 41.2; 1 x 32 K 67.3 50.9 48.2 46.3 /
+// 64.9 50.6 49.1 48.4, of E4M3 keys 70.7 58.7 50.8 48.7 / 65.4 56.7 49.9 52.3.  On four streams 256 workgroups of long chunks to a call lose what waits on CUs that another call could use; the line
+// stays, since such calls gain as much where fewer run at once.  (The priority of the waves, first pass over second or second over first, changes nothing.)
 //
 // One pass over the keys instead of two (OneScan) where a pass takes this long by the costs above: it saves a pass, less a tenth, and
 // costs the sample, the histograms, the bounds and the chosen keys; where histories above 32768 positions are selected by blocks it
@@ -4504,7 +4507,7 @@ static slkv_status run_geometry(const Geometry& g, const void* d_qwin, const voi
   // otherwise the histories are cut into blocks.
   const bool resident_select = select_mode() != 2 && g.longest <= kSelRound;
   const int nseg = (int)S;
-  // The selection starts from the groups' largest scores where a thread would have 32 positions to go through otherwise (with 8 or 2 the shorter
+  // The selection starts from the groups' largest scores where a thread would have 16, 24 or 32 positions to go through otherwise (with 8 or fewer the shorter
   // chain of phases wins: 8 x 8 K keys 25.7 us either way, 8 x 900 keys 22.4 us without, 24.8 with), and not for
   // fp32, whose scoring kernel got slower by it on short calls (4 x 1 K 19.7 -> 20.1).  They lie in the pooled array, which nobody writes then.
   // (a group's place counts the segments before it, see group_off: with thousands of empty ones the array may be too short)
