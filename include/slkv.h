@@ -218,7 +218,7 @@ typedef struct {
 slkv_status slkv_compacted_sizes(const slkv_layer_desc* desc, int64_t* h_out_offsets,
                                  int64_t* total_kept);
 /* Device workspace slkv_compress_layer needs for this descriptor.
- * A workspace has to be ZERO-FILLED ONCE by the caller before the first call that uses it (its
+ * A workspace has to be ZERO-FILLED ONCE by the caller before the first call that uses it, on that call's stream or one it has waited for (its
  * first SLKV_WORKSPACE_HEADER_BYTES are a header of counters through which the workgroups of a launch
  * wait for each other); every call leaves them zero, so the same workspace serves any number of later calls, of any descriptor it is large enough for, also
  * from a replayed HIP graph.  Its other contents are scratch.  Two calls that may overlap in

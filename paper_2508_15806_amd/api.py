@@ -36,36 +36,13 @@ def to_host(t):
 
 
 class _Buffers:
-    """What the two kinds of call share: a workspace whose header has to be zero before every call."""
+    """What the two kinds of call share.  The constructor allocates and zero-fills on the stream that is current there; run() on another stream
+    asks, as for the inputs, that this stream has waited for that one.  Calls of one object use the same buffers: each has to wait for the one before it."""
 
-    def _made(self):
-        """The buffers are allocated, and filled by the stream that is current now: another stream waits for that before its first call."""
-        self._filled = None
-        if self.workspace.is_cuda:
-            with torch.cuda.device(self.workspace.device):
-                if not torch.cuda.is_current_stream_capturing():
-                    self._filled, self._ordered = torch.cuda.Event(), {B._stream(None)}
-                    self._filled.record()
-
-    def _enqueue(self, function, args, stream):
-        handle = stream
-        if self._filled is not None:
-            handle = B._stream(stream)
-            if handle not in self._ordered:
-                self._wait_for_fill(handle, stream)
-        try:
-            function(*args, handle)
-        except B.SlkvError as e:
-            if e.status == B.SLKV_ERR_HIP:      # some of its launches may have run: the next call finds the header clear all the same
-                with torch.cuda.stream(stream):
-                    self.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].zero_()
-            raise
-
-    def _wait_for_fill(self, handle, stream):
-        with torch.cuda.stream(stream):
-            if not torch.cuda.is_current_stream_capturing():      # (a capture begins after what it uses has been filled)
-                torch.cuda.current_stream().wait_event(self._filled)
-                self._ordered.add(handle)
+    def _failed(self, error, stream):
+        if error.status == B.SLKV_ERR_HIP:      # some of its launches may have run: the next call finds the workspace's header clear all the same
+            with torch.cuda.stream(stream):
+                self.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].zero_()
 
 
 class LayerCall(_Buffers):
@@ -91,11 +68,14 @@ class LayerCall(_Buffers):
         if debug_scores:
             self.importance = torch.zeros((max(Hkv * T, 1),), dtype=torch.float32, device=device)
             self.pooled = torch.zeros((max(Hkv * T, 1),), dtype=torch.float32, device=device)
-        self._made()
 
     def run(self, qwin, k, v, stream=None):
-        self._enqueue(B.slkv_compress_layer, (self.layer, qwin, k, v, self.k_out, self.v_out, self.kept_idx, self.workspace,
-                                              self.out_offsets, self.importance, self.pooled), stream)
+        try:
+            B.slkv_compress_layer(self.layer, qwin, k, v, self.k_out, self.v_out, self.kept_idx, self.workspace,
+                                  self.out_offsets, self.importance, self.pooled, stream)
+        except B.SlkvError as e:
+            self._failed(e, stream)
+            raise
 
 
 class RaggedCall(_Buffers):
@@ -119,12 +99,15 @@ class RaggedCall(_Buffers):
         if debug_scores:
             self.importance = torch.zeros((max(rows_in, 1),), dtype=torch.float32, device=device)
             self.pooled = torch.zeros((max(rows_in, 1),), dtype=torch.float32, device=device)
-        self._made()
 
     def run(self, qwin, k_in, v_in, pos_in=None, stream=None):
-        self._enqueue(B.slkv_recompress_layer, (self.rag, qwin, k_in, v_in, self.k_out, self.v_out, self.kept_idx, self.workspace,
-                                                pos_in, self.pos_out if pos_in is not None else None, self.out_offsets,
-                                                self.importance, self.pooled), stream)
+        try:
+            B.slkv_recompress_layer(self.rag, qwin, k_in, v_in, self.k_out, self.v_out, self.kept_idx, self.workspace,
+                                    pos_in, self.pos_out if pos_in is not None else None, self.out_offsets,
+                                    self.importance, self.pooled, stream)
+        except B.SlkvError as e:
+            self._failed(e, stream)
+            raise
 
 
 def score_heads(rows, needle_start, needle_len, topk, acc=None, stream=None):

@@ -146,9 +146,7 @@ def _ptr(t):
 
 def _stream(stream):
     """The stream's handle; None: the current stream of the current device, read without the Stream object that
-    torch.cuda.current_stream() makes (3 us of a call's 16) where torch has the function for it, which is not a public one.  A handle stays what it is."""
-    if type(stream) is int:
-        return stream
+    torch.cuda.current_stream() makes (3 us of a call's 16) where torch has the function for it, which is not a public one."""
     import torch
     if stream is None:
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)

