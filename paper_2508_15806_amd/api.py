@@ -41,8 +41,11 @@ class _Buffers:
 
     def _failed(self, error, stream):
         if error.status == B.SLKV_ERR_HIP:      # some of its launches may have run: the next call finds the workspace's header clear all the same
-            with torch.cuda.stream(stream):
-                self.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].zero_()
+            try:
+                with torch.cuda.stream(stream):
+                    self.workspace[:B.SLKV_WORKSPACE_HEADER_BYTES].zero_()
+            except RuntimeError:                # (a device that takes no launch at all: the call's own error is the one to report)
+                pass
 
 
 class LayerCall(_Buffers):
